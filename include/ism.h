@@ -129,10 +129,11 @@ typedef struct {
   double balance_items; /* > 0: items a large call is split into (replaces the tuned
                            value; sets the item size of large calls)                  */
   double tail_rounds;   /* single calls: the items dispatched once less than this many
-                           rounds of resident waves of work remain are cut smaller so
-                           the launch ends evenly; 0 = no taper, < 0 = default (1)    */
-  double batch_waves;   /* batches: workgroups per SIMD of each persistent launch
-                           (1 .. 16; the grid is 1024 times this); 0 = tuned value */
+                           rounds of resident items of work remain are cut smaller so
+                           the launch ends evenly; 0 = no taper, < 0 = default
+                           (1; FP32: 1/2)                                             */
+  double batch_waves;   /* batches: waves per SIMD of each persistent launch (1 .. 16;
+                           1024 times this in all); 0 = tuned value                */
 } ism_schedule;
 
 /* ---- GPU simulation -------------------------------------------------------------- */
@@ -361,10 +362,10 @@ int ism_batch_prepare(const ism_job *jobs, int n_jobs, int precision, void *ws, 
  * host-device copies, no allocation), so it can be captured in a HIP graph and
  * replayed. Work items are sized from the batch's total work: each job is
  * planned as a single call with item_taps = t = min(B, max(min_item_taps,
- * batch taps / balance_items)) of its class, B the tuned largest batch item
- * of the class, or, for a batch of less than t taps per resident wave, with
- * its taps over the resident waves (at least 1e4); the schedule's item_taps
- * replaces both when given. A
+ * batch taps / balance_items)) of its class, B the largest item
+ * of the class, or, for an FP16 or table-tap batch of less than t taps per
+ * resident wave, with its taps over the resident waves (at least 1e4); the
+ * schedule's item_taps replaces both when given. A
  * job's result therefore agrees within rounding (<= 1e-6 of the RIR peak)
  * with the job alone and with ism_simulate; it is bitwise that of
  * ism_simulate_ex with the same item_taps, and a batch of one job (of fewer

@@ -11,9 +11,12 @@
 //                      enumerates exactly the lattice images whose window can
 //                      reach the tile, computes each image's delay and amplitude
 //                      (Eq. (2)-(4), times the receiver's polar pattern when
-//                      directional) and adds its Hann-windowed-sinc taps
-//                      (Eq. (6): FP32, packed FP16, or read from the table of
-//                      Eq. (9)) into wave-private FP32 LDS tiles (Eq. (5)).
+//                      directional) and adds its Hann-windowed sinc (Eq. (5),
+//                      (6)): FP32 calls sum the moments of the images' delay
+//                      fractions per integer delay and convolve these with the
+//                      taps' polynomials once per item; FP16 and table taps
+//                      (Eq. (9)) are added image by image into wave-private
+//                      FP32 LDS tiles.
 //   reduce_kernel      sums, in a fixed order, the partial tiles of tiles that
 //                      were split over several work items.
 //
@@ -39,13 +42,8 @@ namespace ism {
 constexpr int kBaseBits = (TILE <= 256) ? 8 : 9;
 constexpr uint32_t kBaseMask = (1u << kBaseBits) - 1u;
 static_assert(TILE <= (1 << kBaseBits), "tile-local bases must fit the record");
-// The delay fraction of the table-tap record (and of the FP32 record where
-// cq_base is false), in units of 2^-kFracBits.
+// The delay fraction of the table-tap record, in units of 2^-kFracBits.
 constexpr int kFracBits = 32 - kBaseBits;
-// Whether the FP32 record of window cap wt carries the base in CQ's low
-// mantissa bits (else beside the fraction): all but general windows of the
-// 32-sample cap.
-constexpr bool cq_base(int wt, bool gen) { return !(gen && wt == 32); }
 
 // ---------------------------------------------------------------------------
 // Float-float building blocks (Dekker / Knuth error-free transformations).
@@ -115,33 +113,6 @@ constexpr double cx_cos(double x) {
     sum += term;
   }
   return sum;
-}
-
-// For an even integer window of WT samples and fractional delay f in (0, 1),
-// the taps of one image are j = JLO .. JLO + WT - 1 (JLO = 1 - WT/2) relative to
-// k0 = floor(x). With v = j - f:
-//   sin(pi v) = sigma_j sin(pi f),            sigma_j = (-1)^(j+1)
-//   1 + cos(2 pi v / W) = 1 + cos(th_j) cos(phi) + sin(th_j) sin(phi),
-//                         th_j = 2 pi j / W, phi = 2 pi f / W,
-// so tap_j = [C/2 + (C/2 cos phi) cos th_j + (C/2 sin phi) sin th_j] / (sigma_j (j - f))
-// with C = A sin(pi f) / pi. Only sigma_j, sigma_j j, cos th_j, sin th_j depend on j.
-template <int WT>
-struct TapConsts {
-  float sig[WT], sig_j[WT], cth[WT], sth[WT];
-};
-template <int WT>
-constexpr TapConsts<WT> make_tap_consts() {
-  TapConsts<WT> t{};
-  for (int jj = 0; jj < WT; ++jj) {
-    const int j = jj + 1 - WT / 2;
-    const double sg = (j % 2 == 0) ? -1.0 : 1.0;
-    const double th = 2.0 * kPi * j / WT;  // in (-pi, pi]
-    t.sig[jj] = (float)sg;
-    t.sig_j[jj] = (float)(sg * j);
-    t.cth[jj] = (float)cx_cos(th);
-    t.sth[jj] = (float)cx_sin(th);
-  }
-  return t;
 }
 
 // FP16 taps. For one image with fractional delay f, tap j (Eq. (6) at
@@ -249,23 +220,153 @@ constexpr ChebFit make_cheb_fit() {
 }
 __constant__ ChebFit kChebFit = make_cheb_fit();
 
-// Constants of tap jj (j = jj + 1 - WT/2) of a general-mode window of W
-// samples under cap WT, for FP32 (half == 0) or FP16 (half == 1) taps, into
-// e[0 .. WC_STRIDE). FP16: the interpolant of s_j(t) = tap value at
-// f = t + 1/2 (Eq. (6), 0 where |j - f| >= W/2) at the Chebyshev nodes.
-__device__ void window_const_entry(float W, int WT, int half, int jj, float *e) {
+// FP32 taps by moments. As for FP16, tap j of an image is A s_j(t), t = f - 1/2,
+// and s_j is replaced by its interpolant of degree MOM - 1 at the Chebyshev
+// nodes, c_j0 + c_j1 t + ... (error < 3e-9 for every tap, so it is exact to FP32
+// rounding: a windowed sinc is band-limited, and its Chebyshev coefficients
+// over one sample fall faster than (pi/4)^p / p!). The images of one integer
+// delay k0 then enter the RIR through the MOM sums M_p[k0] = sum A t^p alone,
+//   h[k] = sum_j sum_p c_jp M_p[k - j],
+// which costs an image MOM sums instead of W taps, and a convolution of MOM
+// W per output sample whatever the number of images.
+// The window is even, so s_{1-j}(t) = s_j(-t) and c_{1-j,p} = (-1)^p c_jp: tables
+// hold j = 1 .. W/2.
+constexpr int MOM = 10;
+template <int NP>
+struct ChebFitD {
+  double node[NP];
+  double vinv[NP][NP];  // vinv[k][i]: coefficient of t^k per unit value at node i
+};
+template <int NP>
+constexpr ChebFitD<NP> make_cheb_fit_d() {
+  ChebFitD<NP> F{};
+  for (int i = 0; i < NP; ++i) F.node[i] = 0.5 * cx_cos((2.0 * i + 1.0) * kPi / (2.0 * NP));
+  // column i of the inverse Vandermonde matrix: the Lagrange polynomial of node i
+  for (int i = 0; i < NP; ++i) {
+    double m[NP] = {};  // coefficients of the running product, lowest first
+    m[0] = 1.0;
+    int deg = 0;
+    double den = 1.0;
+    for (int k = 0; k < NP; ++k) {
+      if (k == i) continue;
+      for (int q = ++deg; q > 0; --q) m[q] = m[q - 1] - F.node[k] * m[q];
+      m[0] *= -F.node[k];
+      den *= F.node[i] - F.node[k];
+    }
+    for (int k = 0; k < NP; ++k) F.vinv[k][i] = m[k] / den;
+  }
+  return F;
+}
+__constant__ ChebFitD<MOM> kMomFit = make_cheb_fit_d<MOM>();
+template <int WT>
+struct MomCoef {
+  float c[MOM][WT / 2];  // c[p][j - 1]
+};
+template <int WT>
+constexpr MomCoef<WT> make_mom_coef() {
+  constexpr ChebFitD<MOM> F = make_cheb_fit_d<MOM>();
+  MomCoef<WT> t{};
+  for (int j = 1; j <= WT / 2; ++j) {
+    double y[MOM] = {};
+    for (int i = 0; i < MOM; ++i) y[i] = s_tap(j, F.node[i], WT);
+    for (int p = 0; p < MOM; ++p) {
+      double v = 0.0;
+      for (int i = 0; i < MOM; ++i) v += F.vinv[p][i] * y[i];
+      t.c[p][j - 1] = (float)v;
+    }
+  }
+  return t;
+}
+
+// General-mode windows. W is any real number; with h = W/2, the taps j = 1 ..
+// floor(h) (and their mirrors 1 - j) lie inside the window for every f, while tap
+// j2 = floor(h) + 1 (mirror 1 - j2) is inside only for f > f1 = j2 - h (mirror:
+// f < 1 - f1) and meets the window's end with a jump in its second derivative of
+// about 20 / W^3, which a polynomial over the whole sample cannot follow. Under
+// caps up to kEdgeCap its values are therefore summed image by image, A e(u) with
+// u the distance inside the end and e the polynomial
+//   e(u) = u^2 (e_0 + e_1 (u - 1/2) + ... + e_7 (u - 1/2)^7)
+// of the windowed sinc there (8e-8 at W = 5, below 1e-9 from W = 8); above, the
+// jump moves the fit by less than 2e-8 and the tap takes the moments too. Windows
+// shorter than kDirectWin vary too fast for the moments: their at most four
+// taps are evaluated and summed image by image.
+constexpr int kEdgeCap = 64;
+constexpr int kEdgeCoef = 8;
+constexpr float kDirectWin = 4.0f;
+__constant__ ChebFitD<kEdgeCoef> kEdgeFit = make_cheb_fit_d<kEdgeCoef>();
+// Layout of the FP32 constants of a general window of cap WT: c[p][j - 1] as
+// above, then e_0 .. e_7, f1, j2 (0: no tap is cut).
+constexpr int wc_edge(int WT) { return MOM * (WT / 2); }
+static_assert(wc_edge(32) + kEdgeCoef + 2 <= 32 * WC_STRIDE, "window constants");
+
+// sin(pi x) and cos(pi x) in double for moderate |x| (reduction to |r| <= 1/4,
+// Taylor series with terms below 1e-18 left out).
+__device__ void sincospi_d(double x, double &s, double &c) {
+  const double n = __builtin_rint(2.0 * x);
+  const double y = (x - 0.5 * n) * kPi, y2 = y * y;
+  double ts = y, tc = 1.0;
+  s = y;
+  c = 1.0;
+  for (int k = 1; k <= 9; ++k) {
+    tc *= -y2 / ((2.0 * k - 1.0) * (2.0 * k));
+    ts *= -y2 / ((2.0 * k) * (2.0 * k + 1.0));
+    c += tc;
+    s += ts;
+  }
+  const int q = ((int)n) & 3;
+  const double a = s, b = c;
+  s = q == 0 ? a : q == 1 ? b : q == 2 ? -a : -b;
+  c = q == 0 ? b : q == 1 ? -a : q == 2 ? -b : a;
+}
+// The windowed sinc of Eq. (6) at v != 0, without its cut at |v| = W/2.
+__device__ double windowed_sinc_d(double v, double W) {
+  double sn, cs, wn, wc;
+  sincospi_d(v, sn, cs);
+  sincospi_d(2.0 * v / W, wn, wc);
+  return sn / (kPi * v) * 0.5 * (1.0 + wc);
+}
+// FP32 constants of a general window: thread jj of WT/2 writes tap j = jj + 1,
+// the thread after them the edge polynomial.
+__device__ void moment_const_entry(double W, int WT, int jj, float *wc) {
+  const int half = WT / 2;
+  const int j2 = (int)__builtin_floor(0.5 * W) + 1;
+  const bool edge = WT <= kEdgeCap && (double)j2 - 0.5 * W < 1.0 && j2 <= half;
+  if (jj < half) {
+    const int j = jj + 1;
+    double y[MOM];
+    for (int i = 0; i < MOM; ++i) {
+      const double v = (double)j - (kMomFit.node[i] + 0.5);
+      y[i] = ((edge && j == j2) || !(__builtin_fabs(v) < 0.5 * W)) ? 0.0 : windowed_sinc_d(v, W);
+    }
+    for (int p = 0; p < MOM; ++p) {
+      double v = 0.0;
+      for (int i = 0; i < MOM; ++i) v += kMomFit.vinv[p][i] * y[i];
+      wc[p * half + jj] = (float)v;
+    }
+  } else if (jj == half) {
+    float *e = wc + wc_edge(WT);
+    double y[kEdgeCoef];
+    for (int i = 0; i < kEdgeCoef; ++i) {
+      const double u = kEdgeFit.node[i] + 0.5;
+      y[i] = edge ? windowed_sinc_d(0.5 * W - u, W) / (u * u) : 0.0;
+    }
+    for (int p = 0; p < kEdgeCoef; ++p) {
+      double v = 0.0;
+      for (int i = 0; i < kEdgeCoef; ++i) v += kEdgeFit.vinv[p][i] * y[i];
+      e[p] = (float)v;
+    }
+    e[kEdgeCoef] = (float)((double)j2 - 0.5 * W);
+    e[kEdgeCoef + 1] = edge ? (float)j2 : 0.0f;
+  }
+}
+
+// FP16 constants of tap jj (j = jj + 1 - WT/2) of a general-mode window of W
+// samples under cap WT into e[0 .. WC_STRIDE): the interpolant of s_j(t) = tap
+// value at f = t + 1/2 (Eq. (6), 0 where |j - f| >= W/2) at the Chebyshev nodes.
+__device__ void window_const_entry(float W, int WT, int jj, float *e) {
   const int j = jj + 1 - WT / 2;
   const float sg = (j & 1) ? 1.0f : -1.0f;  // sin(pi (j - f)) = sg sin(pi f)
   for (int k = 0; k < WC_STRIDE; ++k) e[k] = 0.0f;
-  if (!half) {
-    float sn, cs;
-    sincospi_acc(2.0f * (float)j / W, sn, cs);
-    e[0] = cq_base(WT, true) ? -sg : -sg * 0x1p-32f;  // times f, or times float(F) = f 2^32
-    e[1] = sg * (float)j;
-    e[2] = cs;
-    e[3] = sn;
-    return;
-  }
   float y[SPD + 1];
   for (int i = 0; i <= SPD; ++i) {
     const float f = kChebFit.node[i] + 0.5f;
@@ -499,16 +600,15 @@ __device__ __forceinline__ int first_ge(const AxisRange &a, float b) {
 // and hands them to a consumer that turns candidates into image
 // parameters (delay, amplitude; lanes = images) and adds their taps.
 //
-// Tap consumer (lanes = taps, both precisions): the candidates' parameters
-// are staged in LDS; each half-wave then takes one staged image per step and
-// its 32 lanes add W/32 taps each into the half-wave's own FP32 tile. All
-// addresses of one step are distinct and consecutive, so there are no bank
-// conflicts and no lost updates; steps of a half-wave reach LDS in program
-// order. FP32 taps divide by the sinc argument; FP16 taps evaluate a
-// per-tap polynomial in packed FP16.
+// FP32 consumer (moment_item): images are collected per integer delay and
+// enter through their moments. FP16 and table-tap consumer (tap_item, lanes =
+// taps): the candidates' parameters are staged in LDS; each half-wave then
+// takes one staged image per step and its 32 lanes add W/32 taps each into the
+// half-wave's own FP32 tile. All addresses of one step are distinct and
+// consecutive, so there are no bank conflicts and no lost updates; steps of a
+// half-wave reach LDS in program order.
 //
-// Items end with a fixed-order sum of the tiles, so results are bitwise
-// reproducible.
+// Items end with a fixed-order sum, so results are bitwise reproducible.
 // ---------------------------------------------------------------------------
 typedef int int4v __attribute__((ext_vector_type(4)));
 typedef float float2v __attribute__((ext_vector_type(2)));
@@ -560,56 +660,81 @@ __device__ __forceinline__ ItemGeom item_geom(const RoomArgs &ra, const AxisRang
   return g;
 }
 
-// Walks the shell of the item. For every batch of 64 columns with candidates
-// it fills es.col_run and es.col_s and calls consume(total, excl, cnt): total
-// candidates in the batch, and on column lane c its first position excl and
-// its count cnt. The column gain in col_run is the product of the x and y
-// gain factors times gscale.
+// Walks the shell of the item, shared by the NW waves of a workgroup: wave wv
+// takes every NW-th batch of 64 columns (each wave has its own EnumLds and
+// repeats the x step, one lane per 64 x indices). next() goes to the wave's next
+// batch with candidates: it fills es.col_run and es.col_s and sets total, the
+// candidates in the batch, and on column lane c its first position excl and its
+// count cnt; false when there is none left. The column gain in col_run is the
+// product of the x and y gain factors times gscale.
 // DUMP (enumeration check): col_xy receives each column's x and y table
 // indices, (x << 16) | y.
-template <bool POLAR, bool DUMP, class Consume>
-__device__ __forceinline__ void enumerate_shell(const ItemGeom &g, const AxisEntry *__restrict__ tx,
-                                                const AxisEntry *__restrict__ ty, const AxisRange &ay,
-                                                const AxisRange &az, const float gscale, EnumLds &es,
-                                                float *__restrict__ col_p, uint32_t *__restrict__ col_xy,
-                                                Consume &&consume) {
-  const int lane = threadIdx.x & 63;
-  for (int nx0 = g.nx_a; nx0 < g.nx_b; nx0 += 64) {
-    // lanes = x indices: y range of the columns that reach the outer sphere
-    const int nxi = nx0 + lane;
-    int ny_lo = 0, ny_cnt = 0;
-    if (nxi < g.nx_b) {
-      const AxisEntry ex = tx[nxi];
-      float rh, rl;
-      ff_sub(g.r1h, g.r1l, ex.sq_hi, ex.sq_lo, rh, rl);
-      if (rh > 0.0f) {
-        const float R = __builtin_sqrtf(rh) + 1.0f;
-        ny_lo = first_ge(ay, -R);
-        ny_cnt = first_ge(ay, R) - ny_lo;
-      }
-    }
-    const int incl_y = wave_incl_scan(ny_cnt);
-    const int ncols = __builtin_amdgcn_readlane(incl_y, 63);
-    const int col0 = incl_y - ny_cnt;  // first column of this x lane
-    es.nx_col[lane] = ((uint32_t)col0 << 11) | (uint32_t)ny_lo;
+template <bool POLAR, bool DUMP, int NW>
+struct ShellWalk {
+  const ItemGeom &g;
+  const AxisEntry *__restrict__ tx;
+  const AxisEntry *__restrict__ ty;
+  const AxisRange &ay, &az;
+  float gscale;
+  EnumLds &es;
+  float *__restrict__ col_p;
+  uint32_t *__restrict__ col_xy;
+  int wv;
+  int nx_next, nx0 = 0, ncols = 0, cb = 0, base = 0;  // x block, its columns, next batch, batches before the block
+  int col0 = 0, ny_cnt = 0;                           // this x lane's first column and its columns
+  int total = 0, excl = 0, cnt = 0;
 
-    int xcarry = 0;
-    for (int cb = 0; cb * 64 < ncols; ++cb) {
+  __device__ __forceinline__ ShellWalk(const ItemGeom &g_, const AxisEntry *tx_, const AxisEntry *ty_,
+                                       const AxisRange &ay_, const AxisRange &az_, float gscale_, EnumLds &es_,
+                                       float *col_p_, uint32_t *col_xy_, int wv_)
+      : g(g_), tx(tx_), ty(ty_), ay(ay_), az(az_), gscale(gscale_), es(es_), col_p(col_p_), col_xy(col_xy_), wv(wv_),
+        nx_next(g_.nx_a) {}
+
+  __device__ __forceinline__ bool next() {
+    const int lane = threadIdx.x & 63;
+    for (;;) {
+      while (cb * 64 >= ncols) {
+        if (nx_next >= g.nx_b) return false;
+        nx0 = nx_next;
+        nx_next += 64;
+        // lanes = x indices: y range of the columns that reach the outer sphere
+        const int nxi = nx0 + lane;
+        int ny_lo = 0;
+        ny_cnt = 0;
+        if (nxi < g.nx_b) {
+          const AxisEntry ex = tx[nxi];
+          float rh, rl;
+          ff_sub(g.r1h, g.r1l, ex.sq_hi, ex.sq_lo, rh, rl);
+          if (rh > 0.0f) {
+            const float R = __builtin_sqrtf(rh) + 1.0f;
+            ny_lo = first_ge(ay, -R);
+            ny_cnt = first_ge(ay, R) - ny_lo;
+          }
+        }
+        const int incl_y = wave_incl_scan(ny_cnt);
+        ncols = __builtin_amdgcn_readlane(incl_y, 63);
+        col0 = incl_y - ny_cnt;
+        wave_sync();
+        es.nx_col[lane] = ((uint32_t)col0 << 11) | (uint32_t)ny_lo;
+        cb = NW > 1 ? (wv - base) & (NW - 1) : 0;
+        base += (ncols + 63) >> 6;
+      }
       // lanes = columns (nx, ny): z ranges of the shell
       const int gcol = cb * 64 + lane;
       // x lane of the column: the last x lane with columns starting at or
       // before it (each marks its first column in the batch; a running
-      // maximum carries the marks forward, as for the candidates)
+      // maximum carries the marks forward, as for the candidates, from the
+      // x lane of the batch's first column)
       es.mark[lane] = 0;
       wave_sync();
       if (ny_cnt > 0 && (uint32_t)(col0 - cb * 64) < 64u) es.mark[col0 - cb * 64] = lane + 1;
       wave_sync();
-      const int xm = max(wave_incl_max(es.mark[lane]), xcarry);
-      xcarry = __builtin_amdgcn_readlane(xm, 63);
+      const uint64_t before = __ballot(ny_cnt > 0 && col0 <= cb * 64);
+      const int xm = max(wave_incl_max(es.mark[lane]), 64 - (int)__builtin_clzll(before | 1u));
       int z1 = 0, n1 = 0, z2 = 0, n2 = 0;
       float cg = 0.0f;
       if (gcol < ncols) {
-        const int i = max(xm - 1, 0);
+        const int i = xm - 1;
         const uint32_t xc = es.nx_col[i];
         const AxisEntry ex = tx[nx0 + i];
         const int iy = (int)(xc & 0x7ffu) + (gcol - (int)(xc >> 11));
@@ -640,63 +765,34 @@ __device__ __forceinline__ void enumerate_shell(const ItemGeom &g, const AxisEnt
           n2 = first_ge(az, zmax) - z2;
         }
       }
-      const int cnt = n1 + n2;
+      cb += NW;
+      cnt = n1 + n2;
       const int incl = wave_incl_scan(cnt);
-      const int total = __builtin_amdgcn_readlane(incl, 63);
-      const int excl = incl - cnt;
+      total = __builtin_amdgcn_readlane(incl, 63);
+      excl = incl - cnt;
       es.col_run[lane] = int4v{excl + n1, z1 - excl, z2 - n1 - excl, __float_as_int(cg)};
-      if (total > 0) {
-        wave_sync();
-        consume(total, excl, cnt);
-        wave_sync();
-      }
+      wave_sync();
+      if (total > 0) return true;
     }
-    wave_sync();
   }
-}
+};
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef float f4v __attribute__((ext_vector_type(4)));
 
 // Parameters of one image candidate (column part cs of the squared distance,
-// column gain cgain, z table row ez). ok is false when the
-// tile does not own the image. base = k0 - T0 is the tile-local LDS index of its
-// tap j = 1 - W/2 (the LDS tile starts at sample T0 + 1 - W/2). rec is the
-// staged record of the taps, which also carries the base:
-//   FP32: (f, CP, CQ', C/2) with f the fraction in [2^-24, 1 - 2^-24],
-//         C = A sin(pi f)/pi, CP = C/2 cos(2 pi f/W), and CQ' the value
-//         CQ = C/2 sin(2 pi f/W) with the base in its 8 low mantissa bits.
-//         That changes CQ by less than 2^-15 of itself; CQ enters tap j as
-//         CQ sin(2 pi j/W) / (j - f) and |CQ| <= C/2 sin(2 pi/W) (W >= 4), so
-//         a tap moves by less than 2^-15 sin(2 pi/W) A/(2 pi): 4.8e-7 A at
-//         W = 64, 9.5e-7 A at W = 32. General windows of the 32-sample cap
-//         (any W < 32, where that bound grows towards 4.9e-6 A) keep the
-//         fraction and the base in one word instead (cq_base false):
-//         (F, CP, CQ, C/2) with F = fq 2^8 + base, fq the fraction rounded
-//         to 24 bits, and f = float(F) 2^-32 for the taps and the factors;
-//   FP16: (t, A') with t = f - 1/2 in FP32 and A' the amplitude with the
-//         base in its 8 low mantissa bits (relative change < 2^-15);
-//   LUT:  (F, A) with F = fq 2^8 + base (bits of a uint32), fq the fraction
-//         in units of 2^-24, and A in FP32.
-// The column gain cgain carries the constant factor of A: fs / (4 pi c)
-// for FP16 and LUT, and fs / (4 pi c) / (2 pi) for FP32, whose record holds C/2.
-template <bool HALF> struct StageRec { typedef f4v type; };
-template <> struct StageRec<true> { typedef float2v type; };
-template <bool HALF>
+// column gain cgain = fs / (4 pi c) times the x and y gains, z table row ez). ok
+// is false when the tile does not own the image. base = k0 - T0, fr the delay
+// fraction in [0, 1 - 2^-24], A the amplitude of Eq. (4) (times the receiver's
+// polar pattern when directional).
 struct ImageParams {
   bool ok;
   int base;
-  typename StageRec<HALF>::type rec;
+  float fr, A;
 };
-template <bool HALF>
-__device__ __forceinline__ float column_gain_scale(const RoomArgs &ra) {
-  return HALF ? ra.kappa : ra.kappa * (float)(0.5 / kPi);
-}
-template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN = false>
-__device__ __forceinline__ ImageParams<HALF || LUT> image_params(const RoomArgs &ra, const ItemGeom &g,
-                                                                 const float2v cs, const float cgain,
-                                                                 const AxisEntry ez, const float cp) {
-  ImageParams<HALF || LUT> p;
+template <bool POLAR>
+__device__ __forceinline__ ImageParams image_params(const RoomArgs &ra, const ItemGeom &g, const float2v cs,
+                                                    const float cgain, const AxisEntry ez, const float cp) {
+  ImageParams p;
   // S = column part + z part in float-float (Sh + Sl, not renormalised)
   float Sh, Sl;
   two_sum(cs.x, ez.sq_hi, Sh, Sl);
@@ -711,66 +807,98 @@ __device__ __forceinline__ ImageParams<HALF || LUT> image_params(const RoomArgs 
   float kf = floorf(x0);
   float fr = (x0 - kf) + xl;
   const float d = floorf(fr);
-  fr = fminf(fr - d, 0x1.fffffep-1f);
+  p.fr = fminf(fr - d, 0x1.fffffep-1f);
   kf += d;
   const int k0 = (int)kf;
   p.base = k0 - g.T0;
   p.ok = (x0 < 1.0e9f) && (uint32_t)p.base < (uint32_t)(g.K1 - g.T0);
   // Eq. (4) amplitude (times the constant factor carried by the column gain)
-  float A = (cgain * ez.gain) * rx;
+  p.A = (cgain * ez.gain) * rx;
   // receiver polar pattern a + b cos(theta), cos(theta) = (d . o) / |d|
-  if constexpr (POLAR) A *= __builtin_fmaf(ra.dir_b, (cp + ez.proj) * rx, ra.dir_a);
-  if constexpr (HALF) {
-    const float t = fr - 0.5f;
-    const uint32_t Ab = (__float_as_uint(A) & ~kBaseMask) | ((uint32_t)p.base & kBaseMask);
-    p.rec = float2v{t, __uint_as_float(Ab)};
-  } else if constexpr (LUT) {
-    // 24-bit fraction (as in the FP32 record) with the base in the low byte;
-    // its top 4 bits are the table phase, the next 20 the interpolation weight
-    const uint32_t fq = min((uint32_t)__builtin_rintf(fr * (float)(1u << kFracBits)), (1u << kFracBits) - 1u);
-    p.rec = float2v{__uint_as_float((fq << kBaseBits) | ((uint32_t)p.base & kBaseMask)), A};
-  } else {
-    // f at least 2^-24 (fr is at most 1 - 2^-24 already): no tap sits on the
-    // image itself, where the sinc's numerator and denominator both vanish.
-    // Packed beside the base, f is rounded to 24 bits (the delay moves by at
-    // most 3e-8 samples) and float(F) 2^-32 stays in [2^-24, 1 - 2^-24].
-    constexpr bool CQB = cq_base(WT, GEN);
-    uint32_t F = 0;
-    float f;
-    if constexpr (CQB) {
-      f = fmaxf(fr, 0x1p-24f);
-    } else {
-      const uint32_t fq = min(max((uint32_t)__builtin_rintf(fr * (float)(1u << kFracBits)), 1u), (1u << kFracBits) - 2u);
-      F = (fq << kBaseBits) | ((uint32_t)p.base & kBaseMask);
-      f = (float)F * 0x1p-32f;
-    }
-    // The hardware sine and cosine take the angle in turns; their relative
-    // error (< 1e-6, also for the tiny angles of f near 0 or 1) enters each
-    // tap of the image once. sin(pi f) is taken as sin(pi min(f, 1 - f)).
-    const float C2 = A * __builtin_amdgcn_sinf(0.5f * fminf(f, 1.0f - f));
-    const float turn = f * (GEN ? ra.inv_win : 1.0f / (float)WT);  // phi = 2 pi f / W in turns
-    const float CQ = C2 * __builtin_amdgcn_sinf(turn);
-    const float CP = C2 * __builtin_amdgcn_cosf(turn);
-    if constexpr (CQB) {
-      const uint32_t Qb = (__float_as_uint(CQ) & ~kBaseMask) | ((uint32_t)p.base & kBaseMask);
-      p.rec = f4v{f, CP, __uint_as_float(Qb), C2};
-    } else {
-      p.rec = f4v{__uint_as_float(F), CP, CQ, C2};
-    }
-  }
+  if constexpr (POLAR) p.A *= __builtin_fmaf(ra.dir_b, (cp + ez.proj) * rx, ra.dir_a);
   return p;
 }
 
+// Staged record of the FP16 and table taps, with the base in the low bits of a word:
+//   FP16: (t, A') with t = f - 1/2 in FP32 and A' the amplitude with the
+//         base in its 8 low mantissa bits (relative change < 2^-15);
+//   LUT:  (F, A) with F = fq 2^8 + base (bits of a uint32), fq the fraction
+//         in units of 2^-24 (its top 4 bits are the table phase, the next 20 the
+//         interpolation weight), and A in FP32.
+template <bool HALF>
+__device__ __forceinline__ float2v stage_record(const ImageParams &p) {
+  if constexpr (HALF) {
+    const uint32_t Ab = (__float_as_uint(p.A) & ~kBaseMask) | ((uint32_t)p.base & kBaseMask);
+    return float2v{p.fr - 0.5f, __uint_as_float(Ab)};
+  } else {
+    const uint32_t fq = min((uint32_t)__builtin_rintf(p.fr * (float)(1u << kFracBits)), (1u << kFracBits) - 1u);
+    return float2v{__uint_as_float((fq << kBaseBits) | ((uint32_t)p.base & kBaseMask)), p.A};
+  }
+}
+
+// Walks the candidates of a wave's batches in chunks of 64 positions (lane i of
+// chunk q has position q + i). The column of a position is the last one starting
+// at or before it: each column marks its first position in the chunk, a running
+// maximum over the lanes carries the marks forward, and the last lane's column
+// carries into the next chunk (columns start in increasing order). The next
+// chunk's column and z table row are found ahead of its use.
+template <bool POLAR, bool DUMP, int NW>
+struct ChunkWalk {
+  ShellWalk<POLAR, DUMP, NW> &sw;
+  const AxisEntry *__restrict__ tz;
+  int n_z;
+  int q = 0, total = 0, carry = 0;
+  int cl = 0, nz = 0;  // of the chunk at q: column lane, z table index and row, column gain
+  float cg = 0.0f;
+  AxisEntry ez;
+
+  __device__ __forceinline__ ChunkWalk(ShellWalk<POLAR, DUMP, NW> &sw_, const AxisEntry *tz_, int n_z_)
+      : sw(sw_), tz(tz_), n_z(n_z_) {
+    ez = AxisEntry{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  __device__ __forceinline__ void locate(int q0) {
+    const int lane = threadIdx.x & 63;
+    EnumLds &es = sw.es;
+    es.mark[lane] = 0;
+    wave_sync();
+    const int r = sw.excl - q0;
+    if (sw.cnt > 0 && (uint32_t)r < 64u) es.mark[r] = lane + 1;
+    wave_sync();
+    const int m = max(wave_incl_max(es.mark[lane]), carry);
+    carry = __builtin_amdgcn_readlane(m, 63);
+    cl = max(m - 1, 0);
+    const int4v cr = es.col_run[cl];
+    const int pos = q0 + lane;
+    nz = min(max(pos + (pos < cr.x ? cr.y : cr.z), 0), n_z - 1);
+    cg = __int_as_float(cr.w);
+    if (pos < total) ez = tz[nz];
+  }
+  // Goes to the wave's next chunk; false when there is none left.
+  __device__ __forceinline__ bool advance() {
+    if (q >= total) {
+      if (!sw.next()) return false;
+      total = sw.total;
+      q = 0;
+      carry = 0;
+      locate(0);
+    }
+    return true;
+  }
+  // chunk(live, cl, nz, cg, ez) on the current chunk, whose successor is located first.
+  template <class Chunk>
+  __device__ __forceinline__ void visit(Chunk &&chunk) {
+    const int lane = threadIdx.x & 63;
+    const int cl_c = cl, nz_c = nz;
+    const float cg_c = cg;
+    const AxisEntry ez_c = ez;
+    const bool live = q + lane < total;
+    q += 64;
+    if (q < total) locate(q);
+    chunk(live, cl_c, nz_c, cg_c, ez_c);
+  }
+};
+
 // Per-tap constants, indexed by jj = j - (1 - W/2).
-__constant__ TapConsts<32> kTap32 = make_tap_consts<32>();
-__constant__ TapConsts<64> kTap64 = make_tap_consts<64>();
-__constant__ TapConsts<96> kTap96 = make_tap_consts<96>();
-__constant__ TapConsts<128> kTap128 = make_tap_consts<128>();
-template <int WT> __device__ __forceinline__ const TapConsts<WT> &tap_table();
-template <> __device__ __forceinline__ const TapConsts<32> &tap_table<32>() { return kTap32; }
-template <> __device__ __forceinline__ const TapConsts<64> &tap_table<64>() { return kTap64; }
-template <> __device__ __forceinline__ const TapConsts<96> &tap_table<96>() { return kTap96; }
-template <> __device__ __forceinline__ const TapConsts<128> &tap_table<128>() { return kTap128; }
 __constant__ SincPoly<32> kPoly32 = make_sinc_poly<32>();
 __constant__ SincPoly<64> kPoly64 = make_sinc_poly<64>();
 __constant__ SincPoly<96> kPoly96 = make_sinc_poly<96>();
@@ -800,6 +928,15 @@ __constant__ LutPairs<32> kLut32 = make_lut_pairs<32>();
 __constant__ LutPairs<64> kLut64 = make_lut_pairs<64>();
 __constant__ LutPairs<96> kLut96 = make_lut_pairs<96>();
 __constant__ LutPairs<128> kLut128 = make_lut_pairs<128>();
+__constant__ MomCoef<32> kMom32 = make_mom_coef<32>();
+__constant__ MomCoef<64> kMom64 = make_mom_coef<64>();
+__constant__ MomCoef<96> kMom96 = make_mom_coef<96>();
+__constant__ MomCoef<128> kMom128 = make_mom_coef<128>();
+template <int WT> __device__ __forceinline__ const MomCoef<WT> &mom_table();
+template <> __device__ __forceinline__ const MomCoef<32> &mom_table<32>() { return kMom32; }
+template <> __device__ __forceinline__ const MomCoef<64> &mom_table<64>() { return kMom64; }
+template <> __device__ __forceinline__ const MomCoef<96> &mom_table<96>() { return kMom96; }
+template <> __device__ __forceinline__ const MomCoef<128> &mom_table<128>() { return kMom128; }
 template <int WT> __device__ __forceinline__ const LutPairs<WT> &lut_table();
 template <> __device__ __forceinline__ const LutPairs<32> &lut_table<32>() { return kLut32; }
 template <> __device__ __forceinline__ const LutPairs<64> &lut_table<64>() { return kLut64; }
@@ -835,25 +972,25 @@ __device__ __forceinline__ void write_invalid(int n_own, float *__restrict__ dst
   for (int i = tid; i < WT - 1; i += nthreads) marg[i] = __builtin_nanf("");
 }
 
-// One work item on one wave (lanes = taps). Each step takes NQ staged images,
-// one per group of LPG = 64 / NQ lanes; lane l of group g adds the taps
-// j = 1 - W/2 + l + LPG m (m < TPL = W / LPG) of its image into the group's
-// own LDS tile. dst receives the own samples of the tile (or a partial tile
-// when C > 1), marg the margins. HALF selects the FP16 tap arithmetic, LUT
-// the table taps; accumulation is FP32 in all modes.
+// One work item on one wave with FP16 (HALF) or table taps (lanes = taps). Each
+// step takes NQ staged images, one per group of LPG = 64 / NQ lanes; lane l of
+// group g adds the taps j = 1 - W/2 + l + LPG m (m < TPL = W / LPG) of its image
+// into the group's own LDS tile. dst receives the own samples of the tile (or a
+// partial tile when C > 1), marg the margins. Accumulation is FP32.
 // DUMP: the enumeration check. No taps; every owned image is written to
 // dump->rec as a DumpRec of RIR rir (amplitude and fraction as the table
 // taps compute them).
 // GEN: general-mode window (WT is the cap, W = 2 ra.win_hw): the per-lane tap
 // constants come from wc ([WT][WC_STRIDE], written for this window by
-// window_consts_kernel) and FP32 taps with |j - f| >= W/2 are masked.
-template <int WT, bool HALF, int NQ, bool LUT = false, bool POLAR = false, bool DUMP = false, bool GEN = false>
-__device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
-                                                const AxisEntry *__restrict__ tab, const AxisOrigin &org,
-                                                const bool valid, float *__restrict__ dst, float *__restrict__ marg,
-                                                const DumpArgs *dump = nullptr, const int rir = 0,
-                                                const float *__restrict__ wc = nullptr) {
-  static_assert(!(GEN && (LUT || DUMP)), "general-mode windows take FP32 or FP16 taps");
+// window_consts_kernel).
+template <int WT, bool HALF, int NQ, bool POLAR = false, bool DUMP = false, bool GEN = false>
+__device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
+                                         const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
+                                         float *__restrict__ dst, float *__restrict__ marg,
+                                         const DumpArgs *dump = nullptr, const int rir = 0,
+                                         const float *__restrict__ wc = nullptr) {
+  constexpr bool LUT = !HALF && !DUMP;
+  static_assert(!(GEN && !HALF), "general-mode windows take FP16 taps here");
   constexpr int LSPAN = TILE + WT - 1;
   constexpr int LPG = 64 / NQ;          // lanes per image
   constexpr int TPL = WT / LPG;         // taps per lane per step
@@ -863,10 +1000,8 @@ __device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int ti
   static_assert(WT % LPG == 0, "window must be a multiple of the lanes per image");
 
   __shared__ float tile[NQ][LSPAN];
-  static_assert(!(HALF && LUT), "one tap mode");
-  constexpr bool NARROW = HALF || LUT;  // 8-byte stage record
-  typedef typename StageRec<NARROW>::type Rec;
-  __shared__ Rec stp[SCAP];  // staged records (ImageParams::rec)
+  typedef float2v Rec;
+  __shared__ Rec stp[SCAP];  // staged records (stage_record)
   __shared__ EnumLds es;
   __shared__ float col_p[POLAR ? 64 : 1];  // polar calls: column part of |d| cos(theta)
   __shared__ uint32_t col_xy[DUMP ? 64 : 1];  // enumeration check: column table indices
@@ -887,52 +1022,24 @@ __device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int ti
   const ItemGeom g = item_geom(ra, ax, tile_id, C, c);
 
   // per-lane tap constants
-  float nsg[TPL], sgj[TPL], cth[TPL], sth[TPL];  // FP32 taps
-  float pc0[TPL];                                // FP16 taps: c0 of each tap
-  half2_t pq[NPAIR][SPD];                        // and c1..c5 of tap pairs (2p, 2p + 1)
-  if constexpr (GEN && HALF) {
+  float pc0[TPL];          // FP16 taps: c0 of each tap
+  half2_t pq[NPAIR][SPD];  // and c1..c5 of tap pairs (2p, 2p + 1)
+  if constexpr (HALF) {
+    auto coef = [&](int k, int jj) {
+      if constexpr (GEN) return wc[WC_STRIDE * jj + k];
+      else return poly_table<WT>().c[k][jj];
+    };
 #pragma unroll
-    for (int m = 0; m < TPL; ++m) pc0[m] = wc[WC_STRIDE * (l + LPG * m)];
-#pragma unroll
-    for (int pr = 0; pr < NPAIR; ++pr)
-#pragma unroll
-      for (int k = 0; k < SPD; ++k) {
-        const int m0 = 2 * pr, m1 = 2 * pr + 1;
-        const float a = wc[WC_STRIDE * (l + LPG * m0) + k + 1];
-        const float b = m1 < TPL ? wc[WC_STRIDE * (l + LPG * m1) + k + 1] : 0.0f;
-        pq[pr][k] = half2_t{(_Float16)a, (_Float16)b};
-      }
-  } else if constexpr (GEN) {
-#pragma unroll
-    for (int m = 0; m < TPL; ++m) {
-      const float4 e = *reinterpret_cast<const float4 *>(wc + WC_STRIDE * (l + LPG * m));
-      nsg[m] = e.x;
-      sgj[m] = e.y;
-      cth[m] = e.z;
-      sth[m] = e.w;
-    }
-  } else if constexpr (HALF && !DUMP) {
-    const SincPoly<WT> &P = poly_table<WT>();
-#pragma unroll
-    for (int m = 0; m < TPL; ++m) pc0[m] = P.c[0][l + LPG * m];
+    for (int m = 0; m < TPL; ++m) pc0[m] = coef(0, l + LPG * m);
 #pragma unroll
     for (int pr = 0; pr < NPAIR; ++pr)
 #pragma unroll
       for (int k = 0; k < SPD; ++k) {
         const int m0 = 2 * pr, m1 = 2 * pr + 1;
-        const float a = P.c[k + 1][l + LPG * m0];
-        const float b = m1 < TPL ? P.c[k + 1][l + LPG * m1] : 0.0f;
+        const float a = coef(k + 1, l + LPG * m0);
+        const float b = m1 < TPL ? coef(k + 1, l + LPG * m1) : 0.0f;
         pq[pr][k] = half2_t{(_Float16)a, (_Float16)b};
       }
-  } else if constexpr (!LUT && !DUMP) {
-    const TapConsts<WT> &K = tap_table<WT>();
-#pragma unroll
-    for (int m = 0; m < TPL; ++m) {
-      nsg[m] = -K.sig[l + LPG * m];
-      sgj[m] = K.sig_j[l + LPG * m];
-      cth[m] = K.cth[l + LPG * m];
-      sth[m] = K.sth[l + LPG * m];
-    }
   }
   for (int i = lane; i < NQ * LSPAN; i += 64) (&tile[0][0])[i] = 0.0f;
   float *const th = &tile[h][l];
@@ -941,7 +1048,6 @@ __device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int ti
   // beat the vector-memory path, 0.68 against 0.89 ms on the 32-receiver
   // call); lrow is this lane's first entry of row 0 (rows are WT pairs apart)
   __shared__ __attribute__((aligned(16))) float lds_lut[LUT ? kLutQ * WT * 2 : 4];
-  const float hw = ra.win_hw;  // general mode: taps with |j - f| >= W/2 are masked
   if constexpr (LUT) {
     const float *gl = &lut_table<WT>().p[0][0][0];
     for (int i = lane; i < kLutQ * WT * 2; i += 64) lds_lut[i] = gl[i];
@@ -951,13 +1057,10 @@ __device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int ti
 
   // One step: staged image (record P) on this lane group, taps l + LPG m.
   // The empty asm consumes the record as one value where the step starts,
-  // which keeps its LDS read a single wide read (16 bytes for FP32, 8 for
-  // FP16) issued ahead.
+  // which keeps its LDS read a single 8-byte read issued ahead.
   auto step = [&](const Rec P) {
     __asm__ volatile("" ::"v"(P));
-    uint32_t bw;  // record word that carries the base
-    if constexpr (NARROW || !cq_base(WT, GEN)) bw = __float_as_uint(HALF ? P.y : P.x);
-    else bw = __float_as_uint(P.z);
+    const uint32_t bw = __float_as_uint(HALF ? P.y : P.x);  // record word that carries the base
     const int b = (int)(bw & kBaseMask);
     float *t = th + b;
     if constexpr (HALF) {
@@ -974,7 +1077,7 @@ __device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int ti
         t[LPG * m0] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.x, pc0[m0]), t[LPG * m0]);
         if (m1 < TPL) t[LPG * m1] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.y, pc0[m1]), t[LPG * m1]);
       }
-    } else if constexpr (LUT) {
+    } else {
       // tap = A (L[i] + (1 - fr) (L[i + 1] - L[i])) from row ph of the table
       const uint32_t F = __float_as_uint(P.x);
       const float A = P.y;
@@ -987,117 +1090,45 @@ __device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int ti
         const float2v e = *reinterpret_cast<const float2v *>(row + 2 * LPG * m);
         t[LPG * m] = __builtin_fmaf(A, __builtin_fmaf(al, e.y, e.x), t[LPG * m]);
       }
-    } else if constexpr (GEN) {
-      // general window: no half-period symmetry between the lane's taps; a
-      // tap outside |j - f| < W/2 gets a zero reciprocal
-      const float fs = cq_base(WT, GEN) ? P.x : (float)__float_as_uint(P.x);  // f, or f 2^32
-#pragma unroll
-      for (int m = 0; m < TPL; ++m) {
-        float w = __builtin_fmaf(cth[m], P.y, P.w);
-        w = __builtin_fmaf(sth[m], P.z, w);
-        const float u = __builtin_fmaf(nsg[m], fs, sgj[m]);  // sigma (j - f)
-        const float r = __builtin_fabsf(u) < hw ? __builtin_amdgcn_rcpf(u) : 0.0f;
-        t[LPG * m] = __builtin_fmaf(w, r, t[LPG * m]);
-      }
-    } else {
-      // When TPL is even, tap m + TPL/2 sits half a window period after tap
-      // m, where the Hann term flips sign: its numerator is 2 (C/2) - w_m.
-      float w[TPL];
-#pragma unroll
-      for (int m = 0; m < TPL; ++m) {
-        if (TPL % 2 == 0 && m >= TPL / 2) {
-          w[m] = __builtin_fmaf(2.0f, P.w, -w[m - TPL / 2]);
-        } else {
-          w[m] = __builtin_fmaf(cth[m], P.y, P.w);
-          w[m] = __builtin_fmaf(sth[m], P.z, w[m]);
-        }
-      }
-      const float fs = P.x;  // f
-#pragma unroll
-      for (int m = 0; m < TPL; ++m) {
-        const float u = __builtin_fmaf(nsg[m], fs, sgj[m]);
-        const float r = __builtin_amdgcn_rcpf(u);
-        t[LPG * m] = __builtin_fmaf(w[m], r, t[LPG * m]);
-      }
     }
   };
-  // staged record k (read as one 16-byte access: see step)
+  // staged record k (read as one 8-byte access: see step)
   auto rec = [&](int k) { return stp[k]; };
 
   int ns = 0;  // staged images (wave-uniform)
-  enumerate_shell<POLAR, DUMP>(g, tx, ty, ay, az, column_gain_scale<NARROW || DUMP>(ra), es, col_p, col_xy,
-                               [&](int total, int excl, int cnt) {
-    // Chunks of 64 candidate positions; lane i takes position q0 + i. Its
-    // column is the last one starting at or before it: each column marks its
-    // first position in the chunk, a running maximum over the lanes carries
-    // the marks forward, and the last lane's column carries into the next
-    // chunk (columns start in increasing order).
-    int carry = 0;
-    auto locate = [&](int q0, int &cl, int &nz, float &cg) {
-      es.mark[lane] = 0;
-      wave_sync();
-      const int r = excl - q0;
-      if (cnt > 0 && (uint32_t)r < 64u) es.mark[r] = lane + 1;
-      wave_sync();
-      const int m = max(wave_incl_max(es.mark[lane]), carry);
-      carry = __builtin_amdgcn_readlane(m, 63);
-      cl = max(m - 1, 0);
-      const int4v cr = es.col_run[cl];
-      const int pos = q0 + lane;
-      nz = min(max(pos + (pos < cr.x ? cr.y : cr.z), 0), ra.N[2] - 1);
-      cg = __int_as_float(cr.w);
-    };
-    // the next chunk's column and z table row are found ahead of its use
-    int cl, nz;
-    float cg;
-    locate(0, cl, nz, cg);
-    AxisEntry ez{0.0f, 0.0f, 0.0f, 0.0f};
-    if (lane < total) ez = tz[nz];
-    for (int q = 0; q < total; q += 64) {
-      const int cl_c = cl;
-      const float cg_c = cg;
-      const AxisEntry ez_c = ez;
-      const int nz_c = nz;
-      if (q + 64 < total) {
-        locate(q + 64, cl, nz, cg);
-        if (q + 64 + lane < total) ez = tz[nz];
-      }
+  ShellWalk<POLAR, DUMP, 1> sw(g, tx, ty, ay, az, ra.kappa, es, col_p, col_xy, 0);
+  ChunkWalk<POLAR, DUMP, 1> cw(sw, tz, ra.N[2]);
+  while (cw.advance()) {
+    cw.visit([&](bool live, int cl, int nz, float cg, const AxisEntry ez) {
+      // lanes = candidates: parameters, then compaction into the stage
+      ImageParams p;
+      p.ok = false;
+      if (live) p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
+      const uint64_t okm = __ballot(p.ok);
+      const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
       if constexpr (DUMP) {
-        // delay and amplitude exactly as the table taps compute them
-        ImageParams<true> p;
-        p.ok = false;
-        if (q + lane < total) p = image_params<WT, false, true, POLAR>(ra, g, es.col_s[cl_c], cg_c, ez_c, 0.0f);
-        const uint64_t okm = __ballot(p.ok);
-        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
         uint32_t first = 0;
         if (lane == 0 && okm != 0) first = atomicAdd(dump->count, (uint32_t)__builtin_popcountll(okm));
         first = (uint32_t)__builtin_amdgcn_readlane((int)first, 0);
         if (p.ok && first + (uint32_t)rank < dump->cap) {
-          const uint32_t xy = col_xy[cl_c];
+          const uint32_t xy = col_xy[cl];
           // lattice index per table axis, then per room axis (table axis k is room axis perm[k])
-          const int t0 = ra.lo[0] + (int)(xy >> 16), t1 = ra.lo[1] + (int)(xy & 0xffffu), t2 = ra.lo[2] + nz_c;
+          const int t0 = ra.lo[0] + (int)(xy >> 16), t1 = ra.lo[1] + (int)(xy & 0xffffu), t2 = ra.lo[2] + nz;
           DumpRec d;
           d.rir = rir;
           d.n[0] = ra.perm[0] == 0 ? t0 : (ra.perm[1] == 0 ? t1 : t2);
           d.n[1] = ra.perm[0] == 1 ? t0 : (ra.perm[1] == 1 ? t1 : t2);
           d.n[2] = ra.perm[0] == 2 ? t0 : (ra.perm[1] == 2 ? t1 : t2);
           d.k0 = g.T0 + p.base;
-          d.fq = (__float_as_uint(p.rec.x) >> kBaseBits) << (kBaseBits - 8);  // units of 2^-24
-          d.A = p.rec.y;
+          d.fq = (__float_as_uint(stage_record<false>(p).x) >> kBaseBits) << (kBaseBits - 8);  // units of 2^-24
+          d.A = p.A;
           d.pad = 0;
           dump->rec[first + (uint32_t)rank] = d;
         }
         wave_sync();
-        continue;
+        return;
       }
-      // lanes = candidates: parameters, then compaction into the stage
-      ImageParams<NARROW> p;
-      p.ok = false;
-      if (q + lane < total)
-        p = image_params<WT, HALF, LUT, POLAR, GEN>(ra, g, es.col_s[cl_c], cg_c, ez_c, POLAR ? col_p[cl_c] : 0.0f);
-      const uint64_t okm = __ballot(p.ok);
-      const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
-      if (p.ok) stp[ns + rank] = p.rec;
+      if (p.ok) stp[ns + rank] = stage_record<HALF>(p);
       ns += __builtin_popcountll(okm);
       wave_sync();
       // lanes = taps: NQ staged images per step, one per lane group; the next
@@ -1126,13 +1157,294 @@ __device__ __forceinline__ void accumulate_item(const RoomArgs &ra, const int ti
       }
       ns = rem;
       wave_sync();
-    }
-  });
+    });
+  }
   if constexpr (DUMP) return;
   if (h < ns) step(stp[h]);  // last images, fewer than NQ
 
   wave_sync();
   write_item<WT, NQ>(tile, n_own, dst, marg, lane, 64);
+}
+
+// ---------------------------------------------------------------------------
+// One work item on a workgroup of four waves with FP32 taps, by moments (MOM above).
+//
+// Collection (lanes = images): each wave enumerates its share of the columns; an
+// image's record (t, A) goes to the next slot of the wave's part of an LDS pool
+// and is linked into the wave's list of its integer delay with one exchange on
+// the list's head, so images of one delay in one chunk need no ordering and
+// nothing is lost. When the waves have filled their parts, wave w takes the
+// delays 64 w + lane: the four waves' lists of a delay are linked into one,
+// and each lane walks its list and adds every record's moments into its registers
+// (lanes = delays). A list holds its wave's images in program order and the
+// lists are joined in wave order, so a call always adds in the same order.
+// Four waves share a pool because the walk takes as many steps as the longest of
+// 64 lists: with Poisson lengths of mean 15 that is 1.7 steps per image and
+// lane, with a wave's own pool (256 delays, mean 3.7) 2.6.
+// Convolution: at the end of the item the moments go to LDS planes and
+// matrix instructions form the item's TILE + W - 1 output samples: output
+// o = 16 a + r of row r, column a is the sum over planes and k' of
+// coefficient[k' - r] and plane[16 a + k'], an FP32 16 x 16 x 4 product per
+// four k', whose left operand is the same for all columns; wave w takes a
+// quarter of the k'. Planes are kept at x + x / 16 so that the 16 columns read
+// different banks.
+// ---------------------------------------------------------------------------
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+constexpr int MOM_WAVES = 4;
+constexpr int MOM_SLOTS = 960;  // pool slots per wave: 15 chunks of 64 positions
+constexpr int MOM_END = 8 * MOM_WAVES * MOM_SLOTS;  // end of a list (slots are linked by byte offset in rec)
+static_assert(TILE == 64 * MOM_WAVES && MOM_END < 65536, "one delay per thread, 16-bit links");
+struct MomPool {
+  float2v rec[MOM_WAVES * MOM_SLOTS + 1];  // (t, A); the last slot ends every list: (0, 0)
+  uint32_t head[MOM_WAVES][TILE];
+  uint16_t next[MOM_WAVES * MOM_SLOTS + 4];
+  uint16_t tail[MOM_WAVES][TILE];
+};
+template <int WT, bool EDGE>
+struct MomShape {
+  static constexpr int P = MOM + (EDGE ? 2 : 0);          // planes
+  static constexpr int KS = (WT + 16) / 4;                // matrix steps per plane
+  static constexpr int NBLK = (TILE + WT - 1 + 15) / 16;  // output blocks of 16
+  static constexpr int XN = 16 * NBLK + WT;               // plane entries
+  static constexpr int PL = XN + XN / 16;                 // plane length with the bank skew
+  static constexpr int CL = WT + 32;                      // coefficients per plane, zeros around
+  static_assert(NBLK <= 32 && XN % 16 == 0 && KS % 16 % 4 == 0, "convolution shape");
+};
+
+template <int WT, bool POLAR, bool GEN>
+__device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
+                                            const AxisEntry *__restrict__ tab, const AxisOrigin &org,
+                                            const bool valid, float *__restrict__ dst, float *__restrict__ marg,
+                                            const float *__restrict__ wc) {
+  constexpr bool EDGE = GEN && WT <= kEdgeCap;
+  constexpr bool DIRECT = GEN && WT == 32;  // may hold windows shorter than kDirectWin
+  typedef MomShape<WT, EDGE> Sh;
+  constexpr int P = Sh::P, NT = 64 * MOM_WAVES;
+  constexpr int LM = WT / 2 - 1;
+  constexpr uint32_t END = MOM_END;
+  __shared__ union alignas(16) {
+    MomPool pool;
+    float conv[P * (Sh::PL + Sh::CL)];
+    float part[MOM_WAVES][512];
+  } u;
+  __shared__ EnumLds es_all[MOM_WAVES];
+  __shared__ float col_p_all[POLAR ? MOM_WAVES : 1][POLAR ? 64 : 1];  // column part of |d| cos(theta)
+  __shared__ alignas(16) int more_all[MOM_WAVES];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_own = min(TILE, ra.n_samples - tile_id * TILE);  // may be <= 0 past nS
+  if (!valid) {
+    write_invalid<WT>(n_own, dst, marg, tid, NT);
+    return;
+  }
+  const AxisEntry *__restrict__ tx = tab + ra.off[0];
+  const AxisEntry *__restrict__ ty = tab + ra.off[1];
+  const AxisEntry *__restrict__ tz = tab + ra.off[2];
+  const AxisRange ax = axis_range(ra.lo[0], ra.N[0], ra.inv_period[0], org.e_even[0], org.e_odd[0]);
+  const AxisRange ay = axis_range(ra.lo[1], ra.N[1], ra.inv_period[1], org.e_even[1], org.e_odd[1]);
+  const AxisRange az = axis_range(ra.lo[2], ra.N[2], ra.inv_period[2], org.e_even[2], org.e_odd[2]);
+  const ItemGeom g = item_geom(ra, ax, tile_id, C, c);
+
+  float m[P];  // this thread's delay: sums of A t^p (then the edge taps)
+#pragma unroll
+  for (int p = 0; p < P; ++p) m[p] = 0.0f;
+#pragma unroll
+  for (int v = 0; v < MOM_WAVES; ++v) u.pool.head[v][tid] = END;
+  if (tid == 0) {
+    u.pool.rec[END / 8] = float2v{0.0f, 0.0f};
+    u.pool.next[END / 8] = (uint16_t)END;
+  }
+  const bool direct = DIRECT && 2.0f * ra.win_hw < kDirectWin;
+  // edge polynomial (EDGE): coefficients, f1 and whether a tap is cut
+  float ec[EDGE ? kEdgeCoef : 1], f1 = 1.0f;
+  if constexpr (EDGE) {
+#pragma unroll
+    for (int i = 0; i < kEdgeCoef; ++i) ec[i] = wc[wc_edge(WT) + i];
+    f1 = wc[wc_edge(WT) + kEdgeCoef];
+  }
+
+  // one record into the sums
+  auto add = [&](const float2v r, auto taps) {
+    const float t = r.x, A = r.y;
+    if constexpr (decltype(taps)::value) {
+      // tap j at v = j - f, j = -1 .. 2 (|v| < 2), into sum j + 1
+      const float f = fmaxf(t + 0.5f, 0x1p-24f);
+      const float C2 = A * __builtin_amdgcn_sinf(0.5f * fminf(f, 1.0f - f)) * (float)(0.5 / kPi);
+#pragma unroll
+      for (int j = -1; j <= 2; ++j) {
+        const float v = (float)j - f;
+        const float w = __builtin_fabsf(v) < ra.win_hw
+                            ? __builtin_fmaf(C2, __builtin_amdgcn_cosf(v * ra.inv_win), C2) * __builtin_amdgcn_rcpf(v)
+                            : 0.0f;
+        m[j + 1] += (j & 1) ? w : -w;
+      }
+      return;
+    }
+    const float At = A * t, t2 = t * t, t4 = t2 * t2, t6 = t4 * t2, t8 = t4 * t4;
+    m[0] += A;
+    m[1] += At;
+    m[2] = __builtin_fmaf(A, t2, m[2]);
+    m[3] = __builtin_fmaf(At, t2, m[3]);
+    m[4] = __builtin_fmaf(A, t4, m[4]);
+    m[5] = __builtin_fmaf(At, t4, m[5]);
+    m[6] = __builtin_fmaf(A, t6, m[6]);
+    m[7] = __builtin_fmaf(At, t6, m[7]);
+    m[8] = __builtin_fmaf(A, t8, m[8]);
+    m[9] = __builtin_fmaf(At, t8, m[9]);
+    if constexpr (EDGE) {
+      // left end: inside for f < 1 - f1; right end: inside for f > f1
+      const float ul = fmaxf((0.5f - f1) - t, 0.0f), ur = fmaxf(t + (0.5f - f1), 0.0f);
+      const float xl = ul - 0.5f, xr = ur - 0.5f;
+      float pl = ec[kEdgeCoef - 1], pr = ec[kEdgeCoef - 1];
+#pragma unroll
+      for (int i = kEdgeCoef - 2; i >= 0; --i) {
+        pl = __builtin_fmaf(pl, xl, ec[i]);
+        pr = __builtin_fmaf(pr, xr, ec[i]);
+      }
+      m[MOM] = __builtin_fmaf(A * ul, ul * pl, m[MOM]);
+      m[MOM + 1] = __builtin_fmaf(A * ur, ur * pr, m[MOM + 1]);
+    }
+  };
+  char *const rec0 = reinterpret_cast<char *>(u.pool.rec), *const next0 = reinterpret_cast<char *>(u.pool.next);
+  auto rec_at = [&](uint32_t o) { return *reinterpret_cast<const float2v *>(rec0 + o); };
+  auto next_at = [&](uint32_t o) -> uint16_t & { return *reinterpret_cast<uint16_t *>(next0 + (o >> 2)); };
+  // the list's end links to itself and its record adds zero: a lane whose list
+  // is shorter than the longest goes on adding it
+  auto walk = [&](uint32_t i0, auto taps) {
+    while (__any(i0 != END)) {
+      const uint32_t i1 = next_at(i0);
+      const float2v r0 = rec_at(i0);
+      const float2v r1 = rec_at(i1);
+      i0 = next_at(i1);
+      add(r0, taps);
+      add(r1, taps);
+    }
+  };
+
+  ShellWalk<POLAR, false, MOM_WAVES> sw(g, tx, ty, ay, az, ra.kappa, es_all[wv], col_p_all[POLAR ? wv : 0], nullptr,
+                                        wv);
+  ChunkWalk<POLAR, false, MOM_WAVES> cw(sw, tz, ra.N[2]);
+  const EnumLds &es = es_all[wv];
+  const float *const col_p = col_p_all[POLAR ? wv : 0];
+  __syncthreads();
+  for (;;) {
+    bool more = true;
+    for (int slot = 0; slot < MOM_SLOTS; slot += 64) {
+      more = cw.advance();
+      if (!more) break;
+      cw.visit([&](bool live, int cl, int, float cg, const AxisEntry ez) {
+        ImageParams p;
+        p.ok = false;
+        if (live) p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
+        if (p.ok) {
+          const uint32_t i = (uint32_t)(8 * (wv * MOM_SLOTS + slot + lane));
+          const uint32_t old = atomicExch(&u.pool.head[wv][p.base], i);
+          u.pool.rec[i / 8] = float2v{p.fr - 0.5f, p.A};
+          next_at(i) = (uint16_t)old;
+          if (old == END) u.pool.tail[wv][p.base] = (uint16_t)i;
+        }
+      });
+    }
+    if (lane == 0) more_all[wv] = more ? 1 : 0;
+    __syncthreads();
+    const int4v more4 = *reinterpret_cast<const int4v *>(more_all);
+    uint32_t i0 = END;
+#pragma unroll
+    for (int v = MOM_WAVES - 1; v >= 0; --v) {
+      const uint32_t hv = u.pool.head[v][tid];
+      u.pool.head[v][tid] = END;
+      if (hv != END) {
+        next_at(u.pool.tail[v][tid]) = (uint16_t)i0;
+        i0 = hv;
+      }
+    }
+    if constexpr (DIRECT) {
+      if (direct) walk(i0, std::true_type{});
+      else walk(i0, std::false_type{});
+    } else {
+      walk(i0, std::false_type{});
+    }
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(more4.x | more4.y | more4.z | more4.w)) break;
+  }
+
+  // convolution
+  float *const planes = u.conv, *const coefs = u.conv + P * Sh::PL;
+  for (int i = tid; i < P * Sh::PL; i += NT) planes[i] = 0.0f;
+  const int j2 = EDGE ? (int)wc[wc_edge(WT) + kEdgeCoef + 1] : 0;
+  // coefficient of entry e of a plane: tap j = WT/2 + 15 - e (0 outside the window)
+  for (int e = tid; e < Sh::CL; e += NT) {
+    const int j = WT / 2 + 15 - e;
+    const bool in = j > -WT / 2 && j <= WT / 2;
+    const int jj = in ? (j >= 1 ? j - 1 : -j) : 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      float v = 0.0f;
+      if (DIRECT && direct) {
+        v = (p < 4 && j == p - 1) ? 1.0f : 0.0f;
+      } else if (p >= MOM) {
+        v = (j2 > 0 && j == (p == MOM ? 1 - j2 : j2)) ? 1.0f : 0.0f;
+      } else {
+        if constexpr (GEN) v = wc[p * (WT / 2) + jj];
+        else v = mom_table<WT>().c[p][jj];
+        if (!in) v = 0.0f;
+        if (j < 1 && (p & 1)) v = -v;
+      }
+      coefs[p * Sh::CL + e] = v;
+    }
+  }
+  __syncthreads();
+  {
+    const int x = tid + WT - 1;
+#pragma unroll
+    for (int p = 0; p < P; ++p) planes[p * Sh::PL + x + (x >> 4)] = m[p];
+  }
+  __syncthreads();
+  const int lc = lane & 15, lk = lane >> 4;  // matrix row (coefficients) / column (planes), k group
+  const int a0 = min(lc, Sh::NBLK - 1), a1 = min(lc + 16, Sh::NBLK - 1);
+  // sums of planes 0, 1, 2 and of the others apart (then smallest first): each
+  // rounds at its own, smaller size
+  f4v d0[4], d1[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) d0[i] = d1[i] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int p = P - 1; p >= 0; --p) {
+    const int i = p < 3 ? p : 3;
+    const float *cf = coefs + p * Sh::CL + (lk - lc + 15);
+    const float *b0 = planes + p * Sh::PL + 17 * a0 + lk, *b1 = planes + p * Sh::PL + 17 * a1 + lk;
+    constexpr int KQ = Sh::KS / MOM_WAVES;  // steps of this wave: s0 .. s0 + KQ - 1
+    const int s0 = wv * KQ;
+#pragma unroll
+    for (int k = 0; k < KQ; ++k) {
+      const int s = s0 + k;
+      const float cv = cf[4 * s];
+      d0[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b0[4 * s + (s >> 2)], d0[i], 0, 0, 0);
+      d1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b1[4 * s + (s >> 2)], d1[i], 0, 0, 0);
+    }
+  }
+  __syncthreads();
+  *reinterpret_cast<f4v *>(&u.part[wv][16 * lc + 4 * lk]) = (d0[3] + d0[2]) + (d0[1] + d0[0]);
+  *reinterpret_cast<f4v *>(&u.part[wv][256 + 16 * lc + 4 * lk]) = (d1[3] + d1[2]) + (d1[1] + d1[0]);
+  __syncthreads();
+  // output o: sample o - LM of the tile; before and after it the margins
+  for (int o = tid; o < TILE + WT - 1; o += NT) {
+    const float v = (u.part[0][o] + u.part[3][o]) + (u.part[1][o] + u.part[2][o]);
+    if (o < LM) marg[o] = v;
+    else if (o >= LM + TILE) marg[o - TILE] = v;
+    else if (o - LM < n_own) dst[o - LM] = v;
+  }
+}
+
+// The item function of a kernel's precision.
+template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+__device__ __forceinline__ void run_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
+                                         const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
+                                         float *__restrict__ dst, float *__restrict__ marg,
+                                         const float *__restrict__ wc) {
+  if constexpr (HALF || LUT) tap_item<WT, HALF, 2, POLAR, false, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, nullptr, 0, wc);
+  else moment_item<WT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
 }
 
 // First work item of dispatch position pos (see PlanArgs).
@@ -1178,36 +1490,35 @@ __device__ __forceinline__ SingleItem decode_item(const PlanArgs &pa, uint32_t i
   return si;
 }
 
-template <int WT, bool HALF, int NQ, bool LUT, bool POLAR, bool GEN>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAccWavesPerSimd))) void accumulate_kernel(RoomArgs ra, PlanArgs pa,
-                                                             const AxisEntry *__restrict__ tab_all,
-                                                             const AxisOrigin *__restrict__ origin,
-                                                             const int *__restrict__ valid, float *__restrict__ out,
-                                                             float *__restrict__ part, float *__restrict__ marg,
-                                                             const float *__restrict__ wc) {
+template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+__global__ __launch_bounds__(item_threads(HALF, LUT))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
+accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_all,
+                  const AxisOrigin *__restrict__ origin, const int *__restrict__ valid, float *__restrict__ out,
+                  float *__restrict__ part, float *__restrict__ marg, const float *__restrict__ wc) {
   const uint32_t item = blockIdx.x;
   const SingleItem si = decode_item(pa, item);
   // (for a tile past nS, dst is never written: the tile has no own samples)
   float *dst = (si.C == 1) ? out + (size_t)si.rir * ra.n_samples + (size_t)si.tile_id * TILE
                            : part + (size_t)item * TILE;
   const AxisOrigin org = origin[si.rir];
-  accumulate_item<WT, HALF, NQ, LUT, POLAR, false, GEN>(ra, si.tile_id, si.C, si.c,
-                                                        tab_all + (size_t)si.rir * ra.n_tab, org, valid[si.rir] != 0,
-                                                        dst, marg + (size_t)item * WT, nullptr, 0, wc);
+  run_item<WT, HALF, LUT, POLAR, GEN>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
+                                      valid[si.rir] != 0, dst, marg + (size_t)item * WT, wc);
 }
 
-// Per-tap constants of a general-mode window (one thread per tap of the cap).
+// Constants of a general-mode window (one thread per tap of the cap).
+__device__ __forceinline__ void window_consts(float W, int WT, int half, int jj, float *wc) {
+  if (!half) moment_const_entry((double)W, WT, jj, wc);
+  else if (jj < WT) window_const_entry(W, WT, jj, wc + WC_STRIDE * jj);
+}
 __global__ __launch_bounds__(256) void window_consts_kernel(float W, int WT, int half, float *__restrict__ wc) {
-  const int jj = threadIdx.x;
-  if (jj < WT) window_const_entry(W, WT, half, jj, wc + WC_STRIDE * jj);
+  window_consts(W, WT, half, threadIdx.x, wc);
 }
 // Batch mode: one block per job; jobs without general-mode constants exit.
 __global__ __launch_bounds__(256) void window_consts_batch_kernel(const JobDev *__restrict__ jobs, int half) {
   const JobDev &jb = jobs[blockIdx.x];
   if (!jb.wc) return;
-  const int WT = (int)(2.0f * jb.ra.half_w);
-  const int jj = threadIdx.x;
-  if (jj < WT) window_const_entry(2.0f * jb.ra.win_hw, WT, half, jj, jb.wc + WC_STRIDE * jj);
+  window_consts(2.0f * jb.ra.win_hw, (int)(2.0f * jb.ra.half_w), half, threadIdx.x, jb.wc);
 }
 
 // Enumeration check: the items of a single-room launch, images only.
@@ -1218,8 +1529,8 @@ __global__ __launch_bounds__(64) void enumerate_dump_kernel(RoomArgs ra, PlanArg
                                                             const int *__restrict__ valid, DumpArgs dump) {
   const SingleItem si = decode_item(pa, blockIdx.x);
   const AxisOrigin org = origin[si.rir];
-  accumulate_item<WT, false, 2, false, false, true>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab,
-                                                    org, valid[si.rir] != 0, nullptr, nullptr, &dump, si.rir);
+  tap_item<WT, false, 2, false, true>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
+                                      valid[si.rir] != 0, nullptr, nullptr, &dump, si.rir);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int n) {
@@ -1227,18 +1538,22 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int n) {
   if (i < n) p[i] = v;
 }
 
-// Batch launch: persistent. The grid holds at most the resident waves; each
-// workgroup (one wave) takes item blockIdx.x first, then the next unclaimed
+// Batch launch: persistent. The grid holds at most the resident workgroups; each
+// takes item blockIdx.x first, then the next unclaimed
 // item of the largest-first list from the class's queue counter (which the
 // run sets to the grid size before the launch), until the list is exhausted.
 // Without a queue (queue == null) a workgroup takes every gridDim.x-th item.
 // Every item names its job; the job table carries the room.
-template <int WT, bool HALF, int NQ, bool LUT, bool POLAR, bool GEN>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAccWavesPerSimd))) void accumulate_batch_kernel(
+template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+__global__ __launch_bounds__(item_threads(HALF, LUT))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
+accumulate_batch_kernel(
     const JobDev *__restrict__ jobs, const BatchItem *__restrict__ items, uint32_t n_items, uint32_t *queue,
     const AxisEntry *__restrict__ tab_all, const AxisOrigin *__restrict__ origin, const int *__restrict__ valid,
     float *__restrict__ part, float *__restrict__ marg) {
+  constexpr bool MULTI = item_threads(HALF, LUT) > 64;
   const int lane = threadIdx.x & 63;
+  __shared__ uint32_t next_item;
   uint32_t item = blockIdx.x;
   while (item < n_items) {
     const BatchItem it = items[item];
@@ -1248,16 +1563,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAccWavesPer
     float *dst = (it.slot == 0xffffffffu) ? jb.out + (size_t)it.rir * ra.n_samples + (size_t)it.tile * TILE
                                           : part + (size_t)it.slot * TILE;
     const AxisOrigin org = origin[grir];
-    accumulate_item<WT, HALF, NQ, LUT, POLAR, false, GEN>(ra, it.tile, it.chunks, it.chunk,
-                                                         tab_all + jb.tab_base + (size_t)it.rir * ra.n_tab, org,
-                                                         valid[grir] != 0, dst,
-                                                         marg + (size_t)it.mslot * MARG_UNIT, nullptr, 0, jb.wc);
+    run_item<WT, HALF, LUT, POLAR, GEN>(ra, it.tile, it.chunks, it.chunk,
+                                        tab_all + jb.tab_base + (size_t)it.rir * ra.n_tab, org, valid[grir] != 0, dst,
+                                        marg + (size_t)it.mslot * MARG_UNIT, jb.wc);
     if (queue) {
-      uint32_t next = 0;
-      if (lane == 0) next = atomicAdd(queue, 1u);
-      item = (uint32_t)__builtin_amdgcn_readlane((int)next, 0);
+      if constexpr (MULTI) {
+        if (threadIdx.x == 0) next_item = atomicAdd(queue, 1u);
+        __syncthreads();
+        item = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_item);
+        __syncthreads();
+      } else {
+        uint32_t next = 0;
+        if (lane == 0) next = atomicAdd(queue, 1u);
+        item = (uint32_t)__builtin_amdgcn_readlane((int)next, 0);
+      }
     } else {
       item += gridDim.x;
+      if constexpr (MULTI) __syncthreads();
     }
   }
 }
@@ -1453,10 +1775,6 @@ __global__ __launch_bounds__(64) void reduce_margins_kernel(const JobDev *__rest
 // ---------------------------------------------------------------------------
 // Launchers (called from ism_host.cpp).
 // ---------------------------------------------------------------------------
-// Staged images per step (lane groups of 64 / NQ lanes). Two (half-waves) is
-// the measured best: four images per step halve the broadcast reads per tap
-// but need four LDS tiles and more registers per wave, and ran 12 % slower.
-constexpr int images_per_step(int wt, bool half) { return (void)wt, (void)half, 2; }
 int launch_tables(const RoomArgs &ra, const float *src, const float *rcv, const float *orient, AxisEntry *tab,
                   AxisOrigin *origin, int *valid, int n_rir, hipStream_t st) {
   const int64_t total = (int64_t)n_rir * ra.n_tab;
@@ -1471,8 +1789,8 @@ template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
 static int launch_acc_w(const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                         const AxisOrigin *origin, const int *valid, float *out, float *part, float *marg,
                         const float *wc, hipStream_t st) {
-  hipLaunchKernelGGL((accumulate_kernel<WT, HALF, images_per_step(WT, HALF), LUT, POLAR, GEN>), dim3(n_items),
-                     dim3(64), 0, st, ra, pa, tab, origin, valid, out, part, marg, wc);
+  hipLaunchKernelGGL((accumulate_kernel<WT, HALF, LUT, POLAR, GEN>), dim3(n_items),
+                     dim3(item_threads(HALF, LUT)), 0, st, ra, pa, tab, origin, valid, out, part, marg, wc);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -1572,8 +1890,8 @@ template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
 static int launch_acc_batch_w(const JobDev *jobs, const BatchItem *items, uint32_t n_items, uint32_t grid,
                               uint32_t *queue, const AxisEntry *tab, const AxisOrigin *origin, const int *valid,
                               float *part, float *marg, hipStream_t st) {
-  hipLaunchKernelGGL((accumulate_batch_kernel<WT, HALF, images_per_step(WT, HALF), LUT, POLAR, GEN>),
-                     dim3(grid), dim3(64), 0, st, jobs, items, n_items, queue, tab, origin, valid, part, marg);
+  hipLaunchKernelGGL((accumulate_batch_kernel<WT, HALF, LUT, POLAR, GEN>),
+                     dim3(grid), dim3(item_threads(HALF, LUT)), 0, st, jobs, items, n_items, queue, tab, origin, valid, part, marg);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -121,7 +121,28 @@ struct Plan {
 // call's schedule (ism_schedule) replaces them.
 constexpr double kMinItemTaps = 1.2e5;
 constexpr double kBalanceItems = 49152.0;
-double item_target(double total_taps, int wt, bool half, int64_t n_samples, const ism_schedule *sc) {
+// FP32 items (four waves, a convolution per item) cost images rather than taps:
+// at least kMomMinImages images (below, the fixed part dominates: a single
+// 4800-sample RIR took 30, 24.5, 25 and 40 us per call with items of 160, 780,
+// 1600 and 7800 images), about kMomItems per call (the launch holds 768 at a
+// time; a 32-receiver room took 292, 192, 193 and 203 us with items of 3e3, 16e3,
+// 31e3 and 125e3 images), at most kMomMaxImages (or a kMomMaxItems-th of the call) so
+// that long calls end evenly.
+constexpr double kMomMinImages = 800.0;
+constexpr double kMomItems = 512.0;
+constexpr double kMomMaxImages = 65536.0;
+constexpr double kMomMaxItems = 8192.0;
+double item_target(double total_taps, int wt, bool half, bool mom, int64_t n_samples, const ism_schedule *sc) {
+  if (mom) {
+    double min_taps = kMomMinImages * wt, balance = kMomItems,
+           max_taps = std::max(kMomMaxImages * wt, total_taps / kMomMaxItems);
+    if (sc && sc->min_item_taps > 0.0) min_taps = std::max(1e3, sc->min_item_taps);
+    if (sc && sc->balance_items > 0.0) {
+      balance = std::max(1.0, sc->balance_items);
+      max_taps = total_taps;
+    }
+    return std::max(min_taps, std::min(max_taps, total_taps / balance));
+  }
   double min_taps = kMinItemTaps, balance = kBalanceItems;
   for (const ItemTuning &t : kItemTuning)
     if (t.wt == wt && t.half == (half ? 1 : 0) && n_samples <= t.ns_max) {
@@ -143,10 +164,12 @@ double batch_item_taps(int wt, bool half) {
   return kBatchItemTaps;
 }
 
-// Waves of the accumulate kernel resident on the device at once (256 CUs x
-// 4 SIMDs x the waves per SIMD the kernel is built for), and the default
-// rounds of them over which a single call tapers its tail.
-constexpr double kResidentWaves = 256.0 * 4.0 * kAccWavesPerSimd;
+// Workgroups of the accumulate kernel resident on the device at once (256 CUs x
+// 4 SIMDs x the waves per SIMD the kernel is built for, over its waves per
+// item), and the default rounds of them over which a single call tapers its tail.
+double resident_items(bool half, bool lut) {
+  return 256.0 * 4.0 * waves_per_simd(half, lut) * 64.0 / item_threads(half, lut);
+}
 constexpr double kTailRounds = 1.0;
 
 // Small calls: a call whose work does not give every resident wave an item
@@ -156,7 +179,7 @@ constexpr double kTailRounds = 1.0;
 // 1e4-tap items against 35 us with the earlier floor of an eighth of 1.2e5
 // and 103 us with 1.2e5-tap items).
 constexpr double kSmallItemTaps = 1e4;
-double small_call_floor(double total_taps) { return std::max(kSmallItemTaps, total_taps / kResidentWaves); }
+double small_call_floor(double total_taps, double resident) { return std::max(kSmallItemTaps, total_taps / resident); }
 
 bool valid_schedule(const ism_schedule *sc) {
   if (!sc) return true;
@@ -165,6 +188,28 @@ bool valid_schedule(const ism_schedule *sc) {
     if (!std::isfinite(x)) return false;
   return sc->item_taps >= 0.0 && sc->min_item_taps >= 0.0 && sc->balance_items >= 0.0 && sc->batch_waves >= 0.0 &&
          sc->batch_waves <= 16.0;
+}
+
+// Cuts the tiles of a call into items of about target taps (tapered over the
+// last tail_rounds rounds of the resident items, down to floor_taps): the items
+// per tile into chunks (may be null), their total over all RIRs and the part of
+// it in split tiles. False when the total exceeds a launch.
+bool cut_tiles(const Plan &p, double target, double floor_taps, double tail_rounds, double resident, uint8_t *chunks,
+               uint64_t &n_items, uint64_t &n_split) {
+  n_items = n_split = 0;
+  double rem = p.total_taps;
+  for (int t = p.pa.n_tiles - 1; t >= 0; --t) {  // dispatch order: last tile first
+    const double taps = p.tile_taps[t];
+    double tt = target;
+    if (tail_rounds > 0.0) tt = std::max(floor_taps, std::min(target, rem / (tail_rounds * resident)));
+    const int ch = std::max(1, std::min((int)std::ceil(taps / tt), MAX_CHUNKS));
+    if (chunks) chunks[t] = (uint8_t)ch;
+    if (ch > 1) n_split += (uint64_t)p.n_rir * ch;
+    rem -= taps * p.n_rir;
+    n_items += (uint64_t)p.n_rir * ch;
+    if (n_items > 0x7fffffffULL) return false;
+  }
+  return true;
 }
 
 // sched: the call's schedule (null = the tuned default).
@@ -240,35 +285,51 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   }
   // an explicit item size is used as given
   const bool fixed = sched && sched->item_taps > 0.0;
-  double target = fixed ? std::max(1e3, sched->item_taps) : item_target(p.total_taps, p.wt, p.half, nS, sched);
-  if (!fixed && p.total_taps < kResidentWaves * target) target = std::min(target, small_call_floor(p.total_taps));
+  const bool mom = !p.half && !p.lut;  // FP32: items of images (moments), else of taps
+  double target = fixed ? std::max(1e3, sched->item_taps) : item_target(p.total_taps, p.wt, p.half, mom, nS, sched);
+  const double resident = resident_items(p.half, p.lut);
+  if (!fixed && !mom && p.total_taps < resident * target)
+    target = std::min(target, small_call_floor(p.total_taps, resident));
   // Tail taper: tiles are dispatched last first, and the items of a tile
   // dispatched when the work left (this tile included) is below tail_rounds
   // rounds of the resident waves are cut to that work over tail_rounds x the
   // resident waves, down to target / 8 but not below kSmallItemTaps, so the
   // last waves of a launch finish close together instead of one full-size
-  // item after another.
-  const double tail_rounds =
-      (fixed || !taper) ? 0.0 : (sched && sched->tail_rounds >= 0.0 ? sched->tail_rounds : kTailRounds);
-  const double floor_taps = std::min(target, std::max(kSmallItemTaps, target / 8.0));
-  p.any_split = false;
-  double rem = p.total_taps;
-  for (int pos = 0; pos < pa.n_tiles; ++pos) {
-    const int t = pa.n_tiles - 1 - pos;
-    const double taps = p.tile_taps[t];
-    double tt = target;
-    if (tail_rounds > 0.0) tt = std::max(floor_taps, std::min(target, rem / (tail_rounds * kResidentWaves)));
-    int ch = (int)std::ceil(taps / tt);
-    ch = std::max(1, std::min(ch, MAX_CHUNKS));
-    pa.chunks[t] = (uint8_t)ch;
-    if (ch > 1) p.any_split = true;
-    rem -= taps * p.n_rir;
+  // item after another. FP32 items end with a convolution, so theirs are only
+  // halved, over half a round (a call of 4 RIRs of 11200 samples: 79 us with a
+  // full taper, 74 without any; 16 RIRs: 180 and 196 us).
+  auto rounds = [&](double deflt) {
+    return (fixed || !taper) ? 0.0 : (sched && sched->tail_rounds >= 0.0 ? sched->tail_rounds : deflt);
+  };
+  auto taps_floor = [](double tgt) { return std::min(tgt, std::max(kSmallItemTaps, tgt / 8.0)); };
+  // FP32 calls take fewer, larger items than the other taps, but ask for the
+  // workspace of items cut by taps: a call's workspace, and with it what fits a
+  // fixed one, does not depend on how its items are cut, and a schedule that
+  // asks for more items than that is cut by taps as well
+  uint64_t n_items = 0, n_split = 0, ws_items = 0, ws_split = 0;
+  if (mom && !fixed && taper) {
+    double tt = item_target(p.total_taps, p.wt, false, false, nS, sched);
+    const double res = resident_items(true, false);
+    if (p.total_taps < res * tt) tt = std::min(tt, small_call_floor(p.total_taps, res));
+    if (!cut_tiles(p, tt, taps_floor(tt), rounds(kTailRounds), res, pa.chunks, ws_items, ws_split))
+      return ISM_E_TOO_LARGE;
+    p.any_split = ws_split > 0;
+  }
+  if (ws_items == 0 || target >= p.total_taps / (double)ws_items) {
+    uint8_t chunks[MAX_TILES];
+    if (!cut_tiles(p, target, mom ? target / 2.0 : taps_floor(target), rounds(mom ? kTailRounds / 2.0 : kTailRounds),
+                   resident, chunks, n_items, n_split))
+      return ISM_E_TOO_LARGE;
+    if (ws_items == 0 || (n_items <= ws_items && n_split <= ws_split)) {
+      std::memcpy(pa.chunks, chunks, (size_t)pa.n_tiles);
+      p.any_split = n_split > 0;
+      if (ws_items == 0) ws_items = n_items, ws_split = n_split;
+    }
   }
   uint64_t acc = 0;
   for (int pos = 0; pos < pa.n_tiles; ++pos) {
     if (pos % PLAN_BLK == 0) pa.first_blk[pos / PLAN_BLK] = (uint32_t)acc;
     acc += (uint64_t)p.n_rir * pa.chunks[pa.n_tiles - 1 - pos];
-    if (acc > 0x7fffffffULL) return ISM_E_TOO_LARGE;
   }
   pa.first_blk[(pa.n_tiles + PLAN_BLK - 1) / PLAN_BLK] = (uint32_t)acc;
   p.n_items = (uint32_t)acc;
@@ -282,7 +343,10 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   p.off_wc = align_up(p.off_marg + sizeof(float) * (size_t)p.n_items * p.wt);
   // host-position calls copy src then rcv here
   p.off_pos = align_up(p.off_wc + (p.gen ? sizeof(float) * WC_STRIDE * (size_t)p.wt : 0));
-  p.ws_bytes = align_up(p.off_pos + sizeof(float) * 3 * ((size_t)n_src + (size_t)n_rcv));
+  size_t o = align_up(p.off_part + (ws_split > 0 ? sizeof(float) * (size_t)ws_items * TILE : 0));
+  o = align_up(o + sizeof(float) * (size_t)ws_items * p.wt);
+  o = align_up(o + (p.gen ? sizeof(float) * WC_STRIDE * (size_t)p.wt : 0));
+  p.ws_bytes = align_up(o + sizeof(float) * 3 * ((size_t)n_src + (size_t)n_rcv));
   return ISM_OK;
 }
 
@@ -713,17 +777,32 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
   int class_wt[kMaxClasses] = {}, class_gen[kMaxClasses] = {};
   std::vector<int> job_cls(n_jobs);
   uint64_t tab_entries = 0, n_rir = 0, n_items = 0, slots = 0, n_red = 0, marg_units = 0, wc_floats = 0,
-           max_chunks = 0;
+           max_chunks = 0, ws_items = 0, ws_slots = 0, ws_marg = 0;  // ws: counts the workspace is sized for
   std::vector<uint64_t> bucket_count((size_t)kMaxClasses * kCostBuckets, 0);
   for (int j = 0; j < n_jobs; ++j) {
     Plan &p = plans[j];
     if (!(sched && sched->item_taps > 0.0)) {
       ism_schedule js{};
       if (sched) js = *sched;
-      const double t = std::min(batch_item_taps(p.wt, p.half), item_target(batch_taps, p.wt, p.half, p.ra.n_samples, sched));
+      const bool mom = !p.half && !p.lut;
+      double t = item_target(batch_taps, p.wt, p.half, mom, p.ra.n_samples, sched);
+      if (!mom) t = std::min(t, batch_item_taps(p.wt, p.half));
       // a batch too small to give every resident wave an item of that size is
       // spread over them instead (the small-call rule of single calls)
-      js.item_taps = batch_taps < kResidentWaves * t ? std::min(t, small_call_floor(batch_taps)) : t;
+      const double resident = resident_items(p.half, p.lut);
+      js.item_taps = !mom && batch_taps < resident * t ? std::min(t, small_call_floor(batch_taps, resident)) : t;
+      if (mom) {  // the workspace is that of items cut by taps, as for single calls
+        const double res = resident_items(true, false);
+        double tt = std::min(batch_item_taps(p.wt, false),
+                             item_target(batch_taps, p.wt, false, false, p.ra.n_samples, sched));
+        if (batch_taps < res * tt) tt = std::min(tt, small_call_floor(batch_taps, res));
+        js.item_taps = std::max(js.item_taps, tt);
+        uint64_t n = 0, ns = 0;
+        if (!cut_tiles(p, tt, tt, 0.0, res, nullptr, n, ns)) return ISM_E_TOO_LARGE;
+        ws_items += n;
+        ws_slots += ns;
+        ws_marg += n * (uint64_t)(p.wt / MARG_UNIT);
+      }
       const int stt = make_plan(&jobs[j].room, jobs[j].n_src, jobs[j].n_rcv, precision, p, &js, false);
       if (stt != ISM_OK) return stt;
     }
@@ -766,11 +845,12 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     bp.st.class_wt[k] = class_wt[k];
     bp.st.class_gen[k] = class_gen[k];
     // persistent grid: the tuned workgroups per SIMD (or the schedule's)
-    int waves = kAccWavesPerSimd;
+    int waves = waves_per_simd(precision == ISM_FP16, precision == ISM_FP32_LUT);
     for (const BatchTuning &t : kBatchTuning)
       if (t.wt == class_wt[k] && t.half == (precision == ISM_FP16 ? 1 : 0)) waves = t.waves;
     if (sched && sched->batch_waves > 0.0) waves = std::max(1, (int)std::lround(sched->batch_waves));
-    bp.st.class_grid[k] = (uint32_t)std::min<uint64_t>(bp.st.class_count[k], 1024ull * (uint64_t)waves);
+    bp.st.class_grid[k] = (uint32_t)std::min<uint64_t>(
+        bp.st.class_count[k], 1024ull * (uint64_t)waves * 64 / item_threads(precision == ISM_FP16, precision == ISM_FP32_LUT));
   }
   bp.st.n_jobs = (uint32_t)n_jobs;
   bp.st.any_gen = wc_floats > 0 ? 1u : 0u;
@@ -780,41 +860,49 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
   bp.st.polar = polar ? 1u : 0u;
   bp.st.n_rir = (uint32_t)n_rir;
   bp.st.n_red = (uint32_t)n_red;
-  size_t o = 0;
-  bp.st.off_jobs = o;
-  o = align_up(o + sizeof(JobDev) * (size_t)n_jobs);
-  bp.st.off_rirs = o;
-  o = align_up(o + sizeof(BatchRir) * (size_t)n_rir);
-  bp.st.off_items = o;
-  o = align_up(o + sizeof(BatchItem) * (size_t)n_items);
-  bp.st.off_red = o;
-  o = align_up(o + sizeof(BatchReduce) * (size_t)n_red);
+  ws_items = std::max(ws_items, n_items);
+  ws_slots = std::max(ws_slots, slots);
+  ws_marg = std::max(ws_marg, marg_units);
+  if (ws_items > 0x7fffffffULL || ws_slots > 0xffffffffULL || ws_marg > 0xffffffffULL) return ISM_E_TOO_LARGE;
   // positions of every job (ism_simulate_batch copies host positions here)
-  bp.st.off_pos = o;
   bp.pos_off.resize(n_jobs);
   size_t pos_floats = 0;
   for (int j = 0; j < n_jobs; ++j) {
     bp.pos_off[j] = pos_floats;
     pos_floats += 3 * ((size_t)jobs[j].n_src + (size_t)jobs[j].n_rcv * (jobs[j].orient ? 2 : 1));
   }
-  o = align_up(o + sizeof(float) * pos_floats);
-  bp.st.off_valid = o;
-  o = align_up(o + sizeof(int) * n_rir);
-  bp.st.off_origin = o;
-  o = align_up(o + sizeof(AxisOrigin) * n_rir);
-  bp.st.off_tab = o;
-  o = align_up(o + sizeof(AxisEntry) * tab_entries);
-  bp.st.off_part = o;
-  o = align_up(o + sizeof(float) * (size_t)slots * TILE);
-  bp.st.off_marg = o;
-  o = align_up(o + sizeof(float) * MARG_UNIT * (size_t)marg_units);
-  // work-queue counters of the persistent launches, one per window class
-  bp.st.off_queue = o;
-  o = align_up(o + sizeof(uint32_t) * kMaxClasses);
-  // general-mode window constants, one block per such job
-  bp.st.off_wc = o;
-  o = align_up(o + sizeof(float) * (size_t)wc_floats);
-  bp.ws_bytes = o;
+  auto layout = [&](uint64_t items, uint64_t part_slots, uint64_t marg, BatchState &st) {
+    size_t o = 0;
+    st.off_jobs = o;
+    o = align_up(o + sizeof(JobDev) * (size_t)n_jobs);
+    st.off_rirs = o;
+    o = align_up(o + sizeof(BatchRir) * (size_t)n_rir);
+    st.off_items = o;
+    o = align_up(o + sizeof(BatchItem) * (size_t)items);
+    st.off_red = o;
+    o = align_up(o + sizeof(BatchReduce) * (size_t)n_red);
+    st.off_pos = o;
+    o = align_up(o + sizeof(float) * pos_floats);
+    st.off_valid = o;
+    o = align_up(o + sizeof(int) * n_rir);
+    st.off_origin = o;
+    o = align_up(o + sizeof(AxisOrigin) * n_rir);
+    st.off_tab = o;
+    o = align_up(o + sizeof(AxisEntry) * tab_entries);
+    st.off_part = o;
+    o = align_up(o + sizeof(float) * (size_t)part_slots * TILE);
+    st.off_marg = o;
+    o = align_up(o + sizeof(float) * MARG_UNIT * (size_t)marg);
+    // work-queue counters of the persistent launches, one per window class
+    st.off_queue = o;
+    o = align_up(o + sizeof(uint32_t) * kMaxClasses);
+    // general-mode window constants, one block per such job
+    st.off_wc = o;
+    return align_up(o + sizeof(float) * (size_t)wc_floats);
+  };
+  BatchState unused;
+  bp.ws_bytes = layout(ws_items, ws_slots, ws_marg, unused);
+  bp.ws_bytes = std::max(bp.ws_bytes, layout(n_items, slots, marg_units, bp.st));
   if (!fill) return ISM_OK;
 
   // pass 2: tables. Margin records are numbered in (job, tile, RIR, chunk)

@@ -23,9 +23,9 @@ constexpr int MARG_UNIT = 32;
 // constants (exact mode); any other W <= 256 runs with the next cap and
 // per-call constants, masking the taps outside |j - f| < W/2 (general mode).
 constexpr int MAX_WINDOW = 256;
-// Per-tap constants of a general-mode window, 8 floats per tap jj of the cap:
-// FP32 taps (-sigma, sigma j, cos(2 pi j / W), sin(2 pi j / W), 0 ...),
-// FP16 taps (c0, c1, ..., c5, 0, 0) of the tap's interpolant.
+// Constants of a general-mode window: 8 floats per tap of the cap. FP16 taps:
+// (c0, c1, ..., c5, 0, 0) of tap jj's interpolant; FP32: the moment coefficients
+// of the taps j >= 1 and the edge polynomial (wc_edge in ism_device.hip).
 constexpr int WC_STRIDE = 8;
 // Reduce kernels: a run of at least RED_SLICE_MIN partials or margins of one
 // sample is summed as RED_SLICES consecutive slices (each in order from its
@@ -39,8 +39,11 @@ constexpr int kMaxBatchClasses = 8;
 // Work items per tile are capped so the per-tile chunk count fits a byte.
 constexpr int MAX_CHUNKS = 255;
 // Waves per SIMD the accumulate kernels are built for (their LDS and VGPR
-// budget); the planner sizes the tail taper of a launch with it.
-constexpr int kAccWavesPerSimd = 7;
+// budget) and threads per work item: one wave for FP16 and table taps, four
+// waves that share a 43 KB image pool for FP32. The planner sizes items and the
+// tail taper of a launch with them.
+constexpr int waves_per_simd(bool half, bool lut) { return half || lut ? 7 : 3; }
+constexpr int item_threads(bool half, bool lut) { return half || lut ? 64 : 256; }
 
 // Per-call room constants, passed by value as a kernel argument. Lengths are in
 // metres, delays in samples. Float-float pairs (hi, lo) carry double-precision

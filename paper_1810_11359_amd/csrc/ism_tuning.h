@@ -1,12 +1,14 @@
 // Work-item schedule per window length, tap precision and RIR length, read by
-// the host planner, and the grid of the persistent batch launch. Written by
+// the host planner, and the grid of the persistent batch launch. The rows half = 0
+// cut the items of table taps and size the workspace of FP32 calls, whose items
+// are cut by images (item_target in ism_host.cpp). Written by
 // paper_1810_11359_amd/autotune.py from timings on the target GPU (AMD Radeon Graphics).
 //   min_item_taps  estimated taps of the smallest work item
 //   balance_items  items a large call is split into (about eight per
 //                  resident wave), which sets the item size of large calls
 //   ns_max         the entry applies to RIRs of at most this many samples
 //                  (first match in table order)
-//   waves          workgroups per SIMD of a persistent batch launch
+//   waves          waves per SIMD of a persistent batch launch
 //   item_taps      largest work item of a batch job (estimated taps)
 //
 // Score: geometric mean over the bucket's workloads of kernel time relative
@@ -85,7 +87,7 @@ constexpr ItemTuning kItemTuning[] = {
 
 constexpr BatchTuning kBatchTuning[] = {
     {64, 1, 6, 500000},
-    {64, 0, 6, 500000},
+    {64, 0, 3, 500000},
 };
 
 }  // namespace ism
