@@ -1,9 +1,9 @@
 // HIP kernels of the Image Source Method for gfx950 (MI355X).
 //
 // Three kernels per call:
-//   tables_kernel      per (RIR, axis, lattice index): displacement of the image
-//                      coordinate from the receiver in samples (float-float) and
-//                      the axis factor of the reflection gain (Sec. 2.1, Eq. (1)
+//   tables_kernel      per (RIR, axis, lattice index): square of the displacement
+//                      of the image coordinate from the receiver in samples
+//                      (FP64) and the axis factor of the reflection gain (Sec. 2.1, Eq. (1)
 //                      and the gain rule below it); for directional receivers
 //                      also the displacement's share of the projection onto the
 //                      receiver's orientation. Also flags invalid pairs.
@@ -20,9 +20,11 @@
 //   reduce_kernel      sums, in a fixed order, the partial tiles of tiles that
 //                      were split over several work items.
 //
-// Geometry and accumulation are FP32 only; delays use error-free
-// transformations so that the fractional delay keeps ~1e-7 sample accuracy at
-// 1e5-sample distances.
+// Squared distances and delays are FP64 (gfx950 issues FP64 additions,
+// multiplications, fused multiply-adds, roundings and conversions at the FP32
+// rate: 4.5 to 5.4 clocks per wave instruction measured against 4.35), so the
+// fractional delay keeps ~1e-8 sample accuracy at 1e5-sample distances; gains,
+// taps and accumulation are FP32.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -45,52 +47,16 @@ static_assert(TILE <= (1 << kBaseBits), "tile-local bases must fit the record");
 // The delay fraction of the table-tap record, in units of 2^-kFracBits.
 constexpr int kFracBits = 32 - kBaseBits;
 
-// ---------------------------------------------------------------------------
-// Float-float building blocks (Dekker / Knuth error-free transformations).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void two_sum(float a, float b, float &s, float &e) {
-  s = a + b;
-  float bb = s - a;
-  e = (a - (s - bb)) + (b - bb);
-}
-__device__ __forceinline__ void fast_two_sum(float a, float b, float &s, float &e) {  // |a| >= |b|
-  s = a + b;
-  e = b - (s - a);
-}
-__device__ __forceinline__ void two_prod(float a, float b, float &p, float &e) {
-  p = a * b;
-  e = __builtin_fmaf(a, b, -p);
-}
-__device__ __forceinline__ void ff_mul(float ah, float al, float bh, float bl, float &ch, float &cl) {
-  float p, e;
-  two_prod(ah, bh, p, e);
-  e = __builtin_fmaf(ah, bl, e);
-  e = __builtin_fmaf(al, bh, e);
-  fast_two_sum(p, e, ch, cl);
-}
-// (b + bl)^e for e >= 0 by binary powering in float-float (0^0 = 1): the
-// reflection coefficient keeps its double-precision value, so the gain of an
-// image many reflections deep is accurate to a few FP32 ulp.
-__device__ float ff_pow(float b, float b_lo, int e) {
-  float rh = 1.0f, rl = 0.0f, bh = b, bl = b_lo;
+// b^e for e >= 0 by binary powering (0^0 = 1), in FP64: the gain of an image many
+// reflections deep is accurate to its FP32 rounding.
+__device__ double int_pow(double b, int e) {
+  double r = 1.0;
   while (e > 0) {
-    if (e & 1) ff_mul(rh, rl, bh, bl, rh, rl);
+    if (e & 1) r *= b;
     e >>= 1;
-    if (e) ff_mul(bh, bl, bh, bl, bh, bl);
+    b *= b;
   }
-  return rh + rl;
-}
-// a^2 of a float-float value, as float-float.
-__device__ __forceinline__ void ff_sq(float h, float l, float &sh, float &sl) {
-  two_prod(h, h, sh, sl);
-  sl = __builtin_fmaf(2.0f * h, l, sl);
-}
-// (ah, al) - (bh, bl), renormalised.
-__device__ __forceinline__ void ff_sub(float ah, float al, float bh, float bl, float &ch, float &cl) {
-  float s, e;
-  two_sum(ah, -bh, s, e);
-  e += al - bl;
-  fast_two_sum(s, e, ch, cl);
+  return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -436,38 +402,24 @@ __device__ __forceinline__ AxisEntry table_entry(const RoomArgs &ra, const float
   const float s = s3[ra.perm[a]], r = r3[ra.perm[a]];
   // Eq. (1): even n -> n L + s, odd n -> (n + 1) L - s.
   const bool odd = (n & 1) != 0;
-  const float m = (float)(odd ? n + 1 : n);
-  float p, pe;
-  two_prod(m, ra.L_hi[a], p, pe);
-  pe = __builtin_fmaf(m, ra.L_lo[a], pe);
-  float t, te;
-  two_sum(odd ? -s : s, -r, t, te);  // exact
-  float u, ue;
-  two_sum(p, t, u, ue);
-  ue += pe + te;
-  fast_two_sum(u, ue, u, ue);
-  // times fs / c: displacement in samples
-  float v, ve;
-  two_prod(u, ra.q_hi, v, ve);
-  ve = __builtin_fmaf(u, ra.q_lo, ve);
-  ve = __builtin_fmaf(ue, ra.q_hi, ve);
-  fast_two_sum(v, ve, v, ve);
+  const double L = (double)ra.L_hi[a] + (double)ra.L_lo[a], q = (double)ra.q_hi + (double)ra.q_lo;
+  // displacement in samples
+  const double v = ((double)(odd ? n + 1 : n) * L + ((odd ? -(double)s : (double)s) - (double)r)) * q;
   // Gain factor: the path from image n crosses |floor(n/2)| copies of the wall
   // at 0 and |ceil(n/2)| copies of the wall at L along this axis.
   const int e0 = abs(n >> 1), e1 = abs((n + 1) >> 1);
-  const float g = ff_pow(ra.beta[2 * a], ra.beta_lo[2 * a], e0) * ff_pow(ra.beta[2 * a + 1], ra.beta_lo[2 * a + 1], e1);
-  // the enumeration only needs the square of the displacement
-  float sq, sqe;
-  ff_sq(v, ve, sq, sqe);
+  const double g = int_pow((double)ra.beta[2 * a] + (double)ra.beta_lo[2 * a], e0) *
+                   int_pow((double)ra.beta[2 * a + 1] + (double)ra.beta_lo[2 * a + 1], e1);
   // receiver orientation (polar calls): the displacement's share of the
   // projection onto the unit orientation, whose three shares add up to
   // |d| cos(theta) in samples
   float proj = 0.0f;
   if (o3) {
     const float inv = __builtin_amdgcn_rsqf(o3[0] * o3[0] + o3[1] * o3[1] + o3[2] * o3[2]);
-    proj = v * (o3[ra.perm[a]] * inv);
+    proj = (float)v * (o3[ra.perm[a]] * inv);
   }
-  return AxisEntry{sq, sqe, g, proj};
+  // the enumeration only needs the square of the displacement
+  return AxisEntry{v * v, (float)g, proj};
 }
 
 // Validity of a pair (both points strictly inside, distinct) and the family
@@ -542,15 +494,15 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
   return v;
 }
-// Inclusive running maximum over the 64 lanes of non-negative values, same
-// lane pattern as wave_incl_scan.
-__device__ __forceinline__ int wave_incl_max(int v) {
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+// Inclusive running maximum over the 64 lanes of unsigned values, same lane
+// pattern as wave_incl_scan.
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
   return v;
 }
 __device__ __forceinline__ void wave_sync() {
@@ -586,10 +538,16 @@ __device__ __forceinline__ AxisRange axis_range(int lo, int N, float inv_p, floa
   a.n_odd = (float)max(mo1 - mo0 + 1, 0);
   return a;
 }
-__device__ __forceinline__ int first_ge(const AxisRange &a, float b) {
-  const float ce = fminf(fmaxf(ceilf(__builtin_fmaf(b, a.inv_p, a.c_even)), 0.0f), a.n_even);
-  const float co = fminf(fmaxf(ceilf(__builtin_fmaf(b, a.inv_p, a.c_odd)), 0.0f), a.n_odd);
-  return (int)(ce + co);
+__device__ __forceinline__ float first_ge_f(const AxisRange &a, float b) {
+  const float ce = __builtin_amdgcn_fmed3f(ceilf(__builtin_fmaf(b, a.inv_p, a.c_even)), 0.0f, a.n_even);
+  const float co = __builtin_amdgcn_fmed3f(ceilf(__builtin_fmaf(b, a.inv_p, a.c_odd)), 0.0f, a.n_odd);
+  return ce + co;
+}
+__device__ __forceinline__ int first_ge(const AxisRange &a, float b) { return (int)first_ge_f(a, b); }
+
+// Entry i of a table (uniform base, 32-bit offset).
+__device__ __forceinline__ AxisEntry entry_at(const AxisEntry *__restrict__ t, int i) {
+  return *reinterpret_cast<const AxisEntry *>(reinterpret_cast<const char *>(t) + (uint32_t)(i << 4));
 }
 
 // ---------------------------------------------------------------------------
@@ -618,10 +576,10 @@ typedef float float2v __attribute__((ext_vector_type(2)));
 // positions [excl_c, excl_c + n1_c + n2_c), its first run of z indices
 // (z1_c ..) then its second (z2_c ..).
 struct EnumLds {
-  int mark[64];        // per chunk of 64 positions: column lane + 1 where a column starts
+  uint32_t mark[64];   // per chunk of 64 positions: column lane + 1 where a column starts
   int4v col_run[64];   // (excl + n1, z1 - excl, z2 - n1 - excl, gain bits): position p
                        // of the column has z index p + (p < excl + n1 ? z1 - excl : z2 - n1 - excl)
-  float2v col_s[64];   // column part of the squared distance (float-float)
+  double col_s[64];    // column part of the squared distance
   // per x lane of the row batch: (first column << 11) | first y table index
   // (column counts stay below 64 * 2048 = 2^17, table indices below 2^11)
   uint32_t nx_col[64];
@@ -633,7 +591,7 @@ struct ItemGeom {
   int T0, T1;                    // output samples [T0, T1) of the tile (empty past nS)
   int K1;                        // owned integer delays: k0 in [T0, K1)
   float R0, R1;                  // shell radii in samples, widened by 2
-  float r1h, r1l, r0h, r0l;      // their squares (float-float)
+  double r1, r0;                 // their squares (r0 = 0 where R0 < 0)
   int nx_a, nx_b;                // x table indices of the slab
 };
 
@@ -647,10 +605,8 @@ __device__ __forceinline__ ItemGeom item_geom(const RoomArgs &ra, const AxisRang
   // exactly on its integer delay.
   g.R1 = (float)g.K1 + 2.0f;
   g.R0 = (float)g.T0 - 2.0f;
-  two_prod(g.R1, g.R1, g.r1h, g.r1l);
-  g.r0h = 0.0f;
-  g.r0l = 0.0f;
-  if (g.R0 > 0.0f) two_prod(g.R0, g.R0, g.r0h, g.r0l);
+  g.r1 = (double)g.R1 * (double)g.R1;
+  g.r0 = g.R0 > 0.0f ? (double)g.R0 * (double)g.R0 : 0.0;
   // Slab of the shell along the x displacement owned by chunk c of C.
   float dlo = -INFINITY, dhi = INFINITY;
   if (c > 0) dlo = -g.R1 + (2.0f * g.R1) * ((float)c / (float)C);
@@ -702,11 +658,9 @@ struct ShellWalk {
         int ny_lo = 0;
         ny_cnt = 0;
         if (nxi < g.nx_b) {
-          const AxisEntry ex = tx[nxi];
-          float rh, rl;
-          ff_sub(g.r1h, g.r1l, ex.sq_hi, ex.sq_lo, rh, rl);
+          const float rh = (float)(g.r1 - entry_at(tx, nxi).sq);
           if (rh > 0.0f) {
-            const float R = __builtin_sqrtf(rh) + 1.0f;
+            const float R = __builtin_amdgcn_sqrtf(rh) + 1.0f;
             ny_lo = first_ge(ay, -R);
             ny_cnt = first_ge(ay, R) - ny_lo;
           }
@@ -727,46 +681,32 @@ struct ShellWalk {
       // x lane of the batch's first column)
       es.mark[lane] = 0;
       wave_sync();
-      if (ny_cnt > 0 && (uint32_t)(col0 - cb * 64) < 64u) es.mark[col0 - cb * 64] = lane + 1;
+      if (ny_cnt > 0 && (uint32_t)(col0 - cb * 64) < 64u) es.mark[col0 - cb * 64] = (uint32_t)lane + 1u;
       wave_sync();
       const uint64_t before = __ballot(ny_cnt > 0 && col0 <= cb * 64);
-      const int xm = max(wave_incl_max(es.mark[lane]), 64 - (int)__builtin_clzll(before | 1u));
-      int z1 = 0, n1 = 0, z2 = 0, n2 = 0;
-      float cg = 0.0f;
-      if (gcol < ncols) {
-        const int i = xm - 1;
-        const uint32_t xc = es.nx_col[i];
-        const AxisEntry ex = tx[nx0 + i];
-        const int iy = (int)(xc & 0x7ffu) + (gcol - (int)(xc >> 11));
-        const AxisEntry ey = ty[iy];
-        if constexpr (DUMP) col_xy[lane] = ((uint32_t)(nx0 + i) << 16) | (uint32_t)iy;
-        float sh, sl;
-        two_sum(ex.sq_hi, ey.sq_hi, sh, sl);
-        sl += ex.sq_lo + ey.sq_lo;
-        fast_two_sum(sh, sl, sh, sl);
-        es.col_s[lane] = float2v{sh, sl};
-        if constexpr (POLAR) col_p[lane] = ex.proj + ey.proj;  // column part of |d| cos(theta)
-        cg = (ex.gain * ey.gain) * gscale;
-        float rh, rl;
-        ff_sub(g.r1h, g.r1l, sh, sl, rh, rl);
-        if (rh > 0.0f) {
-          const float zmax = __builtin_sqrtf(rh) + 1.0f;
-          float zmin = 0.0f;
-          if (g.R0 > 0.0f) {
-            float hh, hl;
-            ff_sub(g.r0h, g.r0l, sh, sl, hh, hl);
-            if (hh > 0.0f) zmin = fmaxf(__builtin_sqrtf(hh) - 1.0f, 0.0f);
-          }
-          // displacements in [-zmax, -zmin) and [zmin, zmax): two runs of the
-          // table (contiguous when zmin = 0)
-          z1 = first_ge(az, -zmax);
-          n1 = first_ge(az, -zmin) - z1;
-          z2 = first_ge(az, zmin);
-          n2 = first_ge(az, zmax) - z2;
-        }
-      }
+      const uint32_t xm = max(wave_incl_max(es.mark[lane]), 64u - (uint32_t)__builtin_clzll(before | 1u));
+      // (columns past the last repeat it and take no candidates)
+      const int i = (int)xm - 1;
+      const uint32_t xc = es.nx_col[i];
+      const int iy = (int)(xc & 0x7ffu) + (min(gcol, ncols - 1) - (int)(xc >> 11));
+      const AxisEntry ex = entry_at(tx, nx0 + i), ey = entry_at(ty, iy);
+      if constexpr (DUMP) col_xy[lane] = ((uint32_t)(nx0 + i) << 16) | (uint32_t)iy;
+      const double S = ex.sq + ey.sq;
+      es.col_s[lane] = S;
+      if constexpr (POLAR) col_p[lane] = ex.proj + ey.proj;  // column part of |d| cos(theta)
+      const float cg = (ex.gain * ey.gain) * gscale;
+      const float rh = (float)(g.r1 - S), hh = (float)(g.r0 - S);
+      const float zmax = __builtin_amdgcn_sqrtf(fmaxf(rh, 0.0f)) + 1.0f;
+      const float zmin = fmaxf(__builtin_amdgcn_sqrtf(fmaxf(hh, 0.0f)) - 1.0f, 0.0f);
+      // displacements in [-zmax, -zmin) and [zmin, zmax): two runs of the
+      // table (contiguous when zmin = 0)
+      const float f1 = first_ge_f(az, -zmax), f2 = first_ge_f(az, zmin);
+      const bool some = gcol < ncols && rh > 0.0f;
+      const float m1 = first_ge_f(az, -zmin) - f1;
+      const int z1 = (int)f1, z2 = (int)f2;
+      const int n1 = some ? (int)m1 : 0;
+      cnt = some ? (int)(m1 + (first_ge_f(az, zmax) - f2)) : 0;
       cb += NW;
-      cnt = n1 + n2;
       const int incl = wave_incl_scan(cnt);
       total = __builtin_amdgcn_readlane(incl, 63);
       excl = incl - cnt;
@@ -782,7 +722,7 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 // Parameters of one image candidate (column part cs of the squared distance,
 // column gain cgain = fs / (4 pi c) times the x and y gains, z table row ez). ok
 // is false when the tile does not own the image. base = k0 - T0, fr the delay
-// fraction in [0, 1 - 2^-24], A the amplitude of Eq. (4) (times the receiver's
+// fraction in [0, 1] (1 by rounding), A the amplitude of Eq. (4) (times the receiver's
 // polar pattern when directional).
 struct ImageParams {
   bool ok;
@@ -790,28 +730,19 @@ struct ImageParams {
   float fr, A;
 };
 template <bool POLAR>
-__device__ __forceinline__ ImageParams image_params(const RoomArgs &ra, const ItemGeom &g, const float2v cs,
+__device__ __forceinline__ ImageParams image_params(const RoomArgs &ra, const ItemGeom &g, const double cs,
                                                     const float cgain, const AxisEntry ez, const float cp) {
   ImageParams p;
-  // S = column part + z part in float-float (Sh + Sl, not renormalised)
-  float Sh, Sl;
-  two_sum(cs.x, ez.sq_hi, Sh, Sl);
-  Sl += cs.y + ez.sq_lo;
-  // x = sqrt(S) in samples (Eq. (2)-(3)): one Newton correction in float-float
-  const float x0 = __builtin_amdgcn_sqrtf(Sh);
-  const float rx = __builtin_amdgcn_rcpf(x0);
-  const float xl = (__builtin_fmaf(-x0, x0, Sh) + Sl) * (0.5f * rx);
-  // k0 = floor(x), f = x - k0: |xl| is a few ulps of x0 at most, so the
-  // fraction (x0 - floor(x0)) + xl lies in (-1, 2) and one floor moves it into
-  // [0, 1); the clamp catches a tiny negative fraction that rounds up to 1.
-  float kf = floorf(x0);
-  float fr = (x0 - kf) + xl;
-  const float d = floorf(fr);
-  p.fr = fminf(fr - d, 0x1.fffffep-1f);
-  kf += d;
-  const int k0 = (int)kf;
-  p.base = k0 - g.T0;
-  p.ok = (x0 < 1.0e9f) && (uint32_t)p.base < (uint32_t)(g.K1 - g.T0);
+  // x = sqrt(S) in samples (Eq. (2)-(3)): FP32 estimate, one Newton step in FP64
+  const double S = cs + ez.sq;
+  const float sf = (float)S;
+  const float rx = __builtin_amdgcn_rsqf(sf);
+  const double xh = (double)(sf * rx);
+  const double x = __builtin_fma(__builtin_fma(-xh, xh, S), (double)(0.5f * rx), xh);
+  const double k = __builtin_floor(x);
+  p.fr = (float)(x - k);
+  p.base = (int)k - g.T0;
+  p.ok = sf < 1.0e18f && (uint32_t)p.base < (uint32_t)(g.K1 - g.T0);
   // Eq. (4) amplitude (times the constant factor carried by the column gain)
   p.A = (cgain * ez.gain) * rx;
   // receiver polar pattern a + b cos(theta), cos(theta) = (d . o) / |d|
@@ -846,32 +777,30 @@ template <bool POLAR, bool DUMP, int NW>
 struct ChunkWalk {
   ShellWalk<POLAR, DUMP, NW> &sw;
   const AxisEntry *__restrict__ tz;
-  int n_z;
-  int q = 0, total = 0, carry = 0;
+  int q = 0, total = 0;
+  uint32_t carry = 0;
   int cl = 0, nz = 0;  // of the chunk at q: column lane, z table index and row, column gain
   float cg = 0.0f;
-  AxisEntry ez;
+  AxisEntry ez{};
 
-  __device__ __forceinline__ ChunkWalk(ShellWalk<POLAR, DUMP, NW> &sw_, const AxisEntry *tz_, int n_z_)
-      : sw(sw_), tz(tz_), n_z(n_z_) {
-    ez = AxisEntry{0.0f, 0.0f, 0.0f, 0.0f};
-  }
+  __device__ __forceinline__ ChunkWalk(ShellWalk<POLAR, DUMP, NW> &sw_, const AxisEntry *tz_) : sw(sw_), tz(tz_) {}
   __device__ __forceinline__ void locate(int q0) {
     const int lane = threadIdx.x & 63;
     EnumLds &es = sw.es;
     es.mark[lane] = 0;
     wave_sync();
     const int r = sw.excl - q0;
-    if (sw.cnt > 0 && (uint32_t)r < 64u) es.mark[r] = lane + 1;
+    if (sw.cnt > 0 && (uint32_t)r < 64u) es.mark[r] = (uint32_t)lane + 1u;
     wave_sync();
-    const int m = max(wave_incl_max(es.mark[lane]), carry);
-    carry = __builtin_amdgcn_readlane(m, 63);
-    cl = max(m - 1, 0);
+    const uint32_t m = max(wave_incl_max(es.mark[lane]), carry);
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+    cl = (int)m - 1;
     const int4v cr = es.col_run[cl];
-    const int pos = q0 + lane;
-    nz = min(max(pos + (pos < cr.x ? cr.y : cr.z), 0), n_z - 1);
+    // positions past the last repeat it
+    const int pos = min(q0 + lane, total - 1);
+    nz = pos + (pos < cr.x ? cr.y : cr.z);
     cg = __int_as_float(cr.w);
-    if (pos < total) ez = tz[nz];
+    ez = entry_at(tz, nz);
   }
   // Goes to the wave's next chunk; false when there is none left.
   __device__ __forceinline__ bool advance() {
@@ -1097,13 +1026,13 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 
   int ns = 0;  // staged images (wave-uniform)
   ShellWalk<POLAR, DUMP, 1> sw(g, tx, ty, ay, az, ra.kappa, es, col_p, col_xy, 0);
-  ChunkWalk<POLAR, DUMP, 1> cw(sw, tz, ra.N[2]);
+  ChunkWalk<POLAR, DUMP, 1> cw(sw, tz);
   while (cw.advance()) {
     cw.visit([&](bool live, int cl, int nz, float cg, const AxisEntry ez) {
       // lanes = candidates: parameters, then compaction into the stage
       ImageParams p;
-      p.ok = false;
-      if (live) p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
+      p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
+      p.ok = p.ok && live;
       const uint64_t okm = __ballot(p.ok);
       const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
       if constexpr (DUMP) {
@@ -1270,7 +1199,7 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
     const float t = r.x, A = r.y;
     if constexpr (decltype(taps)::value) {
       // tap j at v = j - f, j = -1 .. 2 (|v| < 2), into sum j + 1
-      const float f = fmaxf(t + 0.5f, 0x1p-24f);
+      const float f = fminf(fmaxf(t + 0.5f, 0x1p-24f), 0x1.fffffep-1f);
       const float C2 = A * __builtin_amdgcn_sinf(0.5f * fminf(f, 1.0f - f)) * (float)(0.5 / kPi);
 #pragma unroll
       for (int j = -1; j <= 2; ++j) {
@@ -1325,7 +1254,7 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
 
   ShellWalk<POLAR, false, MOM_WAVES> sw(g, tx, ty, ay, az, ra.kappa, es_all[wv], col_p_all[POLAR ? wv : 0], nullptr,
                                         wv);
-  ChunkWalk<POLAR, false, MOM_WAVES> cw(sw, tz, ra.N[2]);
+  ChunkWalk<POLAR, false, MOM_WAVES> cw(sw, tz);
   const EnumLds &es = es_all[wv];
   const float *const col_p = col_p_all[POLAR ? wv : 0];
   __syncthreads();
@@ -1335,10 +1264,8 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
       more = cw.advance();
       if (!more) break;
       cw.visit([&](bool live, int cl, int, float cg, const AxisEntry ez) {
-        ImageParams p;
-        p.ok = false;
-        if (live) p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
-        if (p.ok) {
+        const ImageParams p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
+        if (live && p.ok) {
           const uint32_t i = (uint32_t)(8 * (wv * MOM_SLOTS + slot + lane));
           const uint32_t old = atomicExch(&u.pool.head[wv][p.base], i);
           u.pool.rec[i / 8] = float2v{p.fr - 0.5f, p.A};

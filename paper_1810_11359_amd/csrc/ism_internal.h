@@ -46,8 +46,8 @@ constexpr int waves_per_simd(bool half, bool lut) { return half || lut ? 7 : 3; 
 constexpr int item_threads(bool half, bool lut) { return half || lut ? 64 : 256; }
 
 // Per-call room constants, passed by value as a kernel argument. Lengths are in
-// metres, delays in samples. Float-float pairs (hi, lo) carry double-precision
-// host values into FP32-only device arithmetic. The per-axis arrays are in
+// metres, delays in samples. Float pairs (hi, lo) carry double-precision host
+// values to about 48 bits. The per-axis arrays are in
 // table-axis order: table axis k is room axis perm[k], with the room's
 // shortest side last (the innermost enumeration axis, whose columns then
 // hold the most images).
@@ -89,12 +89,12 @@ struct PlanArgs {
 };
 
 // Per-RIR table entry for one lattice index of one axis: square of the
-// displacement from the receiver to the image coordinate, in samples^2
-// (float-float, low part not renormalised), the axis factor of the
+// displacement from the receiver to the image coordinate, in samples^2, the axis factor of the
 // reflection gain, and (polar calls) the displacement times the receiver's
 // unit orientation along this axis, in samples (0 otherwise).
 struct AxisEntry {
-  float sq_hi, sq_lo, gain, proj;
+  double sq;
+  float gain, proj;
 };
 
 // Per-RIR offsets of the two image families of each axis, in samples: even
