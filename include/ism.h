@@ -130,8 +130,7 @@ typedef struct {
                            value; sets the item size of large calls)                  */
   double tail_rounds;   /* single calls: the items dispatched once less than this many
                            rounds of resident items of work remain are cut smaller so
-                           the launch ends evenly; 0 = no taper, < 0 = default
-                           (1; FP32: 1/2)                                             */
+                           the launch ends evenly; 0 = no taper, < 0 = default (1)    */
   double batch_waves;   /* batches: waves per SIMD of each persistent launch (1 .. 16;
                            1024 times this in all); 0 = tuned value                */
 } ism_schedule;

@@ -195,8 +195,7 @@ __constant__ ChebFit kChebFit = make_cheb_fit();
 //   h[k] = sum_j sum_p c_jp M_p[k - j],
 // which costs an image MOM sums instead of W taps, and a convolution of MOM
 // W per output sample whatever the number of images.
-// The window is even, so s_{1-j}(t) = s_j(-t) and c_{1-j,p} = (-1)^p c_jp: tables
-// hold j = 1 .. W/2.
+// The window is even, so s_{1-j}(t) = s_j(-t) and c_{1-j,p} = (-1)^p c_jp.
 constexpr int MOM = 10;
 template <int NP>
 struct ChebFitD {
@@ -224,9 +223,11 @@ constexpr ChebFitD<NP> make_cheb_fit_d() {
   return F;
 }
 __constant__ ChebFitD<MOM> kMomFit = make_cheb_fit_d<MOM>();
+// c[p][e]: coefficient of tap j = WT/2 + 15 - e, zero outside the window (the
+// order and padding in which the convolution reads them).
 template <int WT>
 struct MomCoef {
-  float c[MOM][WT / 2];  // c[p][j - 1]
+  float c[MOM][WT + 32];
 };
 template <int WT>
 constexpr MomCoef<WT> make_mom_coef() {
@@ -238,7 +239,8 @@ constexpr MomCoef<WT> make_mom_coef() {
     for (int p = 0; p < MOM; ++p) {
       double v = 0.0;
       for (int i = 0; i < MOM; ++i) v += F.vinv[p][i] * y[i];
-      t.c[p][j - 1] = (float)v;
+      t.c[p][WT / 2 + 15 - j] = (float)v;
+      t.c[p][WT / 2 + 15 - (1 - j)] = (float)(p % 2 ? -v : v);
     }
   }
   return t;
@@ -260,27 +262,41 @@ constexpr int kEdgeCap = 64;
 constexpr int kEdgeCoef = 8;
 constexpr float kDirectWin = 4.0f;
 __constant__ ChebFitD<kEdgeCoef> kEdgeFit = make_cheb_fit_d<kEdgeCoef>();
-// Layout of the FP32 constants of a general window of cap WT: c[p][j - 1] as
-// above, then e_0 .. e_7, f1, j2 (0: no tap is cut).
+// Layout of the FP32 constants of a general window of cap WT: c_jp at [p][j - 1]
+// for j = 1 .. WT/2, then e_0 .. e_7, f1, j2 (0: no tap is cut).
 constexpr int wc_edge(int WT) { return MOM * (WT / 2); }
 static_assert(wc_edge(32) + kEdgeCoef + 2 <= 32 * WC_STRIDE, "window constants");
 
+// Taylor coefficients (-1)^k / (2k)! and (-1)^k / (2k + 1)!, k <= 9.
+struct TrigSeries {
+  double c[10], s[10];
+};
+constexpr TrigSeries make_trig_series() {
+  TrigSeries t{};
+  double f = 1.0;
+  for (int k = 0; k < 10; ++k) {
+    const double sg = k % 2 ? -1.0 : 1.0;
+    if (k > 0) f *= 2.0 * k;
+    t.c[k] = sg / f;
+    f *= 2.0 * k + 1.0;
+    t.s[k] = sg / f;
+  }
+  return t;
+}
 // sin(pi x) and cos(pi x) in double for moderate |x| (reduction to |r| <= 1/4,
 // Taylor series with terms below 1e-18 left out).
-__device__ void sincospi_d(double x, double &s, double &c) {
+__device__ __forceinline__ void sincospi_d(double x, double &s, double &c) {
+  constexpr TrigSeries T = make_trig_series();
   const double n = __builtin_rint(2.0 * x);
   const double y = (x - 0.5 * n) * kPi, y2 = y * y;
-  double ts = y, tc = 1.0;
-  s = y;
-  c = 1.0;
-  for (int k = 1; k <= 9; ++k) {
-    tc *= -y2 / ((2.0 * k - 1.0) * (2.0 * k));
-    ts *= -y2 / ((2.0 * k) * (2.0 * k + 1.0));
-    c += tc;
-    s += ts;
+  double a = T.s[9], b = T.c[9];
+#pragma unroll
+  for (int k = 8; k >= 0; --k) {
+    a = __builtin_fma(a, y2, T.s[k]);
+    b = __builtin_fma(b, y2, T.c[k]);
   }
+  a *= y;
   const int q = ((int)n) & 3;
-  const double a = s, b = c;
   s = q == 0 ? a : q == 1 ? b : q == 2 ? -a : -b;
   c = q == 0 ? b : q == 1 ? -a : q == 2 ? -b : a;
 }
@@ -291,38 +307,40 @@ __device__ double windowed_sinc_d(double v, double W) {
   sincospi_d(2.0 * v / W, wn, wc);
   return sn / (kPi * v) * 0.5 * (1.0 + wc);
 }
-// FP32 constants of a general window: thread jj of WT/2 writes tap j = jj + 1,
-// the thread after them the edge polynomial.
-__device__ void moment_const_entry(double W, int WT, int jj, float *wc) {
-  const int half = WT / 2;
+// FP32 constants of a general window, by one block: the node values of every
+// tap j >= 1 (and of the edge polynomial), then each coefficient.
+__device__ void moment_consts(double W, int WT, float *__restrict__ wc) {
+  __shared__ double y[MAX_WINDOW / 2 + 1][MOM];
+  const int half = WT / 2, nt = (int)blockDim.x;
   const int j2 = (int)__builtin_floor(0.5 * W) + 1;
   const bool edge = WT <= kEdgeCap && (double)j2 - 0.5 * W < 1.0 && j2 <= half;
-  if (jj < half) {
-    const int j = jj + 1;
-    double y[MOM];
-    for (int i = 0; i < MOM; ++i) {
-      const double v = (double)j - (kMomFit.node[i] + 0.5);
-      y[i] = ((edge && j == j2) || !(__builtin_fabs(v) < 0.5 * W)) ? 0.0 : windowed_sinc_d(v, W);
-    }
-    for (int p = 0; p < MOM; ++p) {
-      double v = 0.0;
-      for (int i = 0; i < MOM; ++i) v += kMomFit.vinv[p][i] * y[i];
-      wc[p * half + jj] = (float)v;
-    }
-  } else if (jj == half) {
-    float *e = wc + wc_edge(WT);
-    double y[kEdgeCoef];
-    for (int i = 0; i < kEdgeCoef; ++i) {
+  for (int e = threadIdx.x; e < (half + 1) * MOM; e += nt) {
+    const int j = e / MOM + 1, i = e % MOM;
+    double v = 0.0;
+    if (j <= half) {
+      const double x = (double)j - (kMomFit.node[i] + 0.5);
+      if (!(edge && j == j2) && __builtin_fabs(x) < 0.5 * W) v = windowed_sinc_d(x, W);
+    } else if (edge && i < kEdgeCoef) {
       const double u = kEdgeFit.node[i] + 0.5;
-      y[i] = edge ? windowed_sinc_d(0.5 * W - u, W) / (u * u) : 0.0;
+      v = windowed_sinc_d(0.5 * W - u, W) / (u * u);
     }
-    for (int p = 0; p < kEdgeCoef; ++p) {
-      double v = 0.0;
-      for (int i = 0; i < kEdgeCoef; ++i) v += kEdgeFit.vinv[p][i] * y[i];
-      e[p] = (float)v;
+    y[j - 1][i] = v;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < (half + 1) * MOM; e += nt) {
+    const int p = e / (half + 1), jj = e % (half + 1);
+    double v = 0.0;
+    if (jj < half) {
+      for (int i = 0; i < MOM; ++i) v += kMomFit.vinv[p][i] * y[jj][i];
+      wc[p * half + jj] = (float)v;
+    } else if (p < kEdgeCoef) {
+      for (int i = 0; i < kEdgeCoef; ++i) v += kEdgeFit.vinv[p][i] * y[half][i];
+      wc[wc_edge(WT) + p] = (float)v;
     }
-    e[kEdgeCoef] = (float)((double)j2 - 0.5 * W);
-    e[kEdgeCoef + 1] = edge ? (float)j2 : 0.0f;
+  }
+  if (threadIdx.x == 0) {
+    wc[wc_edge(WT) + kEdgeCoef] = (float)((double)j2 - 0.5 * W);
+    wc[wc_edge(WT) + kEdgeCoef + 1] = edge ? (float)j2 : 0.0f;
   }
 }
 
@@ -437,14 +455,28 @@ __device__ __forceinline__ int rir_header(const RoomArgs &ra, const float *__res
   return (ok && !same) ? 1 : 0;
 }
 
+// Constants of a general-mode window, by one block.
+__device__ __forceinline__ void window_consts(float W, int WT, int half, float *__restrict__ wc) {
+  if (!half) moment_consts((double)W, WT, wc);
+  else
+    for (int jj = threadIdx.x; jj < WT; jj += blockDim.x) window_const_entry(W, WT, jj, wc + WC_STRIDE * jj);
+}
+
+// Blocks 0 .. n_blk - 1 write the tables; a general-mode call (wc set) adds one block
+// that writes its window's constants.
 __global__ __launch_bounds__(256) void tables_kernel(RoomArgs ra, const float *__restrict__ src,
                                                      const float *__restrict__ rcv,
                                                      const float *__restrict__ orient, AxisEntry *__restrict__ tab,
                                                      AxisOrigin *__restrict__ origin, int *__restrict__ valid,
-                                                     int n_rir) {
+                                                     int n_rir, int n_blk, float W, int half,
+                                                     float *__restrict__ wc) {
+  if ((int)blockIdx.x >= n_blk) {
+    window_consts(W, (int)(2.0f * ra.half_w), half, wc);
+    return;
+  }
   const int64_t total = (int64_t)n_rir * ra.n_tab;
   for (int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; gid < total;
-       gid += (int64_t)gridDim.x * blockDim.x) {
+       gid += (int64_t)n_blk * blockDim.x) {
     const int rir = (int)(gid / ra.n_tab);
     const int e = (int)(gid % ra.n_tab);
     const float *s3 = src + 3 * (rir / ra.n_rcv);
@@ -458,15 +490,21 @@ __global__ __launch_bounds__(256) void tables_kernel(RoomArgs ra, const float *_
   }
 }
 
-// Batch mode: one block per batch-wide RIR.
+// Batch mode: one block per batch-wide RIR, then (with general-mode windows) one
+// per job, for its window's constants.
 __global__ __launch_bounds__(256) void tables_batch_kernel(const JobDev *__restrict__ jobs,
                                                            const BatchRir *__restrict__ rirs,
                                                            AxisEntry *__restrict__ tab,
                                                            AxisOrigin *__restrict__ origin,
-                                                           int *__restrict__ valid) {
+                                                           int *__restrict__ valid, uint32_t n_rir, int half) {
+  if (blockIdx.x >= n_rir) {
+    const JobDev &jb = jobs[blockIdx.x - n_rir];
+    if (jb.wc) window_consts(2.0f * jb.ra.win_hw, (int)(2.0f * jb.ra.half_w), half, jb.wc);
+    return;
+  }
   const BatchRir br = rirs[blockIdx.x];
   const JobDev &jb = jobs[br.job];
-  const RoomArgs ra = jb.ra;
+  const RoomArgs &ra = jb.ra;
   const float *s3 = jb.src + 3 * (br.rir / ra.n_rcv);
   const float *r3 = jb.rcv + 3 * (br.rir % ra.n_rcv);
   AxisEntry *t = tab + jb.tab_base + (size_t)br.rir * ra.n_tab;
@@ -616,9 +654,10 @@ __device__ __forceinline__ ItemGeom item_geom(const RoomArgs &ra, const AxisRang
   return g;
 }
 
-// Walks the shell of the item, shared by the NW waves of a workgroup: wave wv
-// takes every NW-th batch of 64 columns (each wave has its own EnumLds and
-// repeats the x step, one lane per 64 x indices). next() goes to the wave's next
+// Walks the shell of the item, shared by the NW waves of a workgroup: the columns
+// of each block of 64 x indices are cut into equal batches of at most 64, the
+// same number for every wave (each wave has its own EnumLds and repeats the x
+// step). next() goes to the wave's next
 // batch with candidates: it fills es.col_run and es.col_s and sets total, the
 // candidates in the batch, and on column lane c its first position excl and its
 // count cnt; false when there is none left. The column gain in col_run is the
@@ -636,7 +675,8 @@ struct ShellWalk {
   float *__restrict__ col_p;
   uint32_t *__restrict__ col_xy;
   int wv;
-  int nx_next, nx0 = 0, ncols = 0, cb = 0, base = 0;  // x block, its columns, next batch, batches before the block
+  int nx_next, nx0 = 0, ncols = 0;     // x block and its columns
+  int gc0 = 0, bs = 0;                 // first column of the wave's next batch, columns per batch
   int col0 = 0, ny_cnt = 0;                           // this x lane's first column and its columns
   int total = 0, excl = 0, cnt = 0;
 
@@ -649,7 +689,7 @@ struct ShellWalk {
   __device__ __forceinline__ bool next() {
     const int lane = threadIdx.x & 63;
     for (;;) {
-      while (cb * 64 >= ncols) {
+      while (gc0 >= ncols) {
         if (nx_next >= g.nx_b) return false;
         nx0 = nx_next;
         nx_next += 64;
@@ -670,20 +710,22 @@ struct ShellWalk {
         col0 = incl_y - ny_cnt;
         wave_sync();
         es.nx_col[lane] = ((uint32_t)col0 << 11) | (uint32_t)ny_lo;
-        cb = NW > 1 ? (wv - base) & (NW - 1) : 0;
-        base += (ncols + 63) >> 6;
+        // (a block without columns gets batches of one, none of which exists)
+        const int rounds = max((ncols + 64 * NW - 1) / (64 * NW), 1);
+        bs = NW > 1 ? max((ncols + NW * rounds - 1) / (NW * rounds), 1) : 64;
+        gc0 = wv * bs;
       }
       // lanes = columns (nx, ny): z ranges of the shell
-      const int gcol = cb * 64 + lane;
+      const int gcol = gc0 + lane;
       // x lane of the column: the last x lane with columns starting at or
       // before it (each marks its first column in the batch; a running
       // maximum carries the marks forward, as for the candidates, from the
       // x lane of the batch's first column)
       es.mark[lane] = 0;
       wave_sync();
-      if (ny_cnt > 0 && (uint32_t)(col0 - cb * 64) < 64u) es.mark[col0 - cb * 64] = (uint32_t)lane + 1u;
+      if (ny_cnt > 0 && (uint32_t)(col0 - gc0) < 64u) es.mark[col0 - gc0] = (uint32_t)lane + 1u;
       wave_sync();
-      const uint64_t before = __ballot(ny_cnt > 0 && col0 <= cb * 64);
+      const uint64_t before = __ballot(ny_cnt > 0 && col0 <= gc0);
       const uint32_t xm = max(wave_incl_max(es.mark[lane]), 64u - (uint32_t)__builtin_clzll(before | 1u));
       // (columns past the last repeat it and take no candidates)
       const int i = (int)xm - 1;
@@ -701,12 +743,12 @@ struct ShellWalk {
       // displacements in [-zmax, -zmin) and [zmin, zmax): two runs of the
       // table (contiguous when zmin = 0)
       const float f1 = first_ge_f(az, -zmax), f2 = first_ge_f(az, zmin);
-      const bool some = gcol < ncols && rh > 0.0f;
+      const bool some = gcol < ncols && lane < bs && rh > 0.0f;
       const float m1 = first_ge_f(az, -zmin) - f1;
       const int z1 = (int)f1, z2 = (int)f2;
       const int n1 = some ? (int)m1 : 0;
       cnt = some ? (int)(m1 + (first_ge_f(az, zmax) - f2)) : 0;
-      cb += NW;
+      gc0 += NW * bs;
       const int incl = wave_incl_scan(cnt);
       total = __builtin_amdgcn_readlane(incl, 63);
       excl = incl - cnt;
@@ -911,7 +953,7 @@ __device__ __forceinline__ void write_invalid(int n_own, float *__restrict__ dst
 // taps compute them).
 // GEN: general-mode window (WT is the cap, W = 2 ra.win_hw): the per-lane tap
 // constants come from wc ([WT][WC_STRIDE], written for this window by
-// window_consts_kernel).
+// tables_kernel).
 template <int WT, bool HALF, int NQ, bool POLAR = false, bool DUMP = false, bool GEN = false>
 __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
@@ -1108,8 +1150,8 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 // (lanes = delays). A list holds its wave's images in program order and the
 // lists are joined in wave order, so a call always adds in the same order.
 // Four waves share a pool because the walk takes as many steps as the longest of
-// 64 lists: with Poisson lengths of mean 15 that is 1.7 steps per image and
-// lane, with a wave's own pool (256 delays, mean 3.7) 2.6.
+// 64 lists: with Poisson lengths of mean 10 that is 1.9 steps per image and
+// lane, with a wave's own pool (256 delays, mean 2.5) 2.9.
 // Convolution: at the end of the item the moments go to LDS planes and
 // matrix instructions form the item's TILE + W - 1 output samples: output
 // o = 16 a + r of row r, column a is the sum over planes and k' of
@@ -1121,7 +1163,11 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int MOM_WAVES = 4;
-constexpr int MOM_SLOTS = 960;  // pool slots per wave: 15 chunks of 64 positions
+// Pool slots per wave: 10 chunks of 64 positions. With these a workgroup takes 40 KB
+// of LDS and four fit a compute unit: 1024-room batch 6.43 ms, 64 microphones at
+// 48 kHz 2.37 ms, against 7.39 and 2.76 with 15 chunks (three workgroups) and 6.90
+// and 2.48 with 7 (five).
+constexpr int MOM_SLOTS = 640;
 constexpr int MOM_END = 8 * MOM_WAVES * MOM_SLOTS;  // end of a list (slots are linked by byte offset in rec)
 static_assert(TILE == 64 * MOM_WAVES && MOM_END < 65536, "one delay per thread, 16-bit links");
 struct MomPool {
@@ -1299,34 +1345,40 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
 
   // convolution
   float *const planes = u.conv, *const coefs = u.conv + P * Sh::PL;
-  for (int i = tid; i < P * Sh::PL; i += NT) planes[i] = 0.0f;
-  const int j2 = EDGE ? (int)wc[wc_edge(WT) + kEdgeCoef + 1] : 0;
-  // coefficient of entry e of a plane: tap j = WT/2 + 15 - e (0 outside the window)
-  for (int e = tid; e < Sh::CL; e += NT) {
-    const int j = WT / 2 + 15 - e;
-    const bool in = j > -WT / 2 && j <= WT / 2;
-    const int jj = in ? (j >= 1 ? j - 1 : -j) : 0;
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      float v = 0.0f;
-      if (DIRECT && direct) {
-        v = (p < 4 && j == p - 1) ? 1.0f : 0.0f;
-      } else if (p >= MOM) {
-        v = (j2 > 0 && j == (p == MOM ? 1 - j2 : j2)) ? 1.0f : 0.0f;
-      } else {
-        if constexpr (GEN) v = wc[p * (WT / 2) + jj];
-        else v = mom_table<WT>().c[p][jj];
-        if (!in) v = 0.0f;
-        if (j < 1 && (p & 1)) v = -v;
-      }
-      coefs[p * Sh::CL + e] = v;
-    }
-  }
-  __syncthreads();
   {
     const int x = tid + WT - 1;
 #pragma unroll
     for (int p = 0; p < P; ++p) planes[p * Sh::PL + x + (x >> 4)] = m[p];
+    // zeros before and after the tile's delays
+    constexpr int NZ = Sh::XN - TILE;
+    for (int e = tid; e < NZ; e += NT) {
+      const int xz = e < WT - 1 ? e : e + TILE;
+#pragma unroll
+      for (int p = 0; p < P; ++p) planes[p * Sh::PL + xz + (xz >> 4)] = 0.0f;
+    }
+  }
+  if constexpr (GEN) {
+    // coefficients in the order of MomCoef
+    const int j2 = EDGE ? (int)wc[wc_edge(WT) + kEdgeCoef + 1] : 0;
+    for (int e = tid; e < Sh::CL; e += NT) {
+      const int j = WT / 2 + 15 - e;
+      const bool in = j > -WT / 2 && j <= WT / 2;
+      const int jj = in ? (j >= 1 ? j - 1 : -j) : 0;
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        float v = 0.0f;
+        if (DIRECT && direct) {
+          v = (p < 4 && j == p - 1) ? 1.0f : 0.0f;
+        } else if (p >= MOM) {
+          v = (j2 > 0 && j == (p == MOM ? 1 - j2 : j2)) ? 1.0f : 0.0f;
+        } else {
+          v = wc[p * (WT / 2) + jj];
+          if (!in) v = 0.0f;
+          if (j < 1 && (p & 1)) v = -v;
+        }
+        coefs[p * Sh::CL + e] = v;
+      }
+    }
   }
   __syncthreads();
   const int lc = lane & 15, lk = lane >> 4;  // matrix row (coefficients) / column (planes), k group
@@ -1336,17 +1388,18 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   f4v d0[4], d1[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) d0[i] = d1[i] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int KQ = Sh::KS / MOM_WAVES;  // steps of this wave: s0 .. s0 + KQ - 1
+  const int s0 = wv * KQ;
 #pragma unroll
   for (int p = P - 1; p >= 0; --p) {
     const int i = p < 3 ? p : 3;
-    const float *cf = coefs + p * Sh::CL + (lk - lc + 15);
     const float *b0 = planes + p * Sh::PL + 17 * a0 + lk, *b1 = planes + p * Sh::PL + 17 * a1 + lk;
-    constexpr int KQ = Sh::KS / MOM_WAVES;  // steps of this wave: s0 .. s0 + KQ - 1
-    const int s0 = wv * KQ;
 #pragma unroll
     for (int k = 0; k < KQ; ++k) {
       const int s = s0 + k;
-      const float cv = cf[4 * s];
+      float cv;
+      if constexpr (GEN) cv = coefs[p * Sh::CL + 4 * s + (lk - lc + 15)];
+      else cv = mom_table<WT>().c[p][(uint32_t)(4 * s + (lk - lc + 15))];
       d0[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b0[4 * s + (s >> 2)], d0[i], 0, 0, 0);
       d1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b1[4 * s + (s >> 2)], d1[i], 0, 0, 0);
     }
@@ -1433,21 +1486,6 @@ accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_al
                                       valid[si.rir] != 0, dst, marg + (size_t)item * WT, wc);
 }
 
-// Constants of a general-mode window (one thread per tap of the cap).
-__device__ __forceinline__ void window_consts(float W, int WT, int half, int jj, float *wc) {
-  if (!half) moment_const_entry((double)W, WT, jj, wc);
-  else if (jj < WT) window_const_entry(W, WT, jj, wc + WC_STRIDE * jj);
-}
-__global__ __launch_bounds__(256) void window_consts_kernel(float W, int WT, int half, float *__restrict__ wc) {
-  window_consts(W, WT, half, threadIdx.x, wc);
-}
-// Batch mode: one block per job; jobs without general-mode constants exit.
-__global__ __launch_bounds__(256) void window_consts_batch_kernel(const JobDev *__restrict__ jobs, int half) {
-  const JobDev &jb = jobs[blockIdx.x];
-  if (!jb.wc) return;
-  window_consts(2.0f * jb.ra.win_hw, (int)(2.0f * jb.ra.half_w), half, threadIdx.x, jb.wc);
-}
-
 // Enumeration check: the items of a single-room launch, images only.
 template <int WT>
 __global__ __launch_bounds__(64) void enumerate_dump_kernel(RoomArgs ra, PlanArgs pa,
@@ -1483,6 +1521,9 @@ accumulate_batch_kernel(
   __shared__ uint32_t next_item;
   uint32_t item = blockIdx.x;
   while (item < n_items) {
+    // the next item's number arrives while this one is worked on
+    uint32_t next = 0;
+    if (MULTI && queue && threadIdx.x == 0) next = atomicAdd(queue, 1u);
     const BatchItem it = items[item];
     const JobDev &jb = jobs[it.job];
     const RoomArgs ra = jb.ra;
@@ -1495,12 +1536,11 @@ accumulate_batch_kernel(
                                         marg + (size_t)it.mslot * MARG_UNIT, jb.wc);
     if (queue) {
       if constexpr (MULTI) {
-        if (threadIdx.x == 0) next_item = atomicAdd(queue, 1u);
+        if (threadIdx.x == 0) next_item = next;
         __syncthreads();
         item = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_item);
         __syncthreads();
       } else {
-        uint32_t next = 0;
         if (lane == 0) next = atomicAdd(queue, 1u);
         item = (uint32_t)__builtin_amdgcn_readlane((int)next, 0);
       }
@@ -1703,12 +1743,12 @@ __global__ __launch_bounds__(64) void reduce_margins_kernel(const JobDev *__rest
 // Launchers (called from ism_host.cpp).
 // ---------------------------------------------------------------------------
 int launch_tables(const RoomArgs &ra, const float *src, const float *rcv, const float *orient, AxisEntry *tab,
-                  AxisOrigin *origin, int *valid, int n_rir, hipStream_t st) {
+                  AxisOrigin *origin, int *valid, int n_rir, float W, bool half, float *wc, hipStream_t st) {
   const int64_t total = (int64_t)n_rir * ra.n_tab;
   int64_t blocks = (total + 255) / 256;
   if (blocks > 65535) blocks = 65535;
-  hipLaunchKernelGGL(tables_kernel, dim3((unsigned)blocks), dim3(256), 0, st, ra, src, rcv, orient, tab, origin,
-                     valid, n_rir);
+  hipLaunchKernelGGL(tables_kernel, dim3((unsigned)(blocks + (wc ? 1 : 0))), dim3(256), 0, st, ra, src, rcv, orient,
+                     tab, origin, valid, n_rir, (int)blocks, W, half ? 1 : 0, wc);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -1751,11 +1791,6 @@ int launch_dump(int wt, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items
 bool supported_window(int wt, bool gen) {
   if (gen) return wt >= 32 && wt <= MAX_WINDOW && wt % 32 == 0;
   return wt == 32 || wt == 64 || wt == 96 || wt == 128;
-}
-
-int launch_window_consts(float W, int wt, bool half, float *wc, hipStream_t st) {
-  hipLaunchKernelGGL(window_consts_kernel, dim3(1), dim3(MAX_WINDOW), 0, st, W, wt, half ? 1 : 0, wc);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // Calls the kernel instance of a window class: exact windows W in {32, 64,
@@ -1834,12 +1869,9 @@ int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *r
                  const BatchReduce *red, uint32_t n_red, uint32_t n_red_split, bool long_runs, AxisEntry *tab,
                  AxisOrigin *origin, int *valid, float *part, float *marg, uint32_t *queue, hipStream_t st,
                  hipEvent_t ev_start, hipEvent_t ev_stop) {
-  hipLaunchKernelGGL(tables_batch_kernel, dim3(n_rir), dim3(256), 0, st, jobs, rirs, tab, origin, valid);
+  hipLaunchKernelGGL(tables_batch_kernel, dim3(n_rir + (any_gen ? (unsigned)n_jobs : 0u)), dim3(256), 0, st, jobs, rirs,
+                     tab, origin, valid, n_rir, half ? 1 : 0);
   if (hipGetLastError() != hipSuccess) return -1;
-  if (any_gen) {
-    hipLaunchKernelGGL(window_consts_batch_kernel, dim3(n_jobs), dim3(MAX_WINDOW), 0, st, jobs, half ? 1 : 0);
-    if (hipGetLastError() != hipSuccess) return -1;
-  }
   if (queue) {
     uint32_t fp[kMaxBatchClasses] = {};
     for (int k = 0; k < n_classes && k < kMaxBatchClasses; ++k) fp[k] = class_grid[k];

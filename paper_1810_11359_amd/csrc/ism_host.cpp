@@ -19,14 +19,13 @@
 
 namespace ism {
 int launch_tables(const RoomArgs &ra, const float *src, const float *rcv, const float *orient, AxisEntry *tab,
-                  AxisOrigin *origin, int *valid, int n_rir, hipStream_t st);
+                  AxisOrigin *origin, int *valid, int n_rir, float W, bool half, float *wc, hipStream_t st);
 int launch_accumulate(int wt, bool gen, bool half, bool lut, bool polar, const RoomArgs &ra, const PlanArgs &pa,
                       uint32_t n_items, const AxisEntry *tab, const AxisOrigin *origin, const int *valid, float *out,
                       float *part, float *marg, const float *wc, hipStream_t st);
 int launch_reduce(const RoomArgs &ra, const PlanArgs &pa, int n_rir, const float *part, const float *marg,
                   float *out, hipStream_t st);
 bool supported_window(int wt, bool gen);
-int launch_window_consts(float W, int wt, bool half, float *wc, hipStream_t st);
 int launch_dump(int wt, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                 const AxisOrigin *origin, const int *valid, DumpArgs dump, hipStream_t st);
 int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *rirs, uint32_t n_rir,
@@ -121,26 +120,33 @@ struct Plan {
 // call's schedule (ism_schedule) replaces them.
 constexpr double kMinItemTaps = 1.2e5;
 constexpr double kBalanceItems = 49152.0;
-// FP32 items (four waves, a convolution per item) cost images rather than taps:
-// at least kMomMinImages images (below, the fixed part dominates: a single
-// 4800-sample RIR took 30, 24.5, 25 and 40 us per call with items of 160, 780,
-// 1600 and 7800 images), about kMomItems per call (the launch holds 768 at a
-// time; a 32-receiver room took 292, 192, 193 and 203 us with items of 3e3, 16e3,
-// 31e3 and 125e3 images), at most kMomMaxImages (or a kMomMaxItems-th of the call) so
-// that long calls end evenly.
+// FP32 items (four waves, a convolution per item) cost images rather than taps.
+// A call is cut into about kMomItems items, one per resident workgroup (a
+// 32-receiver room took 187, 151 and 152 us with 512, 1024 and 2048), but an item's
+// fixed part is worth some thousand images: items hold at least kMomFullImages
+// (a 11200-sample RIR took 34.5 and 40 us with items of 3800 and 1900 images, 6
+// directional RIRs at 44.1 kHz 61, 69 and 78 us with 4000, 2000 and 1000) unless
+// that leaves fewer than kMomFewItems, then at least kMomMinImages (a single
+// 4800-sample RIR took 30, 24.5, 25 and 40 us with items of 160, 780, 1600 and 7800
+// images). At most kMomMaxImages (or a kMomMaxItems-th of the call), so that long
+// calls end evenly.
 constexpr double kMomMinImages = 800.0;
-constexpr double kMomItems = 512.0;
+constexpr double kMomFewItems = 192.0;
+constexpr double kMomFullImages = 4000.0;
+constexpr double kMomItems = 1024.0;
 constexpr double kMomMaxImages = 65536.0;
 constexpr double kMomMaxItems = 8192.0;
 double item_target(double total_taps, int wt, bool half, bool mom, int64_t n_samples, const ism_schedule *sc) {
   if (mom) {
-    double min_taps = kMomMinImages * wt, balance = kMomItems,
+    const double few = std::min(kMomFullImages * wt, total_taps / kMomFewItems);
+    double min_taps = std::max(kMomMinImages * wt, few), balance = kMomItems,
            max_taps = std::max(kMomMaxImages * wt, total_taps / kMomMaxItems);
-    if (sc && sc->min_item_taps > 0.0) min_taps = std::max(1e3, sc->min_item_taps);
     if (sc && sc->balance_items > 0.0) {
       balance = std::max(1.0, sc->balance_items);
+      min_taps = kMomMinImages * wt;
       max_taps = total_taps;
     }
+    if (sc && sc->min_item_taps > 0.0) min_taps = std::max(1e3, sc->min_item_taps);
     return std::max(min_taps, std::min(max_taps, total_taps / balance));
   }
   double min_taps = kMinItemTaps, balance = kBalanceItems;
@@ -296,8 +302,7 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   // resident waves, down to target / 8 but not below kSmallItemTaps, so the
   // last waves of a launch finish close together instead of one full-size
   // item after another. FP32 items end with a convolution, so theirs are only
-  // halved, over half a round (a call of 4 RIRs of 11200 samples: 79 us with a
-  // full taper, 74 without any; 16 RIRs: 180 and 196 us).
+  // halved (16 RIRs of 11200 samples: 145 us per call, without any taper 178).
   auto rounds = [&](double deflt) {
     return (fixed || !taper) ? 0.0 : (sched && sched->tail_rounds >= 0.0 ? sched->tail_rounds : deflt);
   };
@@ -317,7 +322,7 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   }
   if (ws_items == 0 || target >= p.total_taps / (double)ws_items) {
     uint8_t chunks[MAX_TILES];
-    if (!cut_tiles(p, target, mom ? target / 2.0 : taps_floor(target), rounds(mom ? kTailRounds / 2.0 : kTailRounds),
+    if (!cut_tiles(p, target, mom ? target / 2.0 : taps_floor(target), rounds(kTailRounds),
                    resident, chunks, n_items, n_split))
       return ISM_E_TOO_LARGE;
     if (ws_items == 0 || (n_items <= ws_items && n_split <= ws_split)) {
@@ -529,8 +534,8 @@ static int run_plan(const Plan &p, const float *src, const float *rcv, float *ou
   float *part = p.any_split ? (float *)(w + p.off_part) : nullptr;
   float *marg = (float *)(w + p.off_marg);
   float *wc = p.gen ? (float *)(w + p.off_wc) : nullptr;
-  if (launch_tables(p.ra, src, rcv, orient, tab, origin, valid, p.n_rir, s) != 0) return ISM_E_DEVICE;
-  if (wc && launch_window_consts((float)p.win, p.wt, p.half, wc, s) != 0) return ISM_E_DEVICE;
+  if (launch_tables(p.ra, src, rcv, orient, tab, origin, valid, p.n_rir, (float)p.win, p.half, wc, s) != 0)
+    return ISM_E_DEVICE;
   if (ev_start && hipEventRecord((hipEvent_t)ev_start, s) != hipSuccess) return ISM_E_DEVICE;
   if (launch_accumulate(p.wt, p.gen, p.half, p.lut, orient != nullptr, p.ra, p.pa, p.n_items, tab, origin, valid, out,
                         part, marg, wc, s) != 0)
@@ -593,7 +598,7 @@ int ism_debug_enumerate(const ism_room *room, const float *src, int n_src, const
   int *valid = (int *)(w + p.off_valid);
   AxisOrigin *origin = (AxisOrigin *)(w + p.off_origin);
   AxisEntry *tab = (AxisEntry *)(w + p.off_tab);
-  if (launch_tables(p.ra, src, rcv, nullptr, tab, origin, valid, p.n_rir, s) != 0) {
+  if (launch_tables(p.ra, src, rcv, nullptr, tab, origin, valid, p.n_rir, 0.0f, false, nullptr, s) != 0) {
     fprintf(stderr, "ism_debug_enumerate: tables launch failed\n");
     return ISM_E_DEVICE;
   }
@@ -846,8 +851,9 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     bp.st.class_gen[k] = class_gen[k];
     // persistent grid: the tuned workgroups per SIMD (or the schedule's)
     int waves = waves_per_simd(precision == ISM_FP16, precision == ISM_FP32_LUT);
-    for (const BatchTuning &t : kBatchTuning)
-      if (t.wt == class_wt[k] && t.half == (precision == ISM_FP16 ? 1 : 0)) waves = t.waves;
+    if (precision != ISM_FP32)
+      for (const BatchTuning &t : kBatchTuning)
+        if (t.wt == class_wt[k] && t.half == (precision == ISM_FP16 ? 1 : 0)) waves = t.waves;
     if (sched && sched->batch_waves > 0.0) waves = std::max(1, (int)std::lround(sched->batch_waves));
     bp.st.class_grid[k] = (uint32_t)std::min<uint64_t>(
         bp.st.class_count[k], 1024ull * (uint64_t)waves * 64 / item_threads(precision == ISM_FP16, precision == ISM_FP32_LUT));

@@ -40,9 +40,9 @@ constexpr int kMaxBatchClasses = 8;
 constexpr int MAX_CHUNKS = 255;
 // Waves per SIMD the accumulate kernels are built for (their LDS and VGPR
 // budget) and threads per work item: one wave for FP16 and table taps, four
-// waves that share a 43 KB image pool for FP32. The planner sizes items and the
+// waves that share a 32 KB image pool for FP32. The planner sizes items and the
 // tail taper of a launch with them.
-constexpr int waves_per_simd(bool half, bool lut) { return half || lut ? 7 : 3; }
+constexpr int waves_per_simd(bool half, bool lut) { return half || lut ? 7 : 4; }
 constexpr int item_threads(bool half, bool lut) { return half || lut ? 64 : 256; }
 
 // Per-call room constants, passed by value as a kernel argument. Lengths are in

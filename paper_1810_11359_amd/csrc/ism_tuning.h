@@ -87,7 +87,7 @@ constexpr ItemTuning kItemTuning[] = {
 
 constexpr BatchTuning kBatchTuning[] = {
     {64, 1, 6, 500000},
-    {64, 0, 3, 500000},
+    {64, 0, 6, 500000},
 };
 
 }  // namespace ism
