@@ -14,9 +14,9 @@
 //                      directional) and adds its Hann-windowed sinc (Eq. (5),
 //                      (6)): FP32 calls sum the moments of the images' delay
 //                      fractions per integer delay and convolve these with the
-//                      taps' polynomials once per item; FP16 and table taps
-//                      (Eq. (9)) are added image by image into wave-private
-//                      FP32 LDS tiles.
+//                      taps' polynomials once per item, table taps (Eq. (9))
+//                      do so with pulses per table phase; FP16 taps are added
+//                      image by image into wave-private FP32 LDS tiles.
 //   reduce_kernel      sums, in a fixed order, the partial tiles of tiles that
 //                      were split over several work items.
 //
@@ -44,9 +44,6 @@ namespace ism {
 constexpr int kBaseBits = (TILE <= 256) ? 8 : 9;
 constexpr uint32_t kBaseMask = (1u << kBaseBits) - 1u;
 static_assert(TILE <= (1 << kBaseBits), "tile-local bases must fit the record");
-// The delay fraction of the table-tap record, in units of 2^-kFracBits.
-constexpr int kFracBits = 32 - kBaseBits;
-
 // b^e for e >= 0 by binary powering (0^0 = 1), in FP64: the gain of an image many
 // reflections deep is accurate to its FP32 rounding.
 __device__ double int_pow(double b, int e) {
@@ -371,16 +368,13 @@ __device__ void window_const_entry(float W, int WT, int jj, float *e) {
 // n = -QW/2 .. QW/2, and each tap interpolated linearly between the two
 // entries around its delay. For tap j of an image with fraction f = (fl + fr)/Q
 // (fl an integer in [0, Q), fr in [0, 1)), v = j - f lies between entries
-// n0 = Q j - fl - 1 and n0 + 1, with weight 1 - fr on the upper one. All taps
-// of one image share fl, so the table is stored phase-major: entry
-// (ph, m) = (L[i], L[i + 1] - L[i]) with i = n0 + QW/2 = Q m + ph,
-// ph = Q - 1 - fl and m = j + W/2 - 1; the lanes of an image read consecutive
-// entries of one row.
+// Q j - fl - 1 and Q j - fl, with weight 1 - fr on the upper one: the image is a
+// pulse of weight A (1 - fr) at phase fl of its sample and one of A fr at phase
+// fl + 1, each filtered with the table. The pulses of all images of one integer
+// delay are added up per phase (0 .. Q), and
+//   h[k] = sum_j sum_phase L[Q j - phase] pulse[k - j][phase],
+// the convolution of the moments with other coefficients.
 constexpr int kLutQ = 16;
-template <int WT>
-struct alignas(16) LutPairs {
-  float p[kLutQ][WT][2];
-};
 constexpr double lut_entry(int i, int wt) {  // L[i - QW/2]
   const int n = i - kLutQ * wt / 2;
   const double hann = 0.5 * (1.0 + cx_cos(2.0 * kPi * n / (kLutQ * wt)));  // angle in [-pi, pi]
@@ -393,17 +387,19 @@ constexpr double lut_entry(int i, int wt) {  // L[i - QW/2]
   const double v = (double)n / kLutQ;
   return hann * s / (kPi * v);
 }
+// c[phase][e]: L[Q j - phase] of tap j = WT/2 + 15 - e, zero outside the window.
 template <int WT>
-constexpr LutPairs<WT> make_lut_pairs() {
-  LutPairs<WT> t{};
-  double L[kLutQ * WT + 1] = {};
-  for (int i = 0; i <= kLutQ * WT; ++i) L[i] = lut_entry(i, WT);
-  L[kLutQ * WT] = 0.0;  // the window's end (1 + cos(pi) = 0)
-  for (int ph = 0; ph < kLutQ; ++ph)
-    for (int m = 0; m < WT; ++m) {
-      const int i = kLutQ * m + ph;
-      t.p[ph][m][0] = (float)L[i];
-      t.p[ph][m][1] = (float)(L[i + 1] - L[i]);
+struct LutCoef {
+  float c[kLutQ + 1][WT + 32];
+};
+template <int WT>
+constexpr LutCoef<WT> make_lut_coef() {
+  LutCoef<WT> t{};
+  for (int j = 1 - WT / 2; j <= WT / 2; ++j)
+    for (int ph = 0; ph <= kLutQ; ++ph) {
+      const int i = kLutQ * j - ph + kLutQ * WT / 2;
+      // the window's ends (1 + cos(pi) = 0) and what lies past them
+      t.c[ph][WT / 2 + 15 - j] = i <= 0 || i >= kLutQ * WT ? 0.0f : (float)lut_entry(i, WT);
     }
   return t;
 }
@@ -596,8 +592,8 @@ __device__ __forceinline__ AxisEntry entry_at(const AxisEntry *__restrict__ t, i
 // and hands them to a consumer that turns candidates into image
 // parameters (delay, amplitude; lanes = images) and adds their taps.
 //
-// FP32 consumer (moment_item): images are collected per integer delay and
-// enter through their moments. FP16 and table-tap consumer (tap_item, lanes =
+// FP32 and table-tap consumer (moment_item): images are collected per integer
+// delay and enter through their moments (pulses). FP16 consumer (tap_item, lanes =
 // taps): the candidates' parameters are staged in LDS; each half-wave then
 // takes one staged image per step and its 32 lanes add W/32 taps each into the
 // half-wave's own FP32 tile. All addresses of one step are distinct and
@@ -792,21 +788,11 @@ __device__ __forceinline__ ImageParams image_params(const RoomArgs &ra, const It
   return p;
 }
 
-// Staged record of the FP16 and table taps, with the base in the low bits of a word:
-//   FP16: (t, A') with t = f - 1/2 in FP32 and A' the amplitude with the
-//         base in its 8 low mantissa bits (relative change < 2^-15);
-//   LUT:  (F, A) with F = fq 2^8 + base (bits of a uint32), fq the fraction
-//         in units of 2^-24 (its top 4 bits are the table phase, the next 20 the
-//         interpolation weight), and A in FP32.
-template <bool HALF>
+// Staged record of the FP16 taps: (t, A') with t = f - 1/2 in FP32 and A' the
+// amplitude with the base in its 8 low mantissa bits (relative change < 2^-15).
 __device__ __forceinline__ float2v stage_record(const ImageParams &p) {
-  if constexpr (HALF) {
-    const uint32_t Ab = (__float_as_uint(p.A) & ~kBaseMask) | ((uint32_t)p.base & kBaseMask);
-    return float2v{p.fr - 0.5f, __uint_as_float(Ab)};
-  } else {
-    const uint32_t fq = min((uint32_t)__builtin_rintf(p.fr * (float)(1u << kFracBits)), (1u << kFracBits) - 1u);
-    return float2v{__uint_as_float((fq << kBaseBits) | ((uint32_t)p.base & kBaseMask)), p.A};
-  }
+  const uint32_t Ab = (__float_as_uint(p.A) & ~kBaseMask) | ((uint32_t)p.base & kBaseMask);
+  return float2v{p.fr - 0.5f, __uint_as_float(Ab)};
 }
 
 // Walks the candidates of a wave's batches in chunks of 64 positions (lane i of
@@ -882,23 +868,23 @@ template <> __device__ __forceinline__ const SincPoly<128> &poly_table<128>() { 
 // Compile-time checks of the tables: entries within [-0.25, 1], 1 at v = 0,
 // and 0 (to FP32 rounding) at the other integers, where the sinc vanishes.
 template <int WT>
-constexpr bool lut_sane(const LutPairs<WT> &t) {
-  for (int ph = 0; ph < kLutQ; ++ph)
-    for (int m = 0; m < WT; ++m) {
-      const double e = t.p[ph][m][0];
+constexpr bool lut_sane(const LutCoef<WT> &t) {
+  for (int ph = 0; ph <= kLutQ; ++ph)
+    for (int j = 1 - WT / 2; j <= WT / 2; ++j) {
+      const double e = t.c[ph][WT / 2 + 15 - j];
       if (!(e >= -0.25 && e <= 1.0)) return false;
-      const int n = kLutQ * m + ph - kLutQ * WT / 2;
+      const int n = kLutQ * j - ph;
       if (n == 0 && e != 1.0) return false;
       if (n != 0 && n % kLutQ == 0 && (e > 1e-7 || e < -1e-7)) return false;
     }
   return true;
 }
-static_assert(lut_sane(make_lut_pairs<32>()) && lut_sane(make_lut_pairs<64>()), "table of Eq. (9)");
-static_assert(lut_sane(make_lut_pairs<96>()) && lut_sane(make_lut_pairs<128>()), "table of Eq. (9)");
-__constant__ LutPairs<32> kLut32 = make_lut_pairs<32>();
-__constant__ LutPairs<64> kLut64 = make_lut_pairs<64>();
-__constant__ LutPairs<96> kLut96 = make_lut_pairs<96>();
-__constant__ LutPairs<128> kLut128 = make_lut_pairs<128>();
+static_assert(lut_sane(make_lut_coef<32>()) && lut_sane(make_lut_coef<64>()), "table of Eq. (9)");
+static_assert(lut_sane(make_lut_coef<96>()) && lut_sane(make_lut_coef<128>()), "table of Eq. (9)");
+__constant__ LutCoef<32> kLut32 = make_lut_coef<32>();
+__constant__ LutCoef<64> kLut64 = make_lut_coef<64>();
+__constant__ LutCoef<96> kLut96 = make_lut_coef<96>();
+__constant__ LutCoef<128> kLut128 = make_lut_coef<128>();
 __constant__ MomCoef<32> kMom32 = make_mom_coef<32>();
 __constant__ MomCoef<64> kMom64 = make_mom_coef<64>();
 __constant__ MomCoef<96> kMom96 = make_mom_coef<96>();
@@ -908,11 +894,11 @@ template <> __device__ __forceinline__ const MomCoef<32> &mom_table<32>() { retu
 template <> __device__ __forceinline__ const MomCoef<64> &mom_table<64>() { return kMom64; }
 template <> __device__ __forceinline__ const MomCoef<96> &mom_table<96>() { return kMom96; }
 template <> __device__ __forceinline__ const MomCoef<128> &mom_table<128>() { return kMom128; }
-template <int WT> __device__ __forceinline__ const LutPairs<WT> &lut_table();
-template <> __device__ __forceinline__ const LutPairs<32> &lut_table<32>() { return kLut32; }
-template <> __device__ __forceinline__ const LutPairs<64> &lut_table<64>() { return kLut64; }
-template <> __device__ __forceinline__ const LutPairs<96> &lut_table<96>() { return kLut96; }
-template <> __device__ __forceinline__ const LutPairs<128> &lut_table<128>() { return kLut128; }
+template <int WT> __device__ __forceinline__ const LutCoef<WT> &lut_table();
+template <> __device__ __forceinline__ const LutCoef<32> &lut_table<32>() { return kLut32; }
+template <> __device__ __forceinline__ const LutCoef<64> &lut_table<64>() { return kLut64; }
+template <> __device__ __forceinline__ const LutCoef<96> &lut_table<96>() { return kLut96; }
+template <> __device__ __forceinline__ const LutCoef<128> &lut_table<128>() { return kLut128; }
 
 
 // Output of a work item whose taps are in LDS tiles t0 (+ t1): the tile's own
@@ -943,25 +929,22 @@ __device__ __forceinline__ void write_invalid(int n_own, float *__restrict__ dst
   for (int i = tid; i < WT - 1; i += nthreads) marg[i] = __builtin_nanf("");
 }
 
-// One work item on one wave with FP16 (HALF) or table taps (lanes = taps). Each
+// One work item on one wave with FP16 taps (lanes = taps). Each
 // step takes NQ staged images, one per group of LPG = 64 / NQ lanes; lane l of
 // group g adds the taps j = 1 - W/2 + l + LPG m (m < TPL = W / LPG) of its image
 // into the group's own LDS tile. dst receives the own samples of the tile (or a
 // partial tile when C > 1), marg the margins. Accumulation is FP32.
 // DUMP: the enumeration check. No taps; every owned image is written to
-// dump->rec as a DumpRec of RIR rir (amplitude and fraction as the table
-// taps compute them).
+// dump->rec as a DumpRec of RIR rir.
 // GEN: general-mode window (WT is the cap, W = 2 ra.win_hw): the per-lane tap
 // constants come from wc ([WT][WC_STRIDE], written for this window by
 // tables_kernel).
-template <int WT, bool HALF, int NQ, bool POLAR = false, bool DUMP = false, bool GEN = false>
+template <int WT, int NQ, bool POLAR = false, bool DUMP = false, bool GEN = false>
 __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
                                          float *__restrict__ dst, float *__restrict__ marg,
                                          const DumpArgs *dump = nullptr, const int rir = 0,
                                          const float *__restrict__ wc = nullptr) {
-  constexpr bool LUT = !HALF && !DUMP;
-  static_assert(!(GEN && !HALF), "general-mode windows take FP16 taps here");
   constexpr int LSPAN = TILE + WT - 1;
   constexpr int LPG = 64 / NQ;          // lanes per image
   constexpr int TPL = WT / LPG;         // taps per lane per step
@@ -995,7 +978,7 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   // per-lane tap constants
   float pc0[TPL];          // FP16 taps: c0 of each tap
   half2_t pq[NPAIR][SPD];  // and c1..c5 of tap pairs (2p, 2p + 1)
-  if constexpr (HALF) {
+  if constexpr (!DUMP) {
     auto coef = [&](int k, int jj) {
       if constexpr (GEN) return wc[WC_STRIDE * jj + k];
       else return poly_table<WT>().c[k][jj];
@@ -1014,53 +997,25 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   }
   for (int i = lane; i < NQ * LSPAN; i += 64) (&tile[0][0])[i] = 0.0f;
   float *const th = &tile[h][l];
-  // LUT taps: the table is copied into LDS once per work item (8 KB at
-  // W = 64; it costs occupancy, but LDS reads of a row's consecutive pairs
-  // beat the vector-memory path, 0.68 against 0.89 ms on the 32-receiver
-  // call); lrow is this lane's first entry of row 0 (rows are WT pairs apart)
-  __shared__ __attribute__((aligned(16))) float lds_lut[LUT ? kLutQ * WT * 2 : 4];
-  if constexpr (LUT) {
-    const float *gl = &lut_table<WT>().p[0][0][0];
-    for (int i = lane; i < kLutQ * WT * 2; i += 64) lds_lut[i] = gl[i];
-    wave_sync();
-  }
-  const float *const lrow = &lds_lut[LUT ? 2 * l : 0];
-
   // One step: staged image (record P) on this lane group, taps l + LPG m.
   // The empty asm consumes the record as one value where the step starts,
   // which keeps its LDS read a single 8-byte read issued ahead.
   auto step = [&](const Rec P) {
     __asm__ volatile("" ::"v"(P));
-    const uint32_t bw = __float_as_uint(HALF ? P.y : P.x);  // record word that carries the base
-    const int b = (int)(bw & kBaseMask);
+    const int b = (int)(__float_as_uint(P.y) & kBaseMask);
     float *t = th + b;
-    if constexpr (HALF) {
-      // tap = A (c0 + t q(t)), q in packed FP16 two taps at a time, the
-      // rest in FP32 (t q(t) + c0 as one mixed-precision FMA)
-      const float tf = P.x, A = P.y;
-      const half2_t tt = {(_Float16)tf, (_Float16)tf};
+    // tap = A (c0 + t q(t)), q in packed FP16 two taps at a time, the
+    // rest in FP32 (t q(t) + c0 as one mixed-precision FMA)
+    const float tf = P.x, A = P.y;
+    const half2_t tt = {(_Float16)tf, (_Float16)tf};
 #pragma unroll
-      for (int pr = 0; pr < NPAIR; ++pr) {
-        half2_t q = pq[pr][SPD - 1];
+    for (int pr = 0; pr < NPAIR; ++pr) {
+      half2_t q = pq[pr][SPD - 1];
 #pragma unroll
-        for (int k = SPD - 2; k >= 0; --k) q = __builtin_elementwise_fma(q, tt, pq[pr][k]);
-        const int m0 = 2 * pr, m1 = 2 * pr + 1;
-        t[LPG * m0] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.x, pc0[m0]), t[LPG * m0]);
-        if (m1 < TPL) t[LPG * m1] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.y, pc0[m1]), t[LPG * m1]);
-      }
-    } else {
-      // tap = A (L[i] + (1 - fr) (L[i + 1] - L[i])) from row ph of the table
-      const uint32_t F = __float_as_uint(P.x);
-      const float A = P.y;
-      const int ph = (kLutQ - 1) - (int)(F >> 28);
-      const float al = 1.0f - (float)((F >> kBaseBits) & ((1u << (28 - kBaseBits)) - 1u)) *
-                                  (1.0f / (float)(1u << (28 - kBaseBits)));
-      const float *const row = lrow + 2 * WT * ph;
-#pragma unroll
-      for (int m = 0; m < TPL; ++m) {
-        const float2v e = *reinterpret_cast<const float2v *>(row + 2 * LPG * m);
-        t[LPG * m] = __builtin_fmaf(A, __builtin_fmaf(al, e.y, e.x), t[LPG * m]);
-      }
+      for (int k = SPD - 2; k >= 0; --k) q = __builtin_elementwise_fma(q, tt, pq[pr][k]);
+      const int m0 = 2 * pr, m1 = 2 * pr + 1;
+      t[LPG * m0] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.x, pc0[m0]), t[LPG * m0]);
+      if (m1 < TPL) t[LPG * m1] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.y, pc0[m1]), t[LPG * m1]);
     }
   };
   // staged record k (read as one 8-byte access: see step)
@@ -1091,7 +1046,7 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
           d.n[1] = ra.perm[0] == 1 ? t0 : (ra.perm[1] == 1 ? t1 : t2);
           d.n[2] = ra.perm[0] == 2 ? t0 : (ra.perm[1] == 2 ? t1 : t2);
           d.k0 = g.T0 + p.base;
-          d.fq = (__float_as_uint(stage_record<false>(p).x) >> kBaseBits) << (kBaseBits - 8);  // units of 2^-24
+          d.fq = min((uint32_t)__builtin_rintf(p.fr * 0x1p24f), (1u << 24) - 1u);  // units of 2^-24
           d.A = p.A;
           d.pad = 0;
           dump->rec[first + (uint32_t)rank] = d;
@@ -1099,7 +1054,7 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
         wave_sync();
         return;
       }
-      if (p.ok) stp[ns + rank] = stage_record<HALF>(p);
+      if (p.ok) stp[ns + rank] = stage_record(p);
       ns += __builtin_popcountll(okm);
       wave_sync();
       // lanes = taps: NQ staged images per step, one per lane group; the next
@@ -1138,7 +1093,8 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 }
 
 // ---------------------------------------------------------------------------
-// One work item on a workgroup of four waves with FP32 taps, by moments (MOM above).
+// One work item on a workgroup of four waves with FP32 taps, by moments (MOM
+// above), or with table taps (LUT), by pulses per phase (kLutQ above).
 //
 // Collection (lanes = images): each wave enumerates its share of the columns; an
 // image's record (t, A) goes to the next slot of the wave's part of an LDS pool
@@ -1152,6 +1108,8 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 // Four waves share a pool because the walk takes as many steps as the longest of
 // 64 lists: with Poisson lengths of mean 10 that is 1.9 steps per image and
 // lane, with a wave's own pool (256 delays, mean 2.5) 2.9.
+// Table taps add a record's two pulses to the lane's own column of an LDS array
+// [phase][delay] instead, which no other lane touches.
 // Convolution: at the end of the item the moments go to LDS planes and
 // matrix instructions form the item's TILE + W - 1 output samples: output
 // o = 16 a + r of row r, column a is the sum over planes and k' of
@@ -1167,18 +1125,23 @@ constexpr int MOM_WAVES = 4;
 // of LDS and four fit a compute unit: 1024-room batch 6.43 ms, 64 microphones at
 // 48 kHz 2.37 ms, against 7.39 and 2.76 with 15 chunks (three workgroups) and 6.90
 // and 2.48 with 7 (five).
-constexpr int MOM_SLOTS = 640;
-constexpr int MOM_END = 8 * MOM_WAVES * MOM_SLOTS;  // end of a list (slots are linked by byte offset in rec)
-static_assert(TILE == 64 * MOM_WAVES && MOM_END < 65536, "one delay per thread, 16-bit links");
+// Table taps: 6 chunks, three workgroups with the 17 KB of pulses (32 receivers 201 us;
+// 220 with 4 chunks, 253 with 10 and two workgroups; image by image in LDS tiles 703).
+constexpr int mom_slots(bool lut) { return lut ? 384 : 640; }
+// end of a list (slots are linked by byte offset in rec)
+constexpr int mom_end(bool lut) { return 8 * MOM_WAVES * mom_slots(lut); }
+static_assert(TILE == 64 * MOM_WAVES && mom_end(false) < 65536 && mom_end(true) < 65536, "one delay per thread, 16-bit links");
+template <bool LUT>
 struct MomPool {
-  float2v rec[MOM_WAVES * MOM_SLOTS + 1];  // (t, A); the last slot ends every list: (0, 0)
+  float2v rec[MOM_WAVES * mom_slots(LUT) + 1];  // (t, A), table taps (f, A); the last slot ends every list: (0, 0)
   uint32_t head[MOM_WAVES][TILE];
-  uint16_t next[MOM_WAVES * MOM_SLOTS + 4];
+  uint16_t next[MOM_WAVES * mom_slots(LUT) + 4];
   uint16_t tail[MOM_WAVES][TILE];
+  float pulse[LUT ? kLutQ + 1 : 1][LUT ? TILE : 1];
 };
-template <int WT, bool EDGE>
+template <int WT, bool EDGE, bool LUT>
 struct MomShape {
-  static constexpr int P = MOM + (EDGE ? 2 : 0);          // planes
+  static constexpr int P = LUT ? kLutQ + 1 : MOM + (EDGE ? 2 : 0);  // planes
   static constexpr int KS = (WT + 16) / 4;                // matrix steps per plane
   static constexpr int NBLK = (TILE + WT - 1 + 15) / 16;  // output blocks of 16
   static constexpr int XN = 16 * NBLK + WT;               // plane entries
@@ -1187,20 +1150,21 @@ struct MomShape {
   static_assert(NBLK <= 32 && XN % 16 == 0 && KS % 16 % 4 == 0, "convolution shape");
 };
 
-template <int WT, bool POLAR, bool GEN>
+template <int WT, bool LUT, bool POLAR, bool GEN>
 __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                             const AxisEntry *__restrict__ tab, const AxisOrigin &org,
                                             const bool valid, float *__restrict__ dst, float *__restrict__ marg,
                                             const float *__restrict__ wc) {
   constexpr bool EDGE = GEN && WT <= kEdgeCap;
   constexpr bool DIRECT = GEN && WT == 32;  // may hold windows shorter than kDirectWin
-  typedef MomShape<WT, EDGE> Sh;
-  constexpr int P = Sh::P, NT = 64 * MOM_WAVES;
+  static_assert(!(GEN && LUT), "table taps are built for the exact windows");
+  typedef MomShape<WT, EDGE, LUT> Sh;
+  constexpr int P = Sh::P, NT = 64 * MOM_WAVES, SLOTS = mom_slots(LUT);
   constexpr int LM = WT / 2 - 1;
-  constexpr uint32_t END = MOM_END;
+  constexpr uint32_t END = mom_end(LUT);
   __shared__ union alignas(16) {
-    MomPool pool;
-    float conv[P * (Sh::PL + Sh::CL)];
+    MomPool<LUT> pool;
+    float conv[P * (Sh::PL + (GEN ? Sh::CL : 0))];
     float part[MOM_WAVES][512];
   } u;
   __shared__ EnumLds es_all[MOM_WAVES];
@@ -1222,9 +1186,12 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   const AxisRange az = axis_range(ra.lo[2], ra.N[2], ra.inv_period[2], org.e_even[2], org.e_odd[2]);
   const ItemGeom g = item_geom(ra, ax, tile_id, C, c);
 
-  float m[P];  // this thread's delay: sums of A t^p (then the edge taps)
+  float m[P];  // this thread's delay: sums of A t^p (then the edge taps); table taps: its pulses, at the end
 #pragma unroll
-  for (int p = 0; p < P; ++p) m[p] = 0.0f;
+  for (int p = 0; p < P; ++p) {
+    m[p] = 0.0f;
+    if constexpr (LUT) u.pool.pulse[p][tid] = 0.0f;
+  }
 #pragma unroll
   for (int v = 0; v < MOM_WAVES; ++v) u.pool.head[v][tid] = END;
   if (tid == 0) {
@@ -1243,6 +1210,14 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   // one record into the sums
   auto add = [&](const float2v r, auto taps) {
     const float t = r.x, A = r.y;
+    if constexpr (LUT) {
+      const float x = t * (float)kLutQ, fl = fminf(floorf(x), (float)(kLutQ - 1));
+      const float hi = A * (x - fl);
+      float *const g = &u.pool.pulse[(int)fl][tid];
+      g[0] += A - hi;
+      g[TILE] += hi;
+      return;
+    }
     if constexpr (decltype(taps)::value) {
       // tap j at v = j - f, j = -1 .. 2 (|v| < 2), into sum j + 1
       const float f = fminf(fmaxf(t + 0.5f, 0x1p-24f), 0x1.fffffep-1f);
@@ -1306,15 +1281,15 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   __syncthreads();
   for (;;) {
     bool more = true;
-    for (int slot = 0; slot < MOM_SLOTS; slot += 64) {
+    for (int slot = 0; slot < SLOTS; slot += 64) {
       more = cw.advance();
       if (!more) break;
       cw.visit([&](bool live, int cl, int, float cg, const AxisEntry ez) {
         const ImageParams p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
         if (live && p.ok) {
-          const uint32_t i = (uint32_t)(8 * (wv * MOM_SLOTS + slot + lane));
+          const uint32_t i = (uint32_t)(8 * (wv * SLOTS + slot + lane));
           const uint32_t old = atomicExch(&u.pool.head[wv][p.base], i);
-          u.pool.rec[i / 8] = float2v{p.fr - 0.5f, p.A};
+          u.pool.rec[i / 8] = float2v{LUT ? p.fr : p.fr - 0.5f, p.A};
           next_at(i) = (uint16_t)old;
           if (old == END) u.pool.tail[wv][p.base] = (uint16_t)i;
         }
@@ -1343,6 +1318,11 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
     if (!__builtin_amdgcn_readfirstlane(more4.x | more4.y | more4.z | more4.w)) break;
   }
 
+  if constexpr (LUT) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) m[p] = u.pool.pulse[p][tid];
+    __syncthreads();
+  }
   // convolution
   float *const planes = u.conv, *const coefs = u.conv + P * Sh::PL;
   {
@@ -1383,8 +1363,8 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   __syncthreads();
   const int lc = lane & 15, lk = lane >> 4;  // matrix row (coefficients) / column (planes), k group
   const int a0 = min(lc, Sh::NBLK - 1), a1 = min(lc + 16, Sh::NBLK - 1);
-  // sums of planes 0, 1, 2 and of the others apart (then smallest first): each
-  // rounds at its own, smaller size
+  // sums of planes 0, 1, 2 and of the others apart (then smallest first; table
+  // taps: of every fourth phase): each rounds at its own, smaller size
   f4v d0[4], d1[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) d0[i] = d1[i] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
@@ -1392,13 +1372,14 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   const int s0 = wv * KQ;
 #pragma unroll
   for (int p = P - 1; p >= 0; --p) {
-    const int i = p < 3 ? p : 3;
+    const int i = LUT ? p & 3 : p < 3 ? p : 3;
     const float *b0 = planes + p * Sh::PL + 17 * a0 + lk, *b1 = planes + p * Sh::PL + 17 * a1 + lk;
 #pragma unroll
     for (int k = 0; k < KQ; ++k) {
       const int s = s0 + k;
       float cv;
       if constexpr (GEN) cv = coefs[p * Sh::CL + 4 * s + (lk - lc + 15)];
+      else if constexpr (LUT) cv = lut_table<WT>().c[p][(uint32_t)(4 * s + (lk - lc + 15))];
       else cv = mom_table<WT>().c[p][(uint32_t)(4 * s + (lk - lc + 15))];
       d0[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b0[4 * s + (s >> 2)], d0[i], 0, 0, 0);
       d1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b1[4 * s + (s >> 2)], d1[i], 0, 0, 0);
@@ -1423,8 +1404,8 @@ __device__ __forceinline__ void run_item(const RoomArgs &ra, const int tile_id, 
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
                                          float *__restrict__ dst, float *__restrict__ marg,
                                          const float *__restrict__ wc) {
-  if constexpr (HALF || LUT) tap_item<WT, HALF, 2, POLAR, false, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, nullptr, 0, wc);
-  else moment_item<WT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
+  if constexpr (HALF) tap_item<WT, 2, POLAR, false, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, nullptr, 0, wc);
+  else moment_item<WT, LUT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
 }
 
 // First work item of dispatch position pos (see PlanArgs).
@@ -1471,7 +1452,7 @@ __device__ __forceinline__ SingleItem decode_item(const PlanArgs &pa, uint32_t i
 }
 
 template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
-__global__ __launch_bounds__(item_threads(HALF, LUT))
+__global__ __launch_bounds__(item_threads(HALF))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
 accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_all,
                   const AxisOrigin *__restrict__ origin, const int *__restrict__ valid, float *__restrict__ out,
@@ -1494,7 +1475,7 @@ __global__ __launch_bounds__(64) void enumerate_dump_kernel(RoomArgs ra, PlanArg
                                                             const int *__restrict__ valid, DumpArgs dump) {
   const SingleItem si = decode_item(pa, blockIdx.x);
   const AxisOrigin org = origin[si.rir];
-  tap_item<WT, false, 2, false, true>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
+  tap_item<WT, 2, false, true>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
                                       valid[si.rir] != 0, nullptr, nullptr, &dump, si.rir);
 }
 
@@ -1510,13 +1491,13 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int n) {
 // Without a queue (queue == null) a workgroup takes every gridDim.x-th item.
 // Every item names its job; the job table carries the room.
 template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
-__global__ __launch_bounds__(item_threads(HALF, LUT))
+__global__ __launch_bounds__(item_threads(HALF))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
 accumulate_batch_kernel(
     const JobDev *__restrict__ jobs, const BatchItem *__restrict__ items, uint32_t n_items, uint32_t *queue,
     const AxisEntry *__restrict__ tab_all, const AxisOrigin *__restrict__ origin, const int *__restrict__ valid,
     float *__restrict__ part, float *__restrict__ marg) {
-  constexpr bool MULTI = item_threads(HALF, LUT) > 64;
+  constexpr bool MULTI = item_threads(HALF) > 64;
   const int lane = threadIdx.x & 63;
   __shared__ uint32_t next_item;
   uint32_t item = blockIdx.x;
@@ -1757,7 +1738,7 @@ static int launch_acc_w(const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items
                         const AxisOrigin *origin, const int *valid, float *out, float *part, float *marg,
                         const float *wc, hipStream_t st) {
   hipLaunchKernelGGL((accumulate_kernel<WT, HALF, LUT, POLAR, GEN>), dim3(n_items),
-                     dim3(item_threads(HALF, LUT)), 0, st, ra, pa, tab, origin, valid, out, part, marg, wc);
+                     dim3(item_threads(HALF)), 0, st, ra, pa, tab, origin, valid, out, part, marg, wc);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -1853,7 +1834,7 @@ static int launch_acc_batch_w(const JobDev *jobs, const BatchItem *items, uint32
                               uint32_t *queue, const AxisEntry *tab, const AxisOrigin *origin, const int *valid,
                               float *part, float *marg, hipStream_t st) {
   hipLaunchKernelGGL((accumulate_batch_kernel<WT, HALF, LUT, POLAR, GEN>),
-                     dim3(grid), dim3(item_threads(HALF, LUT)), 0, st, jobs, items, n_items, queue, tab, origin, valid, part, marg);
+                     dim3(grid), dim3(item_threads(HALF)), 0, st, jobs, items, n_items, queue, tab, origin, valid, part, marg);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -174,7 +174,7 @@ double batch_item_taps(int wt, bool half) {
 // 4 SIMDs x the waves per SIMD the kernel is built for, over its waves per
 // item), and the default rounds of them over which a single call tapers its tail.
 double resident_items(bool half, bool lut) {
-  return 256.0 * 4.0 * waves_per_simd(half, lut) * 64.0 / item_threads(half, lut);
+  return 256.0 * 4.0 * waves_per_simd(half, lut) * 64.0 / item_threads(half);
 }
 constexpr double kTailRounds = 1.0;
 
@@ -291,7 +291,7 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   }
   // an explicit item size is used as given
   const bool fixed = sched && sched->item_taps > 0.0;
-  const bool mom = !p.half && !p.lut;  // FP32: items of images (moments), else of taps
+  const bool mom = !p.half;  // FP32 and table taps: items of images, FP16: of taps
   double target = fixed ? std::max(1e3, sched->item_taps) : item_target(p.total_taps, p.wt, p.half, mom, nS, sched);
   const double resident = resident_items(p.half, p.lut);
   if (!fixed && !mom && p.total_taps < resident * target)
@@ -789,7 +789,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     if (!(sched && sched->item_taps > 0.0)) {
       ism_schedule js{};
       if (sched) js = *sched;
-      const bool mom = !p.half && !p.lut;
+      const bool mom = !p.half;
       double t = item_target(batch_taps, p.wt, p.half, mom, p.ra.n_samples, sched);
       if (!mom) t = std::min(t, batch_item_taps(p.wt, p.half));
       // a batch too small to give every resident wave an item of that size is
@@ -851,12 +851,12 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     bp.st.class_gen[k] = class_gen[k];
     // persistent grid: the tuned workgroups per SIMD (or the schedule's)
     int waves = waves_per_simd(precision == ISM_FP16, precision == ISM_FP32_LUT);
-    if (precision != ISM_FP32)
+    if (precision == ISM_FP16)
       for (const BatchTuning &t : kBatchTuning)
         if (t.wt == class_wt[k] && t.half == (precision == ISM_FP16 ? 1 : 0)) waves = t.waves;
     if (sched && sched->batch_waves > 0.0) waves = std::max(1, (int)std::lround(sched->batch_waves));
     bp.st.class_grid[k] = (uint32_t)std::min<uint64_t>(
-        bp.st.class_count[k], 1024ull * (uint64_t)waves * 64 / item_threads(precision == ISM_FP16, precision == ISM_FP32_LUT));
+        bp.st.class_count[k], 1024ull * (uint64_t)waves * 64 / item_threads(precision == ISM_FP16));
   }
   bp.st.n_jobs = (uint32_t)n_jobs;
   bp.st.any_gen = wc_floats > 0 ? 1u : 0u;

@@ -39,11 +39,11 @@ constexpr int kMaxBatchClasses = 8;
 // Work items per tile are capped so the per-tile chunk count fits a byte.
 constexpr int MAX_CHUNKS = 255;
 // Waves per SIMD the accumulate kernels are built for (their LDS and VGPR
-// budget) and threads per work item: one wave for FP16 and table taps, four
-// waves that share a 32 KB image pool for FP32. The planner sizes items and the
-// tail taper of a launch with them.
-constexpr int waves_per_simd(bool half, bool lut) { return half || lut ? 7 : 4; }
-constexpr int item_threads(bool half, bool lut) { return half || lut ? 64 : 256; }
+// budget) and threads per work item: one wave for FP16 taps, four waves that share
+// an image pool for FP32 and table taps. The planner sizes items and the tail
+// taper of a launch with them.
+constexpr int waves_per_simd(bool half, bool lut) { return half ? 7 : lut ? 3 : 4; }
+constexpr int item_threads(bool half) { return half ? 64 : 256; }
 
 // Per-call room constants, passed by value as a kernel argument. Lengths are in
 // metres, delays in samples. Float pairs (hi, lo) carry double-precision host

@@ -1,5 +1,5 @@
-"""FP32 taps by moments (ism_simulate) where their paths meet, against the FP64
-oracle: windows around the limits of the directly summed and the edge taps, a
+"""FP32 taps by moments and table taps by pulses (ism_simulate) where their paths
+meet, against the FP64 oracle: windows around the limits of the directly summed and the edge taps, a
 room whose images coincide in delay (long lists), items smaller and larger than
 the image pool, and RIR lengths around the tile."""
 import sys
@@ -37,11 +37,21 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+# Table taps: entries and weights are rounded to FP32 (an entry moves by 6e-8, the
+# weight of a slope of at most 0.1 per entry by 16 x 6e-8): the same bound.
+LUT_CASES = [(f"lut_{c[0]}",) + c[1:] for c in CASES if c[2] == 64.0] + [
+    ("lut_w_32", 8000.0, 32.0, 0.1, [3.0, 4.0, 2.5], False, 0.0),
+    ("lut_w_96", 48000.0, 96.0, 0.02, [3.0, 4.0, 2.5], False, 0.0),
+    ("lut_w_128", 32000.0, 128.0, 0.04, [3.0, 4.0, 2.5], False, 1e9),
+]
+
+
+@pytest.mark.parametrize("case", CASES + LUT_CASES, ids=[c[0] for c in CASES + LUT_CASES])
 def test_moments_match_oracle(oracle_mod, case):
     import torch
 
     name, fs, W, t_max, L, centred, item_taps = case
+    prec, lut_q = ("lut", 16) if name.startswith("lut") else ("fp32", 0)
     n = ism.n_img_for_time(L, 343.0, t_max + W / fs)
     room = ism.Room(L, [0.9, 0.85, 0.8, 0.9, 0.7, 0.95], n, 343.0, fs, t_max, W / fs)
     if centred:
@@ -54,12 +64,13 @@ def test_moments_match_oracle(oracle_mod, case):
     print(f"[case] moments {name}: n_img {n}", flush=True)
     sys.stdout.flush()
     sched = ism.Schedule(item_taps=item_taps) if item_taps else None
-    h = ism.simulate(room, src, rcv, schedule=sched)
+    h = ism.simulate(room, src, rcv, prec, schedule=sched)
     torch.cuda.synchronize()
     got = h.cpu().numpy().astype(np.float64)
     # lists are joined in a fixed order: the same bits again
-    assert torch.equal(h.cpu(), ism.simulate(room, src, rcv, schedule=sched).cpu())
-    ref = oracle_mod.rir(room.room, room.beta, room.n_img, room.c, room.fs, room.t_max, room.t_w, src, rcv)
+    assert torch.equal(h.cpu(), ism.simulate(room, src, rcv, prec, schedule=sched).cpu())
+    ref = oracle_mod.rir(room.room, room.beta, room.n_img, room.c, room.fs, room.t_max, room.t_w, src, rcv,
+                         lut_q=lut_q)
     peak = np.max(np.abs(oracle_mod.rir(room.room, room.beta, room.n_img, room.c, room.fs, max(t_max, 0.02),
                                         room.t_w, src, rcv)), axis=-1)
     err = float(np.max(np.max(np.abs(got - ref), axis=-1) / peak))
