@@ -622,18 +622,18 @@ static_assert(ISM_MAX_N_IMG <= 2048, "nx_col packs y table indices in 11 bits");
 
 // Wave-uniform geometry of one work item.
 struct ItemGeom {
-  int T0, T1;                    // output samples [T0, T1) of the tile (empty past nS)
+  int T0;                        // first sample of the tile
   int K1;                        // owned integer delays: k0 in [T0, K1)
   float R0, R1;                  // shell radii in samples, widened by 2
   double r1, r0;                 // their squares (r0 = 0 where R0 < 0)
   int nx_a, nx_b;                // x table indices of the slab
 };
 
-__device__ __forceinline__ ItemGeom item_geom(const RoomArgs &ra, const AxisRange &ax, int tile_id, int C, int c) {
+__device__ __forceinline__ ItemGeom item_geom(const RoomArgs &ra, const AxisRange &ax, int TL, int tile_id, int C,
+                                              int c) {
   ItemGeom g;
-  g.T0 = tile_id * TILE;
-  g.T1 = min(g.T0 + TILE, ra.n_samples);
-  g.K1 = min(g.T0 + TILE, ra.k_end);
+  g.T0 = tile_id * TL;
+  g.K1 = min(g.T0 + TL, ra.k_end);
   // The owned images have delay x in [T0, K1); the enumeration bounds are
   // widened by two samples on each side and every candidate is then filtered
   // exactly on its integer delay.
@@ -973,7 +973,7 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   const AxisRange ax = axis_range(ra.lo[0], ra.N[0], ra.inv_period[0], org.e_even[0], org.e_odd[0]);
   const AxisRange ay = axis_range(ra.lo[1], ra.N[1], ra.inv_period[1], org.e_even[1], org.e_odd[1]);
   const AxisRange az = axis_range(ra.lo[2], ra.N[2], ra.inv_period[2], org.e_even[2], org.e_odd[2]);
-  const ItemGeom g = item_geom(ra, ax, tile_id, C, c);
+  const ItemGeom g = item_geom(ra, ax, DUMP ? ra.tile : TILE, tile_id, C, c);
 
   // per-lane tap constants
   float pc0[TPL];          // FP16 taps: c0 of each tap
@@ -1100,8 +1100,8 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 // image's record (t, A) goes to the next slot of the wave's part of an LDS pool
 // and is linked into the wave's list of its integer delay with one exchange on
 // the list's head, so images of one delay in one chunk need no ordering and
-// nothing is lost. When the waves have filled their parts, wave w takes the
-// delays 64 w + lane: the four waves' lists of a delay are linked into one,
+// nothing is lost. When the waves have filled their parts, each thread takes
+// its delays of the tile: the four waves' lists of a delay are linked into one,
 // and each lane walks its list and adds every record's moments into its registers
 // (lanes = delays). A list holds its wave's images in program order and the
 // lists are joined in wave order, so a call always adds in the same order.
@@ -1111,7 +1111,7 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 // Table taps add a record's two pulses to the lane's own column of an LDS array
 // [phase][delay] instead, which no other lane touches.
 // Convolution: at the end of the item the moments go to LDS planes and
-// matrix instructions form the item's TILE + W - 1 output samples: output
+// matrix instructions form the item's T + W - 1 output samples: output
 // o = 16 a + r of row r, column a is the sum over planes and k' of
 // coefficient[k' - r] and plane[16 a + k'], an FP32 16 x 16 x 4 product per
 // four k', whose left operand is the same for all columns; wave w takes a
@@ -1124,33 +1124,38 @@ constexpr int MOM_WAVES = 4;
 // Pool slots per wave: 10 chunks of 64 positions. With these a workgroup takes 40 KB
 // of LDS and four fit a compute unit: 1024-room batch 6.43 ms, 64 microphones at
 // 48 kHz 2.37 ms, against 7.39 and 2.76 with 15 chunks (three workgroups) and 6.90
-// and 2.48 with 7 (five).
+// and 2.48 with 7 (five). Long tiles: 7 chunks beside their 12 KB of list ends.
 // Table taps: 6 chunks, three workgroups with the 17 KB of pulses (32 receivers 201 us;
 // 220 with 4 chunks, 253 with 10 and two workgroups; image by image in LDS tiles 703).
-constexpr int mom_slots(bool lut) { return lut ? 384 : 640; }
+constexpr int mom_slots(int TL, bool lut) { return lut ? 384 : TL == TILE ? 640 : 448; }
 // end of a list (slots are linked by byte offset in rec)
-constexpr int mom_end(bool lut) { return 8 * MOM_WAVES * mom_slots(lut); }
-static_assert(TILE == 64 * MOM_WAVES && mom_end(false) < 65536 && mom_end(true) < 65536, "one delay per thread, 16-bit links");
-template <bool LUT>
+constexpr int mom_end(int TL, bool lut) { return 8 * MOM_WAVES * mom_slots(TL, lut); }
+static_assert(mom_end(TILE, false) < 65536, "16-bit links");
+template <int TL, bool LUT>
 struct MomPool {
-  float2v rec[MOM_WAVES * mom_slots(LUT) + 1];  // (t, A), table taps (f, A); the last slot ends every list: (0, 0)
-  uint32_t head[MOM_WAVES][TILE];
-  uint16_t next[MOM_WAVES * mom_slots(LUT) + 4];
-  uint16_t tail[MOM_WAVES][TILE];
-  float pulse[LUT ? kLutQ + 1 : 1][LUT ? TILE : 1];
+  float2v rec[MOM_WAVES * mom_slots(TL, LUT) + 1];  // (t, A), table taps (f, A); the last slot ends every list: (0, 0)
+  uint32_t head[MOM_WAVES][TL];
+  uint16_t next[MOM_WAVES * mom_slots(TL, LUT) + 4];
+  uint16_t tail[MOM_WAVES][TL];
+  float pulse[LUT ? kLutQ + 1 : 1][LUT ? TL : 1];
 };
-template <int WT, bool EDGE, bool LUT>
+template <int WT, int TL, bool EDGE, bool LUT, bool GEN>
 struct MomShape {
+  static constexpr int NB = TL / (64 * MOM_WAVES);                  // delays per thread
   static constexpr int P = LUT ? kLutQ + 1 : MOM + (EDGE ? 2 : 0);  // planes
   static constexpr int KS = (WT + 16) / 4;                // matrix steps per plane
-  static constexpr int NBLK = (TILE + WT - 1 + 15) / 16;  // output blocks of 16
+  static constexpr int NBLK = (TL + WT - 1 + 15) / 16;    // output blocks of 16
+  static constexpr int NCT = (NBLK + 15) / 16;            // column tiles of 16 blocks
   static constexpr int XN = 16 * NBLK + WT;               // plane entries
   static constexpr int PL = XN + XN / 16;                 // plane length with the bank skew
   static constexpr int CL = WT + 32;                      // coefficients per plane, zeros around
-  static_assert(NBLK <= 32 && XN % 16 == 0 && KS % 16 % 4 == 0, "convolution shape");
+  // planes in LDS at a time
+  static constexpr int CG = GEN ? CL : 0;
+  static constexpr int PB = P * (PL + CG) * sizeof(float) <= sizeof(MomPool<TL, LUT>) ? P : (P + 1) / 2;
+  static_assert(TL % (64 * MOM_WAVES) == 0 && XN % 16 == 0 && KS % MOM_WAVES == 0, "convolution shape");
 };
 
-template <int WT, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, bool LUT, bool POLAR, bool GEN>
 __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                             const AxisEntry *__restrict__ tab, const AxisOrigin &org,
                                             const bool valid, float *__restrict__ dst, float *__restrict__ marg,
@@ -1158,14 +1163,14 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   constexpr bool EDGE = GEN && WT <= kEdgeCap;
   constexpr bool DIRECT = GEN && WT == 32;  // may hold windows shorter than kDirectWin
   static_assert(!(GEN && LUT), "table taps are built for the exact windows");
-  typedef MomShape<WT, EDGE, LUT> Sh;
-  constexpr int P = Sh::P, NT = 64 * MOM_WAVES, SLOTS = mom_slots(LUT);
+  typedef MomShape<WT, TL, EDGE, LUT, GEN> Sh;
+  constexpr int P = Sh::P, NT = 64 * MOM_WAVES, SLOTS = mom_slots(TL, LUT), NB = Sh::NB;
   constexpr int LM = WT / 2 - 1;
-  constexpr uint32_t END = mom_end(LUT);
+  constexpr uint32_t END = mom_end(TL, LUT);
   __shared__ union alignas(16) {
-    MomPool<LUT> pool;
-    float conv[P * (Sh::PL + (GEN ? Sh::CL : 0))];
-    float part[MOM_WAVES][512];
+    MomPool<TL, LUT> pool;
+    float conv[Sh::PB * (Sh::PL + Sh::CG)];
+    float part[MOM_WAVES][256 * Sh::NCT];
   } u;
   __shared__ EnumLds es_all[MOM_WAVES];
   __shared__ float col_p_all[POLAR ? MOM_WAVES : 1][POLAR ? 64 : 1];  // column part of |d| cos(theta)
@@ -1173,7 +1178,7 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_own = min(TILE, ra.n_samples - tile_id * TILE);  // may be <= 0 past nS
+  const int n_own = min(TL, ra.n_samples - tile_id * TL);  // may be <= 0 past nS
   if (!valid) {
     write_invalid<WT>(n_own, dst, marg, tid, NT);
     return;
@@ -1184,16 +1189,21 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   const AxisRange ax = axis_range(ra.lo[0], ra.N[0], ra.inv_period[0], org.e_even[0], org.e_odd[0]);
   const AxisRange ay = axis_range(ra.lo[1], ra.N[1], ra.inv_period[1], org.e_even[1], org.e_odd[1]);
   const AxisRange az = axis_range(ra.lo[2], ra.N[2], ra.inv_period[2], org.e_even[2], org.e_odd[2]);
-  const ItemGeom g = item_geom(ra, ax, tile_id, C, c);
+  const ItemGeom g = item_geom(ra, ax, TL, tile_id, C, c);
 
-  float m[P];  // this thread's delay: sums of A t^p (then the edge taps); table taps: its pulses, at the end
+  // this thread's delays tid, tid + NT, ..: sums of A t^p (then the edge taps);
+  // table taps: the pulses, at the end
+  float m[NB][P];
 #pragma unroll
-  for (int p = 0; p < P; ++p) {
-    m[p] = 0.0f;
-    if constexpr (LUT) u.pool.pulse[p][tid] = 0.0f;
+  for (int b = 0; b < NB; ++b) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      m[b][p] = 0.0f;
+      if constexpr (LUT) u.pool.pulse[p][tid + NT * b] = 0.0f;
+    }
+#pragma unroll
+    for (int v = 0; v < MOM_WAVES; ++v) u.pool.head[v][tid + NT * b] = END;
   }
-#pragma unroll
-  for (int v = 0; v < MOM_WAVES; ++v) u.pool.head[v][tid] = END;
   if (tid == 0) {
     u.pool.rec[END / 8] = float2v{0.0f, 0.0f};
     u.pool.next[END / 8] = (uint16_t)END;
@@ -1207,15 +1217,15 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
     f1 = wc[wc_edge(WT) + kEdgeCoef];
   }
 
-  // one record into the sums
-  auto add = [&](const float2v r, auto taps) {
+  // one record into the sums of this thread's delay b
+  auto add = [&](const int b, const float2v r, auto taps) {
     const float t = r.x, A = r.y;
     if constexpr (LUT) {
       const float x = t * (float)kLutQ, fl = fminf(floorf(x), (float)(kLutQ - 1));
       const float hi = A * (x - fl);
-      float *const g = &u.pool.pulse[(int)fl][tid];
+      float *const g = &u.pool.pulse[(int)fl][tid + NT * b];
       g[0] += A - hi;
-      g[TILE] += hi;
+      g[TL] += hi;
       return;
     }
     if constexpr (decltype(taps)::value) {
@@ -1228,21 +1238,21 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
         const float w = __builtin_fabsf(v) < ra.win_hw
                             ? __builtin_fmaf(C2, __builtin_amdgcn_cosf(v * ra.inv_win), C2) * __builtin_amdgcn_rcpf(v)
                             : 0.0f;
-        m[j + 1] += (j & 1) ? w : -w;
+        m[b][j + 1] += (j & 1) ? w : -w;
       }
       return;
     }
     const float At = A * t, t2 = t * t, t4 = t2 * t2, t6 = t4 * t2, t8 = t4 * t4;
-    m[0] += A;
-    m[1] += At;
-    m[2] = __builtin_fmaf(A, t2, m[2]);
-    m[3] = __builtin_fmaf(At, t2, m[3]);
-    m[4] = __builtin_fmaf(A, t4, m[4]);
-    m[5] = __builtin_fmaf(At, t4, m[5]);
-    m[6] = __builtin_fmaf(A, t6, m[6]);
-    m[7] = __builtin_fmaf(At, t6, m[7]);
-    m[8] = __builtin_fmaf(A, t8, m[8]);
-    m[9] = __builtin_fmaf(At, t8, m[9]);
+    m[b][0] += A;
+    m[b][1] += At;
+    m[b][2] = __builtin_fmaf(A, t2, m[b][2]);
+    m[b][3] = __builtin_fmaf(At, t2, m[b][3]);
+    m[b][4] = __builtin_fmaf(A, t4, m[b][4]);
+    m[b][5] = __builtin_fmaf(At, t4, m[b][5]);
+    m[b][6] = __builtin_fmaf(A, t6, m[b][6]);
+    m[b][7] = __builtin_fmaf(At, t6, m[b][7]);
+    m[b][8] = __builtin_fmaf(A, t8, m[b][8]);
+    m[b][9] = __builtin_fmaf(At, t8, m[b][9]);
     if constexpr (EDGE) {
       // left end: inside for f < 1 - f1; right end: inside for f > f1
       const float ul = fmaxf((0.5f - f1) - t, 0.0f), ur = fmaxf(t + (0.5f - f1), 0.0f);
@@ -1253,8 +1263,8 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
         pl = __builtin_fmaf(pl, xl, ec[i]);
         pr = __builtin_fmaf(pr, xr, ec[i]);
       }
-      m[MOM] = __builtin_fmaf(A * ul, ul * pl, m[MOM]);
-      m[MOM + 1] = __builtin_fmaf(A * ur, ur * pr, m[MOM + 1]);
+      m[b][MOM] = __builtin_fmaf(A * ul, ul * pl, m[b][MOM]);
+      m[b][MOM + 1] = __builtin_fmaf(A * ur, ur * pr, m[b][MOM + 1]);
     }
   };
   char *const rec0 = reinterpret_cast<char *>(u.pool.rec), *const next0 = reinterpret_cast<char *>(u.pool.next);
@@ -1262,14 +1272,27 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   auto next_at = [&](uint32_t o) -> uint16_t & { return *reinterpret_cast<uint16_t *>(next0 + (o >> 2)); };
   // the list's end links to itself and its record adds zero: a lane whose list
   // is shorter than the longest goes on adding it
-  auto walk = [&](uint32_t i0, auto taps) {
-    while (__any(i0 != END)) {
-      const uint32_t i1 = next_at(i0);
-      const float2v r0 = rec_at(i0);
-      const float2v r1 = rec_at(i1);
-      i0 = next_at(i1);
-      add(r0, taps);
-      add(r1, taps);
+  auto walk = [&](uint32_t (&i0)[NB], auto taps) {
+    if constexpr (NB == 1) {
+      while (__any(i0[0] != END)) {
+        const uint32_t i1 = next_at(i0[0]);
+        const float2v r0 = rec_at(i0[0]);
+        const float2v r1 = rec_at(i1);
+        i0[0] = next_at(i1);
+        add(0, r0, taps);
+        add(0, r1, taps);
+      }
+    } else {
+      // the lists of the thread's delays side by side, two at a time
+#pragma unroll
+      for (int b = 0; b < NB; b += 2)
+        while (__any(i0[b] != END || i0[b + 1] != END)) {
+          const float2v r0 = rec_at(i0[b]), r1 = rec_at(i0[b + 1]);
+          i0[b] = next_at(i0[b]);
+          i0[b + 1] = next_at(i0[b + 1]);
+          add(b, r0, taps);
+          add(b + 1, r1, taps);
+        }
     }
   };
 
@@ -1298,14 +1321,19 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
     if (lane == 0) more_all[wv] = more ? 1 : 0;
     __syncthreads();
     const int4v more4 = *reinterpret_cast<const int4v *>(more_all);
-    uint32_t i0 = END;
+    uint32_t i0[NB];
 #pragma unroll
-    for (int v = MOM_WAVES - 1; v >= 0; --v) {
-      const uint32_t hv = u.pool.head[v][tid];
-      u.pool.head[v][tid] = END;
-      if (hv != END) {
-        next_at(u.pool.tail[v][tid]) = (uint16_t)i0;
-        i0 = hv;
+    for (int b = 0; b < NB; ++b) {
+      const int k = tid + NT * b;
+      i0[b] = END;
+#pragma unroll
+      for (int v = MOM_WAVES - 1; v >= 0; --v) {
+        const uint32_t hv = u.pool.head[v][k];
+        u.pool.head[v][k] = END;
+        if (hv != END) {
+          next_at(u.pool.tail[v][k]) = (uint16_t)i0[b];
+          i0[b] = hv;
+        }
       }
     }
     if constexpr (DIRECT) {
@@ -1320,92 +1348,110 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
 
   if constexpr (LUT) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) m[p] = u.pool.pulse[p][tid];
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int p = 0; p < P; ++p) m[b][p] = u.pool.pulse[p][tid + NT * b];
     __syncthreads();
   }
-  // convolution
-  float *const planes = u.conv, *const coefs = u.conv + P * Sh::PL;
-  {
-    const int x = tid + WT - 1;
+  // convolution, planes of PB moments at a time (highest first)
+  float *const planes = u.conv, *const coefs = u.conv + Sh::PB * Sh::PL;
+  const int lc = lane & 15, lk = lane >> 4;  // matrix row (coefficients) / column (planes), k group
+  int a[Sh::NCT];                            // this lane's output block of each column tile
 #pragma unroll
-    for (int p = 0; p < P; ++p) planes[p * Sh::PL + x + (x >> 4)] = m[p];
-    // zeros before and after the tile's delays
-    constexpr int NZ = Sh::XN - TILE;
-    for (int e = tid; e < NZ; e += NT) {
-      const int xz = e < WT - 1 ? e : e + TILE;
+  for (int t = 0; t < Sh::NCT; ++t) a[t] = min(lc + 16 * t, Sh::NBLK - 1);
+  // sums of planes 0, 1 and of the others apart (then smallest first; table taps: of
+  // every third phase): each rounds at its own, smaller size
+  f4v d[3][Sh::NCT];
 #pragma unroll
-      for (int p = 0; p < P; ++p) planes[p * Sh::PL + xz + (xz >> 4)] = 0.0f;
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int t = 0; t < Sh::NCT; ++t) d[i][t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int KQ = Sh::KS / MOM_WAVES;  // steps of this wave: s0 .. s0 + KQ - 1
+  const int s0 = wv * KQ;
+#pragma unroll
+  for (int pb = (P - 1) / Sh::PB * Sh::PB; pb >= 0; pb -= Sh::PB) {
+    constexpr int PB = Sh::PB;
+    if (pb + PB < P) __syncthreads();  // the planes above are used up
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int x = tid + NT * b + WT - 1;
+#pragma unroll
+      for (int q = 0; q < PB; ++q)
+        if (pb + q < P) planes[q * Sh::PL + x + (x >> 4)] = m[b][pb + q < P ? pb + q : 0];
     }
-  }
-  if constexpr (GEN) {
-    // coefficients in the order of MomCoef
-    const int j2 = EDGE ? (int)wc[wc_edge(WT) + kEdgeCoef + 1] : 0;
-    for (int e = tid; e < Sh::CL; e += NT) {
-      const int j = WT / 2 + 15 - e;
-      const bool in = j > -WT / 2 && j <= WT / 2;
-      const int jj = in ? (j >= 1 ? j - 1 : -j) : 0;
+    // zeros before and after the tile's delays
+    constexpr int NZ = Sh::XN - TL;
+    for (int e = tid; e < NZ; e += NT) {
+      const int xz = e < WT - 1 ? e : e + TL;
 #pragma unroll
-      for (int p = 0; p < P; ++p) {
-        float v = 0.0f;
-        if (DIRECT && direct) {
-          v = (p < 4 && j == p - 1) ? 1.0f : 0.0f;
-        } else if (p >= MOM) {
-          v = (j2 > 0 && j == (p == MOM ? 1 - j2 : j2)) ? 1.0f : 0.0f;
-        } else {
-          v = wc[p * (WT / 2) + jj];
-          if (!in) v = 0.0f;
-          if (j < 1 && (p & 1)) v = -v;
+      for (int q = 0; q < PB; ++q) planes[q * Sh::PL + xz + (xz >> 4)] = 0.0f;
+    }
+    if constexpr (GEN) {
+      // coefficients in the order of MomCoef
+      const int j2 = EDGE ? (int)wc[wc_edge(WT) + kEdgeCoef + 1] : 0;
+      for (int e = tid; e < Sh::CL; e += NT) {
+        const int j = WT / 2 + 15 - e;
+        const bool in = j > -WT / 2 && j <= WT / 2;
+        const int jj = in ? (j >= 1 ? j - 1 : -j) : 0;
+#pragma unroll
+        for (int q = 0; q < PB; ++q) {
+          const int p = pb + q;
+          float v = 0.0f;
+          if (DIRECT && direct) {
+            v = (p < 4 && j == p - 1) ? 1.0f : 0.0f;
+          } else if (p >= MOM) {
+            v = (j2 > 0 && j == (p == MOM ? 1 - j2 : j2)) ? 1.0f : 0.0f;
+          } else {
+            v = wc[p * (WT / 2) + jj];
+            if (!in) v = 0.0f;
+            if (j < 1 && (p & 1)) v = -v;
+          }
+          coefs[q * Sh::CL + e] = v;
         }
-        coefs[p * Sh::CL + e] = v;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = PB - 1; q >= 0; --q) {
+      const int p = pb + q;
+      if (p >= P) continue;
+      const int i = LUT ? p % 3 : p < 2 ? p : 2;
+      const float *const pl = planes + q * Sh::PL + lk;
+#pragma unroll
+      for (int k = 0; k < KQ; ++k) {
+        const int s = s0 + k;
+        float cv;
+        if constexpr (GEN) cv = coefs[q * Sh::CL + 4 * s + (lk - lc + 15)];
+        else if constexpr (LUT) cv = lut_table<WT>().c[p][(uint32_t)(4 * s + (lk - lc + 15))];
+        else cv = mom_table<WT>().c[p][(uint32_t)(4 * s + (lk - lc + 15))];
+#pragma unroll
+        for (int t = 0; t < Sh::NCT; ++t)
+          d[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, pl[17 * a[t] + 4 * s + (s >> 2)], d[i][t], 0, 0, 0);
       }
     }
   }
   __syncthreads();
-  const int lc = lane & 15, lk = lane >> 4;  // matrix row (coefficients) / column (planes), k group
-  const int a0 = min(lc, Sh::NBLK - 1), a1 = min(lc + 16, Sh::NBLK - 1);
-  // sums of planes 0, 1, 2 and of the others apart (then smallest first; table
-  // taps: of every fourth phase): each rounds at its own, smaller size
-  f4v d0[4], d1[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) d0[i] = d1[i] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-  constexpr int KQ = Sh::KS / MOM_WAVES;  // steps of this wave: s0 .. s0 + KQ - 1
-  const int s0 = wv * KQ;
-#pragma unroll
-  for (int p = P - 1; p >= 0; --p) {
-    const int i = LUT ? p & 3 : p < 3 ? p : 3;
-    const float *b0 = planes + p * Sh::PL + 17 * a0 + lk, *b1 = planes + p * Sh::PL + 17 * a1 + lk;
-#pragma unroll
-    for (int k = 0; k < KQ; ++k) {
-      const int s = s0 + k;
-      float cv;
-      if constexpr (GEN) cv = coefs[p * Sh::CL + 4 * s + (lk - lc + 15)];
-      else if constexpr (LUT) cv = lut_table<WT>().c[p][(uint32_t)(4 * s + (lk - lc + 15))];
-      else cv = mom_table<WT>().c[p][(uint32_t)(4 * s + (lk - lc + 15))];
-      d0[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b0[4 * s + (s >> 2)], d0[i], 0, 0, 0);
-      d1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv, b1[4 * s + (s >> 2)], d1[i], 0, 0, 0);
-    }
-  }
-  __syncthreads();
-  *reinterpret_cast<f4v *>(&u.part[wv][16 * lc + 4 * lk]) = (d0[3] + d0[2]) + (d0[1] + d0[0]);
-  *reinterpret_cast<f4v *>(&u.part[wv][256 + 16 * lc + 4 * lk]) = (d1[3] + d1[2]) + (d1[1] + d1[0]);
+  for (int t = 0; t < Sh::NCT; ++t)
+    *reinterpret_cast<f4v *>(&u.part[wv][256 * t + 16 * lc + 4 * lk]) = d[2][t] + (d[1][t] + d[0][t]);
   __syncthreads();
   // output o: sample o - LM of the tile; before and after it the margins
-  for (int o = tid; o < TILE + WT - 1; o += NT) {
+  for (int o = tid; o < TL + WT - 1; o += NT) {
     const float v = (u.part[0][o] + u.part[3][o]) + (u.part[1][o] + u.part[2][o]);
     if (o < LM) marg[o] = v;
-    else if (o >= LM + TILE) marg[o - TILE] = v;
+    else if (o >= LM + TL) marg[o - TL] = v;
     else if (o - LM < n_own) dst[o - LM] = v;
   }
 }
 
 // The item function of a kernel's precision.
-template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
 __device__ __forceinline__ void run_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
                                          float *__restrict__ dst, float *__restrict__ marg,
                                          const float *__restrict__ wc) {
   if constexpr (HALF) tap_item<WT, 2, POLAR, false, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, nullptr, 0, wc);
-  else moment_item<WT, LUT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
+  else moment_item<WT, TL, LUT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
 }
 
 // First work item of dispatch position pos (see PlanArgs).
@@ -1451,7 +1497,7 @@ __device__ __forceinline__ SingleItem decode_item(const PlanArgs &pa, uint32_t i
   return si;
 }
 
-template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
 __global__ __launch_bounds__(item_threads(HALF))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
 accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_all,
@@ -1460,10 +1506,10 @@ accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_al
   const uint32_t item = blockIdx.x;
   const SingleItem si = decode_item(pa, item);
   // (for a tile past nS, dst is never written: the tile has no own samples)
-  float *dst = (si.C == 1) ? out + (size_t)si.rir * ra.n_samples + (size_t)si.tile_id * TILE
-                           : part + (size_t)item * TILE;
+  float *dst = (si.C == 1) ? out + (size_t)si.rir * ra.n_samples + (size_t)si.tile_id * TL
+                           : part + (size_t)item * TL;
   const AxisOrigin org = origin[si.rir];
-  run_item<WT, HALF, LUT, POLAR, GEN>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
+  run_item<WT, TL, HALF, LUT, POLAR, GEN>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
                                       valid[si.rir] != 0, dst, marg + (size_t)item * WT, wc);
 }
 
@@ -1490,7 +1536,7 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int n) {
 // run sets to the grid size before the launch), until the list is exhausted.
 // Without a queue (queue == null) a workgroup takes every gridDim.x-th item.
 // Every item names its job; the job table carries the room.
-template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
 __global__ __launch_bounds__(item_threads(HALF))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
 accumulate_batch_kernel(
@@ -1509,10 +1555,10 @@ accumulate_batch_kernel(
     const JobDev &jb = jobs[it.job];
     const RoomArgs ra = jb.ra;
     const uint32_t grir = jb.rir_base + it.rir;
-    float *dst = (it.slot == 0xffffffffu) ? jb.out + (size_t)it.rir * ra.n_samples + (size_t)it.tile * TILE
+    float *dst = (it.slot == 0xffffffffu) ? jb.out + (size_t)it.rir * ra.n_samples + (size_t)it.tile * TL
                                           : part + (size_t)it.slot * TILE;
     const AxisOrigin org = origin[grir];
-    run_item<WT, HALF, LUT, POLAR, GEN>(ra, it.tile, it.chunks, it.chunk,
+    run_item<WT, TL, HALF, LUT, POLAR, GEN>(ra, it.tile, it.chunks, it.chunk,
                                         tab_all + jb.tab_base + (size_t)it.rir * ra.n_tab, org, valid[grir] != 0, dst,
                                         marg + (size_t)it.mslot * MARG_UNIT, jb.wc);
     if (queue) {
@@ -1581,7 +1627,7 @@ __device__ __forceinline__ float ordered_sum(float v, const float *__restrict__ 
 // their runs are short). n is uniform over the block (its barriers are);
 // active: this thread's sample takes the run.
 constexpr int RED_SAMPLES = 256 / RED_SLICES;
-static_assert(TILE % RED_SAMPLES == 0, "reduce blocks tile the tile");
+static_assert(TILE % 256 == 0 && LONG_TILE % 256 == 0 && 256 % RED_SAMPLES == 0, "reduce blocks tile the tile");
 __device__ __forceinline__ float run_sum(float v, const float *__restrict__ x, size_t stride, int n, bool active,
                                          int slice, int ks, float (*red)[RED_SAMPLES]) {
   if (n < RED_SLICE_MIN) {
@@ -1609,18 +1655,18 @@ __global__ __launch_bounds__(256) void reduce_kernel(RoomArgs ra, PlanArgs pa, c
   const int tile_id = pa.n_tiles - 1 - pos;
   const int C = pa.chunks[tile_id];
   const int rir = blockIdx.x;
-  const int T0 = tile_id * TILE;
+  const int TL = ra.tile, T0 = tile_id * TL;
   const int ks = (int)threadIdx.x % SPB, slice = (int)threadIdx.x / SPB;
   const int k0 = blockIdx.z * SPB, k = k0 + ks;
   const int W = (int)(2.0f * ra.half_w);
   const int LM = W / 2 - 1;
   // block-uniform: which runs exist for some sample of this block
   const bool has_l = tile_id > 0 && k0 < W / 2;                    // right margin of tile t-1
-  const bool has_r = tile_id + 1 < pa.n_tiles && k0 + SPB > TILE - LM;  // left margin of tile t+1
+  const bool has_r = tile_id + 1 < pa.n_tiles && k0 + SPB > TL - LM;  // left margin of tile t+1
   if (C <= 1 && !has_l && !has_r) return;
-  const bool in = k < ra.n_samples - T0 && k < TILE;
+  const bool in = k < ra.n_samples - T0 && k < TL;
   const bool zl = in && has_l && k < W / 2;
-  const bool zr = in && has_r && k >= TILE - LM;
+  const bool zr = in && has_r && k >= TL - LM;
   auto add = [&](float v, const float *x, size_t stride, int n, bool active) {
     if constexpr (SLICED) return run_sum(v, x, stride, n, active, slice, ks, red);
     else return active ? ordered_sum(v, x, stride, n) : v;  // n < RED_SLICE_MIN
@@ -1629,7 +1675,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(RoomArgs ra, PlanArgs pa, c
   float v = 0.0f;
   if (C > 1) {
     const size_t first = (size_t)plan_first_item(pa, pos) + (size_t)rir * C;
-    v = add(0.0f, part + first * TILE + k, TILE, C, in);
+    v = add(0.0f, part + first * TL + k, TL, C, in);
   } else if (in && slice == 0 && (zl || zr)) {
     v = *o;
   }
@@ -1641,7 +1687,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(RoomArgs ra, PlanArgs pa, c
   if (has_r) {  // tile t+1 is dispatched at pos - 1
     const int Cn = pa.chunks[tile_id + 1];
     const size_t first = (size_t)plan_first_item(pa, pos - 1) + (size_t)rir * Cn;
-    v = add(v, marg + first * W + (k - (TILE - LM)), W, Cn, zr);
+    v = add(v, marg + first * W + (k - (TL - LM)), W, Cn, zr);
   }
   if (in && slice == 0 && (C > 1 || zl || zr)) *o = v;
 }
@@ -1657,17 +1703,18 @@ __global__ __launch_bounds__(256) void reduce_batch_kernel(const JobDev *__restr
   const BatchReduce br = red_tab[blockIdx.x];
   const JobDev &jb = jobs[br.job];
   const int n_samples = jb.ra.n_samples;
-  const int T0 = (int)br.tile * TILE;
+  const int TL = jb.ra.tile, T0 = (int)br.tile * TL;
   const int ks = (int)threadIdx.x % SPB, slice = (int)threadIdx.x / SPB;
   const int k0 = blockIdx.y * SPB, k = k0 + ks;
+  if (k0 >= TL) return;  // the grid covers the batch's longest tiles
   const int W = (int)(2.0f * jb.ra.half_w);
   const int LM = W / 2 - 1;
   const bool has_l = br.nprev > 0 && k0 < W / 2;
-  const bool has_r = br.nnext > 0 && k0 + SPB > TILE - LM;
+  const bool has_r = br.nnext > 0 && k0 + SPB > TL - LM;
   if (br.chunks <= 1 && !has_l && !has_r) return;
-  const bool in = k < n_samples - T0 && k < TILE;
+  const bool in = k < n_samples - T0 && k < TL;
   const bool zl = in && has_l && k < W / 2;
-  const bool zr = in && has_r && k >= TILE - LM;
+  const bool zr = in && has_r && k >= TL - LM;
   auto add = [&](float v, const float *x, size_t stride, int n, bool active) {
     if constexpr (SLICED) return run_sum(v, x, stride, n, active, slice, ks, red);
     else return active ? ordered_sum(v, x, stride, n) : v;  // n < RED_SLICE_MIN
@@ -1675,12 +1722,12 @@ __global__ __launch_bounds__(256) void reduce_batch_kernel(const JobDev *__restr
   float *o = jb.out + (size_t)br.rir * n_samples + T0 + k;
   float v = 0.0f;
   if (br.chunks > 1) {
-    v = add(0.0f, part + (size_t)br.first * TILE + k, TILE, br.chunks, in);
+    v = add(0.0f, part + (size_t)br.first * TILE + k, TL, br.chunks, in);
   } else if (in && slice == 0 && (zl || zr)) {
     v = *o;
   }
   if (has_l) v = add(v, marg + (size_t)br.mprev * MARG_UNIT + LM + k, W, br.nprev, zl);
-  if (has_r) v = add(v, marg + (size_t)br.mnext * MARG_UNIT + (k - (TILE - LM)), W, br.nnext, zr);
+  if (has_r) v = add(v, marg + (size_t)br.mnext * MARG_UNIT + (k - (TL - LM)), W, br.nnext, zr);
   if (in && slice == 0 && (br.chunks > 1 || zl || zr)) *o = v;
 }
 
@@ -1703,19 +1750,19 @@ __global__ __launch_bounds__(64) void reduce_margins_kernel(const JobDev *__rest
   const BatchReduce br = red_tab[blockIdx.x];
   const JobDev &jb = jobs[br.job];
   const int n_samples = jb.ra.n_samples;
-  const int T0 = (int)br.tile * TILE;
+  const int TL = jb.ra.tile, T0 = (int)br.tile * TL;
   const int W = (int)(2.0f * jb.ra.half_w);
   const int LM = W / 2 - 1;
   for (int i = (int)threadIdx.x; i < W - 1; i += 64) {
-    const int k = i < W / 2 ? i : TILE - LM + (i - W / 2);
+    const int k = i < W / 2 ? i : TL - LM + (i - W / 2);
     if (k >= n_samples - T0) continue;
     const bool zl = br.nprev > 0 && k < W / 2;
-    const bool zr = br.nnext > 0 && k >= TILE - LM;
+    const bool zr = br.nnext > 0 && k >= TL - LM;
     if (!zl && !zr) continue;
     float *o = jb.out + (size_t)br.rir * n_samples + T0 + k;
     float v = *o;
     if (zl) v = run_sum_serial(v, marg + (size_t)br.mprev * MARG_UNIT + LM + k, W, br.nprev);
-    if (zr) v = run_sum_serial(v, marg + (size_t)br.mnext * MARG_UNIT + (k - (TILE - LM)), W, br.nnext);
+    if (zr) v = run_sum_serial(v, marg + (size_t)br.mnext * MARG_UNIT + (k - (TL - LM)), W, br.nnext);
     *o = v;
   }
 }
@@ -1733,11 +1780,11 @@ int launch_tables(const RoomArgs &ra, const float *src, const float *rcv, const 
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
 static int launch_acc_w(const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                         const AxisOrigin *origin, const int *valid, float *out, float *part, float *marg,
                         const float *wc, hipStream_t st) {
-  hipLaunchKernelGGL((accumulate_kernel<WT, HALF, LUT, POLAR, GEN>), dim3(n_items),
+  hipLaunchKernelGGL((accumulate_kernel<WT, TL, HALF, LUT, POLAR, GEN>), dim3(n_items),
                      dim3(item_threads(HALF)), 0, st, ra, pa, tab, origin, valid, out, part, marg, wc);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -1776,22 +1823,24 @@ bool supported_window(int wt, bool gen) {
 
 // Calls the kernel instance of a window class: exact windows W in {32, 64,
 // 96, 128} with every tap mode, general-mode caps 32 .. 256 with FP32 or FP16
-// taps. fn is a generic lambda taking the template arguments as values.
+// taps; FP32 taps with tiles of TILE or LONG_TILE samples. fn is a generic lambda
+// taking the template arguments as values.
 template <class Fn>
-static int dispatch_window(int wt, bool gen, bool half, bool lut, bool polar, Fn &&fn) {
-  if (half && lut) return -2;
+static int dispatch_window(int wt, int tile, bool gen, bool half, bool lut, bool polar, Fn &&fn) {
+  if ((half && lut) || (tile != TILE && (half || lut || tile != LONG_TILE))) return -2;
+  using S = std::integral_constant<int, TILE>;
+  using LT = std::integral_constant<int, LONG_TILE>;
   auto by_mode = [&](auto W, auto G) -> int {
     constexpr bool kG = decltype(G)::value;
-    if (half) return polar ? fn(W, std::true_type{}, std::false_type{}, std::true_type{}, G)
-                           : fn(W, std::true_type{}, std::false_type{}, std::false_type{}, G);
-    if constexpr (!kG) {
-      if (lut) return polar ? fn(W, std::false_type{}, std::true_type{}, std::true_type{}, G)
-                            : fn(W, std::false_type{}, std::true_type{}, std::false_type{}, G);
-    } else {
-      if (lut) return -2;
+    using F = std::false_type;
+    using T = std::true_type;
+    if (half) return polar ? fn(W, S{}, T{}, F{}, T{}, G) : fn(W, S{}, T{}, F{}, F{}, G);
+    if (lut) {
+      if constexpr (!kG) return polar ? fn(W, S{}, F{}, T{}, T{}, G) : fn(W, S{}, F{}, T{}, F{}, G);
+      return -2;
     }
-    return polar ? fn(W, std::false_type{}, std::false_type{}, std::true_type{}, G)
-                 : fn(W, std::false_type{}, std::false_type{}, std::false_type{}, G);
+    if (tile == LONG_TILE) return polar ? fn(W, LT{}, F{}, F{}, T{}, G) : fn(W, LT{}, F{}, F{}, F{}, G);
+    return polar ? fn(W, S{}, F{}, F{}, T{}, G) : fn(W, S{}, F{}, F{}, F{}, G);
   };
   using F = std::false_type;
   using T = std::true_type;
@@ -1821,57 +1870,56 @@ static int dispatch_window(int wt, bool gen, bool half, bool lut, bool polar, Fn
 int launch_accumulate(int wt, bool gen, bool half, bool lut, bool polar, const RoomArgs &ra, const PlanArgs &pa,
                       uint32_t n_items, const AxisEntry *tab, const AxisOrigin *origin, const int *valid, float *out,
                       float *part, float *marg, const float *wc, hipStream_t st) {
-  return dispatch_window(wt, gen, half, lut, polar, [&](auto W, auto H, auto L, auto P, auto G) -> int {
-    return launch_acc_w<decltype(W)::value, decltype(H)::value, decltype(L)::value, decltype(P)::value,
-                        decltype(G)::value>(ra, pa, n_items, tab, origin, valid, out, part, marg, wc, st);
+  return dispatch_window(wt, ra.tile, gen, half, lut, polar, [&](auto W, auto Tl, auto H, auto L, auto P, auto G) -> int {
+    return launch_acc_w<decltype(W)::value, decltype(Tl)::value, decltype(H)::value, decltype(L)::value,
+                        decltype(P)::value, decltype(G)::value>(ra, pa, n_items, tab, origin, valid, out, part, marg, wc, st);
   });
 }
 
 // grid: workgroups of the persistent launch (at most n_items; the planner
 // sizes it from the tuned workgroups per SIMD).
-template <int WT, bool HALF, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
 static int launch_acc_batch_w(const JobDev *jobs, const BatchItem *items, uint32_t n_items, uint32_t grid,
                               uint32_t *queue, const AxisEntry *tab, const AxisOrigin *origin, const int *valid,
                               float *part, float *marg, hipStream_t st) {
-  hipLaunchKernelGGL((accumulate_batch_kernel<WT, HALF, LUT, POLAR, GEN>),
+  hipLaunchKernelGGL((accumulate_batch_kernel<WT, TL, HALF, LUT, POLAR, GEN>),
                      dim3(grid), dim3(item_threads(HALF)), 0, st, jobs, items, n_items, queue, tab, origin, valid, part, marg);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // queue[k] = the first item of class k not taken by a workgroup's first pick.
-__global__ void queue_init_kernel(uint32_t *queue, uint4 a, uint4 b) {
-  const uint32_t v[kMaxBatchClasses] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-  if (threadIdx.x < kMaxBatchClasses) queue[threadIdx.x] = v[threadIdx.x];
+struct QueueInit {
+  uint32_t v[kMaxBatchLaunches];
+};
+__global__ void queue_init_kernel(uint32_t *queue, QueueInit q) {
+  if (threadIdx.x < kMaxBatchLaunches) queue[threadIdx.x] = q.v[threadIdx.x];
 }
 
 int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *rirs, uint32_t n_rir,
-                 const BatchItem *items, const uint32_t *class_first, const uint32_t *class_count,
-                 const uint32_t *class_grid, const int *class_wt, const int *class_gen, int n_classes, bool half, bool lut, bool polar,
-                 const BatchReduce *red, uint32_t n_red, uint32_t n_red_split, bool long_runs, AxisEntry *tab,
+                 const BatchItem *items, const BatchClass *cls, int n_classes, bool half, bool lut, bool polar,
+                 const BatchReduce *red, uint32_t n_red, uint32_t n_red_split, bool long_runs, int max_tile, AxisEntry *tab,
                  AxisOrigin *origin, int *valid, float *part, float *marg, uint32_t *queue, hipStream_t st,
                  hipEvent_t ev_start, hipEvent_t ev_stop) {
   hipLaunchKernelGGL(tables_batch_kernel, dim3(n_rir + (any_gen ? (unsigned)n_jobs : 0u)), dim3(256), 0, st, jobs, rirs,
                      tab, origin, valid, n_rir, half ? 1 : 0);
   if (hipGetLastError() != hipSuccess) return -1;
   if (queue) {
-    uint32_t fp[kMaxBatchClasses] = {};
-    for (int k = 0; k < n_classes && k < kMaxBatchClasses; ++k) fp[k] = class_grid[k];
-    hipLaunchKernelGGL(queue_init_kernel, dim3(1), dim3(64), 0, st, queue, make_uint4(fp[0], fp[1], fp[2], fp[3]),
-                       make_uint4(fp[4], fp[5], fp[6], fp[7]));
+    QueueInit q = {};
+    for (int k = 0; k < n_classes && k < kMaxBatchLaunches; ++k) q.v[k] = cls[k].grid;
+    hipLaunchKernelGGL(queue_init_kernel, dim3(1), dim3(64), 0, st, queue, q);
     if (hipGetLastError() != hipSuccess) return -1;
   }
   if (ev_start && hipEventRecord(ev_start, st) != hipSuccess) return -1;
   for (int k = 0; k < n_classes; ++k) {
-    if (class_count[k] == 0) continue;
-    const BatchItem *it = items + class_first[k];
+    if (cls[k].count == 0) continue;
+    const BatchItem *it = items + cls[k].first;
     uint32_t *qk = queue ? queue + k : nullptr;
-    const int rc = dispatch_window(class_wt[k], class_gen[k] != 0, half, lut, polar,
-                                   [&](auto W, auto H, auto L, auto P, auto G) -> int {
-                                     return launch_acc_batch_w<decltype(W)::value, decltype(H)::value,
-                                                               decltype(L)::value, decltype(P)::value,
-                                                               decltype(G)::value>(jobs, it, class_count[k],
-                                                                                   class_grid[k], qk, tab, origin,
-                                                                                   valid, part, marg, st);
+    const int rc = dispatch_window(cls[k].wt, cls[k].tile, cls[k].gen != 0, half, lut, polar,
+                                   [&](auto W, auto Tl, auto H, auto L, auto P, auto G) -> int {
+                                     return launch_acc_batch_w<decltype(W)::value, decltype(Tl)::value,
+                                                               decltype(H)::value, decltype(L)::value,
+                                                               decltype(P)::value, decltype(G)::value>(
+                                         jobs, it, cls[k].count, cls[k].grid, qk, tab, origin, valid, part, marg, st);
                                    });
     if (rc != 0) return -1;
   }
@@ -1879,10 +1927,10 @@ int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *r
   if (n_red_split > 0) {
     // split tiles, whole tiles; runs of RED_SLICE_MIN terms or more: RED_SLICES threads per sample
     if (long_runs)
-      hipLaunchKernelGGL(reduce_batch_kernel<true>, dim3(n_red_split, TILE / RED_SAMPLES), dim3(256), 0, st, jobs, red,
+      hipLaunchKernelGGL(reduce_batch_kernel<true>, dim3(n_red_split, max_tile / RED_SAMPLES), dim3(256), 0, st, jobs, red,
                          part, marg);
     else
-      hipLaunchKernelGGL(reduce_batch_kernel<false>, dim3(n_red_split, TILE / 256), dim3(256), 0, st, jobs, red, part,
+      hipLaunchKernelGGL(reduce_batch_kernel<false>, dim3(n_red_split, max_tile / 256), dim3(256), 0, st, jobs, red, part,
                          marg);
     if (hipGetLastError() != hipSuccess) return -1;
   }
@@ -1899,10 +1947,10 @@ int launch_reduce(const RoomArgs &ra, const PlanArgs &pa, int n_rir, const float
   int max_c = 0;  // longest run: the most items of any tile (its own, or a neighbour's margins)
   for (int t = 0; t < pa.n_tiles; ++t) max_c = max(max_c, (int)pa.chunks[t]);
   if (max_c >= RED_SLICE_MIN)
-    hipLaunchKernelGGL(reduce_kernel<true>, dim3((unsigned)n_rir, (unsigned)pa.n_tiles, TILE / RED_SAMPLES), dim3(256),
+    hipLaunchKernelGGL(reduce_kernel<true>, dim3((unsigned)n_rir, (unsigned)pa.n_tiles, ra.tile / RED_SAMPLES), dim3(256),
                        0, st, ra, pa, part, marg, out);
   else
-    hipLaunchKernelGGL(reduce_kernel<false>, dim3((unsigned)n_rir, (unsigned)pa.n_tiles, TILE / 256), dim3(256), 0, st,
+    hipLaunchKernelGGL(reduce_kernel<false>, dim3((unsigned)n_rir, (unsigned)pa.n_tiles, ra.tile / 256), dim3(256), 0, st,
                        ra, pa, part, marg, out);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -29,9 +29,9 @@ bool supported_window(int wt, bool gen);
 int launch_dump(int wt, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                 const AxisOrigin *origin, const int *valid, DumpArgs dump, hipStream_t st);
 int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *rirs, uint32_t n_rir,
-                 const BatchItem *items, const uint32_t *class_first, const uint32_t *class_count,
-                 const uint32_t *class_grid, const int *class_wt, const int *class_gen, int n_classes, bool half, bool lut, bool polar,
-                 const BatchReduce *red, uint32_t n_red, uint32_t n_red_split, bool long_runs, AxisEntry *tab,
+                 const BatchItem *items, const BatchClass *cls, int n_classes, bool half, bool lut, bool polar,
+                 const BatchReduce *red, uint32_t n_red, uint32_t n_red_split, bool long_runs, int max_tile,
+                 AxisEntry *tab,
                  AxisOrigin *origin, int *valid, float *part, float *marg, uint32_t *queue, hipStream_t st,
                  hipEvent_t ev_start, hipEvent_t ev_stop);
 int launch_diffuse(const float *ism, int k_diff, float *out, int n_samples, int n_rir, double fs, double t_diff,
@@ -200,12 +200,12 @@ bool valid_schedule(const ism_schedule *sc) {
 // last tail_rounds rounds of the resident items, down to floor_taps): the items
 // per tile into chunks (may be null), their total over all RIRs and the part of
 // it in split tiles. False when the total exceeds a launch.
-bool cut_tiles(const Plan &p, double target, double floor_taps, double tail_rounds, double resident, uint8_t *chunks,
-               uint64_t &n_items, uint64_t &n_split) {
+bool cut_tiles(const Plan &p, const double *tile_taps, int n_tiles, double target, double floor_taps,
+               double tail_rounds, double resident, uint8_t *chunks, uint64_t &n_items, uint64_t &n_split) {
   n_items = n_split = 0;
   double rem = p.total_taps;
-  for (int t = p.pa.n_tiles - 1; t >= 0; --t) {  // dispatch order: last tile first
-    const double taps = p.tile_taps[t];
+  for (int t = n_tiles - 1; t >= 0; --t) {  // dispatch order: last tile first
+    const double taps = tile_taps[t];
     double tt = target;
     if (tail_rounds > 0.0) tt = std::max(floor_taps, std::min(target, rem / (tail_rounds * resident)));
     const int ch = std::max(1, std::min((int)std::ceil(taps / tt), MAX_CHUNKS));
@@ -216,6 +216,46 @@ bool cut_tiles(const Plan &p, double target, double floor_taps, double tail_roun
     if (n_items > 0x7fffffffULL) return false;
   }
   return true;
+}
+
+// Estimated taps of the tiles of T samples of one RIR: the owned shell volume over
+// the image density 1 / (Lx Ly Lz) (one image per mirrored room copy), times the
+// window cap. Returns their number; taps has MAX_TILES entries.
+int shell_taps(const ism_room &r, const Plan &p, int T, double *taps) {
+  const double q = r.fs / r.c;
+  const double cell = r.room[0] * r.room[1] * r.room[2] * q * q * q;
+  const double lattice = (double)r.n_img[0] * r.n_img[1] * r.n_img[2];
+  const int n = (p.ra.k_end + T - 1) / T;
+  for (int t = 0; t < n && t < MAX_TILES; ++t) {
+    const double x0 = (double)t * T, x1 = std::min((double)(t + 1) * T, (double)p.ra.k_end);
+    taps[t] = std::min(4.0 / 3.0 * kPi * (x1 * x1 * x1 - x0 * x0 * x0) / cell, lattice) * (double)p.wt;
+  }
+  return n;
+}
+
+// Whether an FP32 call takes tiles of LONG_TILE samples. A long tile halves the
+// columns walked per image, whose number grows with the shortest side (a column's
+// images lie half of its period apart), and a tile's fixed part; its lists are
+// shorter, which costs every image about 15 lane instructions. In lane
+// instructions per image, columns take 0.045 per sample of the shortest side and
+// the fixed part 9e4 over the images of a TILE-sample tile.
+// TILE against LONG_TILE, us per pass: 32 receivers in 4 x 5 x 3 m (11) 150 and 165,
+// 4 receivers in 3 x 4 x 2.5 m (7) 70 and 81; 64 microphones at 48 kHz in
+// 6 x 9 x 3.5 m (27) 2359 and 2219, 1024 diffuse RIRs of 2400 samples (50) 223 and
+// 193.
+// alone: a single call, whose few items are held up by their own length: fewer than
+// kLongTileItems long tiles are not taken (8 RIRs of 7900 samples at 44.1 kHz, 128
+// long tiles: 25.8 us with TILE, 27.8 with LONG_TILE; 30 RIRs at 32 kHz, 690: 49.8
+// and 47.5).
+constexpr double kLongTileGain = 19.0;
+constexpr int64_t kLongTileItems = 512;
+bool long_tiles(const ism_room &r, const Plan &p, bool alone) {
+  if (alone && (int64_t)p.n_rir * ((p.ra.k_end + LONG_TILE - 1) / LONG_TILE) < kLongTileItems) return false;
+  const double q = r.fs / r.c, k = (double)p.ra.k_end;
+  const double side = std::min(r.room[0], std::min(r.room[1], r.room[2])) * q;
+  const double images = std::min(4.0 / 3.0 * kPi * k * k * k / (r.room[0] * r.room[1] * r.room[2] * q * q * q),
+                                 (double)r.n_img[0] * r.n_img[1] * r.n_img[2]);
+  return 0.045 * side + 9.0e4 * k / (TILE * std::max(images, 1.0)) > kLongTileGain;
 }
 
 // sched: the call's schedule (null = the tuned default).
@@ -271,24 +311,17 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   ra.n_src = n_src;
   ra.n_rcv = n_rcv;
 
-  // Work split: tile t owns the images with k0 in [t TILE, min((t+1) TILE, k_end));
-  // its estimated taps are the owned shell volume over the image density
-  // 1 / (Lx Ly Lz) (one image per mirrored room copy), times W.
+  // Work split: tile t owns the images with k0 in [t T, min((t+1) T, k_end)).
   p.n_rir = n_src * n_rcv;
   PlanArgs &pa = p.pa;
   std::memset(&pa, 0, sizeof(pa));
-  pa.n_tiles = (ra.k_end + TILE - 1) / TILE;
-  if (pa.n_tiles > MAX_TILES) return ISM_E_TOO_LARGE;
+  const bool tapered = taper && !(sched && (sched->item_taps > 0.0 || sched->tail_rounds == 0.0));
+  ra.tile = !p.half && !p.lut && long_tiles(*r, p, tapered) ? LONG_TILE : TILE;
   pa.n_rir = p.n_rir;
-  const double cell = r->room[0] * r->room[1] * r->room[2] * q * q * q;
-  const double lattice = (double)r->n_img[0] * r->n_img[1] * r->n_img[2];
+  pa.n_tiles = shell_taps(*r, p, ra.tile, p.tile_taps);
+  if ((ra.k_end + TILE - 1) / TILE > MAX_TILES) return ISM_E_TOO_LARGE;
   p.total_taps = 0.0;
-  for (int t = 0; t < pa.n_tiles; ++t) {
-    const double x0 = (double)t * TILE, x1 = std::min((double)(t + 1) * TILE, (double)ra.k_end);
-    const double imgs = std::min(4.0 / 3.0 * kPi * (x1 * x1 * x1 - x0 * x0 * x0) / cell, lattice);
-    p.tile_taps[t] = imgs * W;
-    p.total_taps += p.tile_taps[t] * p.n_rir;
-  }
+  for (int t = 0; t < pa.n_tiles; ++t) p.total_taps += p.tile_taps[t] * p.n_rir;
   // an explicit item size is used as given
   const bool fixed = sched && sched->item_taps > 0.0;
   const bool mom = !p.half;  // FP32 and table taps: items of images, FP16: of taps
@@ -311,26 +344,30 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   // workspace of items cut by taps: a call's workspace, and with it what fits a
   // fixed one, does not depend on how its items are cut, and a schedule that
   // asks for more items than that is cut by taps as well
-  uint64_t n_items = 0, n_split = 0, ws_items = 0, ws_split = 0;
+  uint64_t n_items = 0, n_split = 0;
+  size_t ws_arrays = 0;  // bytes of the partial tiles and margins the workspace is sized for
+  auto arrays = [&](uint64_t items, uint64_t split, int T) {
+    return align_up(split > 0 ? sizeof(float) * (size_t)items * T : 0) + align_up(sizeof(float) * (size_t)items * p.wt);
+  };
   if (mom && !fixed && taper) {
     double tt = item_target(p.total_taps, p.wt, false, false, nS, sched);
     const double res = resident_items(true, false);
     if (p.total_taps < res * tt) tt = std::min(tt, small_call_floor(p.total_taps, res));
-    if (!cut_tiles(p, tt, taps_floor(tt), rounds(kTailRounds), res, pa.chunks, ws_items, ws_split))
+    double taps[MAX_TILES];
+    const int n = shell_taps(*r, p, TILE, taps);
+    if (!cut_tiles(p, taps, n, tt, taps_floor(tt), rounds(kTailRounds), res, nullptr, n_items, n_split))
       return ISM_E_TOO_LARGE;
-    p.any_split = ws_split > 0;
+    ws_arrays = arrays(n_items, n_split, TILE);
   }
-  if (ws_items == 0 || target >= p.total_taps / (double)ws_items) {
-    uint8_t chunks[MAX_TILES];
-    if (!cut_tiles(p, target, mom ? target / 2.0 : taps_floor(target), rounds(kTailRounds),
-                   resident, chunks, n_items, n_split))
+  for (;;) {
+    if (!cut_tiles(p, p.tile_taps, pa.n_tiles, target, mom ? target / 2.0 : taps_floor(target), rounds(kTailRounds),
+                   resident, pa.chunks, n_items, n_split))
       return ISM_E_TOO_LARGE;
-    if (ws_items == 0 || (n_items <= ws_items && n_split <= ws_split)) {
-      std::memcpy(pa.chunks, chunks, (size_t)pa.n_tiles);
-      p.any_split = n_split > 0;
-      if (ws_items == 0) ws_items = n_items, ws_split = n_split;
-    }
+    if (ws_arrays == 0 || arrays(n_items, n_split, ra.tile) <= ws_arrays || n_split == 0) break;
+    target *= 2.0;
   }
+  ws_arrays = std::max(ws_arrays, arrays(n_items, n_split, ra.tile));
+  p.any_split = n_split > 0;
   uint64_t acc = 0;
   for (int pos = 0; pos < pa.n_tiles; ++pos) {
     if (pos % PLAN_BLK == 0) pa.first_blk[pos / PLAN_BLK] = (uint32_t)acc;
@@ -343,13 +380,12 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   p.off_origin = align_up(sizeof(int) * (size_t)p.n_rir);
   p.off_tab = align_up(p.off_origin + sizeof(AxisOrigin) * (size_t)p.n_rir);
   p.off_part = align_up(p.off_tab + sizeof(AxisEntry) * (size_t)p.n_rir * ra.n_tab);
-  p.off_marg = align_up(p.off_part + (p.any_split ? sizeof(float) * (size_t)p.n_items * TILE : 0));
+  p.off_marg = align_up(p.off_part + (p.any_split ? sizeof(float) * (size_t)p.n_items * ra.tile : 0));
   // general-mode window constants
   p.off_wc = align_up(p.off_marg + sizeof(float) * (size_t)p.n_items * p.wt);
   // host-position calls copy src then rcv here
   p.off_pos = align_up(p.off_wc + (p.gen ? sizeof(float) * WC_STRIDE * (size_t)p.wt : 0));
-  size_t o = align_up(p.off_part + (ws_split > 0 ? sizeof(float) * (size_t)ws_items * TILE : 0));
-  o = align_up(o + sizeof(float) * (size_t)ws_items * p.wt);
+  size_t o = p.off_part + ws_arrays;
   o = align_up(o + (p.gen ? sizeof(float) * WC_STRIDE * (size_t)p.wt : 0));
   p.ws_bytes = align_up(o + sizeof(float) * 3 * ((size_t)n_src + (size_t)n_rcv));
   return ISM_OK;
@@ -707,7 +743,7 @@ int ism_simulate_diffuse_polar(const ism_room *room, double t_diff, double t60, 
 
 namespace {
 
-constexpr int kMaxClasses = kMaxBatchClasses;
+constexpr int kMaxClasses = kMaxBatchLaunches;
 
 struct BatchState {  // stored in ism_batch::opaque
   uint64_t ws;
@@ -717,8 +753,8 @@ struct BatchState {  // stored in ism_batch::opaque
   uint32_t polar, n_jobs, any_gen, long_runs;  // polar: directional kernels; any_gen: general-mode windows;
                                                // long_runs: a tile of RED_SLICE_MIN items or more
   uint32_t n_red_split, pad;                    // reduce entries of split tiles (they come first)
-  uint32_t class_first[kMaxClasses], class_count[kMaxClasses], class_grid[kMaxClasses];
-  int32_t class_wt[kMaxClasses], class_gen[kMaxClasses];
+  uint32_t class_count[kMaxClasses];
+  uint16_t class_code[kMaxClasses];             // cap / 32, general mode << 4, long tiles << 5, waves per SIMD << 8
 };
 static_assert(sizeof(BatchState) <= sizeof(ism_batch), "ism_batch too small");
 
@@ -779,10 +815,10 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
   }
   // pass 1: plans, window classes and counts
   int n_classes = 0;
-  int class_wt[kMaxClasses] = {}, class_gen[kMaxClasses] = {};
+  int class_wt[kMaxClasses] = {}, class_gen[kMaxClasses] = {}, class_tile[kMaxClasses] = {}, n_windows = 0;
   std::vector<int> job_cls(n_jobs);
   uint64_t tab_entries = 0, n_rir = 0, n_items = 0, slots = 0, n_red = 0, marg_units = 0, wc_floats = 0,
-           max_chunks = 0, ws_items = 0, ws_slots = 0, ws_marg = 0;  // ws: counts the workspace is sized for
+           max_chunks = 0, ws_items = 0, ws_slots = 0, ws_marg = 0, ws_red = 0;  // ws: counts the workspace is sized for
   std::vector<uint64_t> bucket_count((size_t)kMaxClasses * kCostBuckets, 0);
   for (int j = 0; j < n_jobs; ++j) {
     Plan &p = plans[j];
@@ -803,22 +839,30 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
         if (batch_taps < res * tt) tt = std::min(tt, small_call_floor(batch_taps, res));
         js.item_taps = std::max(js.item_taps, tt);
         uint64_t n = 0, ns = 0;
-        if (!cut_tiles(p, tt, tt, 0.0, res, nullptr, n, ns)) return ISM_E_TOO_LARGE;
+        double taps[MAX_TILES];
+        const int nt = shell_taps(jobs[j].room, p, TILE, taps);
+        if (!cut_tiles(p, taps, nt, tt, tt, 0.0, res, nullptr, n, ns)) return ISM_E_TOO_LARGE;
         ws_items += n;
         ws_slots += ns;
         ws_marg += n * (uint64_t)(p.wt / MARG_UNIT);
+        ws_red += (uint64_t)nt * p.n_rir;
       }
       const int stt = make_plan(&jobs[j].room, jobs[j].n_src, jobs[j].n_rcv, precision, p, &js, false);
       if (stt != ISM_OK) return stt;
     }
     int cls = -1;
+    bool window_known = false;
     for (int k = 0; k < n_classes; ++k)
-      if (class_wt[k] == p.wt && class_gen[k] == (p.gen ? 1 : 0)) cls = k;
+      if (class_wt[k] == p.wt && class_gen[k] == (p.gen ? 1 : 0)) {
+        window_known = true;
+        if (class_tile[k] == p.ra.tile) cls = k;
+      }
     if (cls < 0) {
-      if (n_classes == kMaxClasses) return ISM_E_UNSUPPORTED;
+      if (!window_known && n_windows++ == kMaxBatchClasses) return ISM_E_UNSUPPORTED;
       cls = n_classes++;
       class_wt[cls] = p.wt;
       class_gen[cls] = p.gen ? 1 : 0;
+      class_tile[cls] = p.ra.tile;
     }
     job_cls[j] = cls;
     if (p.gen) wc_floats += (uint64_t)WC_STRIDE * p.wt;
@@ -827,7 +871,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
       max_chunks = std::max(max_chunks, C);
       n_items += C * p.n_rir;
       marg_units += C * p.n_rir * (uint64_t)(p.wt / MARG_UNIT);
-      if (C > 1) slots += C * p.n_rir;
+      if (C > 1) slots += C * p.n_rir * (uint64_t)(p.ra.tile / TILE);
       bucket_count[(size_t)cls * kCostBuckets + cost_bucket(p.tile_taps[t] / C)] += C * p.n_rir;
     }
     n_red += (uint64_t)p.pa.n_tiles * p.n_rir;
@@ -841,22 +885,20 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
   std::vector<uint64_t> bucket_next((size_t)kMaxClasses * kCostBuckets, 0);
   uint64_t acc = 0;
   for (int k = 0; k < n_classes; ++k) {
-    bp.st.class_first[k] = (uint32_t)acc;
+    const uint64_t first = acc;
     for (int b = kCostBuckets - 1; b >= 0; --b) {
       bucket_next[(size_t)k * kCostBuckets + b] = acc;
       acc += bucket_count[(size_t)k * kCostBuckets + b];
     }
-    bp.st.class_count[k] = (uint32_t)(acc - bp.st.class_first[k]);
-    bp.st.class_wt[k] = class_wt[k];
-    bp.st.class_gen[k] = class_gen[k];
-    // persistent grid: the tuned workgroups per SIMD (or the schedule's)
+    bp.st.class_count[k] = (uint32_t)(acc - first);
+    // persistent grid: the tuned waves per SIMD (or the schedule's)
     int waves = waves_per_simd(precision == ISM_FP16, precision == ISM_FP32_LUT);
     if (precision == ISM_FP16)
       for (const BatchTuning &t : kBatchTuning)
-        if (t.wt == class_wt[k] && t.half == (precision == ISM_FP16 ? 1 : 0)) waves = t.waves;
+        if (t.wt == class_wt[k] && t.half == 1) waves = t.waves;
     if (sched && sched->batch_waves > 0.0) waves = std::max(1, (int)std::lround(sched->batch_waves));
-    bp.st.class_grid[k] = (uint32_t)std::min<uint64_t>(
-        bp.st.class_count[k], 1024ull * (uint64_t)waves * 64 / item_threads(precision == ISM_FP16));
+    bp.st.class_code[k] =
+        (uint16_t)(class_wt[k] / 32 | class_gen[k] << 4 | (class_tile[k] == LONG_TILE ? 1 : 0) << 5 | waves << 8);
   }
   bp.st.n_jobs = (uint32_t)n_jobs;
   bp.st.any_gen = wc_floats > 0 ? 1u : 0u;
@@ -866,10 +908,8 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
   bp.st.polar = polar ? 1u : 0u;
   bp.st.n_rir = (uint32_t)n_rir;
   bp.st.n_red = (uint32_t)n_red;
-  ws_items = std::max(ws_items, n_items);
-  ws_slots = std::max(ws_slots, slots);
-  ws_marg = std::max(ws_marg, marg_units);
-  if (ws_items > 0x7fffffffULL || ws_slots > 0xffffffffULL || ws_marg > 0xffffffffULL) return ISM_E_TOO_LARGE;
+  if (ws_items > 0x7fffffffULL || ws_slots > 0xffffffffULL || ws_marg > 0xffffffffULL || ws_red > 0x7fffffffULL)
+    return ISM_E_TOO_LARGE;
   // positions of every job (ism_simulate_batch copies host positions here)
   bp.pos_off.resize(n_jobs);
   size_t pos_floats = 0;
@@ -877,7 +917,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     bp.pos_off[j] = pos_floats;
     pos_floats += 3 * ((size_t)jobs[j].n_src + (size_t)jobs[j].n_rcv * (jobs[j].orient ? 2 : 1));
   }
-  auto layout = [&](uint64_t items, uint64_t part_slots, uint64_t marg, BatchState &st) {
+  auto layout = [&](uint64_t items, uint64_t part_slots, uint64_t marg, uint64_t red, BatchState &st) {
     size_t o = 0;
     st.off_jobs = o;
     o = align_up(o + sizeof(JobDev) * (size_t)n_jobs);
@@ -886,7 +926,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     st.off_items = o;
     o = align_up(o + sizeof(BatchItem) * (size_t)items);
     st.off_red = o;
-    o = align_up(o + sizeof(BatchReduce) * (size_t)n_red);
+    o = align_up(o + sizeof(BatchReduce) * (size_t)red);
     st.off_pos = o;
     o = align_up(o + sizeof(float) * pos_floats);
     st.off_valid = o;
@@ -906,9 +946,9 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     st.off_wc = o;
     return align_up(o + sizeof(float) * (size_t)wc_floats);
   };
-  BatchState unused;
-  bp.ws_bytes = layout(ws_items, ws_slots, ws_marg, unused);
-  bp.ws_bytes = std::max(bp.ws_bytes, layout(n_items, slots, marg_units, bp.st));
+  BatchState unused = {};
+  bp.ws_bytes = layout(n_items, slots, marg_units, n_red, bp.st);
+  bp.ws_bytes = std::max(bp.ws_bytes, layout(ws_items, ws_slots, ws_marg, ws_red, unused));
   if (!fill) return ISM_OK;
 
   // pass 2: tables. Margin records are numbered in (job, tile, RIR, chunk)
@@ -939,6 +979,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     }
     for (int r = 0; r < p.n_rir; ++r) bp.rirs[rir_base + r] = BatchRir{(uint32_t)j, (uint32_t)r};
     const int nt = p.pa.n_tiles;
+    const uint32_t su = (uint32_t)(p.ra.tile / TILE);  // partial tile, in units of TILE floats
     // margin records (units of MARG_UNIT floats, wu units each): the first
     // record of (tile t, RIR r) is mfirst_t + r * chunks[t] * wu
     const uint64_t wu = (uint64_t)(p.wt / MARG_UNIT);
@@ -968,9 +1009,9 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
         }
         for (int c = 0; c < C; ++c)
           bp.items[pos++] = BatchItem{(uint32_t)j, (uint32_t)r, (uint16_t)t, (uint8_t)c, (uint8_t)C,
-                                      C > 1 ? slot + (uint32_t)c : 0xffffffffu,
+                                      C > 1 ? slot + (uint32_t)c * su : 0xffffffffu,
                                       (uint32_t)(mfirst[t] + ((uint64_t)r * C + c) * wu)};
-        if (C > 1) slot += (uint32_t)C;
+        if (C > 1) slot += (uint32_t)C * su;
       }
     }
     tab_base += (uint64_t)p.n_rir * p.ra.n_tab;
@@ -1092,11 +1133,24 @@ int ism_batch_run_timed(const ism_batch *batch, void *stream, void *ev_start, vo
   if (!b.ws || b.n_rir == 0 || b.n_classes == 0 || b.n_classes > (uint32_t)kMaxClasses || b.n_red_split > b.n_red)
     return ISM_E_INVALID_ARG;
   char *w = (char *)(uintptr_t)b.ws;
+  BatchClass cls[kMaxClasses];
+  uint32_t first = 0;
+  int max_tile = TILE;
+  for (uint32_t k = 0; k < b.n_classes; ++k) {
+    const uint32_t code = b.class_code[k], waves = code >> 8;
+    cls[k].first = first;
+    cls[k].count = b.class_count[k];
+    cls[k].grid = std::min(b.class_count[k], 1024u * waves * 64u / (uint32_t)item_threads(b.mode == 1));
+    cls[k].wt = (int)(code & 15u) * 32;
+    cls[k].gen = (int)(code >> 4 & 1u);
+    cls[k].tile = (code >> 5 & 1u) ? LONG_TILE : TILE;
+    max_tile = std::max(max_tile, cls[k].tile);
+    first += b.class_count[k];
+  }
   const int rc = launch_batch((const JobDev *)(w + b.off_jobs), (int)b.n_jobs, b.any_gen != 0,
-                              (const BatchRir *)(w + b.off_rirs), b.n_rir,
-                              (const BatchItem *)(w + b.off_items), b.class_first, b.class_count, b.class_grid,
-                              b.class_wt, b.class_gen, (int)b.n_classes, b.mode == 1, b.mode == 2, b.polar != 0,
-                              (const BatchReduce *)(w + b.off_red), b.n_red, b.n_red_split, b.long_runs != 0,
+                              (const BatchRir *)(w + b.off_rirs), b.n_rir, (const BatchItem *)(w + b.off_items), cls,
+                              (int)b.n_classes, b.mode == 1, b.mode == 2, b.polar != 0,
+                              (const BatchReduce *)(w + b.off_red), b.n_red, b.n_red_split, b.long_runs != 0, max_tile,
                               (AxisEntry *)(w + b.off_tab), (AxisOrigin *)(w + b.off_origin),
                               (int *)(w + b.off_valid), (float *)(w + b.off_part), (float *)(w + b.off_marg),
                               (uint32_t *)(w + b.off_queue), (hipStream_t)stream,

@@ -7,10 +7,12 @@
 namespace ism {
 
 // Tiles partition the integer delays k0 = floor(x) of the images: tile t owns
-// the images with k0 in [t*TILE, (t+1)*TILE) and writes output samples
-// [t*TILE, (t+1)*TILE) plus two margins, the W/2 - 1 samples before and the
-// W/2 samples after, which belong to the neighbouring tiles.
+// the images with k0 in [t T, (t+1) T) and writes output samples [t T, (t+1) T)
+// plus two margins, the W/2 - 1 samples before and the W/2 samples after, which
+// belong to the neighbouring tiles. T = TILE, or LONG_TILE for FP32 calls whose
+// shells hold few images (chosen by make_plan in ism_host.cpp).
 constexpr int TILE = 256;
+constexpr int LONG_TILE = 512;
 // Most tiles per RIR: ceil((ISM_MAX_SAMPLES + 128/2 - 1) / TILE).
 constexpr int MAX_TILES = 1025;
 // Dispatch positions per block of the plan's coarse first-item table.
@@ -34,8 +36,10 @@ constexpr int WC_STRIDE = 8;
 // use one thread per sample, others RED_SLICES threads per sample.
 constexpr int RED_SLICES = 4;
 constexpr int RED_SLICE_MIN = 64;
-// Window classes (cap, mode) one batch may hold: one persistent launch each.
+// Window classes (cap, mode) one batch may hold, and persistent launches: one per
+// class and tile length.
 constexpr int kMaxBatchClasses = 8;
+constexpr int kMaxBatchLaunches = 2 * kMaxBatchClasses;
 // Work items per tile are capped so the per-tile chunk count fits a byte.
 constexpr int MAX_CHUNKS = 255;
 // Waves per SIMD the accumulate kernels are built for (their LDS and VGPR
@@ -65,6 +69,7 @@ struct RoomArgs {
   float half_w;            // WT / 2, WT the window cap (layout of tiles and margins)
   float win_hw;            // W / 2, W = t_w fs the window [samples]
   float inv_win;           // 1 / W
+  int tile;                // samples per tile (TILE or LONG_TILE)
   int gen;                 // 1: general-mode window (per-call tap constants, masked taps)
   int n_samples;           // nS
   int k_end;               // nS + W/2 - 1: images with k0 >= k_end add nothing
@@ -76,7 +81,7 @@ struct RoomArgs {
 
 // Work decomposition of one call. Items are ordered by tile (last tile first,
 // where the images are densest), then by RIR, then by chunk. Tile t owns the
-// images with k0 in [t*TILE, min((t+1)*TILE, k_end)); that shell is split into
+// images with k0 in [t*tile, min((t+1)*tile, k_end)); that shell is split into
 // chunks[t] slabs along the x displacement.
 // The first item of dispatch position pos (tile n_tiles - 1 - pos) is
 // first_blk[pos / PLAN_BLK] plus n_rir * chunks of the positions before pos in
@@ -117,13 +122,21 @@ struct JobDev {
   uint32_t pad;
 };
 
+// One persistent launch of a batch: items [first, first + count) of the list on
+// grid workgroups, window cap wt (gen: general mode), tiles of tile samples.
+struct BatchClass {
+  uint32_t first, count, grid;
+  int wt, tile, gen;
+};
+
 // Batch-wide RIR index -> (job, RIR within the job).
 struct BatchRir {
   uint32_t job, rir;
 };
 
 // One work item of a batch (same meaning as in single-room mode). slot is the
-// partial tile written when the tile is split (chunks > 1), else 0xffffffff;
+// offset (in units of TILE floats) of the partial tile written when the tile is
+// split (chunks > 1), else 0xffffffff;
 // mslot is the offset of its margin record in units of MARG_UNIT floats.
 struct BatchItem {
   uint32_t job, rir;
@@ -133,8 +146,8 @@ struct BatchItem {
   uint32_t mslot;
 };
 
-// One output tile of a batch RIR: its own partials (slots first ..
-// first + chunks - 1 when chunks > 1) and the margin records of the items of
+// One output tile of a batch RIR: its own partials (chunks consecutive tiles from
+// offset first, in units of TILE floats, when chunks > 1) and the margin records of the items of
 // the previous and next tile (nprev records from offset mprev, nnext from
 // mnext, in units of MARG_UNIT floats, consecutive records WT floats apart;
 // counts are 0 where there is no such tile).

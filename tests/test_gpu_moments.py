@@ -34,6 +34,13 @@ CASES = [
     ("one_sample", 16000.0, 64.0, 1.0 / 16000.0, [3.0, 4.0, 2.5], False, 0.0),
     ("tile_less_one", 16000.0, 64.0, 255.0 / 16000.0, [3.0, 4.0, 2.5], False, 0.0),
     ("tile_plus_one", 16000.0, 64.0, 257.0 / 16000.0, [3.0, 4.0, 2.5], False, 0.0),
+    # few images per tile: tiles of 512 samples (a given item size takes them on small calls too)
+    ("long_w_32", 16000.0, 32.0, 0.06, [9.0, 8.0, 7.0], False, 1e9),
+    ("long_w_64_split", 16000.0, 64.0, 0.12, [9.0, 8.0, 7.0], False, 1e3),
+    ("long_w_128", 16000.0, 128.0, 513.0 / 16000.0, [9.0, 8.0, 7.0], False, 1e9),
+    ("long_w_33_edge", 16000.0, 33.0, 511.0 / 16000.0, [9.0, 8.0, 7.0], False, 1e9),
+    ("long_w_3.2_direct", 16000.0, 3.2, 0.06, [9.0, 8.0, 7.0], False, 1e9),
+    ("long_w_176.4_two_passes", 44100.0, 176.4, 0.03, [9.0, 8.0, 7.0], False, 1e9),
 ]
 
 
