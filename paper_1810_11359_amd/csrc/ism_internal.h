@@ -176,12 +176,14 @@ struct DumpArgs {
   uint32_t cap;
 };
 
-// Workspace layout of one FFT filter call (offsets in bytes): block size B,
-// transform size N = 2B, RIR partitions P, pieces per input block R, segment
-// length L, input and output block counts.
+// One FFT filter call. Fixed blocks (c = 0): block size B, transform size N = 2B,
+// RIR partitions P, pieces per input block R, segment length L, input and output
+// block counts. Segment blocks (c >= 1): partitions of c L taps, in S groups of
+// PS. Offsets into the workspace in bytes.
 struct FftPlan {
   int B, N, P, R, n_in_blocks, n_out_blocks, L;
-  size_t off_tw, off_H, off_X, off_Y, off_z, bytes;
+  int c, S, PS;
+  size_t off_H, off_X, off_Y, off_z, bytes;
 };
 
 }  // namespace ism
