@@ -1454,11 +1454,24 @@ __device__ __forceinline__ void run_item(const RoomArgs &ra, const int tile_id, 
   else moment_item<WT, TL, LUT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
 }
 
+// The 16 dispatch positions of plan block blk on lanes 0 .. 15: chunks per RIR, and the
+// items before the position within the block.
+struct PlanLanes {
+  int chunks;
+  uint32_t before;
+};
+__device__ __forceinline__ PlanLanes plan_lanes(const PlanArgs &pa, int blk) {
+  const int lane = (int)(threadIdx.x & 63), p = blk * PLAN_BLK + lane;
+  PlanLanes l;
+  l.chunks = lane < PLAN_BLK && p < pa.n_tiles ? (int)pa.chunks[pa.n_tiles - 1 - p] : 0;
+  const int n = pa.n_rir * l.chunks;
+  l.before = (uint32_t)(wave_incl_scan(n) - n);
+  return l;
+}
 // First work item of dispatch position pos (see PlanArgs).
 __device__ __forceinline__ uint32_t plan_first_item(const PlanArgs &pa, int pos) {
-  uint32_t f = pa.first_blk[pos / PLAN_BLK];
-  for (int p = pos - pos % PLAN_BLK; p < pos; ++p) f += (uint32_t)pa.n_rir * pa.chunks[pa.n_tiles - 1 - p];
-  return f;
+  const PlanLanes l = plan_lanes(pa, pos / PLAN_BLK);
+  return pa.first_blk[pos / PLAN_BLK] + (uint32_t)__builtin_amdgcn_readlane((int)l.before, pos % PLAN_BLK);
 }
 
 // Work item of a single-room launch: the item index decodes through the
@@ -1468,29 +1481,30 @@ struct SingleItem {
   uint32_t first;  // first item of the dispatch position
 };
 __device__ __forceinline__ SingleItem decode_item(const PlanArgs &pa, uint32_t item) {
-  // largest dispatch position pos whose first item is <= item: the block by
-  // binary search over first_blk, then the position within the block
+  // largest dispatch position pos whose first item is <= item: the block, then the
+  // position within it, each by one load on all lanes (a search in scalar loads takes
+  // up to 20 one after the other: a call of 4 receivers 67.2 -> 65.6 us)
+  const int lane = (int)(threadIdx.x & 63);
   const int nblk = (pa.n_tiles + PLAN_BLK - 1) / PLAN_BLK;
-  int lo = 0, hi = nblk;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pa.first_blk[mid] <= item) lo = mid;
-    else hi = mid;
+  int blk = 0;
+  uint32_t base = 0;
+  for (int b0 = 0; b0 < nblk && nblk > 1; b0 += 64) {
+    const uint32_t f = b0 + lane < nblk ? pa.first_blk[b0 + lane] : 0xffffffffu;
+    const int n = __builtin_popcountll(__ballot(b0 + lane < nblk && f <= item));
+    if (n == 0) break;
+    blk = b0 + n - 1;
+    base = (uint32_t)__builtin_amdgcn_readlane((int)f, n - 1);
+    if (n < 64) break;
   }
-  int pos = lo * PLAN_BLK;
-  uint32_t first = pa.first_blk[lo];
-  const int pend = min(pa.n_tiles, pos + PLAN_BLK);
-  for (;;) {
-    const uint32_t next = first + (uint32_t)pa.n_rir * pa.chunks[pa.n_tiles - 1 - pos];
-    if (pos + 1 >= pend || next > item) break;
-    first = next;
-    ++pos;
-  }
+  const PlanLanes l = plan_lanes(pa, blk);
+  const int at = __builtin_popcountll(__ballot(lane < PLAN_BLK && blk * PLAN_BLK + lane < pa.n_tiles &&
+                                               base + l.before <= item)) - 1;
+  const uint32_t first = base + (uint32_t)__builtin_amdgcn_readlane((int)l.before, at);
   SingleItem si;
-  si.pos = pos;
+  si.pos = blk * PLAN_BLK + at;
   si.first = first;
-  si.tile_id = pa.n_tiles - 1 - pos;
-  si.C = pa.chunks[si.tile_id];
+  si.tile_id = pa.n_tiles - 1 - si.pos;
+  si.C = __builtin_amdgcn_readlane(l.chunks, at);
   const uint32_t rel = item - first;
   si.rir = (int)(rel / (uint32_t)si.C);
   si.c = (int)(rel % (uint32_t)si.C);
@@ -1646,14 +1660,63 @@ __device__ __forceinline__ float run_sum(float v, const float *__restrict__ x, s
   return v;
 }
 
-template <bool SLICED>
+// One run of a sample's terms: n of them, stride apart.
+struct Run {
+  const float *x;
+  size_t stride;
+  int n;       // uniform over the block
+  bool active;
+};
+
+// The reduce launches: plain (no tile was split), gather, sliced (a run of RED_SLICE_MIN
+// terms or more).
+enum { RED_PLAIN, RED_GATHER, RED_SLICED };
+
+// v and the terms of the runs a, l and r in that order (run_sum). RED_GATHER: where no run
+// has more than eight terms, all of them are loaded together, one memory round trip instead
+// of three (one receiver: 6.0 -> 4.8 us; 32 receivers: 6.9 -> 4.6). Not for launches whose
+// tiles were not split: they have thousands of blocks to hide the latency and would pay for
+// the padding to eight loads (1024 RIRs of 2427 samples: 16 us; term by term 9.7; with one
+// item per tile known, so no plan lookups either, 6.3).
+template <int MODE, class Red>
+__device__ __forceinline__ float add_runs(float v, const Run &a, const Run &l, const Run &r, int slice, int ks,
+                                          Red &red) {
+  const Run *const runs[3] = {&a, &l, &r};
+  if constexpr (MODE == RED_SLICED) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v = run_sum(v, runs[i]->x, runs[i]->stride, runs[i]->n, runs[i]->active, slice, ks, red);
+  } else if (MODE == RED_GATHER && max(a.n, max(l.n, r.n)) <= 8) {
+    float t[3][8];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (runs[i]->n > 0 && runs[i]->active) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[i][u] = runs[i]->x[(size_t)min(u, runs[i]->n - 1) * runs[i]->stride];
+      }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (runs[i]->n > 0 && runs[i]->active) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v = u < runs[i]->n ? v + t[i][u] : v;
+      }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (runs[i]->active) v = ordered_sum(v, runs[i]->x, runs[i]->stride, runs[i]->n);
+  }
+  return v;
+}
+
+template <int MODE>
 __global__ __launch_bounds__(256) void reduce_kernel(RoomArgs ra, PlanArgs pa, const float *__restrict__ part,
                                                      const float *__restrict__ marg, float *__restrict__ out) {
+  constexpr bool SLICED = MODE == RED_SLICED;
   constexpr int SPB = SLICED ? RED_SAMPLES : 256;  // samples per block
   __shared__ float red[SLICED ? RED_SLICES : 1][SLICED ? RED_SAMPLES : 1];
   const int pos = blockIdx.y;
   const int tile_id = pa.n_tiles - 1 - pos;
-  const int C = pa.chunks[tile_id];
+  // (plain: one item per tile, so item pos * n_rir is a position's first)
+  const int C = MODE == RED_PLAIN ? 1 : pa.chunks[tile_id];
   const int rir = blockIdx.x;
   const int TL = ra.tile, T0 = tile_id * TL;
   const int ks = (int)threadIdx.x % SPB, slice = (int)threadIdx.x / SPB;
@@ -1667,37 +1730,35 @@ __global__ __launch_bounds__(256) void reduce_kernel(RoomArgs ra, PlanArgs pa, c
   const bool in = k < ra.n_samples - T0 && k < TL;
   const bool zl = in && has_l && k < W / 2;
   const bool zr = in && has_r && k >= TL - LM;
-  auto add = [&](float v, const float *x, size_t stride, int n, bool active) {
-    if constexpr (SLICED) return run_sum(v, x, stride, n, active, slice, ks, red);
-    else return active ? ordered_sum(v, x, stride, n) : v;  // n < RED_SLICE_MIN
-  };
   float *o = out + (size_t)rir * ra.n_samples + T0 + k;
+  Run own{part, (size_t)TL, 0, in}, left{marg, (size_t)W, 0, zl}, right{marg, (size_t)W, 0, zr};
   float v = 0.0f;
+  const uint32_t first = MODE == RED_PLAIN ? (uint32_t)pos * (uint32_t)pa.n_rir : plan_first_item(pa, pos);
   if (C > 1) {
-    const size_t first = (size_t)plan_first_item(pa, pos) + (size_t)rir * C;
-    v = add(0.0f, part + first * TL + k, TL, C, in);
+    own.x = part + ((size_t)first + (size_t)rir * C) * TL + k;
+    own.n = C;
   } else if (in && slice == 0 && (zl || zr)) {
     v = *o;
   }
   if (has_l) {  // tile t-1 is dispatched at pos + 1
-    const int Cp = pa.chunks[tile_id - 1];
-    const size_t first = (size_t)plan_first_item(pa, pos + 1) + (size_t)rir * Cp;
-    v = add(v, marg + first * W + LM + k, W, Cp, zl);
+    left.n = MODE == RED_PLAIN ? 1 : pa.chunks[tile_id - 1];
+    left.x = marg + ((size_t)first + (size_t)pa.n_rir * C + (size_t)rir * left.n) * W + LM + k;
   }
   if (has_r) {  // tile t+1 is dispatched at pos - 1
-    const int Cn = pa.chunks[tile_id + 1];
-    const size_t first = (size_t)plan_first_item(pa, pos - 1) + (size_t)rir * Cn;
-    v = add(v, marg + first * W + (k - (TL - LM)), W, Cn, zr);
+    right.n = MODE == RED_PLAIN ? 1 : pa.chunks[tile_id + 1];
+    right.x = marg + ((size_t)first - (size_t)pa.n_rir * right.n + (size_t)rir * right.n) * W + (k - (TL - LM));
   }
+  v = add_runs<MODE>(v, own, left, right, slice, ks, red);
   if (in && slice == 0 && (C > 1 || zl || zr)) *o = v;
 }
 
 // Batch mode: grid = (output tile of a batch RIR, segment of the tile).
-template <bool SLICED>
+template <int MODE>
 __global__ __launch_bounds__(256) void reduce_batch_kernel(const JobDev *__restrict__ jobs,
                                                            const BatchReduce *__restrict__ red_tab,
                                                            const float *__restrict__ part,
                                                            const float *__restrict__ marg) {
+  constexpr bool SLICED = MODE == RED_SLICED;
   constexpr int SPB = SLICED ? RED_SAMPLES : 256;
   __shared__ float red[SLICED ? RED_SLICES : 1][SLICED ? RED_SAMPLES : 1];
   const BatchReduce br = red_tab[blockIdx.x];
@@ -1715,19 +1776,13 @@ __global__ __launch_bounds__(256) void reduce_batch_kernel(const JobDev *__restr
   const bool in = k < n_samples - T0 && k < TL;
   const bool zl = in && has_l && k < W / 2;
   const bool zr = in && has_r && k >= TL - LM;
-  auto add = [&](float v, const float *x, size_t stride, int n, bool active) {
-    if constexpr (SLICED) return run_sum(v, x, stride, n, active, slice, ks, red);
-    else return active ? ordered_sum(v, x, stride, n) : v;  // n < RED_SLICE_MIN
-  };
   float *o = jb.out + (size_t)br.rir * n_samples + T0 + k;
   float v = 0.0f;
-  if (br.chunks > 1) {
-    v = add(0.0f, part + (size_t)br.first * TILE + k, TL, br.chunks, in);
-  } else if (in && slice == 0 && (zl || zr)) {
-    v = *o;
-  }
-  if (has_l) v = add(v, marg + (size_t)br.mprev * MARG_UNIT + LM + k, W, br.nprev, zl);
-  if (has_r) v = add(v, marg + (size_t)br.mnext * MARG_UNIT + (k - (TL - LM)), W, br.nnext, zr);
+  if (br.chunks <= 1 && in && slice == 0 && (zl || zr)) v = *o;
+  const Run own{part + (size_t)br.first * TILE + k, (size_t)TL, br.chunks > 1 ? (int)br.chunks : 0, in};
+  const Run left{marg + (size_t)br.mprev * MARG_UNIT + LM + k, (size_t)W, has_l ? (int)br.nprev : 0, zl};
+  const Run right{marg + (size_t)br.mnext * MARG_UNIT + (k - (TL - LM)), (size_t)W, has_r ? (int)br.nnext : 0, zr};
+  v = add_runs<MODE>(v, own, left, right, slice, ks, red);
   if (in && slice == 0 && (br.chunks > 1 || zl || zr)) *o = v;
 }
 
@@ -1927,10 +1982,10 @@ int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *r
   if (n_red_split > 0) {
     // split tiles, whole tiles; runs of RED_SLICE_MIN terms or more: RED_SLICES threads per sample
     if (long_runs)
-      hipLaunchKernelGGL(reduce_batch_kernel<true>, dim3(n_red_split, max_tile / RED_SAMPLES), dim3(256), 0, st, jobs, red,
+      hipLaunchKernelGGL(reduce_batch_kernel<RED_SLICED>, dim3(n_red_split, max_tile / RED_SAMPLES), dim3(256), 0, st, jobs, red,
                          part, marg);
     else
-      hipLaunchKernelGGL(reduce_batch_kernel<false>, dim3(n_red_split, max_tile / 256), dim3(256), 0, st, jobs, red, part,
+      hipLaunchKernelGGL(reduce_batch_kernel<RED_GATHER>, dim3(n_red_split, max_tile / 256), dim3(256), 0, st, jobs, red, part,
                          marg);
     if (hipGetLastError() != hipSuccess) return -1;
   }
@@ -1946,12 +2001,12 @@ int launch_reduce(const RoomArgs &ra, const PlanArgs &pa, int n_rir, const float
                   float *out, hipStream_t st) {
   int max_c = 0;  // longest run: the most items of any tile (its own, or a neighbour's margins)
   for (int t = 0; t < pa.n_tiles; ++t) max_c = max(max_c, (int)pa.chunks[t]);
-  if (max_c >= RED_SLICE_MIN)
-    hipLaunchKernelGGL(reduce_kernel<true>, dim3((unsigned)n_rir, (unsigned)pa.n_tiles, ra.tile / RED_SAMPLES), dim3(256),
-                       0, st, ra, pa, part, marg, out);
-  else
-    hipLaunchKernelGGL(reduce_kernel<false>, dim3((unsigned)n_rir, (unsigned)pa.n_tiles, ra.tile / 256), dim3(256), 0, st,
-                       ra, pa, part, marg, out);
+  const int spb = max_c >= RED_SLICE_MIN ? RED_SAMPLES : 256;
+  const dim3 grid((unsigned)n_rir, (unsigned)pa.n_tiles, ra.tile / spb);
+  auto *const kernel = max_c >= RED_SLICE_MIN ? &reduce_kernel<RED_SLICED>
+                       : max_c > 1            ? &reduce_kernel<RED_GATHER>
+                                              : &reduce_kernel<RED_PLAIN>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, ra, pa, part, marg, out);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
