@@ -37,9 +37,14 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 METRIC = "image-source sinc taps/s (G/s) + RIRs/s, FP32 vs FP16; p50/p99 serving latency"
-# frozen accounting of one windowed-sinc tap: 1 sub, 1 mul, 1 mul, 5 FMA,
-# 1 mul, 1 reciprocal, 2 mul, 1 add, an FMA counting 2
+# FP16 taps are evaluated one by one: the accounting of one windowed-sinc tap is 1 sub,
+# 1 mul, 1 mul, 5 FMA, 1 mul, 1 reciprocal, 2 mul, 1 add, an FMA counting 2
 FLOP_PER_TAP = 18
+# FP32 and table taps are not: an image costs 24 FLOP for its distance, delay and amplitude
+# and enters through ten moments (FMAs) or two pulses, and every output sample costs, per
+# sample of the window, an FMA per moment or phase (10 or 17)
+FLOP_PER_IMAGE = {"fp32": 24 + 2 * 10, "lut": 24 + 6}
+FLOP_PER_SAMPLE_TAP = {"fp32": 2 * 10, "lut": 2 * 17}
 FP32_VECTOR_PEAK = 157.3   # TFLOP/s, MI355X FP32 vector peak (256 CUs x 2.4 GHz x 256 FLOP/clk)
 # Host threads the oracle may use: the host CPU share of one GPU on a shared node.
 CPU_THREADS_MAX = 16
@@ -417,14 +422,21 @@ def calibrate_hbm(mib: int = 256) -> int:
     return 0
 
 
-def _roofline(taps: int, kern_ms, workload: str, precision: str, kernel: str):
+def _roofline(taps: int, window: float, samples: int, kern_ms, workload: str, precision: str, kernel: str):
+    """taps: windowed-sinc taps of a launch, about ``window`` per image; samples: its output samples."""
     kmean = float(np.mean(kern_ms))
-    achieved = FLOP_PER_TAP * taps / (kmean / 1e3) / 1e12
+    if precision == "fp16":
+        flop, accounting = FLOP_PER_TAP * taps, {"flop_per_tap": FLOP_PER_TAP}
+    else:
+        per_image, per_sample = FLOP_PER_IMAGE[precision], FLOP_PER_SAMPLE_TAP[precision]
+        flop = per_image * taps / window + per_sample * window * samples
+        accounting = {"flop_per_image": per_image, "flop_per_sample_and_window_tap": per_sample}
+    achieved = flop / (kmean / 1e3) / 1e12
     return {"bound": "alu", "achieved": achieved, "peak": FP32_VECTOR_PEAK, "unit": "TFLOP/s",
             "frac": achieved / FP32_VECTOR_PEAK, "traffic": measured_traffic(workload, precision),
             "traffic_unit": "B per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
             "kernel": kernel, "kernel_ms_mean": kmean, "kernel_ms_p50": float(np.median(kern_ms)),
-            "flop_per_tap": FLOP_PER_TAP}
+            **accounting}
 
 
 def bench_batch(args) -> int:
@@ -438,6 +450,7 @@ def bench_batch(args) -> int:
     rooms = [ism.room_for(w) for w in ws]
     jobs = [(r, w.src, w.rcv) for r, w in zip(rooms, ws)]
     taps = sum(ism.count_taps(r, w.src, w.rcv) for r, w in zip(rooms, ws))
+    samples = sum(len(w.src) * len(w.rcv) * r.n_samples for r, w in zip(rooms, ws))
     sample = _sample_jobs(ws, args.cpu_sample)
     n_rooms_sample = len(sample)
 
@@ -462,7 +475,8 @@ def bench_batch(args) -> int:
            "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": args.precision, "data": "synthetic", "config": config,
            "rirs_per_s": n_rir / (ms_step / 1e3),
-           "roofline": _roofline(taps, head["kern_ms"], "batch_rooms", args.precision, "accumulate_batch_kernel")}
+           "roofline": _roofline(taps, 64.0, samples, head["kern_ms"], "batch_rooms", args.precision,
+                                "accumulate_batch_kernel")}
     if "fp16" in legs and args.precision != "fp16":
         h = legs["fp16"]
         kmean = float(np.mean(h["kern_ms"]))
@@ -535,6 +549,7 @@ def bench_single(args) -> int:
         taps = ism.count_taps(ism_room, w.src, w.rcv)
     else:
         sim = ism.Simulator(room, w.src, w.rcv, precision=args.precision)
+        ism_room = room
         taps = ism.count_taps(room, w.src, w.rcv)
     n_rir = sim.n_src * sim.n_rcv
     config = {"workload": w.name, "room_m": list(map(float, w.room)), "t60_s": w.t60, "fs": w.fs,
@@ -548,7 +563,8 @@ def bench_single(args) -> int:
            "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": args.precision, "data": "synthetic", "config": config,
            "rirs_per_s": n_rir / (ms_step / 1e3),
-           "roofline": _roofline(taps, kern_ms, args.workload, args.precision, "accumulate_kernel")}
+           "roofline": _roofline(taps, w.t_w * w.fs, n_rir * ism_room.n_samples, kern_ms, args.workload, args.precision,
+                                "accumulate_kernel")}
     if not args.no_cpu_baseline and w.t_diff == 0.0:
         base, errs = cpu_baseline([w], args.cpu_sample, {args.precision: [sim.out.cpu().numpy()]},
                                   lut_q=16 if args.precision == "lut" else 0)

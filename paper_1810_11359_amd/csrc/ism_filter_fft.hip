@@ -591,9 +591,8 @@ template <int M> constexpr bool kKeepRoots = M <= 4096;
 // z[row] of row = (m n_blk + b) S + g: the inverse transform of the sum over the
 // partitions q of group g (PS of them) of X[b - c q] H_{b - c q, m}[q], with
 // 2M points of which the first (c + 1) L are kept. RIRs are read once and no RIR spectrum
-// goes to memory (fixed blocks write and read twice the RIRs). Bounded by the transforms'
-// arithmetic (about 75 instructions per point, two thirds of the FP32 rate) with the LDS
-// passes beside it. 8 microphones, 100 segments of 4800 samples, RIRs of 96000 taps (307
+// goes to memory (fixed blocks write and read twice the RIRs). Bounded by the transforms:
+// VALU issue (0.47 of the slots) and waits for the LDS passes and their barriers. 8 microphones, 100 segments of 4800 samples, RIRs of 96000 taps (307
 // MB): 293 us with the launches around it 310, fixed blocks of radix 8 677; segments of
 // 1600, RIRs of 8000 taps: 35 and 47.5 against 81.
 template <int M>
