@@ -319,7 +319,8 @@ int ism_filter_workspace_size(int n_x, int n_pos, int n_mic, int n_rir, int meth
  * of the B-tap partitions of their segment's RIR. Both use real FP32 transforms
  * (half-size complex Stockham transforms in LDS), add in a fixed order and
  * overlap-add the inverse transforms: results are bitwise reproducible and
- * agree with the direct sum to FP32 transform rounding.
+ * agree with the direct sum to FP32 transform rounding (of a block's norm; a
+ * sample or tap that is not finite spreads over the blocks it enters).
  *   ws: ism_filter_workspace_size() bytes (may be NULL for the direct sum). With
  *   less, a call takes fixed blocks if they fit, and auto the direct sum where a
  *   fixed block would touch more than 4 segments.

@@ -1124,7 +1124,7 @@ constexpr int MOM_WAVES = 4;
 // Pool slots per wave: 10 chunks of 64 positions. With these a workgroup takes 40 KB
 // of LDS and four fit a compute unit: 1024-room batch 6.43 ms, 64 microphones at
 // 48 kHz 2.37 ms, against 7.39 and 2.76 with 15 chunks (three workgroups) and 6.90
-// and 2.48 with 7 (five). Long tiles: 7 chunks beside their 12 KB of list ends.
+// and 2.48 with 7 (five), all before long tiles (now 5.97 and 2.18). Long tiles: 7 chunks beside their 12 KB of list ends.
 // Table taps: 6 chunks, three workgroups with the 17 KB of pulses (32 receivers 201 us;
 // 220 with 4 chunks, 253 with 10 and two workgroups; image by image in LDS tiles 703).
 constexpr int mom_slots(int TL, bool lut) { return lut ? 384 : TL == TILE ? 640 : 448; }

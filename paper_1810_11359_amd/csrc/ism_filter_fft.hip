@@ -729,7 +729,9 @@ static size_t fft_align(size_t v) { return (v + 255) & ~(size_t)255; }
 constexpr int64_t kSegLongRows = 128;
 
 // Segment-block plan: transform size N (512 .. 16384, least work), partitions of
-// c L taps, groups of partitions so that the launch holds about 512 workgroups.
+// c L taps, groups of partitions so that the launch holds up to 512 workgroups, two per
+// CU, in one round (8 microphones, 100 segments of 1600, RIRs of 8000 taps: 47.6 us; up to
+// 1024 57.4, up to 2048 63.4).
 // False when a segment is longer than half the longest transform or the sizes leave
 // a grid.
 bool seg_plan(int n_x, int n_pos, int n_mic, int n_rir, FftPlan &f) {
