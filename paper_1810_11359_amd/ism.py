@@ -7,6 +7,7 @@ library must be built (``python -m paper_1810_11359_amd.build`` or
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from dataclasses import dataclass, field
@@ -512,22 +513,37 @@ def filter_trajectory(x, rirs, stream=None, method: str = "auto", ws=None):
     n_rir] float32 device tensor (ism_simulate output with the trajectory points as
     sources). Returns y [n_mic, n_x + n_rir - 1] on the same device.
     method: "direct" (direct sum), "fft" (partitioned FFT convolution) or
-    "auto"; ws: optional uint8 device tensor of at least filter_workspace_size bytes."""
+    "auto"; ws: optional uint8 device tensor of at least filter_workspace_size bytes.
+    stream: stream of the launches (default: torch's current stream); it has to come
+    after what wrote x and rirs, and any of the tensors may be dropped once the call
+    returns."""
     import torch
 
     if x.dtype != torch.float32 or rirs.dtype != torch.float32 or x.dim() != 1 or rirs.dim() != 3:
         raise IsmError(ISM_E_INVALID_ARG, "filter_trajectory")
-    x = x.contiguous()
-    rirs = rirs.contiguous()
     n_pos, n_mic, n_rir = rirs.shape
     nbytes = filter_workspace_size(x.shape[0], n_pos, n_mic, n_rir, method)
-    if nbytes and (ws is None or ws.numel() < nbytes):
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
-    y = torch.empty((n_mic, x.shape[0] + n_rir - 1), dtype=torch.float32, device=x.device)
-    st = stream if stream is not None else torch.cuda.current_stream()
-    _check(lib().ism_filter_trajectory_ex(x.data_ptr(), int(x.shape[0]), rirs.data_ptr(), int(n_pos), int(n_mic),
+    cur = torch.cuda.current_stream()
+    st = stream if stream is not None else cur
+    side = None
+    if st.cuda_stream != cur.cuda_stream:
+        side = st if isinstance(st, torch.cuda.Stream) else torch.cuda.ExternalStream(st.cuda_stream, device=x.device)
+    # copies, workspace and output of a call on another stream are allocated there, so
+    # that their memory is reused in the order of that stream, not of the current one
+    with contextlib.nullcontext() if side is None else torch.cuda.stream(side):
+        xc, rc = x.contiguous(), rirs.contiguous()
+        w = ws
+        if nbytes and (ws is None or ws.numel() < nbytes):
+            w = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+        y = torch.empty((n_mic, x.shape[0] + n_rir - 1), dtype=torch.float32, device=x.device)
+    if side is not None:
+        y.record_stream(cur)
+        for t in (x, rirs, ws):  # the caller's: not reused before that stream is done with them
+            if t is not None:
+                t.record_stream(side)
+    _check(lib().ism_filter_trajectory_ex(xc.data_ptr(), int(x.shape[0]), rc.data_ptr(), int(n_pos), int(n_mic),
                                           int(n_rir), FILTER_METHODS[method], y.data_ptr(),
-                                          ws.data_ptr() if nbytes else None, nbytes, st.cuda_stream),
+                                          w.data_ptr() if nbytes else None, nbytes, st.cuda_stream),
            "ism_filter_trajectory_ex")
     return y
 
