@@ -1516,8 +1516,9 @@ __global__ __launch_bounds__(item_threads(HALF))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
 accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_all,
                   const AxisOrigin *__restrict__ origin, const int *__restrict__ valid, float *__restrict__ out,
-                  float *__restrict__ part, float *__restrict__ marg, const float *__restrict__ wc) {
-  const uint32_t item = blockIdx.x;
+                  float *__restrict__ part, float *__restrict__ marg, const float *__restrict__ wc,
+                  uint32_t first_item) {
+  const uint32_t item = first_item + blockIdx.x;
   const SingleItem si = decode_item(pa, item);
   // (for a tile past nS, dst is never written: the tile has no own samples)
   float *dst = (si.C == 1) ? out + (size_t)si.rir * ra.n_samples + (size_t)si.tile_id * TL
@@ -1835,13 +1836,29 @@ int launch_tables(const RoomArgs &ra, const float *src, const float *rcv, const 
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// Items [first, first + count) of a call, one workgroup of the given threads each, by as
+// many launches as the limit of 2^32 - 1 threads per launch asks for (16.7 million items
+// of 256 threads).
+template <class Launch>
+static int launch_items(uint32_t n_items, int threads, Launch &&launch) {
+  const uint32_t most = 0xffffffffu / (uint32_t)threads;
+  for (uint32_t first = 0; first < n_items;) {
+    const uint32_t count = min(n_items - first, most);
+    launch(first, count);
+    if (hipGetLastError() != hipSuccess) return -1;
+    first += count;
+  }
+  return 0;
+}
+
 template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
 static int launch_acc_w(const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                         const AxisOrigin *origin, const int *valid, float *out, float *part, float *marg,
                         const float *wc, hipStream_t st) {
-  hipLaunchKernelGGL((accumulate_kernel<WT, TL, HALF, LUT, POLAR, GEN>), dim3(n_items),
-                     dim3(item_threads(HALF)), 0, st, ra, pa, tab, origin, valid, out, part, marg, wc);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  return launch_items(n_items, item_threads(HALF), [&](uint32_t first, uint32_t count) {
+    hipLaunchKernelGGL((accumulate_kernel<WT, TL, HALF, LUT, POLAR, GEN>), dim3(count), dim3(item_threads(HALF)), 0,
+                       st, ra, pa, tab, origin, valid, out, part, marg, wc, first);
+  });
 }
 
 int launch_dump(int wt, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
