@@ -95,9 +95,17 @@ __global__ __launch_bounds__(256) void diffuse_kernel(const float *__restrict__ 
     float v[SPT];
     if (k0 + SPT > k_diff) {
       const u32x4 bits = philox4x32_10(u32x4{(uint32_t)(k0 / 4), (uint32_t)rir, 0u, 0u}, key0, key1);
-      const float amp = level * exp2_split(env.slope * ((double)k0 - env.k0));
+      if (k0 >= k_diff) {
+        const float amp = level * exp2_split(env.slope * ((double)k0 - env.k0));
 #pragma unroll
-      for (int j = 0; j < SPT; ++j) v[j] = logistic_from_bits(bits[j]) * (amp * env.step[j]);
+        for (int j = 0; j < SPT; ++j) v[j] = logistic_from_bits(bits[j]) * (amp * env.step[j]);
+      } else {
+        // the tail begins inside: before it the envelope is above the level, and for T60
+        // of a fraction of a sample beyond FP32
+#pragma unroll
+        for (int j = 0; j < SPT; ++j)
+          v[j] = logistic_from_bits(bits[j]) * (level * exp2_split(env.slope * ((double)max(k0 + j, k_diff) - env.k0)));
+      }
     }
 #pragma unroll
     for (int j = 0; j < SPT; ++j)
