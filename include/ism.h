@@ -319,8 +319,13 @@ int ism_filter_workspace_size(int n_x, int n_pos, int n_mic, int n_rir, int meth
  * of the B-tap partitions of their segment's RIR. Both use real FP32 transforms
  * (half-size complex Stockham transforms in LDS), add in a fixed order and
  * overlap-add the inverse transforms: results are bitwise reproducible and
- * agree with the direct sum to FP32 transform rounding (of a block's norm; a
- * sample or tap that is not finite spreads over the blocks it enters).
+ * agree with the direct sum to FP32 transform rounding, which is relative to
+ * a block's norm: an output far quieter than its block, or zero before the first
+ * sound, carries rounding of about 3e-7 of that norm (the direct sum does not).
+ * A sample or tap that is not finite spreads over the blocks it enters, except
+ * in automatic calls that take segment blocks in place of the direct sum (an
+ * input block would touch more than 4 segments): there only the outputs that use
+ * it are not finite, as in the sum.
  *   ws: ism_filter_workspace_size() bytes (may be NULL for the direct sum). With
  *   less, a call takes fixed blocks if they fit, and auto the direct sum where a
  *   fixed block would touch more than 4 segments.

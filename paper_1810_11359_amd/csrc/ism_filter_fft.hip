@@ -687,11 +687,21 @@ __global__ __launch_bounds__(FftShape<M>::NT) __attribute__((amdgpu_waves_per_eu
 // y[m][n]: sum of z over the blocks that cover n, block by block, group by group; eight
 // reads in flight (one after the other the up to (c + 1) S of them made this launch as
 // long as the transforms of a short signal).
+// CONTAIN (calls that take segment blocks in place of the direct sum): a sample or tap that
+// is not finite makes every output of the blocks it enters so, in a transform; the outputs
+// that come out infinite or NaN are therefore summed directly, each by its wave, so that
+// only those that use such a value keep it (and sums that overflow in a transform alone
+// are finite again). Nothing but a test of the value otherwise.
+template <bool CONTAIN>
 __global__ __launch_bounds__(256) void seg_overlap_kernel(const float *__restrict__ z, int N, int L, int c, int S,
-                                                          int n_blk, float *__restrict__ y, int n_y) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
+                                                          int n_blk, float *__restrict__ y, int n_y,
+                                                          const float *__restrict__ x, int n_x,
+                                                          const float *__restrict__ rir, int n_mic, int n_rir) {
+  const uint32_t at = blockIdx.x * 256u + threadIdx.x;
   const int m = blockIdx.y;
-  if (n >= n_y) return;
+  const bool in = at < (uint32_t)n_y;
+  if (!CONTAIN && !in) return;
+  const int n = in ? (int)at : n_y - 1;  // (lanes past the end repeat the last output)
   const int top = n / L, hi = min(top, n_blk - 1);
   // block top - c ends one sample before the next multiple of L
   const int lo = max(0, top - c + (n - top * L == L - 1 ? 1 : 0));
@@ -717,7 +727,26 @@ __global__ __launch_bounds__(256) void seg_overlap_kernel(const float *__restric
       if (u < left) v += t[u];
     left -= 8;
   }
-  y[(size_t)m * n_y + n] = v;
+  if constexpr (CONTAIN) {
+    const int lane = threadIdx.x & 63;
+    uint64_t bad = __ballot(in && !(__builtin_fabsf(v) <= 3.402823466e38f));
+    while (bad) {
+      const int l = __builtin_ctzll(bad);
+      bad &= bad - 1;
+      const int nn = __builtin_amdgcn_readlane(n, l);
+      // taps whose sample nn - k is in the signal
+      const int k1 = min(n_rir - 1, nn);
+      float s = 0.0f;
+      for (int k = max(0, nn - (n_x - 1)) + lane; k <= k1; k += 64) {
+        const int i = nn - k;
+        s = __builtin_fmaf(x[i], rir[((size_t)(i / L) * n_mic + m) * n_rir + k], s);
+      }
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
+      if (lane == l) v = s;
+    }
+  }
+  if (in) y[(size_t)m * n_y + n] = v;
 }
 
 static size_t fft_align(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -774,7 +803,7 @@ bool seg_plan(int n_x, int n_pos, int n_mic, int n_rir, FftPlan &f) {
 
 template <int M>
 static int launch_seg_m(const float *x, int n_x, const float *rir, int n_mic, int n_rir, float *y, const FftPlan &f,
-                        char *w, hipStream_t st) {
+                        bool contain, char *w, hipStream_t st) {
   typedef FftShape<M> Sh;
   float2 *X = (float2 *)(w + f.off_X);
   float *z = (float *)(w + f.off_z);
@@ -784,8 +813,9 @@ static int launch_seg_m(const float *x, int n_x, const float *rir, int n_mic, in
   hipLaunchKernelGGL(seg_filter_kernel<M>, dim3((rows + Sh::FPB - 1) / Sh::FPB), dim3(Sh::NT), 0, st, rir, n_mic,
                      n_rir, X, n_seg, f.L, f.c, f.P, f.S, f.PS, f.n_out_blocks, rows, z);
   const int n_y = n_x + n_rir - 1;
-  hipLaunchKernelGGL(seg_overlap_kernel, dim3((n_y + 255) / 256, n_mic), dim3(256), 0, st, z, f.N, f.L, f.c, f.S,
-                     f.n_out_blocks, y, n_y);
+  auto *const overlap = contain ? &seg_overlap_kernel<true> : &seg_overlap_kernel<false>;
+  hipLaunchKernelGGL(overlap, dim3((n_y + 255) / 256, n_mic), dim3(256), 0, st, z, f.N, f.L, f.c, f.S,
+                     f.n_out_blocks, y, n_y, x, n_x, rir, n_mic, n_rir);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -843,16 +873,16 @@ static int launch_fft_m(const float *x, int n_x, const float *rir, int n_pos, in
 }
 
 int launch_filter_fft(const float *x, int n_x, const float *rir, int n_pos, int n_mic, int n_rir, float *y,
-                      const FftPlan &f, void *ws, hipStream_t st) {
+                      const FftPlan &f, bool contain, void *ws, hipStream_t st) {
   char *w = (char *)ws;
   if (f.c > 0) {  // segment blocks
     switch (f.B) {
-      case 256: return launch_seg_m<256>(x, n_x, rir, n_mic, n_rir, y, f, w, st);
-      case 512: return launch_seg_m<512>(x, n_x, rir, n_mic, n_rir, y, f, w, st);
-      case 1024: return launch_seg_m<1024>(x, n_x, rir, n_mic, n_rir, y, f, w, st);
-      case 2048: return launch_seg_m<2048>(x, n_x, rir, n_mic, n_rir, y, f, w, st);
-      case 4096: return launch_seg_m<4096>(x, n_x, rir, n_mic, n_rir, y, f, w, st);
-      case 8192: return launch_seg_m<8192>(x, n_x, rir, n_mic, n_rir, y, f, w, st);
+      case 256: return launch_seg_m<256>(x, n_x, rir, n_mic, n_rir, y, f, contain, w, st);
+      case 512: return launch_seg_m<512>(x, n_x, rir, n_mic, n_rir, y, f, contain, w, st);
+      case 1024: return launch_seg_m<1024>(x, n_x, rir, n_mic, n_rir, y, f, contain, w, st);
+      case 2048: return launch_seg_m<2048>(x, n_x, rir, n_mic, n_rir, y, f, contain, w, st);
+      case 4096: return launch_seg_m<4096>(x, n_x, rir, n_mic, n_rir, y, f, contain, w, st);
+      case 8192: return launch_seg_m<8192>(x, n_x, rir, n_mic, n_rir, y, f, contain, w, st);
       default: return -1;
     }
   }

@@ -41,7 +41,7 @@ int launch_filter(const float *x, int n_x, const float *rir, int n_pos, int n_mi
 bool fft_plan(int n_x, int n_pos, int n_mic, int n_rir, int max_pieces, FftPlan &f);
 bool seg_plan(int n_x, int n_pos, int n_mic, int n_rir, FftPlan &f);
 int launch_filter_fft(const float *x, int n_x, const float *rir, int n_pos, int n_mic, int n_rir, float *y,
-                      const FftPlan &f, void *ws, hipStream_t st);
+                      const FftPlan &f, bool contain, void *ws, hipStream_t st);
 }  // namespace ism
 
 using namespace ism;
@@ -1227,7 +1227,9 @@ int ism_filter_trajectory_ex(const float *x, int n_x, const float *rir, int n_po
   if (!seg && !p.fixed) return ism_filter_trajectory(x, n_x, rir, n_pos, n_mic, n_rir, y, stream);
   const FftPlan &f = seg ? p.s : p.f;
   if (!ws || ws_bytes < f.bytes) return ISM_E_WORKSPACE;
-  if (launch_filter_fft(x, n_x, rir, n_pos, n_mic, n_rir, y, f, ws, (hipStream_t)stream) != 0) return ISM_E_DEVICE;
+  // (segment blocks in place of the direct sum keep what is not finite where it belongs)
+  if (launch_filter_fft(x, n_x, rir, n_pos, n_mic, n_rir, y, f, seg && !p.fixed, ws, (hipStream_t)stream) != 0)
+    return ISM_E_DEVICE;
   return ISM_OK;
 }
 
