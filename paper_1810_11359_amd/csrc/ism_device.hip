@@ -250,17 +250,20 @@ constexpr MomCoef<WT> make_mom_coef() {
 // about 20 / W^3, which a polynomial over the whole sample cannot follow. Under
 // caps up to kEdgeCap its values are therefore summed image by image, A e(u) with
 // u the distance inside the end and e the polynomial
-//   e(u) = u^2 (e_0 + e_1 (u - 1/2) + ... + e_7 (u - 1/2)^7)
-// of the windowed sinc there (8e-8 at W = 5, below 1e-9 from W = 8); above, the
-// jump moves the fit by less than 2e-8 and the tap takes the moments too. Windows
-// shorter than kDirectWin vary too fast for the moments: their at most four
-// taps are evaluated and summed image by image.
+//   e(u) = u^2 (e_0 + e_1 (u - 1/2) + ... + e_9 (u - 1/2)^9)
+// of the windowed sinc there (off by at most 1.9e-9, just below W = 6; with two
+// coefficients fewer 2.5e-7 there and 9.5e-8 just below W = 8); above, the
+// jump moves the fit by at most 3.3e-8 (just below W = 65) and the tap takes the
+// moments too. The moments of the other taps are off by at most 7.6e-8 at W = 4,
+// 2.0e-8 from W = 6 and 8.4e-9 from W = 8, where the Hann window still bends
+// within a sample. Windows shorter than kDirectWin vary too fast for the moments:
+// their at most four taps are evaluated and summed image by image.
 constexpr int kEdgeCap = 64;
-constexpr int kEdgeCoef = 8;
+constexpr int kEdgeCoef = 10;
 constexpr float kDirectWin = 4.0f;
 __constant__ ChebFitD<kEdgeCoef> kEdgeFit = make_cheb_fit_d<kEdgeCoef>();
 // Layout of the FP32 constants of a general window of cap WT: c_jp at [p][j - 1]
-// for j = 1 .. WT/2, then e_0 .. e_7, f1, j2 (0: no tap is cut).
+// for j = 1 .. WT/2, then e_0 .. e_9, f1, j2 (0: no tap is cut).
 constexpr int wc_edge(int WT) { return MOM * (WT / 2); }
 static_assert(wc_edge(32) + kEdgeCoef + 2 <= 32 * WC_STRIDE, "window constants");
 
@@ -307,6 +310,7 @@ __device__ double windowed_sinc_d(double v, double W) {
 // FP32 constants of a general window, by one block: the node values of every
 // tap j >= 1 (and of the edge polynomial), then each coefficient.
 __device__ void moment_consts(double W, int WT, float *__restrict__ wc) {
+  static_assert(kEdgeCoef <= MOM, "one row of node values holds either fit");
   __shared__ double y[MAX_WINDOW / 2 + 1][MOM];
   const int half = WT / 2, nt = (int)blockDim.x;
   const int j2 = (int)__builtin_floor(0.5 * W) + 1;
