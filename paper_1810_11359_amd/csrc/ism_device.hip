@@ -612,9 +612,14 @@ typedef float float2v __attribute__((ext_vector_type(2)));
 // Per-wave LDS of the shell enumeration. The candidates of a batch of 64
 // columns are numbered 0 .. total-1, column by column; column lane c holds
 // positions [excl_c, excl_c + n1_c + n2_c), its first run of z indices
-// (z1_c ..) then its second (z2_c ..).
+// (z1_c ..) then its second (z2_c ..). Directional receivers: 16-bit marks (up to 64), so
+// that four workgroups fit a compute unit beside the columns' projections (256 rooms with
+// cardioid receivers in one batch 1.59 ms, three workgroups with 32-bit marks 1.82; 64
+// rooms with a window of 244.5 samples, whose kernel held two, 0.76 and 0.92).
+template <bool POLAR>
 struct EnumLds {
-  uint32_t mark[64];   // per chunk of 64 positions: column lane + 1 where a column starts
+  typedef typename std::conditional<POLAR, uint16_t, uint32_t>::type Mark;
+  Mark mark[64];       // per chunk of 64 positions: column lane + 1 where a column starts
   int4v col_run[64];   // (excl + n1, z1 - excl, z2 - n1 - excl, gain bits): position p
                        // of the column has z index p + (p < excl + n1 ? z1 - excl : z2 - n1 - excl)
   double col_s[64];    // column part of the squared distance
@@ -671,7 +676,7 @@ struct ShellWalk {
   const AxisEntry *__restrict__ ty;
   const AxisRange &ay, &az;
   float gscale;
-  EnumLds &es;
+  EnumLds<POLAR> &es;
   float *__restrict__ col_p;
   uint32_t *__restrict__ col_xy;
   int wv;
@@ -681,7 +686,7 @@ struct ShellWalk {
   int total = 0, excl = 0, cnt = 0;
 
   __device__ __forceinline__ ShellWalk(const ItemGeom &g_, const AxisEntry *tx_, const AxisEntry *ty_,
-                                       const AxisRange &ay_, const AxisRange &az_, float gscale_, EnumLds &es_,
+                                       const AxisRange &ay_, const AxisRange &az_, float gscale_, EnumLds<POLAR> &es_,
                                        float *col_p_, uint32_t *col_xy_, int wv_)
       : g(g_), tx(tx_), ty(ty_), ay(ay_), az(az_), gscale(gscale_), es(es_), col_p(col_p_), col_xy(col_xy_), wv(wv_),
         nx_next(g_.nx_a) {}
@@ -723,7 +728,7 @@ struct ShellWalk {
       // x lane of the batch's first column)
       es.mark[lane] = 0;
       wave_sync();
-      if (ny_cnt > 0 && (uint32_t)(col0 - gc0) < 64u) es.mark[col0 - gc0] = (uint32_t)lane + 1u;
+      if (ny_cnt > 0 && (uint32_t)(col0 - gc0) < 64u) es.mark[col0 - gc0] = (typename EnumLds<POLAR>::Mark)(lane + 1);
       wave_sync();
       const uint64_t before = __ballot(ny_cnt > 0 && col0 <= gc0);
       const uint32_t xm = max(wave_incl_max(es.mark[lane]), 64u - (uint32_t)__builtin_clzll(before | 1u));
@@ -818,11 +823,11 @@ struct ChunkWalk {
   __device__ __forceinline__ ChunkWalk(ShellWalk<POLAR, DUMP, NW> &sw_, const AxisEntry *tz_) : sw(sw_), tz(tz_) {}
   __device__ __forceinline__ void locate(int q0) {
     const int lane = threadIdx.x & 63;
-    EnumLds &es = sw.es;
+    EnumLds<POLAR> &es = sw.es;
     es.mark[lane] = 0;
     wave_sync();
     const int r = sw.excl - q0;
-    if (sw.cnt > 0 && (uint32_t)r < 64u) es.mark[r] = (uint32_t)lane + 1u;
+    if (sw.cnt > 0 && (uint32_t)r < 64u) es.mark[r] = (typename EnumLds<POLAR>::Mark)(lane + 1);
     wave_sync();
     const uint32_t m = max(wave_incl_max(es.mark[lane]), carry);
     carry = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
@@ -960,7 +965,7 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   __shared__ float tile[NQ][LSPAN];
   typedef float2v Rec;
   __shared__ Rec stp[SCAP];  // staged records (stage_record)
-  __shared__ EnumLds es;
+  __shared__ EnumLds<POLAR> es;
   __shared__ float col_p[POLAR ? 64 : 1];  // polar calls: column part of |d| cos(theta)
   __shared__ uint32_t col_xy[DUMP ? 64 : 1];  // enumeration check: column table indices
 
@@ -1171,14 +1176,19 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   constexpr int P = Sh::P, NT = 64 * MOM_WAVES, SLOTS = mom_slots(TL, LUT), NB = Sh::NB;
   constexpr int LM = WT / 2 - 1;
   constexpr uint32_t END = mom_end(TL, LUT);
-  __shared__ union alignas(16) {
+  union alignas(16) Lds {
     MomPool<TL, LUT> pool;
     float conv[Sh::PB * (Sh::PL + Sh::CG)];
     float part[MOM_WAVES][256 * Sh::NCT];
-  } u;
-  __shared__ EnumLds es_all[MOM_WAVES];
+  };
+  __shared__ Lds u;
+  __shared__ EnumLds<POLAR> es_all[MOM_WAVES];
   __shared__ float col_p_all[POLAR ? MOM_WAVES : 1][POLAR ? 64 : 1];  // column part of |d| cos(theta)
   __shared__ alignas(16) int more_all[MOM_WAVES];
+  // the planner and the batch grid count on waves_per_simd workgroups per compute unit (16
+  // bytes for the next item of a batch); the compiler allots registers by what the LDS allows
+  static_assert(sizeof(Lds) + sizeof(es_all) + (POLAR ? sizeof(col_p_all) : 0) + sizeof(more_all) + 16 <=
+                    160 * 1024 / waves_per_simd(false, LUT), "workgroups per compute unit");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1303,7 +1313,7 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   ShellWalk<POLAR, false, MOM_WAVES> sw(g, tx, ty, ay, az, ra.kappa, es_all[wv], col_p_all[POLAR ? wv : 0], nullptr,
                                         wv);
   ChunkWalk<POLAR, false, MOM_WAVES> cw(sw, tz);
-  const EnumLds &es = es_all[wv];
+  const EnumLds<POLAR> &es = es_all[wv];
   const float *const col_p = col_p_all[POLAR ? wv : 0];
   __syncthreads();
   for (;;) {
