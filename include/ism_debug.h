@@ -20,13 +20,14 @@ typedef struct {
   int32_t rir;     /* source * n_rcv + receiver                                      */
   int32_t n[3];    /* lattice index per room axis (x, y, z), Sec. 2.1               */
   int32_t k0;      /* floor(x), x = d fs / c the delay in samples (Eq. (3))          */
-  uint32_t fq;     /* x - k0 rounded to units of 2^-24 (as the table taps use it)    */
+  uint32_t fq;     /* x - k0 rounded to units of 2^-24                               */
   float amp;       /* Eq. (4) amplitude beta_n / (4 pi d_n), FP32                   */
   uint32_t pad;
 } ism_image_record;
 
 /* Runs the image enumeration of ism_simulate_ex (same room, positions, plan and
- * schedule, FP32 mode) without computing taps, and writes one record per image
+ * schedule, FP32 mode) without computing taps, on as many waves per work item as
+ * the taps take (four share an item's columns), and writes one record per image
  * that some work item owns: every lattice image whose integer delay k0 lies in
  * [0, nS + W/2 - 1), i.e. every image with a tap inside the RIR, once.
  *   src, rcv  device float32 [n][3] as for ism_simulate;
@@ -40,6 +41,12 @@ typedef struct {
 int ism_debug_enumerate(const ism_room *room, const float *src, int n_src, const float *rcv, int n_rcv,
                         const ism_schedule *sched, void *records, uint32_t cap, uint32_t *count, void *ws,
                         size_t ws_bytes, void *stream);
+
+/* ism_debug_enumerate for the items of another precision (ISM_FP16: one wave per
+ * item; ISM_FP32_LUT), with the workspace of that precision. */
+int ism_debug_enumerate_ex(const ism_room *room, const float *src, int n_src, const float *rcv, int n_rcv,
+                           int precision, const ism_schedule *sched, void *records, uint32_t cap, uint32_t *count,
+                           void *ws, size_t ws_bytes, void *stream);
 
 #ifdef __cplusplus
 }

@@ -943,17 +943,14 @@ __device__ __forceinline__ void write_invalid(int n_own, float *__restrict__ dst
 // group g adds the taps j = 1 - W/2 + l + LPG m (m < TPL = W / LPG) of its image
 // into the group's own LDS tile. dst receives the own samples of the tile (or a
 // partial tile when C > 1), marg the margins. Accumulation is FP32.
-// DUMP: the enumeration check. No taps; every owned image is written to
-// dump->rec as a DumpRec of RIR rir.
 // GEN: general-mode window (WT is the cap, W = 2 ra.win_hw): the per-lane tap
 // constants come from wc ([WT][WC_STRIDE], written for this window by
 // tables_kernel).
-template <int WT, int NQ, bool POLAR = false, bool DUMP = false, bool GEN = false>
+template <int WT, int NQ, bool POLAR, bool GEN>
 __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
                                          float *__restrict__ dst, float *__restrict__ marg,
-                                         const DumpArgs *dump = nullptr, const int rir = 0,
-                                         const float *__restrict__ wc = nullptr) {
+                                         const float *__restrict__ wc) {
   constexpr int LSPAN = TILE + WT - 1;
   constexpr int LPG = 64 / NQ;          // lanes per image
   constexpr int TPL = WT / LPG;         // taps per lane per step
@@ -967,13 +964,12 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   __shared__ Rec stp[SCAP];  // staged records (stage_record)
   __shared__ EnumLds<POLAR> es;
   __shared__ float col_p[POLAR ? 64 : 1];  // polar calls: column part of |d| cos(theta)
-  __shared__ uint32_t col_xy[DUMP ? 64 : 1];  // enumeration check: column table indices
 
   const int lane = threadIdx.x & 63;
   const int h = lane / LPG, l = lane % LPG;  // image group, lane within it
   const int n_own = min(TILE, ra.n_samples - tile_id * TILE);  // may be <= 0 past nS
   if (!valid) {
-    if constexpr (!DUMP) write_invalid<WT>(n_own, dst, marg, lane, 64);
+    write_invalid<WT>(n_own, dst, marg, lane, 64);
     return;
   }
   const AxisEntry *__restrict__ tx = tab + ra.off[0];
@@ -982,28 +978,26 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   const AxisRange ax = axis_range(ra.lo[0], ra.N[0], ra.inv_period[0], org.e_even[0], org.e_odd[0]);
   const AxisRange ay = axis_range(ra.lo[1], ra.N[1], ra.inv_period[1], org.e_even[1], org.e_odd[1]);
   const AxisRange az = axis_range(ra.lo[2], ra.N[2], ra.inv_period[2], org.e_even[2], org.e_odd[2]);
-  const ItemGeom g = item_geom(ra, ax, DUMP ? ra.tile : TILE, tile_id, C, c);
+  const ItemGeom g = item_geom(ra, ax, TILE, tile_id, C, c);
 
   // per-lane tap constants
   float pc0[TPL];          // FP16 taps: c0 of each tap
   half2_t pq[NPAIR][SPD];  // and c1..c5 of tap pairs (2p, 2p + 1)
-  if constexpr (!DUMP) {
-    auto coef = [&](int k, int jj) {
-      if constexpr (GEN) return wc[WC_STRIDE * jj + k];
-      else return poly_table<WT>().c[k][jj];
-    };
+  auto coef = [&](int k, int jj) {
+    if constexpr (GEN) return wc[WC_STRIDE * jj + k];
+    else return poly_table<WT>().c[k][jj];
+  };
 #pragma unroll
-    for (int m = 0; m < TPL; ++m) pc0[m] = coef(0, l + LPG * m);
+  for (int m = 0; m < TPL; ++m) pc0[m] = coef(0, l + LPG * m);
 #pragma unroll
-    for (int pr = 0; pr < NPAIR; ++pr)
+  for (int pr = 0; pr < NPAIR; ++pr)
 #pragma unroll
-      for (int k = 0; k < SPD; ++k) {
-        const int m0 = 2 * pr, m1 = 2 * pr + 1;
-        const float a = coef(k + 1, l + LPG * m0);
-        const float b = m1 < TPL ? coef(k + 1, l + LPG * m1) : 0.0f;
-        pq[pr][k] = half2_t{(_Float16)a, (_Float16)b};
-      }
-  }
+    for (int k = 0; k < SPD; ++k) {
+      const int m0 = 2 * pr, m1 = 2 * pr + 1;
+      const float a = coef(k + 1, l + LPG * m0);
+      const float b = m1 < TPL ? coef(k + 1, l + LPG * m1) : 0.0f;
+      pq[pr][k] = half2_t{(_Float16)a, (_Float16)b};
+    }
   for (int i = lane; i < NQ * LSPAN; i += 64) (&tile[0][0])[i] = 0.0f;
   float *const th = &tile[h][l];
   // One step: staged image (record P) on this lane group, taps l + LPG m.
@@ -1031,38 +1025,16 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   auto rec = [&](int k) { return stp[k]; };
 
   int ns = 0;  // staged images (wave-uniform)
-  ShellWalk<POLAR, DUMP, 1> sw(g, tx, ty, ay, az, ra.kappa, es, col_p, col_xy, 0);
-  ChunkWalk<POLAR, DUMP, 1> cw(sw, tz);
+  ShellWalk<POLAR, false, 1> sw(g, tx, ty, ay, az, ra.kappa, es, col_p, nullptr, 0);
+  ChunkWalk<POLAR, false, 1> cw(sw, tz);
   while (cw.advance()) {
-    cw.visit([&](bool live, int cl, int nz, float cg, const AxisEntry ez) {
+    cw.visit([&](bool live, int cl, int, float cg, const AxisEntry ez) {
       // lanes = candidates: parameters, then compaction into the stage
       ImageParams p;
       p = image_params<POLAR>(ra, g, es.col_s[cl], cg, ez, POLAR ? col_p[cl] : 0.0f);
       p.ok = p.ok && live;
       const uint64_t okm = __ballot(p.ok);
       const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
-      if constexpr (DUMP) {
-        uint32_t first = 0;
-        if (lane == 0 && okm != 0) first = atomicAdd(dump->count, (uint32_t)__builtin_popcountll(okm));
-        first = (uint32_t)__builtin_amdgcn_readlane((int)first, 0);
-        if (p.ok && first + (uint32_t)rank < dump->cap) {
-          const uint32_t xy = col_xy[cl];
-          // lattice index per table axis, then per room axis (table axis k is room axis perm[k])
-          const int t0 = ra.lo[0] + (int)(xy >> 16), t1 = ra.lo[1] + (int)(xy & 0xffffu), t2 = ra.lo[2] + nz;
-          DumpRec d;
-          d.rir = rir;
-          d.n[0] = ra.perm[0] == 0 ? t0 : (ra.perm[1] == 0 ? t1 : t2);
-          d.n[1] = ra.perm[0] == 1 ? t0 : (ra.perm[1] == 1 ? t1 : t2);
-          d.n[2] = ra.perm[0] == 2 ? t0 : (ra.perm[1] == 2 ? t1 : t2);
-          d.k0 = g.T0 + p.base;
-          d.fq = min((uint32_t)__builtin_rintf(p.fr * 0x1p24f), (1u << 24) - 1u);  // units of 2^-24
-          d.A = p.A;
-          d.pad = 0;
-          dump->rec[first + (uint32_t)rank] = d;
-        }
-        wave_sync();
-        return;
-      }
       if (p.ok) stp[ns + rank] = stage_record(p);
       ns += __builtin_popcountll(okm);
       wave_sync();
@@ -1094,7 +1066,6 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
       wave_sync();
     });
   }
-  if constexpr (DUMP) return;
   if (h < ns) step(stp[h]);  // last images, fewer than NQ
 
   wave_sync();
@@ -1140,6 +1111,7 @@ constexpr int mom_slots(int TL, bool lut) { return lut ? 384 : TL == TILE ? 640 
 // end of a list (slots are linked by byte offset in rec)
 constexpr int mom_end(int TL, bool lut) { return 8 * MOM_WAVES * mom_slots(TL, lut); }
 static_assert(mom_end(TILE, false) < 65536, "16-bit links");
+static_assert(item_threads(false) == 64 * MOM_WAVES && item_threads(true) == 64, "threads per item");
 template <int TL, bool LUT>
 struct MomPool {
   float2v rec[MOM_WAVES * mom_slots(TL, LUT) + 1];  // (t, A), table taps (f, A); the last slot ends every list: (0, 0)
@@ -1464,7 +1436,7 @@ __device__ __forceinline__ void run_item(const RoomArgs &ra, const int tile_id, 
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
                                          float *__restrict__ dst, float *__restrict__ marg,
                                          const float *__restrict__ wc) {
-  if constexpr (HALF) tap_item<WT, 2, POLAR, false, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, nullptr, 0, wc);
+  if constexpr (HALF) tap_item<WT, 2, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
   else moment_item<WT, TL, LUT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
 }
 
@@ -1542,16 +1514,56 @@ accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_al
                                       valid[si.rir] != 0, dst, marg + (size_t)item * WT, wc);
 }
 
-// Enumeration check: the items of a single-room launch, images only.
-template <int WT>
-__global__ __launch_bounds__(64) void enumerate_dump_kernel(RoomArgs ra, PlanArgs pa,
-                                                            const AxisEntry *__restrict__ tab_all,
-                                                            const AxisOrigin *__restrict__ origin,
-                                                            const int *__restrict__ valid, DumpArgs dump) {
-  const SingleItem si = decode_item(pa, blockIdx.x);
+// Enumeration check: the items of a single-room launch, images only, on the walk of the
+// item kernels: shared by the four waves of a workgroup (FP32 and table taps) or on one
+// wave (FP16). Every owned image is written to dump.rec.
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void enumerate_dump_kernel(RoomArgs ra, PlanArgs pa,
+                                                                 const AxisEntry *__restrict__ tab_all,
+                                                                 const AxisOrigin *__restrict__ origin,
+                                                                 const int *__restrict__ valid, DumpArgs dump,
+                                                                 uint32_t first_item) {
+  __shared__ EnumLds<false> es_all[NW];
+  __shared__ uint32_t col_xy_all[NW][64];  // column table indices
+  const SingleItem si = decode_item(pa, first_item + blockIdx.x);
+  if (valid[si.rir] == 0) return;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const AxisEntry *__restrict__ tab = tab_all + (size_t)si.rir * ra.n_tab;
   const AxisOrigin org = origin[si.rir];
-  tap_item<WT, 2, false, true>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
-                                      valid[si.rir] != 0, nullptr, nullptr, &dump, si.rir);
+  const AxisRange ax = axis_range(ra.lo[0], ra.N[0], ra.inv_period[0], org.e_even[0], org.e_odd[0]);
+  const AxisRange ay = axis_range(ra.lo[1], ra.N[1], ra.inv_period[1], org.e_even[1], org.e_odd[1]);
+  const AxisRange az = axis_range(ra.lo[2], ra.N[2], ra.inv_period[2], org.e_even[2], org.e_odd[2]);
+  const ItemGeom g = item_geom(ra, ax, ra.tile, si.tile_id, si.C, si.c);
+  EnumLds<false> &es = es_all[wv];
+  const uint32_t *const col_xy = col_xy_all[wv];
+  ShellWalk<false, true, NW> sw(g, tab + ra.off[0], tab + ra.off[1], ay, az, ra.kappa, es, nullptr, col_xy_all[wv], wv);
+  ChunkWalk<false, true, NW> cw(sw, tab + ra.off[2]);
+  while (cw.advance()) {
+    cw.visit([&](bool live, int cl, int nz, float cg, const AxisEntry ez) {
+      const ImageParams p = image_params<false>(ra, g, es.col_s[cl], cg, ez, 0.0f);
+      const bool ok = live && p.ok;
+      const uint64_t okm = __ballot(ok);
+      const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
+      uint32_t first = 0;
+      if (lane == 0 && okm != 0) first = atomicAdd(dump.count, (uint32_t)__builtin_popcountll(okm));
+      first = (uint32_t)__builtin_amdgcn_readlane((int)first, 0);
+      if (ok && first + (uint32_t)rank < dump.cap) {
+        const uint32_t xy = col_xy[cl];
+        // lattice index per table axis, then per room axis (table axis k is room axis perm[k])
+        const int t0 = ra.lo[0] + (int)(xy >> 16), t1 = ra.lo[1] + (int)(xy & 0xffffu), t2 = ra.lo[2] + nz;
+        DumpRec d;
+        d.rir = si.rir;
+        d.n[0] = ra.perm[0] == 0 ? t0 : (ra.perm[1] == 0 ? t1 : t2);
+        d.n[1] = ra.perm[0] == 1 ? t0 : (ra.perm[1] == 1 ? t1 : t2);
+        d.n[2] = ra.perm[0] == 2 ? t0 : (ra.perm[1] == 2 ? t1 : t2);
+        d.k0 = g.T0 + p.base;
+        d.fq = min((uint32_t)__builtin_rintf(p.fr * 0x1p24f), (1u << 24) - 1u);  // units of 2^-24
+        d.A = p.A;
+        d.pad = 0;
+        dump.rec[first + (uint32_t)rank] = d;
+      }
+    });
+  }
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int n) {
@@ -1875,31 +1887,21 @@ static int launch_acc_w(const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items
   });
 }
 
-int launch_dump(int wt, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
+int launch_dump(bool half, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                 const AxisOrigin *origin, const int *valid, DumpArgs dump, hipStream_t st) {
   hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, dump.count, 0u, 1);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     fprintf(stderr, "ism_debug_enumerate: fill launch: %s\n", hipGetErrorString(e));
     return -1;
   }
-  switch (wt) {
-    case 32: hipLaunchKernelGGL(enumerate_dump_kernel<32>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    case 64: hipLaunchKernelGGL(enumerate_dump_kernel<64>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    case 96: hipLaunchKernelGGL(enumerate_dump_kernel<96>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    case 128: hipLaunchKernelGGL(enumerate_dump_kernel<128>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    case 160: hipLaunchKernelGGL(enumerate_dump_kernel<160>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    case 192: hipLaunchKernelGGL(enumerate_dump_kernel<192>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    case 224: hipLaunchKernelGGL(enumerate_dump_kernel<224>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    case 256: hipLaunchKernelGGL(enumerate_dump_kernel<256>, dim3(n_items), dim3(64), 0, st, ra, pa, tab, origin, valid, dump); break;
-    default: return -2;
-  }
-  e = hipGetLastError();
-  if (e != hipSuccess) {
-    fprintf(stderr, "ism_debug_enumerate: enumeration launch: %s\n", hipGetErrorString(e));
-    return -1;
-  }
-  return 0;
+  auto *const kernel = half ? &enumerate_dump_kernel<1> : &enumerate_dump_kernel<MOM_WAVES>;
+  const int threads = item_threads(half);
+  const int rc = launch_items(n_items, threads, [&](uint32_t first, uint32_t count) {
+    hipLaunchKernelGGL(kernel, dim3(count), dim3(threads), 0, st, ra, pa, tab, origin, valid, dump, first);
+  });
+  if (rc != 0) fprintf(stderr, "ism_debug_enumerate: enumeration launch failed\n");
+  return rc;
 }
 
 bool supported_window(int wt, bool gen) {

@@ -26,7 +26,7 @@ int launch_accumulate(int wt, bool gen, bool half, bool lut, bool polar, const R
 int launch_reduce(const RoomArgs &ra, const PlanArgs &pa, int n_rir, const float *part, const float *marg,
                   float *out, hipStream_t st);
 bool supported_window(int wt, bool gen);
-int launch_dump(int wt, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
+int launch_dump(bool half, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                 const AxisOrigin *origin, const int *valid, DumpArgs dump, hipStream_t st);
 int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *rirs, uint32_t n_rir,
                  const BatchItem *items, const BatchClass *cls, int n_classes, bool half, bool lut, bool polar,
@@ -625,8 +625,15 @@ int ism_simulate_host(const ism_room *room, const float *src, int n_src, const f
 int ism_debug_enumerate(const ism_room *room, const float *src, int n_src, const float *rcv, int n_rcv,
                         const ism_schedule *sched, void *records, uint32_t cap, uint32_t *count, void *ws,
                         size_t ws_bytes, void *stream) {
+  return ism_debug_enumerate_ex(room, src, n_src, rcv, n_rcv, ISM_FP32, sched, records, cap, count, ws, ws_bytes,
+                                stream);
+}
+
+int ism_debug_enumerate_ex(const ism_room *room, const float *src, int n_src, const float *rcv, int n_rcv,
+                           int precision, const ism_schedule *sched, void *records, uint32_t cap, uint32_t *count,
+                           void *ws, size_t ws_bytes, void *stream) {
   Plan p;
-  const int st = make_plan(room, n_src, n_rcv, ISM_FP32, p, sched);
+  const int st = make_plan(room, n_src, n_rcv, precision, p, sched);
   if (st != ISM_OK) return st;
   if (!src || !rcv || !count || (cap > 0 && !records)) return ISM_E_INVALID_ARG;
   if (!ws || ws_bytes < p.ws_bytes) return ISM_E_WORKSPACE;
@@ -640,7 +647,7 @@ int ism_debug_enumerate(const ism_room *room, const float *src, int n_src, const
     return ISM_E_DEVICE;
   }
   DumpArgs d{(DumpRec *)records, count, cap};
-  if (launch_dump(p.wt, p.ra, p.pa, p.n_items, tab, origin, valid, d, s) != 0) return ISM_E_DEVICE;
+  if (launch_dump(p.half, p.ra, p.pa, p.n_items, tab, origin, valid, d, s) != 0) return ISM_E_DEVICE;
   return ISM_OK;
 }
 

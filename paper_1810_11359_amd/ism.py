@@ -43,7 +43,7 @@ EXPORTS = (
     "ism_diffuse_workspace_size", "ism_simulate_diffuse", "ism_simulate_diffuse_timed",
     "ism_filter_trajectory", "ism_workspace_size_ex", "ism_simulate_ex", "ism_simulate_host",
     "ism_batch_workspace_size_ex", "ism_batch_prepare_ex", "ism_simulate_batch", "ism_debug_enumerate",
-    "ism_simulate_noalloc", "ism_filter_workspace_size", "ism_filter_trajectory_ex",
+    "ism_debug_enumerate_ex", "ism_simulate_noalloc", "ism_filter_workspace_size", "ism_filter_trajectory_ex",
 )
 
 
@@ -187,6 +187,9 @@ def lib() -> ctypes.CDLL:
         L.ism_debug_enumerate.restype = ctypes.c_int
         L.ism_debug_enumerate.argtypes = [rp, fp, ctypes.c_int, fp, ctypes.c_int, sp, fp, ctypes.c_uint32, fp, fp,
                                           ctypes.c_size_t, fp]
+        L.ism_debug_enumerate_ex.restype = ctypes.c_int
+        L.ism_debug_enumerate_ex.argtypes = [rp, fp, ctypes.c_int, fp, ctypes.c_int, ctypes.c_int, sp, fp,
+                                             ctypes.c_uint32, fp, fp, ctypes.c_size_t, fp]
         L.ism_filter_workspace_size.restype = ctypes.c_int
         L.ism_filter_workspace_size.argtypes = [ctypes.c_int] * 5 + [ctypes.POINTER(ctypes.c_size_t)]
         L.ism_filter_trajectory_ex.restype = ctypes.c_int
@@ -365,8 +368,9 @@ def simulate_host(room: Room, src, rcv, precision: str = "fp32", out=None, devic
     return out
 
 
-def debug_enumerate(room: Room, src, rcv, schedule: Schedule = None, cap: int = None, device: str = "cuda"):
-    """``ism_debug_enumerate``: every image the work items of ``ism_simulate_ex``
+def debug_enumerate(room: Room, src, rcv, schedule: Schedule = None, cap: int = None, device: str = "cuda",
+                    precision: str = "fp32"):
+    """``ism_debug_enumerate_ex``: every image the work items of ``ism_simulate_ex``
     own, as a numpy array of IMAGE_RECORD (unordered). ``cap`` bounds the
     records fetched (default: the lattice size of all pairs)."""
     import torch
@@ -376,15 +380,16 @@ def debug_enumerate(room: Room, src, rcv, schedule: Schedule = None, cap: int = 
     if cap is None:
         cap = n_rir * int(np.prod(room.n_img))
     rc = room._c()
-    nbytes = workspace_size(room, s.shape[0], r.shape[0], "fp32", schedule)
+    nbytes = workspace_size(room, s.shape[0], r.shape[0], precision, schedule)
     ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
     rec = torch.empty(max(cap, 1) * IMAGE_RECORD.itemsize, dtype=torch.uint8, device=device)
     cnt = torch.zeros(1, dtype=torch.int32, device=device)
     src_d, rcv_d = torch.from_numpy(s).to(device), torch.from_numpy(r).to(device)
     st = torch.cuda.current_stream()
-    _check(lib().ism_debug_enumerate(ctypes.byref(rc), src_d.data_ptr(), s.shape[0], rcv_d.data_ptr(), r.shape[0],
-                                     _sched(schedule), rec.data_ptr(), int(cap), cnt.data_ptr(), ws.data_ptr(),
-                                     nbytes, st.cuda_stream), "ism_debug_enumerate")
+    _check(lib().ism_debug_enumerate_ex(ctypes.byref(rc), src_d.data_ptr(), s.shape[0], rcv_d.data_ptr(), r.shape[0],
+                                        PRECISIONS[precision], _sched(schedule), rec.data_ptr(), int(cap),
+                                        cnt.data_ptr(), ws.data_ptr(), nbytes, st.cuda_stream),
+           "ism_debug_enumerate_ex")
     n = int(cnt.item()) & 0xFFFFFFFF
     if n > cap:
         raise IsmError(ISM_E_TOO_LARGE, f"ism_debug_enumerate: {n} images, cap {cap}")
