@@ -207,13 +207,10 @@ __device__ __forceinline__ float2 root(Tables T, int off, int i) {
   return *reinterpret_cast<const float2 *>(T + off + (uint32_t)(i << 3));
 }
 
-#ifndef PADL
-#define PADL 4
-#endif
 // LDS place of point i: one slot in 17 stays empty, so that the strided writes of the
 // first pass spread over the banks.
-__device__ __forceinline__ constexpr int pad(int i) { return PADL ? i + (i >> (PADL ? PADL : 1)) : i; }
-template <int M> constexpr int kBufLen = PADL ? M + (M >> (PADL ? PADL : 1)) : M;
+__device__ __forceinline__ constexpr int pad(int i) { return i + (i >> 4); }
+template <int M> constexpr int kBufLen = M + M / 16;
 
 // 4-point DFT in place, kernel exp(-+2 pi i t s / 4); TW: points 2 and 3 times w2 and w3.
 template <bool TW>

@@ -295,7 +295,6 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
     ra.N[k] = r->n_img[a];
     ra.off[k] = off;
     off += r->n_img[a];
-    ra.period[k] = (float)(2.0 * r->room[a] * q);
     ra.inv_period[k] = (float)(1.0 / (2.0 * r->room[a] * q));
     split(r->beta[2 * a], ra.beta[2 * k], ra.beta_lo[2 * k]);
     split(r->beta[2 * a + 1], ra.beta[2 * k + 1], ra.beta_lo[2 * k + 1]);
@@ -306,7 +305,6 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   ra.half_w = (float)(W / 2.0);
   ra.win_hw = (float)(p.win / 2.0);
   ra.inv_win = (float)(1.0 / p.win);
-  ra.gen = p.gen ? 1 : 0;
   ra.n_samples = (int)nS;
   ra.k_end = (int)nS + p.wt / 2 - 1;
   ra.n_src = n_src;

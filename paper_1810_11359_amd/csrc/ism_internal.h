@@ -70,12 +70,10 @@ struct RoomArgs {
   float win_hw;            // W / 2, W = t_w fs the window [samples]
   float inv_win;           // 1 / W
   int tile;                // samples per tile (TILE or LONG_TILE)
-  int gen;                 // 1: general-mode window (per-call tap constants, masked taps)
   int n_samples;           // nS
   int k_end;               // nS + W/2 - 1: images with k0 >= k_end add nothing
   int n_src, n_rcv;
-  float period[3];         // 2 L q: displacement step between images of one parity [samples]
-  float inv_period[3];     // 1 / period
+  float inv_period[3];     // 1 / period, 2 L q: displacement step between images of one parity [samples]
   float dir_a, dir_b;      // receiver polar pattern a + b cos(theta) (b = 1 - a); polar calls only
 };
 
