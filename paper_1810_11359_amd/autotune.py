@@ -1,8 +1,8 @@
-"""Work-schedule tuner. Run it on the target GPU:
+"""Work-schedule tuner of the FP16 taps. Run it on the target GPU:
 
     python -m paper_1810_11359_amd.autotune --out paper_1810_11359_amd/csrc/ism_tuning.h
 
-For every window length W (32, 64, 96, 128 samples), tap precision and RIR
+For every window length W (32, 64, 96, 128 samples) and RIR
 length bucket (up to 8192, 32768 and more samples) it times the
 tap-accumulation kernel (HIP events the library records around it) on
 representative single-room and batch workloads of that bucket over a grid of
@@ -12,16 +12,22 @@ candidate of a grid is prepared first and the candidates are timed in
 interleaved rounds once the clocks have settled, since neighbouring
 candidates differ by less than a box drifts over a minute. For the
 persistent batch launches of W = 64 it also picks, on the 1024-room batch, the
-workgroups per SIMD of the grid and the largest item of a batch job. It writes
+waves per SIMD of the grid and the largest item of a batch job. It writes
 the table header the host planner compiles in; rebuild
 the library afterwards. Candidate values reach the library as the call's
 explicit schedule (``ism_schedule``).
 
-The kernel's compile-time shape (256-sample tiles, two images per step,
-seven waves per SIMD) is not a knob here: 512-sample tiles (five waves per
+FP32 and table taps are not tuned here: their items are cut by images, by the
+rules of item_target in ism_host.cpp, whose constants carry the timings that
+they were taken from. The header's rows for them (half = 0) only size their
+workspaces, and with that decide what fits a fixed one: they are constants,
+written back as they are (WORKSPACE_ROWS).
+
+The FP16 kernel's compile-time shape (256-sample tiles, two images per step,
+seven waves per SIMD) is not a knob either: 512-sample tiles (five waves per
 SIMD) and four images per step were built and timed on the 1024-room batch,
 the 32-receiver room, the 64-microphone 48 kHz room and a single RIR, and
-were no faster anywhere (the timings are in the design notes).
+were no faster anywhere.
 """
 from __future__ import annotations
 
@@ -41,6 +47,16 @@ BALANCE = (24576.0, 49152.0, 98304.0, 196608.0)
 NS_BUCKETS = (8192, 32768, 2147483647)   # RIR length buckets (samples), upper bounds
 BATCH_WAVES = (4, 5, 6, 7, 8)
 BATCH_ITEM_TAPS = (1.2e5, 2.5e5, 5.0e5)
+# (window, RIR length bucket): (min_item_taps, balance_items) of the taps that FP32 and
+# table-tap calls size their workspace by; and of their batches, per window, (unused,
+# largest item)
+WORKSPACE_ROWS = {
+    (32, 8192): (240000.0, 196608.0), (32, 32768): (240000.0, 24576.0), (32, 2147483647): (240000.0, 24576.0),
+    (64, 8192): (480000.0, 24576.0), (64, 32768): (120000.0, 49152.0), (64, 2147483647): (240000.0, 196608.0),
+    (96, 8192): (480000.0, 98304.0), (96, 32768): (480000.0, 49152.0), (96, 2147483647): (120000.0, 196608.0),
+    (128, 8192): (240000.0, 24576.0), (128, 32768): (120000.0, 98304.0), (128, 2147483647): (240000.0, 24576.0),
+}
+WORKSPACE_BATCH_ROWS = {64: (6, 500000.0)}
 
 
 class _Events:
@@ -166,9 +182,11 @@ def _score(times, n_loads):
     return {k: math.exp(np.mean([math.log(t / b) for t, b in zip(v, best_each)])) for k, v in times.items()}
 
 
-def tune(reps: int = 3, classes=(32, 64, 96, 128), precisions=("fp32", "fp16"), log=print):
+def tune(reps: int = 3, classes=(32, 64, 96, 128), precisions=("fp16",), log=print):
     """Returns ({(wt, prec, ns_max): (best pair, scores, times, names)},
     {(wt, prec): ((best waves, best batch item taps), scores)})."""
+    if any(p != "fp16" for p in precisions):
+        raise ValueError("only FP16 taps are cut by the tuned values")
     ev = _Events()
     results, waves = {}, {}
     for wt in classes:
@@ -200,15 +218,18 @@ def tune(reps: int = 3, classes=(32, 64, 96, 128), precisions=("fp32", "fp16"), 
 
 def write_header(results, waves, path: str, device: str) -> None:
     lines = [
-        "// Work-item schedule per window length, tap precision and RIR length, read by",
-        "// the host planner, and the grid of the persistent batch launch. Written by",
+        "// Work-item schedule of the FP16 taps (half = 1) per window length and RIR length,",
+        "// read by the host planner, and the grid of their persistent batch launch. Written by",
         f"// paper_1810_11359_amd/autotune.py from timings on the target GPU ({device}).",
+        "// The rows half = 0 are not tuned: FP32 and table-tap calls ask for the workspace of",
+        "// items cut by them (of their batches, of items of at most item_taps), whatever their",
+        "// items, which are cut by images (item_target in ism_host.cpp).",
         "//   min_item_taps  estimated taps of the smallest work item",
         "//   balance_items  items a large call is split into (about eight per",
         "//                  resident wave), which sets the item size of large calls",
         "//   ns_max         the entry applies to RIRs of at most this many samples",
         "//                  (first match in table order)",
-        "//   waves          workgroups per SIMD of a persistent batch launch",
+        "//   waves          waves per SIMD of a persistent batch launch",
         "//   item_taps      largest work item of a batch job (estimated taps)",
         "//",
         "// Score: geometric mean over the bucket's workloads of kernel time relative",
@@ -221,18 +242,20 @@ def write_header(results, waves, path: str, device: str) -> None:
         lines.append(f"// W={wt} {prec} batch: best {best[0]} waves per SIMD, items <= {best[1]:g} taps; "
                      + ", ".join(f"({k}, {it:g}): {v:.4f}" for (k, it), v in sorted(sc.items())))
     lines += ["#pragma once", "", "namespace ism {", "", "struct ItemTuning {",
-              "  int wt;        // window cap in samples", "  int half;      // 1: FP16 taps, 0: FP32 taps",
+              "  int wt;        // window cap in samples", "  int half;      // 1: FP16 taps, 0: workspace of the others",
               "  int ns_max;    // RIR length bucket (samples)", "  double min_item_taps;", "  double balance_items;",
               "};", "", "struct BatchTuning {", "  int wt;", "  int half;", "  int waves;", "  double item_taps;", "};",
               "",
               "constexpr ItemTuning kItemTuning[] = {"]
-    for (wt, prec, ns_max), (best, _, _, _) in sorted(results.items()):
-        lines.append(f"    {{{wt}, {1 if prec == 'fp16' else 0}, {ns_max}, {best[0]:.6g}, {best[1]:.1f}}},")
+    rows = {(wt, 0, ns_max): pair for (wt, ns_max), pair in WORKSPACE_ROWS.items()}
+    rows.update({(wt, 1 if prec == "fp16" else 0, ns_max): r[0] for (wt, prec, ns_max), r in results.items()})
+    for (wt, half, ns_max), pair in sorted(rows.items()):
+        lines.append(f"    {{{wt}, {half}, {ns_max}, {pair[0]:.6g}, {pair[1]:.1f}}},")
     lines += ["};", "", "constexpr BatchTuning kBatchTuning[] = {"]
-    for (wt, prec), (best, _) in sorted(waves.items()):
-        lines.append(f"    {{{wt}, {1 if prec == 'fp16' else 0}, {best[0]}, {best[1]:.6g}}},")
-    if not waves:
-        lines.append("    {0, 0, 0, 0.0},")
+    rows = {(wt, 0): best for wt, best in WORKSPACE_BATCH_ROWS.items()}
+    rows.update({(wt, 1 if prec == "fp16" else 0): r[0] for (wt, prec), r in waves.items()})
+    for (wt, half), best in sorted(rows.items()):
+        lines.append(f"    {{{wt}, {half}, {best[0]}, {best[1]:.6g}}},")
     lines += ["};", "", "}  // namespace ism", ""]
     with open(path, "w") as f:
         f.write("\n".join(lines))

@@ -114,11 +114,11 @@ struct Plan {
   size_t off_valid, off_origin, off_tab, off_part, off_marg, off_wc, off_pos, ws_bytes;
 };
 
-// Work-item size in estimated taps. A launch should hold about balance_items
+// Work-item size in estimated taps. FP16: a launch should hold about balance_items
 // items (some eight per resident wave) so that the largest-first order keeps
 // every CU busy to the end; small calls keep items of min_item_taps. Both come
-// from the tuning table (ism_tuning.h) for the window and precision unless the
-// call's schedule (ism_schedule) replaces them.
+// from the tuning table (ism_tuning.h) for the window unless the call's schedule
+// (ism_schedule) replaces them.
 constexpr double kMinItemTaps = 1.2e5;
 constexpr double kBalanceItems = 49152.0;
 // FP32 items (four waves, a convolution per item) cost images rather than taps.
@@ -137,6 +137,8 @@ constexpr double kMomFullImages = 4000.0;
 constexpr double kMomItems = 1024.0;
 constexpr double kMomMaxImages = 65536.0;
 constexpr double kMomMaxItems = 8192.0;
+// mom: items cut by images; otherwise by taps, the FP16 items (half) or the cut that sizes
+// the workspace of the others.
 double item_target(double total_taps, int wt, bool half, bool mom, int64_t n_samples, const ism_schedule *sc) {
   if (mom) {
     const double few = std::min(kMomFullImages * wt, total_taps / kMomFewItems);
@@ -162,8 +164,8 @@ double item_target(double total_taps, int wt, bool half, bool mom, int64_t n_sam
   return std::max(min_taps, total_taps / balance);
 }
 
-// Largest work item of a batch job (the tuned value of its window class and
-// precision; classes the tuner has no batch workload for take kBatchItemTaps).
+// Largest work item of an FP16 batch job, or of the cut that sizes the workspace of the
+// others (by window class; classes without a row take kBatchItemTaps).
 constexpr double kBatchItemTaps = 2.5e5;
 double batch_item_taps(int wt, bool half) {
   for (const BatchTuning &t : kBatchTuning)
