@@ -373,16 +373,18 @@ int ism_batch_prepare(const ism_job *jobs, int n_jobs, int precision, void *ws, 
 /* Simulates every job of a prepared batch on stream: kernel launches only (no
  * host-device copies, no allocation), so it can be captured in a HIP graph and
  * replayed. Work items are sized from the batch's total work: each job is
- * planned as a single call with item_taps = t = min(B, max(min_item_taps,
- * batch taps / balance_items)) of its class, B the largest item
- * of the class, or, for an FP16 or table-tap batch of less than t taps per
- * resident wave, with its taps over the resident waves (at least 1e4); the
- * schedule's item_taps replaces both when given. A
+ * planned as a single call with an item_taps that follows from the estimated
+ * taps of the whole batch as a single call's does from its own (the schedule's
+ * item_taps replaces it when given). FP16: t = min(B, max(min_item_taps, batch
+ * taps / balance_items)) of its class, B the largest item of the class, or, for
+ * a batch of less than t taps per resident wave, its taps over the resident
+ * waves (at least 1e4). FP32 and table taps: by images per item, doubled for a
+ * job whose items would take more workspace than a cut by taps. A
  * job's result therefore agrees within rounding (<= 1e-6 of the RIR peak)
- * with the job alone and with ism_simulate; it is bitwise that of
- * ism_simulate_ex with the same item_taps, and a batch of one job (of fewer
- * than B x balance_items estimated taps) is bitwise ism_simulate_ex with
- * tail_rounds = 0. */
+ * with the job alone and with ism_simulate. With an item_taps in the schedule it
+ * is bitwise that of ism_simulate_ex with the same schedule, and a batch of one
+ * job (FP16: of fewer than B x balance_items estimated taps) is bitwise
+ * ism_simulate_ex with tail_rounds = 0. */
 int ism_batch_run(const ism_batch *batch, void *stream);
 
 /* ism_batch_run that also records the caller's HIP events ev_start before the

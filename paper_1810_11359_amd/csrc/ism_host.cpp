@@ -221,6 +221,11 @@ bool cut_tiles(const Plan &p, const double *tile_taps, int n_tiles, double targe
   return true;
 }
 
+// Bytes of the partial tiles (where some tile is split) and margins of a call's items.
+size_t item_arrays(uint64_t items, bool split, int tile, int wt) {
+  return align_up(split ? sizeof(float) * (size_t)items * tile : 0) + align_up(sizeof(float) * (size_t)items * wt);
+}
+
 // Estimated taps of the tiles of T samples of one RIR: the owned shell volume over
 // the image density 1 / (Lx Ly Lz) (one image per mirrored room copy), times the
 // window cap. Returns their number; taps has MAX_TILES entries.
@@ -347,9 +352,7 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   // asks for more items than that is cut by taps as well
   uint64_t n_items = 0, n_split = 0;
   size_t ws_arrays = 0;  // bytes of the partial tiles and margins the workspace is sized for
-  auto arrays = [&](uint64_t items, uint64_t split, int T) {
-    return align_up(split > 0 ? sizeof(float) * (size_t)items * T : 0) + align_up(sizeof(float) * (size_t)items * p.wt);
-  };
+  auto arrays = [&](uint64_t items, uint64_t split, int T) { return item_arrays(items, split > 0, T, p.wt); };
   if (mom && !fixed && taper) {
     double tt = item_target(p.total_taps, p.wt, false, false, nS, sched);
     const double res = resident_items(true, false);
@@ -810,9 +813,9 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
   // pass 0: every job's estimated work. The batch fills the device with all
   // of it, so its items are sized from the batch's total as a single call
   // sizes them from its own (max(min_item_taps, total / balance_items) of
-  // the job's class), capped at the tuned batch item size: many small items
-  // cost margin and partial writes, a few large ones leave an uneven tail;
-  // a batch with less work than that per resident wave gets items of its
+  // the job's class), FP16 items capped at the tuned batch item size: many small
+  // items cost margin and partial writes, a few large ones leave an uneven tail;
+  // an FP16 batch with less work than that per resident wave gets items of its
   // work over the resident waves (at least kSmallItemTaps).
   double batch_taps = 0.0;
   for (int j = 0; j < n_jobs; ++j) {
@@ -840,23 +843,28 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
       // spread over them instead (the small-call rule of single calls)
       const double resident = resident_items(p.half, p.lut);
       js.item_taps = !mom && batch_taps < resident * t ? std::min(t, small_call_floor(batch_taps, resident)) : t;
+      size_t ws_arrays = 0;
       if (mom) {  // the workspace is that of items cut by taps, as for single calls
         const double res = resident_items(true, false);
         double tt = std::min(batch_item_taps(p.wt, false),
                              item_target(batch_taps, p.wt, false, false, p.ra.n_samples, sched));
         if (batch_taps < res * tt) tt = std::min(tt, small_call_floor(batch_taps, res));
-        js.item_taps = std::max(js.item_taps, tt);
         uint64_t n = 0, ns = 0;
         double taps[MAX_TILES];
         const int nt = shell_taps(jobs[j].room, p, TILE, taps);
         if (!cut_tiles(p, taps, nt, tt, tt, 0.0, res, nullptr, n, ns)) return ISM_E_TOO_LARGE;
+        ws_arrays = item_arrays(n, ns > 0, TILE, p.wt);
         ws_items += n;
         ws_slots += ns;
         ws_marg += n * (uint64_t)(p.wt / MARG_UNIT);
         ws_red += (uint64_t)nt * p.n_rir;
       }
-      const int stt = make_plan(&jobs[j].room, jobs[j].n_src, jobs[j].n_rcv, precision, p, &js, false);
-      if (stt != ISM_OK) return stt;
+      for (;;) {  // items that outgrow it are doubled, as in a single call
+        const int stt = make_plan(&jobs[j].room, jobs[j].n_src, jobs[j].n_rcv, precision, p, &js, false);
+        if (stt != ISM_OK) return stt;
+        if (!mom || !p.any_split || item_arrays(p.n_items, true, p.ra.tile, p.wt) <= ws_arrays) break;
+        js.item_taps *= 2.0;
+      }
     }
     int cls = -1;
     bool window_known = false;
