@@ -41,8 +41,8 @@ enum {
   ISM_E_UNSUPPORTED = -7     /* valid request the library does not implement       */
 };
 
-/* Arithmetic used for the windowed-sinc taps. Geometry, delays and the
- * accumulation are FP32 in every mode.
+/* Arithmetic used for the windowed-sinc taps. In every mode image distances and
+ * delays are FP64, gains, amplitudes and the accumulation FP32.
  * ISM_FP32_LUT: each tap is read from a table of the windowed sinc of Eq. (6)
  *   at Q = 16 points per sample (Eq. (9), Sec. 3.5) and interpolated linearly
  *   between the two entries around its delay, in FP32. The interpolation
@@ -116,8 +116,8 @@ int ism_count_taps(const ism_room *room, const float *src, int n_src, const floa
 /* ---- Work schedule ------------------------------------------------------------------ */
 
 /* How a call splits its work into work items (units of the accumulation
- * kernel: one RIR, one 256-sample output tile, one slab of the image shell
- * that tile owns). The split changes the summation order, so results agree
+ * kernel: one RIR, one output tile of 256 samples (512 in FP32 calls of few
+ * images per tile), one slab of the image shell that tile owns). The split changes the summation order, so results agree
  * across schedules within rounding (<= 1e-6 of the RIR peak), not bitwise; a
  * given schedule always gives the same bits. NULL means the tuned default. A
  * field left at 0 (tail_rounds: < 0) keeps its default. Used by tuning and
@@ -170,7 +170,10 @@ int ism_simulate_host(const ism_room *room, const float *src, int n_src, const f
  * source or receiver is not strictly inside the room, or whose source equals
  * its receiver, gets an RIR filled with NaN (ism_simulate_host returns a
  * status instead). The summation order is fixed, so repeated calls with the
- * same arguments give bitwise identical results.
+ * same arguments give bitwise identical results. (FP32 and table taps: images of
+ * one integer delay that a wave finds in the same step are added in the order in
+ * which an LDS atomic of the wave serves its lanes. No document states that order;
+ * gfx950 keeps it from call to call, and the tests compare repeated calls.)
  * Asynchronous; out and ws must stay valid until the stream reaches it. */
 int ism_simulate(const ism_room *room, const float *src, int n_src, const float *rcv, int n_rcv,
                  int precision, float *out, void *ws, size_t ws_bytes, void *stream);
