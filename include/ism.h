@@ -382,7 +382,8 @@ int ism_batch_prepare(const ism_job *jobs, int n_jobs, int precision, void *ws, 
  * taps / balance_items)) of its class, B the largest item of the class, or, for
  * a batch of less than t taps per resident wave, its taps over the resident
  * waves (at least 1e4). FP32 and table taps: by images per item, doubled for a
- * job whose items would take more workspace than a cut by taps. A
+ * job whose items would take more workspace than a cut by taps; where tiles hold
+ * few images (up to some hundred in large launches), by taps as FP16. A
  * job's result therefore agrees within rounding (<= 1e-6 of the RIR peak)
  * with the job alone and with ism_simulate. With an item_taps in the schedule it
  * is bitwise that of ism_simulate_ex with the same schedule, and a batch of one

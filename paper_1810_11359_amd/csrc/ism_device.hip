@@ -15,8 +15,9 @@
 //                      (6)): FP32 calls sum the moments of the images' delay
 //                      fractions per integer delay and convolve these with the
 //                      taps' polynomials once per item, table taps (Eq. (9))
-//                      do so with pulses per table phase; FP16 taps are added
-//                      image by image into wave-private FP32 LDS tiles.
+//                      do so with pulses per table phase; FP16 taps, and the others
+//                      in calls of few images per tile, are added image by image into
+//                      wave-private FP32 LDS tiles.
 //   reduce_kernel      sums, in a fixed order, the partial tiles of tiles that
 //                      were split over several work items.
 //
@@ -597,28 +598,30 @@ __device__ __forceinline__ AxisEntry entry_at(const AxisEntry *__restrict__ t, i
 // parameters (delay, amplitude; lanes = images) and adds their taps.
 //
 // FP32 and table-tap consumer (moment_item): images are collected per integer
-// delay and enter through their moments (pulses). FP16 consumer (tap_item, lanes =
-// taps): the candidates' parameters are staged in LDS; each half-wave then
-// takes one staged image per step and its 32 lanes add W/32 taps each into the
-// half-wave's own FP32 tile. All addresses of one step are distinct and
+// delay and enter through their moments (pulses). One-wave consumer (tap_item, lanes =
+// taps; FP16, and the others in calls of few images per tile): the candidates' parameters
+// are staged in LDS; each half-wave (FP32 windows above 96 samples: the wave) then
+// takes one staged image per step and its lanes add its taps into the
+// group's own FP32 tile. All addresses of one step are distinct and
 // consecutive, so there are no bank conflicts and no lost updates; steps of a
-// half-wave reach LDS in program order.
+// group reach LDS in program order.
 //
 // Items end with a fixed-order sum, so results are bitwise reproducible.
 // ---------------------------------------------------------------------------
 typedef int int4v __attribute__((ext_vector_type(4)));
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef float f4v __attribute__((ext_vector_type(4)));
 
 // Per-wave LDS of the shell enumeration. The candidates of a batch of 64
 // columns are numbered 0 .. total-1, column by column; column lane c holds
 // positions [excl_c, excl_c + n1_c + n2_c), its first run of z indices
-// (z1_c ..) then its second (z2_c ..). Directional receivers: 16-bit marks (up to 64), so
-// that four workgroups fit a compute unit beside the columns' projections (256 rooms with
+// (z1_c ..) then its second (z2_c ..). M16 (directional receivers on four waves): 16-bit
+// marks (up to 64), so that four workgroups fit a compute unit beside the columns' projections (256 rooms with
 // cardioid receivers in one batch 1.59 ms, three workgroups with 32-bit marks 1.82; 64
 // rooms with a window of 244.5 samples, whose kernel held two, 0.76 and 0.92).
-template <bool POLAR>
+template <bool M16>
 struct EnumLds {
-  typedef typename std::conditional<POLAR, uint16_t, uint32_t>::type Mark;
+  typedef typename std::conditional<M16, uint16_t, uint32_t>::type Mark;
   Mark mark[64];       // per chunk of 64 positions: column lane + 1 where a column starts
   int4v col_run[64];   // (excl + n1, z1 - excl, z2 - n1 - excl, gain bits): position p
                        // of the column has z index p + (p < excl + n1 ? z1 - excl : z2 - n1 - excl)
@@ -676,7 +679,8 @@ struct ShellWalk {
   const AxisEntry *__restrict__ ty;
   const AxisRange &ay, &az;
   float gscale;
-  EnumLds<POLAR> &es;
+  typedef EnumLds<POLAR && (NW > 1)> Lds;
+  Lds &es;
   float *__restrict__ col_p;
   uint32_t *__restrict__ col_xy;
   int wv;
@@ -686,7 +690,7 @@ struct ShellWalk {
   int total = 0, excl = 0, cnt = 0;
 
   __device__ __forceinline__ ShellWalk(const ItemGeom &g_, const AxisEntry *tx_, const AxisEntry *ty_,
-                                       const AxisRange &ay_, const AxisRange &az_, float gscale_, EnumLds<POLAR> &es_,
+                                       const AxisRange &ay_, const AxisRange &az_, float gscale_, Lds &es_,
                                        float *col_p_, uint32_t *col_xy_, int wv_)
       : g(g_), tx(tx_), ty(ty_), ay(ay_), az(az_), gscale(gscale_), es(es_), col_p(col_p_), col_xy(col_xy_), wv(wv_),
         nx_next(g_.nx_a) {}
@@ -728,7 +732,7 @@ struct ShellWalk {
       // x lane of the batch's first column)
       es.mark[lane] = 0;
       wave_sync();
-      if (ny_cnt > 0 && (uint32_t)(col0 - gc0) < 64u) es.mark[col0 - gc0] = (typename EnumLds<POLAR>::Mark)(lane + 1);
+      if (ny_cnt > 0 && (uint32_t)(col0 - gc0) < 64u) es.mark[col0 - gc0] = (typename Lds::Mark)(lane + 1);
       wave_sync();
       const uint64_t before = __ballot(ny_cnt > 0 && col0 <= gc0);
       const uint32_t xm = max(wave_incl_max(es.mark[lane]), 64u - (uint32_t)__builtin_clzll(before | 1u));
@@ -823,11 +827,12 @@ struct ChunkWalk {
   __device__ __forceinline__ ChunkWalk(ShellWalk<POLAR, DUMP, NW> &sw_, const AxisEntry *tz_) : sw(sw_), tz(tz_) {}
   __device__ __forceinline__ void locate(int q0) {
     const int lane = threadIdx.x & 63;
-    EnumLds<POLAR> &es = sw.es;
+    typedef typename ShellWalk<POLAR, DUMP, NW>::Lds Lds;
+    Lds &es = sw.es;
     es.mark[lane] = 0;
     wave_sync();
     const int r = sw.excl - q0;
-    if (sw.cnt > 0 && (uint32_t)r < 64u) es.mark[r] = (typename EnumLds<POLAR>::Mark)(lane + 1);
+    if (sw.cnt > 0 && (uint32_t)r < 64u) es.mark[r] = (typename Lds::Mark)(lane + 1);
     wave_sync();
     const uint32_t m = max(wave_incl_max(es.mark[lane]), carry);
     carry = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
@@ -938,31 +943,242 @@ __device__ __forceinline__ void write_invalid(int n_own, float *__restrict__ dst
   for (int i = tid; i < WT - 1; i += nthreads) marg[i] = __builtin_nanf("");
 }
 
-// One work item on one wave with FP16 taps (lanes = taps). Each
-// step takes NQ staged images, one per group of LPG = 64 / NQ lanes; lane l of
-// group g adds the taps j = 1 - W/2 + l + LPG m (m < TPL = W / LPG) of its image
-// into the group's own LDS tile. dst receives the own samples of the tile (or a
+// The taps of a general window that its end cuts: e(u) at the left and the right end of
+// the window of an image (t = f - 1/2).
+template <bool EDGE>
+struct EdgeTaps {
+  float ec[EDGE ? kEdgeCoef : 1], f1;
+  __device__ __forceinline__ void load(const float *__restrict__ e) {
+#pragma unroll
+    for (int i = 0; i < kEdgeCoef; ++i) ec[i] = e[i];
+    f1 = e[kEdgeCoef];
+  }
+  __device__ __forceinline__ void taps(float t, float &el, float &er) const {
+    // left end: inside for f < 1 - f1; right end: inside for f > f1
+    const float ul = fmaxf((0.5f - f1) - t, 0.0f), ur = fmaxf(t + (0.5f - f1), 0.0f);
+    const float xl = ul - 0.5f, xr = ur - 0.5f;
+    float pl = ec[kEdgeCoef - 1], pr = ec[kEdgeCoef - 1];
+#pragma unroll
+    for (int i = kEdgeCoef - 2; i >= 0; --i) {
+      pl = __builtin_fmaf(pl, xl, ec[i]);
+      pr = __builtin_fmaf(pr, xr, ec[i]);
+    }
+    el = ul * (ul * pl);
+    er = ur * (ur * pr);
+  }
+};
+// A times the taps j = -1 .. 2 of a window shorter than kDirectWin, at v = j - f (|v| < 2).
+__device__ __forceinline__ void direct_taps(const RoomArgs &ra, float t, float A, float (&w)[4]) {
+  const float f = fminf(fmaxf(t + 0.5f, 0x1p-24f), 0x1.fffffep-1f);
+  const float C2 = A * __builtin_amdgcn_sinf(0.5f * fminf(f, 1.0f - f)) * (float)(0.5 / kPi);
+#pragma unroll
+  for (int j = -1; j <= 2; ++j) {
+    const float v = (float)j - f;
+    const float x = __builtin_fabsf(v) < ra.win_hw
+                        ? __builtin_fmaf(C2, __builtin_amdgcn_cosf(v * ra.inv_win), C2) * __builtin_amdgcn_rcpf(v)
+                        : 0.0f;
+    w[j + 1] = (j & 1) ? x : -x;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Taps of the one-wave items (lanes = taps): groups of LPG lanes, NQ = 64 / LPG images per
+// step. init() loads the lane's constants (l: lane within its group), record() forms the
+// staged record of an image (lanes = images), and step() adds the taps of the record's image
+// to the group's LDS tile (sample k0 + j at base + j - 1 + W/2).
+// ---------------------------------------------------------------------------
+// FP16 taps: lane l adds the taps j = 1 - W/2 + l + LPG m (m < TPL).
+template <int WT, bool GEN>
+struct HalfTaps {
+  static constexpr int LPG = 32, NQ = 64 / LPG;
+  static constexpr int TPL = WT / LPG;          // taps per lane per step
+  static constexpr int NPAIR = (TPL + 1) / 2;   // packed FP16 tap pairs per lane
+  static_assert(WT % LPG == 0, "window must be a multiple of the lanes per image");
+  typedef float2v Rec;
+  float pc0[TPL];          // c0 of each tap
+  half2_t pq[NPAIR][SPD];  // and c1..c5 of tap pairs (2p, 2p + 1)
+  // GEN: general-mode window (WT is the cap, W = 2 ra.win_hw): the constants come from wc
+  // ([WT][WC_STRIDE], written for this window by tables_kernel)
+  __device__ __forceinline__ void init(const RoomArgs &, const float *__restrict__ wc, int l) {
+    auto coef = [&](int k, int jj) {
+      if constexpr (GEN) return wc[WC_STRIDE * jj + k];
+      else return poly_table<WT>().c[k][jj];
+    };
+#pragma unroll
+    for (int m = 0; m < TPL; ++m) pc0[m] = coef(0, l + LPG * m);
+#pragma unroll
+    for (int pr = 0; pr < NPAIR; ++pr)
+#pragma unroll
+      for (int k = 0; k < SPD; ++k) {
+        const int m0 = 2 * pr, m1 = 2 * pr + 1;
+        const float a = coef(k + 1, l + LPG * m0);
+        const float b = m1 < TPL ? coef(k + 1, l + LPG * m1) : 0.0f;
+        pq[pr][k] = half2_t{(_Float16)a, (_Float16)b};
+      }
+  }
+  __device__ __forceinline__ Rec record(const RoomArgs &, const ImageParams &p) const { return stage_record(p); }
+  // The empty asm consumes the record as one value where the step starts,
+  // which keeps its LDS read a single 8-byte read issued ahead.
+  __device__ __forceinline__ void step(const Rec P, float *tile, int l) const {
+    __asm__ volatile("" ::"v"(P));
+    const int b = (int)(__float_as_uint(P.y) & kBaseMask);
+    float *t = tile + l + b;
+    // tap = A (c0 + t q(t)), q in packed FP16 two taps at a time, the
+    // rest in FP32 (t q(t) + c0 as one mixed-precision FMA)
+    const float tf = P.x, A = P.y;
+    const half2_t tt = {(_Float16)tf, (_Float16)tf};
+#pragma unroll
+    for (int pr = 0; pr < NPAIR; ++pr) {
+      half2_t q = pq[pr][SPD - 1];
+#pragma unroll
+      for (int k = SPD - 2; k >= 0; --k) q = __builtin_elementwise_fma(q, tt, pq[pr][k]);
+      const int m0 = 2 * pr, m1 = 2 * pr + 1;
+      t[LPG * m0] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.x, pc0[m0]), t[LPG * m0]);
+      if (m1 < TPL) t[LPG * m1] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.y, pc0[m1]), t[LPG * m1]);
+    }
+  }
+};
+
+// FP32 taps: with the moments' polynomials s_j(t) = E(t^2) + t O(t^2) and s_{1-j}(t) =
+// E - t O, so lane l adds the pairs of taps j and 1 - j, j = 1 + l + LPG m, for 13
+// instructions a pair (W = 32: 32 lanes per image, one tap each, t negated for 1 - j).
+// General windows: the taps that the window's end cuts, or all of a window shorter than
+// kDirectWin, are formed with the record (lanes = images).
+template <int WT, bool GEN>
+struct PairTaps {
+  static constexpr int LPG = WT <= 96 ? 32 : 64, NQ = 64 / LPG;
+  static constexpr bool ONE = WT == 32;  // one tap per lane
+  static constexpr int PPL = ONE ? 1 : (WT / 2 + LPG - 1) / LPG;  // pairs per lane
+  static constexpr bool EDGE = GEN && WT <= kEdgeCap, DIRECT = GEN && WT == 32;
+  struct Plain { float t, A; int base; };
+  // x1, x0: A times the cut taps j2 and 1 - j2; windows shorter than kDirectWin: taps 1
+  // and 0, t and A then hold taps 2 and -1
+  struct Cut { float t, A; int base; float x1, x0; };
+  typedef typename std::conditional<EDGE, Cut, Plain>::type Rec;
+  float c[PPL][MOM];
+  float sign;  // ONE: of t
+  int at[2];   // offsets of the lane's first pair (ONE: its tap) from the base
+  int cut;     // 1: this lane's pair is cut; 2: it is taps 2 and -1 of a short window
+  const float *edge;
+  __device__ __forceinline__ void init(const RoomArgs &ra, const float *__restrict__ wc, int l) {
+    const bool direct = DIRECT && 2.0f * ra.win_hw < kDirectWin;
+    const int first = ONE ? l & 15 : l;  // pair: j = 1 + first
+    sign = ONE && l >= 16 ? -1.0f : 1.0f;
+    at[0] = WT / 2 + first;
+    at[1] = WT / 2 - 1 - first;
+    if (ONE && l >= 16) at[0] = at[1];
+#pragma unroll
+    for (int m = 0; m < PPL; ++m) {
+      const int q = min(first + LPG * m, WT / 2 - 1);
+#pragma unroll
+      for (int p = 0; p < MOM; ++p) {
+        if constexpr (GEN) c[m][p] = direct ? 0.0f : wc[p * (WT / 2) + q];
+        else c[m][p] = mom_table<WT>().c[p][(uint32_t)(WT / 2 + 14 - q)];
+      }
+    }
+    cut = 0;
+    if constexpr (EDGE) {
+      edge = wc + wc_edge(WT);
+      if (DIRECT && direct) cut = first < 2 ? first + 1 : 0;
+      else if (first + 1 == (int)edge[kEdgeCoef + 1]) cut = 1;
+    }
+  }
+  __device__ __forceinline__ Rec record(const RoomArgs &ra, const ImageParams &p) const {
+    const float t = p.fr - 0.5f;
+    if constexpr (EDGE) {
+      if (DIRECT && 2.0f * ra.win_hw < kDirectWin) {
+        float w[4];
+        direct_taps(ra, t, p.A, w);
+        return Rec{w[3], w[0], p.base, w[2], w[1]};
+      }
+      EdgeTaps<true> et;
+      et.load(edge);
+      float el, er;
+      et.taps(t, el, er);
+      return Rec{t, p.A, p.base, p.A * er, p.A * el};
+    } else {
+      return Rec{t, p.A, p.base};
+    }
+  }
+  __device__ __forceinline__ void step(const Rec &P, float *tile, int l) const {
+    const float t = P.t, A = P.A, u = t * t;
+#pragma unroll
+    for (int m = 0; m < PPL; ++m) {
+      float e = c[m][8], d = c[m][9];
+#pragma unroll
+      for (int p = 6; p >= 0; p -= 2) {
+        e = __builtin_fmaf(e, u, c[m][p]);
+        d = __builtin_fmaf(d, u, c[m][p + 1]);
+      }
+      float x1 = 0.0f, x0 = 0.0f;
+      if constexpr (EDGE) {
+        x1 = cut == 1 ? P.x1 : cut == 2 ? t : 0.0f;
+        x0 = cut == 1 ? P.x0 : cut == 2 ? A : 0.0f;
+      }
+      float *const o1 = tile + (P.base + at[0] + LPG * m);
+      if constexpr (ONE) {
+        const float v = __builtin_fmaf(A, __builtin_fmaf(sign * t, d, e), *o1);
+        *o1 = EDGE ? v + (sign > 0.0f ? x1 : x0) : v;
+      } else if (PPL * LPG == WT / 2 || l + LPG * m < WT / 2) {
+        float *const o0 = tile + (P.base + at[1] - LPG * m);
+        d *= t;
+        const float v1 = __builtin_fmaf(A, e + d, *o1), v0 = __builtin_fmaf(A, e - d, *o0);
+        *o1 = EDGE ? v1 + x1 : v1;
+        *o0 = EDGE ? v0 + x0 : v0;
+      }
+    }
+  }
+};
+
+// Table taps (Eq. (9)): the image's two pulses, A (1 - fr) at phase fl and A fr at
+// fl + 1, times the table's points; lane l adds the taps of HalfTaps.
+template <int WT>
+struct TableTaps {
+  static constexpr int LPG = 32, NQ = 64 / LPG, TPL = WT / LPG;
+  typedef struct { f4v a; } Rec;  // pulses, base, phase
+  int first;  // the lane's first tap in a row of the table
+  __device__ __forceinline__ void init(const RoomArgs &, const float *__restrict__, int l) { first = WT + 14 - l; }
+  __device__ __forceinline__ Rec record(const RoomArgs &, const ImageParams &p) const {
+    const float x = p.fr * (float)kLutQ, fl = fminf(floorf(x), (float)(kLutQ - 1));
+    const float hi = p.A * (x - fl);
+    return Rec{f4v{p.A - hi, hi, __int_as_float(p.base), __int_as_float((int)fl)}};
+  }
+  __device__ __forceinline__ void step(const Rec &P, float *tile, int l) const {
+    const float *const row = &lut_table<WT>().c[0][0] + (uint32_t)(__float_as_int(P.a.w) * (WT + 32) + first);
+    float *const t = tile + l + __float_as_int(P.a.z);
+    float c0[TPL], c1[TPL];
+#pragma unroll
+    for (int m = 0; m < TPL; ++m) {
+      c0[m] = row[-LPG * m];
+      c1[m] = row[WT + 32 - LPG * m];
+    }
+#pragma unroll
+    for (int m = 0; m < TPL; ++m)
+      t[LPG * m] = __builtin_fmaf(P.a.x, c0[m], __builtin_fmaf(P.a.y, c1[m], t[LPG * m]));
+  }
+};
+
+// One work item on one wave: FP16 taps, and the other taps in calls of few images per tile
+// (few_images in ism_host.cpp). Bound by the taps' VALU and LDS updates where there are
+// images and by the item's chain of table reads where there are none; 24 items share a
+// compute unit (FP16 28), so a call of many small items has six times as many in flight as
+// with moments: 1024 RIRs of 4800 samples, direct path alone 36 us (moments 149), lattice of
+// 15 per axis 122 (172); table taps 36 (312) and 126 (342). dst receives the own samples of the tile (or a
 // partial tile when C > 1), marg the margins. Accumulation is FP32.
-// GEN: general-mode window (WT is the cap, W = 2 ra.win_hw): the per-lane tap
-// constants come from wc ([WT][WC_STRIDE], written for this window by
-// tables_kernel).
-template <int WT, int NQ, bool POLAR, bool GEN>
+template <int WT, class Taps, bool POLAR>
 __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
                                          float *__restrict__ dst, float *__restrict__ marg,
                                          const float *__restrict__ wc) {
   constexpr int LSPAN = TILE + WT - 1;
-  constexpr int LPG = 64 / NQ;          // lanes per image
-  constexpr int TPL = WT / LPG;         // taps per lane per step
-  constexpr int NPAIR = (TPL + 1) / 2;  // packed FP16 tap pairs per lane
+  constexpr int NQ = Taps::NQ, LPG = Taps::LPG;  // images per step, lanes per image
   // staged images: up to 64 new + NQ - 1 carried, + the read-ahead of a step
   constexpr int SCAP = 64 + 3 * NQ;
-  static_assert(WT % LPG == 0, "window must be a multiple of the lanes per image");
 
   __shared__ float tile[NQ][LSPAN];
-  typedef float2v Rec;
-  __shared__ Rec stp[SCAP];  // staged records (stage_record)
-  __shared__ EnumLds<POLAR> es;
+  typedef typename Taps::Rec Rec;
+  __shared__ Rec stp[SCAP];  // staged records
+  __shared__ EnumLds<false> es;
   __shared__ float col_p[POLAR ? 64 : 1];  // polar calls: column part of |d| cos(theta)
 
   const int lane = threadIdx.x & 63;
@@ -980,48 +1196,12 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
   const AxisRange az = axis_range(ra.lo[2], ra.N[2], ra.inv_period[2], org.e_even[2], org.e_odd[2]);
   const ItemGeom g = item_geom(ra, ax, TILE, tile_id, C, c);
 
-  // per-lane tap constants
-  float pc0[TPL];          // FP16 taps: c0 of each tap
-  half2_t pq[NPAIR][SPD];  // and c1..c5 of tap pairs (2p, 2p + 1)
-  auto coef = [&](int k, int jj) {
-    if constexpr (GEN) return wc[WC_STRIDE * jj + k];
-    else return poly_table<WT>().c[k][jj];
-  };
-#pragma unroll
-  for (int m = 0; m < TPL; ++m) pc0[m] = coef(0, l + LPG * m);
-#pragma unroll
-  for (int pr = 0; pr < NPAIR; ++pr)
-#pragma unroll
-    for (int k = 0; k < SPD; ++k) {
-      const int m0 = 2 * pr, m1 = 2 * pr + 1;
-      const float a = coef(k + 1, l + LPG * m0);
-      const float b = m1 < TPL ? coef(k + 1, l + LPG * m1) : 0.0f;
-      pq[pr][k] = half2_t{(_Float16)a, (_Float16)b};
-    }
+  Taps taps;
+  taps.init(ra, wc, l);
   for (int i = lane; i < NQ * LSPAN; i += 64) (&tile[0][0])[i] = 0.0f;
-  float *const th = &tile[h][l];
-  // One step: staged image (record P) on this lane group, taps l + LPG m.
-  // The empty asm consumes the record as one value where the step starts,
-  // which keeps its LDS read a single 8-byte read issued ahead.
-  auto step = [&](const Rec P) {
-    __asm__ volatile("" ::"v"(P));
-    const int b = (int)(__float_as_uint(P.y) & kBaseMask);
-    float *t = th + b;
-    // tap = A (c0 + t q(t)), q in packed FP16 two taps at a time, the
-    // rest in FP32 (t q(t) + c0 as one mixed-precision FMA)
-    const float tf = P.x, A = P.y;
-    const half2_t tt = {(_Float16)tf, (_Float16)tf};
-#pragma unroll
-    for (int pr = 0; pr < NPAIR; ++pr) {
-      half2_t q = pq[pr][SPD - 1];
-#pragma unroll
-      for (int k = SPD - 2; k >= 0; --k) q = __builtin_elementwise_fma(q, tt, pq[pr][k]);
-      const int m0 = 2 * pr, m1 = 2 * pr + 1;
-      t[LPG * m0] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.x, pc0[m0]), t[LPG * m0]);
-      if (m1 < TPL) t[LPG * m1] = __builtin_fmaf(A, __builtin_fmaf(tf, (float)q.y, pc0[m1]), t[LPG * m1]);
-    }
-  };
-  // staged record k (read as one 8-byte access: see step)
+  float *const th = tile[h];
+  auto step = [&](const Rec &P) { taps.step(P, th, l); };
+  // staged record k
   auto rec = [&](int k) { return stp[k]; };
 
   int ns = 0;  // staged images (wave-uniform)
@@ -1035,7 +1215,7 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
       p.ok = p.ok && live;
       const uint64_t okm = __ballot(p.ok);
       const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
-      if (p.ok) stp[ns + rank] = stage_record(p);
+      if (p.ok) stp[ns + rank] = taps.record(ra, p);
       ns += __builtin_popcountll(okm);
       wave_sync();
       // lanes = taps: NQ staged images per step, one per lane group; the next
@@ -1057,10 +1237,25 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
       // not overlap when np > 0)
       const int rem = ns - NQ * np;
       if (np > 0 && rem > 0) {
-        Rec P{};
-        if (lane < rem) P = stp[NQ * np + lane];
-        wave_sync();
-        if (lane < rem) stp[lane] = P;
+        if constexpr (std::is_class<Rec>::value) {  // (word by word: a struct would go through memory)
+          typedef uint32_t __attribute__((may_alias)) Word;
+          const Word *const from = reinterpret_cast<const Word *>(&stp[NQ * np + lane]);
+          uint32_t w[sizeof(Rec) / 4] = {};
+          if (lane < rem) {
+#pragma unroll
+            for (int i = 0; i < (int)(sizeof(Rec) / 4); ++i) w[i] = from[i];
+          }
+          wave_sync();
+          if (lane < rem) {
+#pragma unroll
+            for (int i = 0; i < (int)(sizeof(Rec) / 4); ++i) reinterpret_cast<Word *>(&stp[lane])[i] = w[i];
+          }
+        } else {
+          Rec P{};
+          if (lane < rem) P = stp[NQ * np + lane];
+          wave_sync();
+          if (lane < rem) stp[lane] = P;
+        }
       }
       ns = rem;
       wave_sync();
@@ -1100,8 +1295,6 @@ __device__ __forceinline__ void tap_item(const RoomArgs &ra, const int tile_id, 
 // quarter of the k'. Planes are kept at x + x / 16 so that the 16 columns read
 // different banks.
 // ---------------------------------------------------------------------------
-typedef float f4v __attribute__((ext_vector_type(4)));
-
 constexpr int MOM_WAVES = 4;
 // Pool slots per wave: 10 chunks of 64 positions. With these a workgroup takes 40 KB
 // of LDS and four fit a compute unit: 1024-room batch 6.43 ms, 64 microphones at
@@ -1113,7 +1306,7 @@ constexpr int mom_slots(int TL, bool lut) { return lut ? 384 : TL == TILE ? 640 
 // end of a list (slots are linked by byte offset in rec)
 constexpr int mom_end(int TL, bool lut) { return 8 * MOM_WAVES * mom_slots(TL, lut); }
 static_assert(mom_end(TILE, false) < 65536, "16-bit links");
-static_assert(item_threads(false) == 64 * MOM_WAVES && item_threads(true) == 64, "threads per item");
+static_assert(item_threads(ITEM_MOMENTS) == 64 * MOM_WAVES && item_threads(ITEM_FP16) == 64, "threads per item");
 template <int TL, bool LUT>
 struct MomPool {
   float2v rec[MOM_WAVES * mom_slots(TL, LUT) + 1];  // (t, A), table taps (f, A); the last slot ends every list: (0, 0)
@@ -1162,7 +1355,7 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   // the planner and the batch grid count on waves_per_simd workgroups per compute unit (16
   // bytes for the next item of a batch); the compiler allots registers by what the LDS allows
   static_assert(sizeof(Lds) + sizeof(es_all) + (POLAR ? sizeof(col_p_all) : 0) + sizeof(more_all) + 16 <=
-                    160 * 1024 / waves_per_simd(false, LUT), "workgroups per compute unit");
+                    160 * 1024 / waves_per_simd(ITEM_MOMENTS, LUT), "workgroups per compute unit");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1197,13 +1390,8 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
     u.pool.next[END / 8] = (uint16_t)END;
   }
   const bool direct = DIRECT && 2.0f * ra.win_hw < kDirectWin;
-  // edge polynomial (EDGE): coefficients, f1 and whether a tap is cut
-  float ec[EDGE ? kEdgeCoef : 1], f1 = 1.0f;
-  if constexpr (EDGE) {
-#pragma unroll
-    for (int i = 0; i < kEdgeCoef; ++i) ec[i] = wc[wc_edge(WT) + i];
-    f1 = wc[wc_edge(WT) + kEdgeCoef];
-  }
+  EdgeTaps<EDGE> et;
+  if constexpr (EDGE) et.load(wc + wc_edge(WT));
 
   // one record into the sums of this thread's delay b
   auto add = [&](const int b, const float2v r, auto taps) {
@@ -1217,17 +1405,11 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
       return;
     }
     if constexpr (decltype(taps)::value) {
-      // tap j at v = j - f, j = -1 .. 2 (|v| < 2), into sum j + 1
-      const float f = fminf(fmaxf(t + 0.5f, 0x1p-24f), 0x1.fffffep-1f);
-      const float C2 = A * __builtin_amdgcn_sinf(0.5f * fminf(f, 1.0f - f)) * (float)(0.5 / kPi);
+      // into sum j + 1
+      float w[4];
+      direct_taps(ra, t, A, w);
 #pragma unroll
-      for (int j = -1; j <= 2; ++j) {
-        const float v = (float)j - f;
-        const float w = __builtin_fabsf(v) < ra.win_hw
-                            ? __builtin_fmaf(C2, __builtin_amdgcn_cosf(v * ra.inv_win), C2) * __builtin_amdgcn_rcpf(v)
-                            : 0.0f;
-        m[b][j + 1] += (j & 1) ? w : -w;
-      }
+      for (int j = 0; j < 4; ++j) m[b][j] += w[j];
       return;
     }
     const float At = A * t, t2 = t * t, t4 = t2 * t2, t6 = t4 * t2, t8 = t4 * t4;
@@ -1242,17 +1424,10 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
     m[b][8] = __builtin_fmaf(A, t8, m[b][8]);
     m[b][9] = __builtin_fmaf(At, t8, m[b][9]);
     if constexpr (EDGE) {
-      // left end: inside for f < 1 - f1; right end: inside for f > f1
-      const float ul = fmaxf((0.5f - f1) - t, 0.0f), ur = fmaxf(t + (0.5f - f1), 0.0f);
-      const float xl = ul - 0.5f, xr = ur - 0.5f;
-      float pl = ec[kEdgeCoef - 1], pr = ec[kEdgeCoef - 1];
-#pragma unroll
-      for (int i = kEdgeCoef - 2; i >= 0; --i) {
-        pl = __builtin_fmaf(pl, xl, ec[i]);
-        pr = __builtin_fmaf(pr, xr, ec[i]);
-      }
-      m[b][MOM] = __builtin_fmaf(A * ul, ul * pl, m[b][MOM]);
-      m[b][MOM + 1] = __builtin_fmaf(A * ur, ur * pr, m[b][MOM + 1]);
+      float el, er;
+      et.taps(t, el, er);
+      m[b][MOM] = __builtin_fmaf(A, el, m[b][MOM]);
+      m[b][MOM + 1] = __builtin_fmaf(A, er, m[b][MOM + 1]);
     }
   };
   char *const rec0 = reinterpret_cast<char *>(u.pool.rec), *const next0 = reinterpret_cast<char *>(u.pool.next);
@@ -1432,14 +1607,20 @@ __device__ __forceinline__ void moment_item(const RoomArgs &ra, const int tile_i
   }
 }
 
-// The item function of a kernel's precision.
-template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
+// The item function of a kernel's item kind.
+template <int WT, int TL, int KIND, bool LUT, bool POLAR, bool GEN>
 __device__ __forceinline__ void run_item(const RoomArgs &ra, const int tile_id, const int C, const int c,
                                          const AxisEntry *__restrict__ tab, const AxisOrigin &org, const bool valid,
                                          float *__restrict__ dst, float *__restrict__ marg,
                                          const float *__restrict__ wc) {
-  if constexpr (HALF) tap_item<WT, 2, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
-  else moment_item<WT, TL, LUT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
+  if constexpr (KIND == ITEM_FP16)
+    tap_item<WT, HalfTaps<WT, GEN>, POLAR>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
+  else if constexpr (KIND == ITEM_FEW && LUT)
+    tap_item<WT, TableTaps<WT>, POLAR>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
+  else if constexpr (KIND == ITEM_FEW)
+    tap_item<WT, PairTaps<WT, GEN>, POLAR>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
+  else
+    moment_item<WT, TL, LUT, POLAR, GEN>(ra, tile_id, C, c, tab, org, valid, dst, marg, wc);
 }
 
 // The 16 dispatch positions of plan block blk on lanes 0 .. 15: chunks per RIR, and the
@@ -1499,9 +1680,9 @@ __device__ __forceinline__ SingleItem decode_item(const PlanArgs &pa, uint32_t i
   return si;
 }
 
-template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
-__global__ __launch_bounds__(item_threads(HALF))
-__attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
+template <int WT, int TL, int KIND, bool LUT, bool POLAR, bool GEN>
+__global__ __launch_bounds__(item_threads(KIND))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd(KIND, LUT)))) void
 accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_all,
                   const AxisOrigin *__restrict__ origin, const int *__restrict__ valid, float *__restrict__ out,
                   float *__restrict__ part, float *__restrict__ marg, const float *__restrict__ wc,
@@ -1512,7 +1693,7 @@ accumulate_kernel(RoomArgs ra, PlanArgs pa, const AxisEntry *__restrict__ tab_al
   float *dst = (si.C == 1) ? out + (size_t)si.rir * ra.n_samples + (size_t)si.tile_id * TL
                            : part + (size_t)item * TL;
   const AxisOrigin org = origin[si.rir];
-  run_item<WT, TL, HALF, LUT, POLAR, GEN>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
+  run_item<WT, TL, KIND, LUT, POLAR, GEN>(ra, si.tile_id, si.C, si.c, tab_all + (size_t)si.rir * ra.n_tab, org,
                                       valid[si.rir] != 0, dst, marg + (size_t)item * WT, wc);
 }
 
@@ -1579,14 +1760,14 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int n) {
 // run sets to the grid size before the launch), until the list is exhausted.
 // Without a queue (queue == null) a workgroup takes every gridDim.x-th item.
 // Every item names its job; the job table carries the room.
-template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
-__global__ __launch_bounds__(item_threads(HALF))
-__attribute__((amdgpu_waves_per_eu(waves_per_simd(HALF, LUT)))) void
+template <int WT, int TL, int KIND, bool LUT, bool POLAR, bool GEN>
+__global__ __launch_bounds__(item_threads(KIND))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd(KIND, LUT)))) void
 accumulate_batch_kernel(
     const JobDev *__restrict__ jobs, const BatchItem *__restrict__ items, uint32_t n_items, uint32_t *queue,
     const AxisEntry *__restrict__ tab_all, const AxisOrigin *__restrict__ origin, const int *__restrict__ valid,
     float *__restrict__ part, float *__restrict__ marg) {
-  constexpr bool MULTI = item_threads(HALF) > 64;
+  constexpr bool MULTI = item_threads(KIND) > 64;
   const int lane = threadIdx.x & 63;
   __shared__ uint32_t next_item;
   uint32_t item = blockIdx.x;
@@ -1601,7 +1782,7 @@ accumulate_batch_kernel(
     float *dst = (it.slot == 0xffffffffu) ? jb.out + (size_t)it.rir * ra.n_samples + (size_t)it.tile * TL
                                           : part + (size_t)it.slot * TILE;
     const AxisOrigin org = origin[grir];
-    run_item<WT, TL, HALF, LUT, POLAR, GEN>(ra, it.tile, it.chunks, it.chunk,
+    run_item<WT, TL, KIND, LUT, POLAR, GEN>(ra, it.tile, it.chunks, it.chunk,
                                         tab_all + jb.tab_base + (size_t)it.rir * ra.n_tab, org, valid[grir] != 0, dst,
                                         marg + (size_t)it.mslot * MARG_UNIT, jb.wc);
     if (queue) {
@@ -1879,12 +2060,12 @@ static int launch_items(uint32_t n_items, int threads, Launch &&launch) {
   return 0;
 }
 
-template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, int KIND, bool LUT, bool POLAR, bool GEN>
 static int launch_acc_w(const RoomArgs &ra, const PlanArgs &pa, uint32_t n_items, const AxisEntry *tab,
                         const AxisOrigin *origin, const int *valid, float *out, float *part, float *marg,
                         const float *wc, hipStream_t st) {
-  return launch_items(n_items, item_threads(HALF), [&](uint32_t first, uint32_t count) {
-    hipLaunchKernelGGL((accumulate_kernel<WT, TL, HALF, LUT, POLAR, GEN>), dim3(count), dim3(item_threads(HALF)), 0,
+  return launch_items(n_items, item_threads(KIND), [&](uint32_t first, uint32_t count) {
+    hipLaunchKernelGGL((accumulate_kernel<WT, TL, KIND, LUT, POLAR, GEN>), dim3(count), dim3(item_threads(KIND)), 0,
                        st, ra, pa, tab, origin, valid, out, part, marg, wc, first);
   });
 }
@@ -1898,7 +2079,7 @@ int launch_dump(bool half, const RoomArgs &ra, const PlanArgs &pa, uint32_t n_it
     return -1;
   }
   auto *const kernel = half ? &enumerate_dump_kernel<1> : &enumerate_dump_kernel<MOM_WAVES>;
-  const int threads = item_threads(half);
+  const int threads = item_threads(half ? ITEM_FP16 : ITEM_MOMENTS);
   const int rc = launch_items(n_items, threads, [&](uint32_t first, uint32_t count) {
     hipLaunchKernelGGL(kernel, dim3(count), dim3(threads), 0, st, ra, pa, tab, origin, valid, dump, first);
   });
@@ -1913,27 +2094,31 @@ bool supported_window(int wt, bool gen) {
 
 // Calls the kernel instance of a window class: exact windows W in {32, 64,
 // 96, 128} with every tap mode, general-mode caps 32 .. 256 with FP32 or FP16
-// taps; FP32 taps with tiles of TILE or LONG_TILE samples. fn is a generic lambda
-// taking the template arguments as values.
+// taps; FP32 taps with tiles of TILE or LONG_TILE samples, FP32 and table taps also on
+// one-wave items (kind ITEM_FEW). fn is a generic lambda taking the template arguments as
+// values.
 template <class Fn>
-static int dispatch_window(int wt, int tile, bool gen, bool half, bool lut, bool polar, Fn &&fn) {
-  if ((half && lut) || (tile != TILE && (half || lut || tile != LONG_TILE))) return -2;
-  using S = std::integral_constant<int, TILE>;
-  using LT = std::integral_constant<int, LONG_TILE>;
-  auto by_mode = [&](auto W, auto G) -> int {
-    constexpr bool kG = decltype(G)::value;
-    using F = std::false_type;
-    using T = std::true_type;
-    if (half) return polar ? fn(W, S{}, T{}, F{}, T{}, G) : fn(W, S{}, T{}, F{}, F{}, G);
-    if (lut) {
-      if constexpr (!kG) return polar ? fn(W, S{}, F{}, T{}, T{}, G) : fn(W, S{}, F{}, T{}, F{}, G);
-      return -2;
-    }
-    if (tile == LONG_TILE) return polar ? fn(W, LT{}, F{}, F{}, T{}, G) : fn(W, LT{}, F{}, F{}, F{}, G);
-    return polar ? fn(W, S{}, F{}, F{}, T{}, G) : fn(W, S{}, F{}, F{}, F{}, G);
-  };
+static int dispatch_window(int wt, int tile, bool gen, int kind, bool lut, bool polar, Fn &&fn) {
+  if ((kind == ITEM_FP16 && lut) || (tile != TILE && (kind != ITEM_MOMENTS || lut || tile != LONG_TILE))) return -2;
   using F = std::false_type;
   using T = std::true_type;
+  auto by_mode = [&](auto W, auto G) -> int {
+    using S = std::integral_constant<int, TILE>;
+    using LT = std::integral_constant<int, LONG_TILE>;
+    using Mom = std::integral_constant<int, ITEM_MOMENTS>;
+    using Half = std::integral_constant<int, ITEM_FP16>;
+    using Few = std::integral_constant<int, ITEM_FEW>;
+    auto by_polar = [&](auto Tl, auto K, auto L) -> int {
+      return polar ? fn(W, Tl, K, L, T{}, G) : fn(W, Tl, K, L, F{}, G);
+    };
+    if (kind == ITEM_FP16) return by_polar(S{}, Half{}, F{});
+    if (lut) {
+      if constexpr (!decltype(G)::value) return kind == ITEM_FEW ? by_polar(S{}, Few{}, T{}) : by_polar(S{}, Mom{}, T{});
+      return -2;
+    }
+    if (kind == ITEM_FEW) return by_polar(S{}, Few{}, F{});
+    return tile == LONG_TILE ? by_polar(LT{}, Mom{}, F{}) : by_polar(S{}, Mom{}, F{});
+  };
   if (!gen) {
     switch (wt) {
       case 32: return by_mode(std::integral_constant<int, 32>{}, F{});
@@ -1956,11 +2141,11 @@ static int dispatch_window(int wt, int tile, bool gen, bool half, bool lut, bool
   }
 }
 
-// polar: directional receivers (any tap mode; half and lut exclusive).
-int launch_accumulate(int wt, bool gen, bool half, bool lut, bool polar, const RoomArgs &ra, const PlanArgs &pa,
+// polar: directional receivers (any tap mode; FP16 items and lut exclusive).
+int launch_accumulate(int wt, bool gen, int kind, bool lut, bool polar, const RoomArgs &ra, const PlanArgs &pa,
                       uint32_t n_items, const AxisEntry *tab, const AxisOrigin *origin, const int *valid, float *out,
                       float *part, float *marg, const float *wc, hipStream_t st) {
-  return dispatch_window(wt, ra.tile, gen, half, lut, polar, [&](auto W, auto Tl, auto H, auto L, auto P, auto G) -> int {
+  return dispatch_window(wt, ra.tile, gen, kind, lut, polar, [&](auto W, auto Tl, auto H, auto L, auto P, auto G) -> int {
     return launch_acc_w<decltype(W)::value, decltype(Tl)::value, decltype(H)::value, decltype(L)::value,
                         decltype(P)::value, decltype(G)::value>(ra, pa, n_items, tab, origin, valid, out, part, marg, wc, st);
   });
@@ -1968,12 +2153,12 @@ int launch_accumulate(int wt, bool gen, bool half, bool lut, bool polar, const R
 
 // grid: workgroups of the persistent launch (at most n_items; the planner
 // sizes it from the tuned workgroups per SIMD).
-template <int WT, int TL, bool HALF, bool LUT, bool POLAR, bool GEN>
+template <int WT, int TL, int KIND, bool LUT, bool POLAR, bool GEN>
 static int launch_acc_batch_w(const JobDev *jobs, const BatchItem *items, uint32_t n_items, uint32_t grid,
                               uint32_t *queue, const AxisEntry *tab, const AxisOrigin *origin, const int *valid,
                               float *part, float *marg, hipStream_t st) {
-  hipLaunchKernelGGL((accumulate_batch_kernel<WT, TL, HALF, LUT, POLAR, GEN>),
-                     dim3(grid), dim3(item_threads(HALF)), 0, st, jobs, items, n_items, queue, tab, origin, valid, part, marg);
+  hipLaunchKernelGGL((accumulate_batch_kernel<WT, TL, KIND, LUT, POLAR, GEN>),
+                     dim3(grid), dim3(item_threads(KIND)), 0, st, jobs, items, n_items, queue, tab, origin, valid, part, marg);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -2004,7 +2189,7 @@ int launch_batch(const JobDev *jobs, int n_jobs, bool any_gen, const BatchRir *r
     if (cls[k].count == 0) continue;
     const BatchItem *it = items + cls[k].first;
     uint32_t *qk = queue ? queue + k : nullptr;
-    const int rc = dispatch_window(cls[k].wt, cls[k].tile, cls[k].gen != 0, half, lut, polar,
+    const int rc = dispatch_window(cls[k].wt, cls[k].tile, cls[k].gen != 0, cls[k].kind, lut, polar,
                                    [&](auto W, auto Tl, auto H, auto L, auto P, auto G) -> int {
                                      return launch_acc_batch_w<decltype(W)::value, decltype(Tl)::value,
                                                                decltype(H)::value, decltype(L)::value,

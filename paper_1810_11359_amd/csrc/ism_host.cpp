@@ -20,7 +20,7 @@
 namespace ism {
 int launch_tables(const RoomArgs &ra, const float *src, const float *rcv, const float *orient, AxisEntry *tab,
                   AxisOrigin *origin, int *valid, int n_rir, float W, bool half, float *wc, hipStream_t st);
-int launch_accumulate(int wt, bool gen, bool half, bool lut, bool polar, const RoomArgs &ra, const PlanArgs &pa,
+int launch_accumulate(int wt, bool gen, int kind, bool lut, bool polar, const RoomArgs &ra, const PlanArgs &pa,
                       uint32_t n_items, const AxisEntry *tab, const AxisOrigin *origin, const int *valid, float *out,
                       float *part, float *marg, const float *wc, hipStream_t st);
 int launch_reduce(const RoomArgs &ra, const PlanArgs &pa, int n_rir, const float *part, const float *marg,
@@ -108,6 +108,7 @@ struct Plan {
   double win; // W = t_w fs
   bool half;
   bool lut;  // table taps (Eq. (9)); FP32 arithmetic otherwise
+  int kind;  // of its work items
   int n_rir;
   uint32_t n_items;
   bool any_split;
@@ -176,8 +177,8 @@ double batch_item_taps(int wt, bool half) {
 // Workgroups of the accumulate kernel resident on the device at once (256 CUs x
 // 4 SIMDs x the waves per SIMD the kernel is built for, over its waves per
 // item), and the default rounds of them over which a single call tapers its tail.
-double resident_items(bool half, bool lut) {
-  return 256.0 * 4.0 * waves_per_simd(half, lut) * 64.0 / item_threads(half);
+double resident_items(int kind, bool lut) {
+  return 256.0 * 4.0 * waves_per_simd(kind, lut) * 64.0 / item_threads(kind);
 }
 constexpr double kTailRounds = 1.0;
 
@@ -266,11 +267,44 @@ bool long_tiles(const ism_room &r, const Plan &p, bool alone) {
   return 0.045 * side + 9.0e4 * k / (TILE * std::max(images, 1.0)) > kLongTileGain;
 }
 
+// Whether an FP32 or table-tap call takes one-wave items, image by image. An item of
+// moments costs its lists and its product whatever it holds, and 1024 run at once; one
+// wave pays 64 lanes x (W / 64) taps per image, but 6144 run at once. n: tiles over all RIRs
+// of the launch. One wave is taken where even the fullest tile, the last whole one, holds
+// few images, or, where the launch fills the chip with them, where tiles hold few on
+// average: up to 250 images (table taps, whose moment items hold 17 planes, 800), and fewer
+// in launches of fewer tiles, which the fullest item holds up. Moments against one wave, us
+// per call at W = 64 and 30, 150 and 400 images per tile: 512 RIRs of 9600 samples (20 000
+// tiles) 158 and 49, 168 and 109, 187 and 201; 64 RIRs of 2400 (630) 19 and 16, 19 and 21,
+// 21 and 25; 8 RIRs of 2400 (80) 15 and 15, 15 and 20, 16 and 21. Table taps, the same: 335
+// and 49, 346 and 114, 371 and 201; 24 and 17, 24 and 23, 26 and 28; 15 and 16, 16 and 22,
+// 18 and 26. The limits are about the least of W = 32 .. 244.
+// scale: times the tiles' average (jobs of a batch that holds others, below).
+constexpr double kFewFullest = 60.0;
+constexpr double kFewTiles = 16.0, kFewMean = 250.0;
+constexpr double kFewLutFirst = 500.0, kFewLutTiles = 4.0, kFewLutMean = 800.0;
+bool few_images(const ism_room &r, const Plan &p, int64_t n, double scale = 1.0) {
+  const double q = r.fs / r.c, k = (double)p.ra.k_end, k0 = std::max(k - TILE, 0.0);
+  const double cell = r.room[0] * r.room[1] * r.room[2] * q * q * q;
+  const double lattice = (double)r.n_img[0] * r.n_img[1] * r.n_img[2];
+  const double mean = std::min(4.0 / 3.0 * kPi * k * k * k / cell, lattice) / std::ceil(k / TILE);
+  const double fullest = std::min(4.0 / 3.0 * kPi * (k * k * k - k0 * k0 * k0) / cell, lattice);
+  if (fullest <= kFewFullest) return true;
+  return mean * scale <= (p.lut ? std::min(((double)n - kFewLutFirst) / kFewLutTiles, kFewLutMean)
+                                : std::min((double)n / kFewTiles, kFewMean));
+}
+int64_t rir_tiles(const Plan &p) { return (int64_t)p.n_rir * ((p.ra.k_end + TILE - 1) / TILE); }
+// Jobs of few images in a batch of others get a launch of their own, some 10 us with its
+// tail, only from this many tiles on (one wave saves 3 to 5 ns a tile), and with half the
+// images on average.
+constexpr int64_t kFewBatchTiles = 4096;
+
 // sched: the call's schedule (null = the tuned default).
 // taper: cut the items dispatched last (single calls; a batch's tail is the
 // largest-first order over all its jobs' items instead).
+// kind: of FP32 and table-tap items (-1: the call's own).
 int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, const ism_schedule *sched = nullptr,
-              bool taper = true) {
+              bool taper = true, int kind = -1) {
   int st = ism_check_room(r);
   if (st != ISM_OK) return st;
   if (!valid_schedule(sched)) return ISM_E_INVALID_ARG;
@@ -322,7 +356,8 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   PlanArgs &pa = p.pa;
   std::memset(&pa, 0, sizeof(pa));
   const bool tapered = taper && !(sched && (sched->item_taps > 0.0 || sched->tail_rounds == 0.0));
-  ra.tile = !p.half && !p.lut && long_tiles(*r, p, tapered) ? LONG_TILE : TILE;
+  p.kind = p.half ? ITEM_FP16 : kind >= 0 ? kind : few_images(*r, p, rir_tiles(p)) ? ITEM_FEW : ITEM_MOMENTS;
+  ra.tile = p.kind == ITEM_MOMENTS && !p.lut && long_tiles(*r, p, tapered) ? LONG_TILE : TILE;
   pa.n_rir = p.n_rir;
   pa.n_tiles = shell_taps(*r, p, ra.tile, p.tile_taps);
   if ((ra.k_end + TILE - 1) / TILE > MAX_TILES) return ISM_E_TOO_LARGE;
@@ -330,9 +365,9 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   for (int t = 0; t < pa.n_tiles; ++t) p.total_taps += p.tile_taps[t] * p.n_rir;
   // an explicit item size is used as given
   const bool fixed = sched && sched->item_taps > 0.0;
-  const bool mom = !p.half;  // FP32 and table taps: items of images, FP16: of taps
+  const bool mom = p.kind == ITEM_MOMENTS;  // items of images, otherwise of taps
   double target = fixed ? std::max(1e3, sched->item_taps) : item_target(p.total_taps, p.wt, p.half, mom, nS, sched);
-  const double resident = resident_items(p.half, p.lut);
+  const double resident = resident_items(p.kind, p.lut);
   if (!fixed && !mom && p.total_taps < resident * target)
     target = std::min(target, small_call_floor(p.total_taps, resident));
   // Tail taper: tiles are dispatched last first, and the items of a tile
@@ -353,9 +388,9 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   uint64_t n_items = 0, n_split = 0;
   size_t ws_arrays = 0;  // bytes of the partial tiles and margins the workspace is sized for
   auto arrays = [&](uint64_t items, uint64_t split, int T) { return item_arrays(items, split > 0, T, p.wt); };
-  if (mom && !fixed && taper) {
+  if (!p.half && !fixed && taper) {
     double tt = item_target(p.total_taps, p.wt, false, false, nS, sched);
-    const double res = resident_items(true, false);
+    const double res = resident_items(ITEM_FP16, false);
     if (p.total_taps < res * tt) tt = std::min(tt, small_call_floor(p.total_taps, res));
     double taps[MAX_TILES];
     const int n = shell_taps(*r, p, TILE, taps);
@@ -577,7 +612,7 @@ static int run_plan(const Plan &p, const float *src, const float *rcv, float *ou
   if (launch_tables(p.ra, src, rcv, orient, tab, origin, valid, p.n_rir, (float)p.win, p.half, wc, s) != 0)
     return ISM_E_DEVICE;
   if (ev_start && hipEventRecord((hipEvent_t)ev_start, s) != hipSuccess) return ISM_E_DEVICE;
-  if (launch_accumulate(p.wt, p.gen, p.half, p.lut, orient != nullptr, p.ra, p.pa, p.n_items, tab, origin, valid, out,
+  if (launch_accumulate(p.wt, p.gen, p.kind, p.lut, orient != nullptr, p.ra, p.pa, p.n_items, tab, origin, valid, out,
                         part, marg, wc, s) != 0)
     return ISM_E_DEVICE;
   if (ev_stop && hipEventRecord((hipEvent_t)ev_stop, s) != hipSuccess) return ISM_E_DEVICE;
@@ -765,7 +800,7 @@ struct BatchState {  // stored in ism_batch::opaque
                                                // long_runs: a tile of RED_SLICE_MIN items or more
   uint32_t n_red_split, pad;                    // reduce entries of split tiles (they come first)
   uint32_t class_count[kMaxClasses];
-  uint16_t class_code[kMaxClasses];             // cap / 32, general mode << 4, long tiles << 5, waves per SIMD << 8
+  uint16_t class_code[kMaxClasses];             // cap / 32, general << 4, long tiles << 5, few images << 6, waves per SIMD << 8
 };
 static_assert(sizeof(BatchState) <= sizeof(ism_batch), "ism_batch too small");
 
@@ -818,15 +853,24 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
   // an FP16 batch with less work than that per resident wave gets items of its
   // work over the resident waves (at least kSmallItemTaps).
   double batch_taps = 0.0;
+  int64_t batch_tiles = 0;
   for (int j = 0; j < n_jobs; ++j) {
     Plan &p = plans[j];
     const int stt = make_plan(&jobs[j].room, jobs[j].n_src, jobs[j].n_rcv, precision, p, sched, false);
     if (stt != ISM_OK) return stt;
     batch_taps += p.total_taps;
+    batch_tiles += rir_tiles(p);
+  }
+  bool all_few = true;
+  int64_t few_tiles = 0;
+  for (int j = 0; j < n_jobs; ++j) {
+    all_few = all_few && few_images(jobs[j].room, plans[j], batch_tiles);
+    if (few_images(jobs[j].room, plans[j], batch_tiles, 2.0)) few_tiles += rir_tiles(plans[j]);
   }
   // pass 1: plans, window classes and counts
   int n_classes = 0;
-  int class_wt[kMaxClasses] = {}, class_gen[kMaxClasses] = {}, class_tile[kMaxClasses] = {}, n_windows = 0;
+  int class_wt[kMaxClasses] = {}, class_gen[kMaxClasses] = {}, class_tile[kMaxClasses] = {}, class_kind[kMaxClasses] = {},
+      n_windows = 0;
   std::vector<int> job_cls(n_jobs);
   uint64_t tab_entries = 0, n_rir = 0, n_items = 0, slots = 0, n_red = 0, marg_units = 0, wc_floats = 0,
            max_chunks = 0, ws_items = 0, ws_slots = 0, ws_marg = 0, ws_red = 0;  // ws: counts the workspace is sized for
@@ -836,16 +880,19 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     if (!(sched && sched->item_taps > 0.0)) {
       ism_schedule js{};
       if (sched) js = *sched;
-      const bool mom = !p.half;
+      if (!p.half)
+        p.kind = all_few || (few_tiles >= kFewBatchTiles && few_images(jobs[j].room, p, batch_tiles, 2.0)) ? ITEM_FEW
+                                                                                                          : ITEM_MOMENTS;
+      const bool mom = p.kind == ITEM_MOMENTS;
       double t = item_target(batch_taps, p.wt, p.half, mom, p.ra.n_samples, sched);
       if (!mom) t = std::min(t, batch_item_taps(p.wt, p.half));
       // a batch too small to give every resident wave an item of that size is
       // spread over them instead (the small-call rule of single calls)
-      const double resident = resident_items(p.half, p.lut);
+      const double resident = resident_items(p.kind, p.lut);
       js.item_taps = !mom && batch_taps < resident * t ? std::min(t, small_call_floor(batch_taps, resident)) : t;
       size_t ws_arrays = 0;
-      if (mom) {  // the workspace is that of items cut by taps, as for single calls
-        const double res = resident_items(true, false);
+      if (!p.half) {  // the workspace is that of items cut by taps, as for single calls
+        const double res = resident_items(ITEM_FP16, false);
         double tt = std::min(batch_item_taps(p.wt, false),
                              item_target(batch_taps, p.wt, false, false, p.ra.n_samples, sched));
         if (batch_taps < res * tt) tt = std::min(tt, small_call_floor(batch_taps, res));
@@ -860,9 +907,9 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
         ws_red += (uint64_t)nt * p.n_rir;
       }
       for (;;) {  // items that outgrow it are doubled, as in a single call
-        const int stt = make_plan(&jobs[j].room, jobs[j].n_src, jobs[j].n_rcv, precision, p, &js, false);
+        const int stt = make_plan(&jobs[j].room, jobs[j].n_src, jobs[j].n_rcv, precision, p, &js, false, p.kind);
         if (stt != ISM_OK) return stt;
-        if (!mom || !p.any_split || item_arrays(p.n_items, true, p.ra.tile, p.wt) <= ws_arrays) break;
+        if (p.half || !p.any_split || item_arrays(p.n_items, true, p.ra.tile, p.wt) <= ws_arrays) break;
         js.item_taps *= 2.0;
       }
     }
@@ -871,7 +918,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     for (int k = 0; k < n_classes; ++k)
       if (class_wt[k] == p.wt && class_gen[k] == (p.gen ? 1 : 0)) {
         window_known = true;
-        if (class_tile[k] == p.ra.tile) cls = k;
+        if (class_tile[k] == p.ra.tile && class_kind[k] == p.kind) cls = k;
       }
     if (cls < 0) {
       if (!window_known && n_windows++ == kMaxBatchClasses) return ISM_E_UNSUPPORTED;
@@ -879,6 +926,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
       class_wt[cls] = p.wt;
       class_gen[cls] = p.gen ? 1 : 0;
       class_tile[cls] = p.ra.tile;
+      class_kind[cls] = p.kind;
     }
     job_cls[j] = cls;
     if (p.gen) wc_floats += (uint64_t)WC_STRIDE * p.wt;
@@ -908,13 +956,14 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     }
     bp.st.class_count[k] = (uint32_t)(acc - first);
     // persistent grid: the tuned waves per SIMD (or the schedule's)
-    int waves = waves_per_simd(precision == ISM_FP16, precision == ISM_FP32_LUT);
+    int waves = waves_per_simd(class_kind[k], precision == ISM_FP32_LUT);
     if (precision == ISM_FP16)
       for (const BatchTuning &t : kBatchTuning)
         if (t.wt == class_wt[k] && t.half == 1) waves = t.waves;
     if (sched && sched->batch_waves > 0.0) waves = std::max(1, (int)std::lround(sched->batch_waves));
     bp.st.class_code[k] =
-        (uint16_t)(class_wt[k] / 32 | class_gen[k] << 4 | (class_tile[k] == LONG_TILE ? 1 : 0) << 5 | waves << 8);
+        (uint16_t)(class_wt[k] / 32 | class_gen[k] << 4 | (class_tile[k] == LONG_TILE ? 1 : 0) << 5 |
+                   (class_kind[k] == ITEM_FEW ? 1 : 0) << 6 | waves << 8);
   }
   bp.st.n_jobs = (uint32_t)n_jobs;
   bp.st.any_gen = wc_floats > 0 ? 1u : 0u;
@@ -1156,7 +1205,8 @@ int ism_batch_run_timed(const ism_batch *batch, void *stream, void *ev_start, vo
     const uint32_t code = b.class_code[k], waves = code >> 8;
     cls[k].first = first;
     cls[k].count = b.class_count[k];
-    cls[k].grid = std::min(b.class_count[k], 1024u * waves * 64u / (uint32_t)item_threads(b.mode == 1));
+    cls[k].kind = b.mode == 1 ? ITEM_FP16 : (code >> 6 & 1u) ? ITEM_FEW : ITEM_MOMENTS;
+    cls[k].grid = std::min(b.class_count[k], 1024u * waves * 64u / (uint32_t)item_threads(cls[k].kind));
     cls[k].wt = (int)(code & 15u) * 32;
     cls[k].gen = (int)(code >> 4 & 1u);
     cls[k].tile = (code >> 5 & 1u) ? LONG_TILE : TILE;

@@ -37,17 +37,20 @@ constexpr int WC_STRIDE = 8;
 constexpr int RED_SLICES = 4;
 constexpr int RED_SLICE_MIN = 64;
 // Window classes (cap, mode) one batch may hold, and persistent launches: one per
-// class and tile length.
+// class and kind of item (of moments: and tile length).
 constexpr int kMaxBatchClasses = 8;
-constexpr int kMaxBatchLaunches = 2 * kMaxBatchClasses;
+constexpr int kMaxBatchLaunches = 3 * kMaxBatchClasses;
 // Work items per tile are capped so the per-tile chunk count fits a byte.
 constexpr int MAX_CHUNKS = 255;
+// Kinds of work items: FP32 and table taps by moments (pulses) on four waves that share an
+// image pool, FP16 taps on one wave, and FP32 and table taps on one wave, image by image, in
+// calls of few images per tile.
+enum { ITEM_MOMENTS, ITEM_FP16, ITEM_FEW };
 // Waves per SIMD the accumulate kernels are built for (their LDS and VGPR
-// budget) and threads per work item: one wave for FP16 taps, four waves that share
-// an image pool for FP32 and table taps. The planner sizes items and the tail
+// budget) and threads per work item. The planner sizes items and the tail
 // taper of a launch with them.
-constexpr int waves_per_simd(bool half, bool lut) { return half ? 7 : lut ? 3 : 4; }
-constexpr int item_threads(bool half) { return half ? 64 : 256; }
+constexpr int waves_per_simd(int kind, bool lut) { return kind == ITEM_FP16 ? 7 : kind == ITEM_FEW ? 6 : lut ? 3 : 4; }
+constexpr int item_threads(int kind) { return kind == ITEM_MOMENTS ? 256 : 64; }
 
 // Per-call room constants, passed by value as a kernel argument. Lengths are in
 // metres, delays in samples. Float pairs (hi, lo) carry double-precision host
@@ -126,7 +129,7 @@ struct JobDev {
 // grid workgroups, window cap wt (gen: general mode), tiles of tile samples.
 struct BatchClass {
   uint32_t first, count, grid;
-  int wt, tile, gen;
+  int wt, tile, gen, kind;
 };
 
 // Batch-wide RIR index -> (job, RIR within the job).
