@@ -587,7 +587,8 @@ template <int M> constexpr bool kKeepRoots = M <= 4096;
 
 // z[row] of row = (m n_blk + b) S + g: the inverse transform of the sum over the
 // partitions q of group g (PS of them) of X[b - c q] H_{b - c q, m}[q], with
-// 2M points of which the first (c + 1) L are kept. RIRs are read once and no RIR spectrum
+// 2M points of which the first (c + 1) L are kept. q counts from 0, or (window: signals of
+// fewer segments than the RIR's partitions span) from the first that meets a segment. RIRs are read once and no RIR spectrum
 // goes to memory (fixed blocks write and read twice the RIRs). Bounded by the transforms:
 // VALU issue (0.47 of the slots) and waits for the LDS passes and their barriers. 8 microphones, 100 segments of 4800 samples, RIRs of 96000 taps (307
 // MB): 293 us with the launches around it 310, fixed blocks of radix 8 677; segments of
@@ -595,7 +596,7 @@ template <int M> constexpr bool kKeepRoots = M <= 4096;
 template <int M>
 __global__ __launch_bounds__(FftShape<M>::NT) __attribute__((amdgpu_waves_per_eu(kKeepRoots<M> ? 2 : 4))) void seg_filter_kernel(
     const float *__restrict__ rir, int n_mic, int n_rir, const float2 *__restrict__ X, int n_seg, int L, int c, int P,
-    int S, int PS, int n_blk, int n_rows, float *__restrict__ z) {
+    int S, int PS, bool window, int n_blk, int n_rows, float *__restrict__ z) {
   typedef FftShape<M> Sh;
   constexpr int TPF = Sh::TPF, PAIRS = Sh::PAIRS;
   Tables T = reinterpret_cast<Tables>(&kTables);
@@ -611,6 +612,8 @@ __global__ __launch_bounds__(FftShape<M>::NT) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
   for (int u = 0; u < PAIRS; ++u) y1[u] = y2[u] = make_float2(0.0f, 0.0f);
   const int part = c * L;
+  int q0 = g * PS;
+  if (window) q0 += max(b - n_seg + c, 0) / c;
   Fft<M, kKeepRoots<M>> fft;
   fft.init(T, tid0);
   // (every transform of the workgroup takes PS turns: the barriers are the workgroup's)
@@ -618,7 +621,7 @@ __global__ __launch_bounds__(FftShape<M>::NT) __attribute__((amdgpu_waves_per_eu
     // keeps twiddles and addresses in the loop: held across it they take 100 registers
     int tid = tid0;
     if constexpr (!kKeepRoots<M>) __asm__ volatile("" : "+s"(T), "+v"(tid));
-    const int q = g * PS + i, p = b - c * q;
+    const int q = q0 + i, p = b - c * q;
     const bool has = live && q < P && p >= 0 && p < n_seg;
     if (Sh::FPB == 1 && !has) continue;  // uniform over the workgroup
     const int len = has ? min(part, n_rir - q * part) : 0;
@@ -786,9 +789,15 @@ bool seg_plan(int n_x, int n_pos, int n_mic, int n_rir, FftPlan &f) {
   f.n_in_blocks = n_seg;
   const int fpb = f.B < 4096 ? 4096 / f.B : 1;
   const int64_t rows = (int64_t)n_mic * f.n_out_blocks;
-  f.S = (int)std::min<int64_t>(f.P, std::max<int64_t>(1, 512 * fpb / std::max<int64_t>(rows, 1)));
-  f.PS = (f.P + f.S - 1) / f.S;
-  f.S = (f.P + f.PS - 1) / f.PS;
+  // an output block meets at most ceil(n_seg / c) partitions: groups of those where that is
+  // fewer (3 segments of 101 samples, 8 microphones, RIRs of 20 879 taps: 52 partitions, one
+  // per block; 54 us with groups of all of them, most of it transforms of nothing)
+  const int met = (n_seg + f.c - 1) / f.c;
+  f.window = met < f.P;
+  const int K = f.window ? met : f.P;
+  f.S = (int)std::min<int64_t>(K, std::max<int64_t>(1, 512 * fpb / std::max<int64_t>(rows, 1)));
+  f.PS = (K + f.S - 1) / f.S;
+  f.S = (K + f.PS - 1) / f.PS;
   if (rows * f.S > 0x7fffff00LL) return false;
   size_t o = 0;
   f.off_X = o;
@@ -808,7 +817,7 @@ static int launch_seg_m(const float *x, int n_x, const float *rir, int n_mic, in
   hipLaunchKernelGGL(seg_input_kernel<M>, dim3((n_seg + Sh::FPB - 1) / Sh::FPB), dim3(Sh::NT), 0, st, x, n_x, f.L,
                      n_seg, X);
   hipLaunchKernelGGL(seg_filter_kernel<M>, dim3((rows + Sh::FPB - 1) / Sh::FPB), dim3(Sh::NT), 0, st, rir, n_mic,
-                     n_rir, X, n_seg, f.L, f.c, f.P, f.S, f.PS, f.n_out_blocks, rows, z);
+                     n_rir, X, n_seg, f.L, f.c, f.P, f.S, f.PS, f.window, f.n_out_blocks, rows, z);
   const int n_y = n_x + n_rir - 1;
   auto *const overlap = contain ? &seg_overlap_kernel<true> : &seg_overlap_kernel<false>;
   hipLaunchKernelGGL(overlap, dim3((n_y + 255) / 256, n_mic), dim3(256), 0, st, z, f.N, f.L, f.c, f.S,
@@ -821,6 +830,7 @@ static int launch_seg_m(const float *x, int n_x, const float *rir, int n_mic, in
 // Returns false when the pieces per block exceed max_pieces.
 bool fft_plan(int n_x, int n_pos, int n_mic, int n_rir, int max_pieces, FftPlan &f) {
   f.c = 0;
+  f.window = false;
   int np2 = 1;
   while (np2 < n_rir) np2 <<= 1;
   f.B = np2 >= 16384 ? 4096 : (np2 / 4 < 256 ? 256 : np2 / 4);

@@ -182,10 +182,11 @@ struct DumpArgs {
 // One FFT filter call. Fixed blocks (c = 0): block size B, transform size N = 2B,
 // RIR partitions P, pieces per input block R, segment length L, input and output
 // block counts. Segment blocks (c >= 1): partitions of c L taps, in S groups of
-// PS. Offsets into the workspace in bytes.
+// PS (window: of those that meet a segment in the block). Offsets into the workspace in bytes.
 struct FftPlan {
   int B, N, P, R, n_in_blocks, n_out_blocks, L;
   int c, S, PS;
+  bool window;
   size_t off_H, off_X, off_Y, off_z, bytes;
 };
 

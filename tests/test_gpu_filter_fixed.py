@@ -33,20 +33,21 @@ LONG = [
     (60000, 13, 1, 4000, "auto"),  # 1024, 2, 4616: too few partitions for the longest transform
 ]
 SHORT = [
-    (236, 3, 1, 910, "fft"),       # 256, 3
-    (297, 5, 2, 1002, "fft"),      # 256, 5
-    (446, 15, 1, 488, "fft"),      # 256, 10
-    (429, 25, 1, 493, "fft"),      # 256, 16
-    (187, 3, 1, 1038, "auto"),     # 512, 3
-    (390, 9, 1, 1453, "fft"),      # 512, 9
-    (260, 16, 1, 1237, "fft"),     # 512, 16
-    (165, 4, 1, 2286, "auto"),     # 1024, 4
-    (158, 8, 2, 2067, "fft"),      # 1024, 8
-    (153, 16, 1, 2460, "fft"),     # 1024, 16
-    (201, 5, 1, 5683, "fft"),      # 2048, 5
-    (385, 16, 1, 4511, "fft"),     # 2048, 16
+    (709, 4, 1, 915, "fft"),       # 256, 3
+    (526, 9, 2, 434, "fft"),       # 256, 6
+    (733, 24, 1, 491, "fft"),      # 256, 10
+    (549, 31, 2, 496, "fft"),      # 256, 16
+    (1560, 4, 2, 2024, "auto"),    # 512, 3
+    (161, 8, 1, 2041, "fft"),      # 512, 8
+    (1785, 51, 8, 1448, "fft"),    # 512, 16
+    (3113, 7, 2, 2965, "auto"),    # 1024, 4
+    (3588, 24, 8, 2438, "fft"),    # 1024, 8
+    (3140, 46, 8, 3032, "fft"),    # 1024, 16
+    (8896, 20, 1, 8069, "fft"),    # 2048, 6
+    (7788, 53, 1, 7637, "fft"),    # 2048, 15
     (116, 4, 1, 24832, "auto"),    # 4096, 4: 7 partitions
     (104, 7, 1, 32771, "fft"),     # 4096, 7: the last partition of 3 taps
+    (114, 16, 1, 15548, "fft"),    # 4096, 16
 ]
 
 
