@@ -383,7 +383,8 @@ int ism_batch_prepare(const ism_job *jobs, int n_jobs, int precision, void *ws, 
  * a batch of less than t taps per resident wave, its taps over the resident
  * waves (at least 1e4). FP32 and table taps: by images per item, doubled for a
  * job whose items would take more workspace than a cut by taps; where tiles hold
- * few images (up to some hundred in large launches), by taps as FP16. A
+ * few images (FP32 up to 40 on average in batches of fewer than 4096 tiles, table
+ * taps up to 300 in large batches), by taps as FP16. A
  * job's result therefore agrees within rounding (<= 1e-6 of the RIR peak)
  * with the job alone and with ism_simulate. With an item_taps in the schedule it
  * is bitwise that of ism_simulate_ex with the same schedule, and a batch of one

@@ -279,25 +279,41 @@ bool long_tiles(const ism_room &r, const Plan &p, bool alone) {
 // 21 and 25; 8 RIRs of 2400 (80) 15 and 15, 15 and 20, 16 and 21. Table taps, the same: 335
 // and 49, 346 and 114, 371 and 201; 24 and 17, 24 and 23, 26 and 28; 15 and 16, 16 and 22,
 // 18 and 26. The limits are about the least of W = 32 .. 244.
-// scale: times the tiles' average (jobs of a batch that holds others, below).
-constexpr double kFewFullest = 60.0;
+constexpr double kFewFullest = 40.0;
 constexpr double kFewTiles = 16.0, kFewMean = 250.0;
 constexpr double kFewLutFirst = 500.0, kFewLutTiles = 4.0, kFewLutMean = 800.0;
-bool few_images(const ism_room &r, const Plan &p, int64_t n, double scale = 1.0) {
+struct TileImages {
+  double mean, fullest;
+};
+TileImages tile_images(const ism_room &r, const Plan &p) {
   const double q = r.fs / r.c, k = (double)p.ra.k_end, k0 = std::max(k - TILE, 0.0);
   const double cell = r.room[0] * r.room[1] * r.room[2] * q * q * q;
   const double lattice = (double)r.n_img[0] * r.n_img[1] * r.n_img[2];
-  const double mean = std::min(4.0 / 3.0 * kPi * k * k * k / cell, lattice) / std::ceil(k / TILE);
-  const double fullest = std::min(4.0 / 3.0 * kPi * (k * k * k - k0 * k0 * k0) / cell, lattice);
-  if (fullest <= kFewFullest) return true;
-  return mean * scale <= (p.lut ? std::min(((double)n - kFewLutFirst) / kFewLutTiles, kFewLutMean)
-                                : std::min((double)n / kFewTiles, kFewMean));
+  return {std::min(4.0 / 3.0 * kPi * k * k * k / cell, lattice) / std::ceil(k / TILE),
+          std::min(4.0 / 3.0 * kPi * (k * k * k - k0 * k0 * k0) / cell, lattice)};
+}
+bool few_images(TileImages t, bool lut, int64_t n) {
+  if (t.fullest <= kFewFullest) return true;
+  return t.mean <= (lut ? std::min(((double)n - kFewLutFirst) / kFewLutTiles, kFewLutMean)
+                        : std::min((double)n / kFewTiles, kFewMean));
 }
 int64_t rir_tiles(const Plan &p) { return (int64_t)p.n_rir * ((p.ra.k_end + TILE - 1) / TILE); }
-// Jobs of few images in a batch of others get a launch of their own, some 10 us with its
-// tail, only from this many tiles on (one wave saves 3 to 5 ns a tile), and with half the
-// images on average.
-constexpr int64_t kFewBatchTiles = 4096;
+// The same for a batch of several jobs, whose items all cost some 10 ns to fetch: t is the
+// average over its tiles and the fullest tile of all. FP32 batches that fill the chip keep to
+// moments, and the limits are lower, since the long jobs of a mixed batch hold it up. Moments
+// against one wave, us, 64 jobs of one length x 16 RIRs, at 20, 80, 160 and 300 images: 3072
+// tiles 56 and 50, 58 and 52, 59 and 83, 59 and 109; 10 240 tiles 104 and 138, 106 and 171,
+// 110 and 177, 115 and 193; table taps 81 and 52, 81 and 53, 83 and 85, 84 and 113; 203 and
+// 139, 204 and 174, 206 and 184, 212 and 200. Lengths and rooms at random (4 jobs x 8: 96
+// tiles) at 40 and 80: 18.9 and 20.0, 19.5 and 24.2; table taps 19.5 and 22.5, 19.7 and 26.9.
+constexpr double kFewBatchMean = 40.0, kFewBatchFull = 4096.0;
+constexpr double kFewLutBatchFirst = 75.0, kFewLutBatchTiles = 64.0, kFewLutBatchMean = 300.0;
+bool few_images_batch(TileImages t, bool lut, int64_t n) {
+  if (!lut && (double)n > kFewBatchFull) return false;
+  if (t.fullest <= kFewFullest) return true;
+  const double most = lut ? std::min(kFewLutBatchFirst + (double)n / kFewLutBatchTiles, kFewLutBatchMean) : kFewBatchMean;
+  return t.mean <= std::min((double)n / kFewTiles, most);
+}
 
 // sched: the call's schedule (null = the tuned default).
 // taper: cut the items dispatched last (single calls; a batch's tail is the
@@ -356,7 +372,10 @@ int make_plan(const ism_room *r, int n_src, int n_rcv, int precision, Plan &p, c
   PlanArgs &pa = p.pa;
   std::memset(&pa, 0, sizeof(pa));
   const bool tapered = taper && !(sched && (sched->item_taps > 0.0 || sched->tail_rounds == 0.0));
-  p.kind = p.half ? ITEM_FP16 : kind >= 0 ? kind : few_images(*r, p, rir_tiles(p)) ? ITEM_FEW : ITEM_MOMENTS;
+  p.kind = p.half                                                    ? ITEM_FP16
+           : kind >= 0                                               ? kind
+           : few_images(tile_images(*r, p), p.lut, rir_tiles(p))     ? ITEM_FEW
+                                                                     : ITEM_MOMENTS;
   ra.tile = p.kind == ITEM_MOMENTS && !p.lut && long_tiles(*r, p, tapered) ? LONG_TILE : TILE;
   pa.n_rir = p.n_rir;
   pa.n_tiles = shell_taps(*r, p, ra.tile, p.tile_taps);
@@ -861,12 +880,16 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     batch_taps += p.total_taps;
     batch_tiles += rir_tiles(p);
   }
-  bool all_few = true;
-  int64_t few_tiles = 0;
+  // one kind of items for the whole batch: two are two launches, each with a tail of its own
+  TileImages images{0.0, 0.0};
   for (int j = 0; j < n_jobs; ++j) {
-    all_few = all_few && few_images(jobs[j].room, plans[j], batch_tiles);
-    if (few_images(jobs[j].room, plans[j], batch_tiles, 2.0)) few_tiles += rir_tiles(plans[j]);
+    const TileImages t = tile_images(jobs[j].room, plans[j]);
+    images.mean += t.mean * (double)rir_tiles(plans[j]) / (double)batch_tiles;
+    images.fullest = std::max(images.fullest, t.fullest);
   }
+  int kind = plans[0].kind;  // of one job: that of its single call
+  if (n_jobs > 1 && precision != ISM_FP16)
+    kind = few_images_batch(images, precision == ISM_FP32_LUT, batch_tiles) ? ITEM_FEW : ITEM_MOMENTS;
   // pass 1: plans, window classes and counts
   int n_classes = 0;
   int class_wt[kMaxClasses] = {}, class_gen[kMaxClasses] = {}, class_tile[kMaxClasses] = {}, class_kind[kMaxClasses] = {},
@@ -880,9 +903,7 @@ int plan_batch(const ism_job *jobs, int n_jobs, int precision, const ism_schedul
     if (!(sched && sched->item_taps > 0.0)) {
       ism_schedule js{};
       if (sched) js = *sched;
-      if (!p.half)
-        p.kind = all_few || (few_tiles >= kFewBatchTiles && few_images(jobs[j].room, p, batch_tiles, 2.0)) ? ITEM_FEW
-                                                                                                          : ITEM_MOMENTS;
+      p.kind = kind;
       const bool mom = p.kind == ITEM_MOMENTS;
       double t = item_target(batch_taps, p.wt, p.half, mom, p.ra.n_samples, sched);
       if (!mom) t = std::min(t, batch_item_taps(p.wt, p.half));
