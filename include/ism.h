@@ -117,9 +117,10 @@ int ism_count_taps(const ism_room *room, const float *src, int n_src, const floa
 
 /* How a call splits its work into work items (units of the accumulation
  * kernel: one RIR, one output tile of 256 samples (512 in FP32 calls of few
- * images per tile), one slab of the image shell that tile owns). The split changes the summation order, so results agree
- * across schedules within rounding (<= 1e-6 of the RIR peak), not bitwise; a
- * given schedule always gives the same bits. NULL means the tuned default. A
+ * images per tile), one slab of the image shell that tile owns). The split
+ * changes the summation order, so results agree across schedules within
+ * rounding (<= 1e-6 of the RIR peak), not bitwise; a given schedule always
+ * gives the same bits. NULL means the tuned default. A
  * field left at 0 (tail_rounds: < 0) keeps its default. Used by tuning and
  * tests; the library reads no environment variables. */
 typedef struct {
@@ -384,9 +385,9 @@ int ism_batch_prepare(const ism_job *jobs, int n_jobs, int precision, void *ws, 
  * waves (at least 1e4). FP32 and table taps: by images per item, doubled for a
  * job whose items would take more workspace than a cut by taps; where tiles hold
  * few images (FP32 up to 40 on average in batches of fewer than 4096 tiles, table
- * taps up to 300 in large batches), by taps as FP16. A
- * job's result therefore agrees within rounding (<= 1e-6 of the RIR peak)
- * with the job alone and with ism_simulate. With an item_taps in the schedule it
+ * taps up to 300 in large batches), by taps as FP16. A job's result therefore
+ * agrees within rounding (<= 1e-6 of the RIR peak) with the job alone and with
+ * ism_simulate. With an item_taps in the schedule it
  * is bitwise that of ism_simulate_ex with the same schedule, and a batch of one
  * job (FP16: of fewer than B x balance_items estimated taps) is bitwise
  * ism_simulate_ex with tail_rounds = 0. */

@@ -304,7 +304,7 @@ int64_t rir_tiles(const Plan &p) { return (int64_t)p.n_rir * ((p.ra.k_end + TILE
 // against one wave, us, 64 jobs of one length x 16 RIRs, at 20, 80, 160 and 300 images: 3072
 // tiles 56 and 50, 58 and 52, 59 and 83, 59 and 109; 10 240 tiles 104 and 138, 106 and 171,
 // 110 and 177, 115 and 193; table taps 81 and 52, 81 and 53, 83 and 85, 84 and 113; 203 and
-// 139, 204 and 174, 206 and 184, 212 and 200. Lengths and rooms at random (4 jobs x 8: 96
+// 139, 204 and 174, 206 and 184, 212 and 200. Lengths and rooms at random (8 jobs x 4: 96
 // tiles) at 40 and 80: 18.9 and 20.0, 19.5 and 24.2; table taps 19.5 and 22.5, 19.7 and 26.9.
 constexpr double kFewBatchMean = 40.0, kFewBatchFull = 4096.0;
 constexpr double kFewLutBatchFirst = 75.0, kFewLutBatchTiles = 64.0, kFewLutBatchMean = 300.0;
