@@ -29,8 +29,9 @@ typedef struct {
  * schedule, FP32 mode) without computing taps, on four waves per work item that
  * share its columns (the walk of its taps, but in calls of few images per tile,
  * whose items walk on one wave like those of FP16, see ism_debug_enumerate_ex),
- * and writes one record per image that some work item owns: every lattice image whose integer delay k0 lies in
- * [0, nS + W/2 - 1), i.e. every image with a tap inside the RIR, once.
+ * and writes one record per image that some work item owns: every lattice image
+ * whose integer delay k0 lies in [0, nS + W/2 - 1), i.e. every image with a tap
+ * inside the RIR, once.
  *   src, rcv  device float32 [n][3] as for ism_simulate;
  *   sched     as for ism_simulate_ex (NULL = default);
  *   records   device array of cap ism_image_record, in no particular order;
