@@ -139,3 +139,34 @@ def test_batches_of_both_kinds(precision):
             alone = ism.BatchSimulator([(room, src, rcv)], precision=precision).run()[0]
             untapered = ism.simulate(room, src, rcv, precision, schedule=ism.Schedule(tail_rounds=0.0))
             assert torch.equal(alone, untapered), i
+
+
+@pytest.mark.parametrize("per_tile", [10, 60, 200])
+@pytest.mark.parametrize("n_jobs,n_rcv", [(2, 1), (20, 16), (70, 16)])
+@pytest.mark.parametrize("precision", ["fp32", "lut"])
+def test_batch_on_either_side_of_its_limits(oracle_mod, precision, n_jobs, n_rcv, per_tile):
+    """Batches of 8, 1280 and 4480 tiles of few and of some more images: within rounding of
+    the single calls (1e-6 of the peak), one pair of each fourth job against the oracle."""
+    import torch
+
+    rng = np.random.default_rng(n_jobs + per_tile)
+    jobs = []
+    for i in range(n_jobs):
+        k, fs = 900.0, 16000.0
+        side = (4 / 3 * np.pi * (k + 32) ** 3 / (4 * per_tile)) ** (1 / 3) * 343.0 / fs
+        L = [side * 1.1, side, side / 1.1]
+        room = ism.Room(L, [0.9, 0.85, 0.8, 0.9, 0.7, 0.95], ism.n_img_for_time(L, 343.0, (k + 32) / fs), 343.0, fs,
+                        k / fs, 0.004)
+        src = rng.uniform(0.4 * side, 0.6 * side, (1, 3)).astype(np.float32)
+        jobs.append((room, src, (src + rng.uniform(-0.2, 0.2, (n_rcv, 3)) * side).astype(np.float32)))
+    _say(f"batch limits {precision} {n_jobs} x {n_rcv}, {per_tile}")
+    outs = [o.clone() for o in ism.BatchSimulator(jobs, precision=precision).run()]
+    torch.cuda.synchronize()
+    for i, ((room, src, rcv), o) in enumerate(zip(jobs, outs)):
+        single = ism.simulate(room, src, rcv, precision)
+        peak = torch.amax(torch.abs(single), dim=-1, keepdim=True)
+        assert float((torch.abs(o - single) / peak).max()) <= 1e-6, i
+        if i % 4 == 0:
+            e = _err(oracle_mod, room, src, rcv[:1], o[:, :1].cpu().numpy().astype(np.float64),
+                     16 if precision == "lut" else 0)
+            assert e <= TOL, i
